@@ -190,9 +190,9 @@ int flowcache_scatter_kv(const void* k_new, const void* v_new, void* k_cache, vo
 // ------------------------------------------------------------------ attend
 size_t flowcache_attend_workspace(int A, int L_c, int H_q, int H_k, int d, int mass_len,
                                   int obs_window) {
-    (void)H_k; (void)d;
-    if (A < 1 || L_c < 1 || H_q < 1) return 0;
-    size_t need = 256;
+    (void)H_k;
+    if (A < 1 || A > FC_MAX_ACTIVE || L_c < 1 || H_q < 1) return 0;
+    size_t need = 256 + fc_attend_split_workspace(A, L_c, H_q, d);
     if (mass_len > 0) {
         const int W = (obs_window <= 0 || obs_window > L_c) ? L_c : obs_window;
         need += fc_mass_workspace(W, H_q, mass_len);
@@ -244,6 +244,7 @@ int flowcache_attend(const void* q, const void* k_new, const void* v_new, void* 
     at.H_q = H_q; at.H_k = H_k; at.d = d; at.L_c = L_c; at.L_clean = L_clean; at.A = A;
     std::memcpy(at.active_off, active_off, sizeof(int32_t) * A);
     at.rec_idx = recompute_idx; at.n_rec = n_recompute; at.scale = scale;
+    at.ws = workspace; at.ws_bytes = workspace ? workspace_bytes : 0;
     st = (dtype == FC_BF16) ? fc_launch_attend_bf16(at, s) : fc_launch_attend_f32(at, s);
     if (st != FC_OK) return st;
 

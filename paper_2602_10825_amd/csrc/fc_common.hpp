@@ -110,7 +110,9 @@ struct FcAttendArgs {
     fc_dtype dtype; int H_q; int H_k; int d; int L_c; int L_clean; int A;
     int32_t active_off[FC_MAX_ACTIVE];
     const int32_t* rec_idx; const int32_t* n_rec; float scale;
+    void* ws; size_t ws_bytes;   // room for the partials of split keys; may be absent (no splitting then)
 };
+size_t fc_attend_split_workspace(int A, int L_c, int H_q, int d);
 int fc_launch_attend_f32(const FcAttendArgs& a, hipStream_t s);
 int fc_launch_attend_bf16(const FcAttendArgs& a, hipStream_t s);
 

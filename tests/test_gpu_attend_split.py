@@ -1,0 +1,55 @@
+"""The attention kernels that divide a block's keys over its wavefronts and, where a launch has few
+query rows, over several blocks: row tiles of 32, key tiles of 32, key ranges per block.  The sizes
+sit at the edges of those (one row, one key, a tile more or less, fewer tiles than wavefronts,
+ranges that split inside a segment), against the float64 oracle at the bars of the parity tests."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2602_10825_amd import binding as B
+from paper_2602_10825_amd import synth
+from tests.test_gpu_parity import DEV, check_attend, dev, run_attend
+
+pytestmark = pytest.mark.gpu
+
+# (H_q, H_k, d, A, L_c, L_clean, recompute list)
+SHAPES = [
+    (1, 1, 64, 1, 1, 0, [0]),                 # one row, one key
+    (2, 1, 128, 2, 31, 1, [0, 1]),            # a tile less one
+    (2, 2, 128, 1, 33, 31, [0]),              # a tile and one; ragged end of both segments
+    (1, 1, 128, 3, 32, 255, [2]),             # exactly one row tile, eight key tiles in the clean region
+    (4, 2, 64, 2, 65, 1025, [1]),             # two ranges and more
+    (1, 1, 128, 2, 5, 9000, [0, 1]),          # few rows, long context: the most ranges
+    (3, 1, 64, 16, 40, 700, [0, 3, 15]),      # ranges over many segments
+    (8, 8, 128, 4, 321, 64, [0, 1, 2, 3]),    # enough rows that nothing is split over blocks
+]
+
+
+@pytest.mark.parametrize("dtype", ["f32"])
+@pytest.mark.parametrize("H_q,H_k,d,A,L_c,L_clean,rec", SHAPES)
+def test_attend_split_edges(dtype, H_q, H_k, d, A, L_c, L_clean, rec):
+    wl = synth.Workload("split", dtype, H_q, H_k, d, A, L_c, L_clean, 1)
+    a = synth.attend_inputs(wl, seed=L_c)
+    got, ref, res, ref_lse, *_ = run_attend(wl, a, rec)
+    check_attend(wl, got, ref, res, ref_lse, len(rec))
+
+
+@pytest.mark.parametrize("dtype", ["f32"])
+def test_attend_without_room_for_partials(dtype):
+    """A workspace too small for the partials (or none) leaves the keys of a unit in one block."""
+    wl = synth.Workload("split", dtype, 2, 2, 64, 2, 48, 4000, 1)
+    a = synth.attend_inputs(wl, seed=3)
+    idx = torch.tensor([1, -1], dtype=torch.int32, device=DEV)
+    n = torch.tensor([1], dtype=torch.int32, device=DEV)
+    q, k, v = dev(a["q"], dtype), dev(a["k_cache"], dtype), dev(a["v_cache"], dtype)
+    need = B.lib().flowcache_attend_workspace(wl.A, wl.L_c, wl.H_q, wl.H_k, wl.d, 0, 50)
+    outs = []
+    for nbytes in (need, 256):
+        ws = torch.empty(nbytes, dtype=torch.uint8, device=DEV)
+        r = B.flowcache_attend(q, None, None, k, v, wl.L_c, wl.L_clean, a["active_off"], idx, n, workspace=ws)
+        outs.append((r["out"][:wl.L_c].float().cpu().numpy(), r["lse"][:, :wl.L_c].cpu().numpy()))
+    # the same products summed in another grouping: fp32 sums of at most 4096 terms, and for bf16 one
+    # rounding of weights and outputs each
+    tol = 1e-5 if dtype == "f32" else 1e-2
+    for x, y in zip(*outs):
+        assert np.linalg.norm(x - y) <= tol * np.linalg.norm(y)
