@@ -77,6 +77,21 @@ inline int fc_split_parts_bound(int A, int L_c, int H_q) {
 inline size_t fc_split_part_bytes(int d) { return (size_t)kUnitRows * (d + 2) * sizeof(float); }
 
 // ---- device side ---------------------------------------------------------------------------
+// The recompute list is the device's: a count above A is cut to A and an entry outside [0, A) is
+// skipped (nothing is read or written for it).  Bit r of the mask = row block r holds a chunk; R =
+// the number of such blocks, so that a malformed list is planned like the well-formed one.
+__device__ __forceinline__ uint32_t valid_blocks(const FcAttendArgs& a) {
+    const int lane = threadIdx.x & (FC_WAVE - 1);
+    const int c = a.rec_idx[lane < a.A ? lane : 0];
+    const uint32_t mask = (uint32_t)__ballot(lane < min(*a.n_rec, a.A) && (unsigned)c < (unsigned)a.A);
+    return mask;
+}
+// the row block with `rank` valid ones above it: latest (heaviest) chunk first
+__device__ __forceinline__ int block_of_rank(uint32_t mask, int rank) {
+    for (int i = 0; i < rank; ++i) mask &= ~(0x80000000u >> __clz((int)mask));
+    return 31 - __clz((int)mask);
+}
+
 struct SplitItem { int R, S, r, c, h, tile, s; int64_t part; bool ok; };
 
 // Block -> (head, chunk, key range, row tile).  Consecutive blocks go round the 8 XCDs, so item
@@ -85,8 +100,9 @@ struct SplitItem { int R, S, r, c, h, tile, s; int64_t part; bool ok; };
 __device__ __forceinline__ SplitItem split_item(const FcAttendArgs& a, const FcSplitPlan& p, int bid) {
     SplitItem it;
     it.ok = false;
-    it.R = min(*a.n_rec, a.A);
-    if (it.R <= 0) return it;
+    const uint32_t valid = valid_blocks(a);
+    it.R = __popc(valid);
+    if (it.R == 0) return it;
     it.S = p.splits[it.R - 1];
     const int n = it.R * a.H_q * p.tiles * it.S;
     const int per = (n + 7) / 8;
@@ -97,11 +113,12 @@ __device__ __forceinline__ SplitItem split_item(const FcAttendArgs& a, const FcS
     int rest = item / p.tiles;
     it.s = rest % it.S;
     rest /= it.S;
-    it.r = it.R - 1 - rest % it.R;       // latest (heaviest) chunk first
+    const int rank = rest % it.R;
     it.h = rest / it.R;
-    it.part = (int64_t)((it.h * it.R + it.r) * p.tiles + it.tile) * it.S + it.s;
+    it.part = (int64_t)((it.h * it.R + rank) * p.tiles + it.tile) * it.S + it.s;
+    it.r = block_of_rank(valid, rank);
     it.c = a.rec_idx[it.r];
-    it.ok = (unsigned)it.c < (unsigned)a.A;   // not a chunk: skipped, never followed
+    it.ok = true;
     return it;
 }
 
@@ -186,14 +203,14 @@ __device__ __forceinline__ void finish_unit(const FcAttendArgs& a, const FcSplit
 template <typename T, int D>
 __global__ __launch_bounds__(256) void attend_merge_kernel(FcAttendArgs a, FcSplitPlan p, const float* parts) {
     constexpr int PER = D / 8;
-    const int R = min(*a.n_rec, a.A);
-    if (R <= 0) return;
+    const uint32_t valid = valid_blocks(a);
+    const int R = __popc(valid);
+    if (R == 0) return;
     const int S = p.splits[R - 1];
     const int unit = blockIdx.x;
     if (S == 1 || unit >= R * a.H_q * p.tiles) return;
     const int tile = unit % p.tiles;
-    const int r = (unit / p.tiles) % R, h = unit / (p.tiles * R);
-    if ((unsigned)a.rec_idx[r] >= (unsigned)a.A) return;
+    const int r = block_of_rank(valid, (unit / p.tiles) % R), h = unit / (p.tiles * R);
     const int row = threadIdx.x >> 3, c0 = (threadIdx.x & 7) * PER;
     const int row_in_chunk = tile * kUnitRows + row;
     if (row_in_chunk >= a.L_c) return;
