@@ -37,20 +37,28 @@
 // lets run at full clock, 1495 against 1620; head dimension 64 590 against 575 us.)
 // Work-groups are mapped so that the 32 compute units of one XCD work on the same head
 // and chunk at the same time and share the K/V stream through that XCD's L2.
+//
+// Launches that do not fill the chip.  Where the units of 256 rows are fewer than the compute
+// units, their keys are split over several blocks; where they are more, those of the last, partly
+// filled round are (the plan and the merge of the partials: attend_split.hpp).  Where 256-row units
+// would be mostly padding or still too few, a second body takes 32 rows per block and divides the
+// keys over the block's wavefronts.  attend alone, us before / now: 8 heads on 2, 328 rows on 1984
+// keys 53 / 18; 12 x 128, 600 rows on 5200 keys 126 / 40, 1500 rows on 51689 keys 1141 / 433, 256
+// rows on 49201 keys 1076 / 106; 2 x 64, 278 rows on 60724 keys 982 / 36; 24 x 64, 2 chunks of 2040
+// rows on 18360 keys (1.5 rounds of units) 550 / 451.
 #include <utility>
 
-#include "fc_common.hpp"
+#include "attend_split.hpp"
 
 namespace {
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
-constexpr int BQ = 256;      // query rows per workgroup
+constexpr int BQ = kWideRows;   // query rows per workgroup
 constexpr int BK = 64;       // keys per tile
-constexpr int NXCD = 8;
-constexpr float kNegBig = -1.0e30f;
 
 typedef short s16x4_t __attribute__((ext_vector_type(4)));
 typedef short s16x8_t __attribute__((ext_vector_type(8)));
@@ -85,12 +93,12 @@ struct WideSmem {
     __attribute__((aligned(16))) bf16_t K[4][BK * KROW];
     __attribute__((aligned(16))) bf16_t V[2][BK * VROW];
     int seg_start[FC_MAX_ACTIVE + 2], seg_len[FC_MAX_ACTIVE + 2];
-    int n_tiles;
+    int seg_first, off_first, n_tiles;
 };
 
 template <int D>
-__global__ __launch_bounds__(NT) void attend_bf16_kernel(FcAttendArgs a, int tiles, int per) {
-    __shared__ WideSmem<D> sm;
+__device__ __forceinline__ void attend_wide(const FcAttendArgs& a, const FcAttendPlan& p, uint32_t valid,
+                                            WideSmem<D>& sm, float* parts) {
     constexpr int KS = D / 16;        // contraction steps of Q K^T
     constexpr int DVB = D / 32;       // 32-wide blocks of the value dimension
     constexpr int KROW = WideSmem<D>::KROW, VROW = WideSmem<D>::VROW;
@@ -100,17 +108,10 @@ __global__ __launch_bounds__(NT) void attend_bf16_kernel(FcAttendArgs a, int til
     constexpr int NPV = 4 * DVB, NQK = 2 * KS, N = NPV + NQK;   // matrix products of a step: P V, Q K^T
     constexpr int PF = 4;             // fragments are read this many products ahead
 
-    const int bid = blockIdx.x;
-    const int xcd = bid % NXCD, slot = bid / NXCD;
-    const int rank = slot / per;
-    const int item = xcd * per + slot % per;
-    if (item >= a.H_q * tiles) return;
-    const int R = min(*a.n_rec, a.A);         // a count or an entry outside the valid range
-    if (rank >= R) return;                    // (a caller's mistake) is skipped, never followed
-    const int r = R - 1 - rank;               // heaviest (latest) chunk first
+    const WideItem wi = wide_item(a, p, valid, blockIdx.x);
+    if (!wi.ok) return;
+    const int r = wi.r, h = wi.h, tile = wi.tile;
     const int c = a.rec_idx[r];
-    if ((unsigned)c >= (unsigned)a.A) return;
-    const int h = item / tiles, tile = item % tiles;
     const int hk = h / (a.H_q / a.H_k);
 
     const int tid = threadIdx.x;
@@ -130,7 +131,8 @@ __global__ __launch_bounds__(NT) void attend_bf16_kernel(FcAttendArgs a, int til
     const bf16_t* kbase = (const bf16_t*)a.k_cache + (int64_t)hk * a.head_stride;
     const bf16_t* vbase = (const bf16_t*)a.v_cache + (int64_t)hk * a.head_stride;
 
-    // ---- visible key segments (clean region, then active chunks 0..c; adjacent ones merged)
+    // ---- visible key segments (clean region, then active chunks 0..c; adjacent ones merged) and
+    //      this block's range of their 64-key tiles
     if (tid == 0) {
         int n = 0, sgi = -1, nt = 0;
         while (sgi <= c) {
@@ -140,13 +142,19 @@ __global__ __launch_bounds__(NT) void attend_bf16_kernel(FcAttendArgs a, int til
             while (sgi <= c && a.active_off[sgi] == start + len) { len += a.L_c; ++sgi; }
             if (len > 0) { sm.seg_start[n] = start; sm.seg_len[n] = len; ++n; nt += (len + BK - 1) / BK; }
         }
-        sm.n_tiles = nt;
+        const int lo = (int)((int64_t)nt * wi.s / wi.S);
+        int skip = lo, sg = 0;
+        while (sg < n - 1 && skip >= (sm.seg_len[sg] + BK - 1) / BK) { skip -= (sm.seg_len[sg] + BK - 1) / BK; ++sg; }
+        sm.seg_first = sg;
+        sm.off_first = skip * BK < sm.seg_len[sg] ? skip * BK : 0;
+        sm.n_tiles = (int)((int64_t)nt * (wi.s + 1) / wi.S) - lo;
     }
     __syncthreads();
     const int nt = __builtin_amdgcn_readfirstlane(sm.n_tiles);
-    int seg = 0, t0 = 0;
-    int start = __builtin_amdgcn_readfirstlane(sm.seg_start[0]);
-    int len = __builtin_amdgcn_readfirstlane(sm.seg_len[0]);
+    int seg = __builtin_amdgcn_readfirstlane(sm.seg_first);
+    int start = __builtin_amdgcn_readfirstlane(sm.seg_start[seg]);
+    int len = __builtin_amdgcn_readfirstlane(sm.seg_len[seg]);
+    int t0 = __builtin_amdgcn_readfirstlane(sm.off_first);
     int to_step = nt - 1;             // tiles after the one (start, len, t0) point at
 
     u32x4_native kreg[LD], vreg[LD];
@@ -248,155 +256,173 @@ __global__ __launch_bounds__(NT) void attend_bf16_kernel(FcAttendArgs a, int til
         P[q >> 1][(q & 1) * 2 + 1] = w1;
     };
 
-    // ---- K(0), K(1) into the ring, K(2) and V(0) on their way, S(0); "V(-1)" finite (its P is zero)
-    int nv_prev = BK, nv_cur, nv_next;   // valid keys of the tile before S's, of S's and of the next one
-    {
-        step_tile();
-        nv_cur = nv_k;
+    if (nt > 0) {
+        // ---- K(0), K(1) into the ring, K(2) and V(0) on their way, S(0); "V(-1)" finite (its P is zero)
+        int nv_prev = BK, nv_cur, nv_next;   // valid keys of the tile before S's, of S's and of the next one
+        {
+            step_tile();
+            nv_cur = nv_k;
 #pragma unroll
-        for (int i = 0; i < LD; ++i) load_rows(kreg[i], kbase, pos_k, nv_k, i);
-        step_tile();
-        nv_next = nv_k;
+            for (int i = 0; i < LD; ++i) load_rows(kreg[i], kbase, pos_k, nv_k, i);
+            step_tile();
+            nv_next = nv_k;
 #pragma unroll
-        for (int i = 0; i < LD; ++i) load_rows(vreg[i], kbase, pos_k, nv_k, i);
+            for (int i = 0; i < LD; ++i) load_rows(vreg[i], kbase, pos_k, nv_k, i);
 #pragma unroll
-        for (int i = 0; i < LD; ++i) {
-            *reinterpret_cast<u32x4_native*>(&sm.K[0][st_k + i * RPP * KROW]) = kreg[i];
-            *reinterpret_cast<u32x4_native*>(&sm.K[1][st_k + i * RPP * KROW]) = vreg[i];
+            for (int i = 0; i < LD; ++i) {
+                *reinterpret_cast<u32x4_native*>(&sm.K[0][st_k + i * RPP * KROW]) = kreg[i];
+                *reinterpret_cast<u32x4_native*>(&sm.K[1][st_k + i * RPP * KROW]) = vreg[i];
+            }
+            for (int i = tid; i < BK * VROW / 8; i += NT) reinterpret_cast<uint4*>(sm.V[1])[i] = make_uint4(0, 0, 0, 0);
+            step_tile();
+#pragma unroll
+            for (int i = 0; i < LD; ++i) {
+                load_rows(kreg[i], kbase, pos_k, nv_k, i);
+                load_rows(vreg[i], vbase, pos_v, nv_v, i);
+            }
         }
-        for (int i = tid; i < BK * VROW / 8; i += NT) reinterpret_cast<uint4*>(sm.V[1])[i] = make_uint4(0, 0, 0, 0);
-        step_tile();
+        __syncthreads();
+        qk(&sm.K[0][k_frag], s);
+        if (nv_cur < BK) mask_tail(s, nv_cur);
+        bf16x8_t frag[PF];
 #pragma unroll
-        for (int i = 0; i < LD; ++i) {
-            load_rows(kreg[i], kbase, pos_k, nv_k, i);
-            load_rows(vreg[i], vbase, pos_v, nv_v, i);
-        }
-    }
-    __syncthreads();
-    qk(&sm.K[0][k_frag], s);
-    if (nv_cur < BK) mask_tail(s, nv_cur);
-    bf16x8_t frag[PF];
+        for (int f = 0; f < PF; ++f) frag[f] = read_v(&sm.V[1][v_frag], f);
+        float psum = 0.f;
+        int j = 0;
+        // Inner loop = steady state.  It is left when a row sum shows that m must be raised; the outer
+        // loop does that and re-enters.
+        for (;;) {
+        bool finished = false, raise;
+        do {
+            lsum += psum;
+            if (j == nt) { finished = true; break; }
+            const bf16_t* Kn = &sm.K[(j + 1) & 3][k_frag];
+            const bf16_t* Vp = &sm.V[(j + 1) & 1][v_frag];
+            const bf16_t* Vn = &sm.V[j & 1][v_frag];
+            bf16_t* Kw = &sm.K[(j + 2) & 3][st_k];
+            bf16_t* Vw = &sm.V[j & 1][st_v];
+            const float mneg = -m;
+            float wt[8];                               // weights on their way into P
+            ps0 = ps1 = 0.f;
+            constexpr int NEXP = NPV + KS - 1;         // products over which the exponentials are spread
+            constexpr int BAR = NPV + KS / 2;
+            static_for<N>([&](auto F) __attribute__((always_inline)) {
+                constexpr int f = F;
+                // matrix cores: O += V P(j-1), then S(j+1) = K Q^T
+                const bf16x8_t fr = frag[f % PF];
+                if constexpr (f < NPV) {
+                    o[f % DVB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr, __builtin_bit_cast(bf16x8_t, P[f / DVB]), o[f % DVB], 0, 0, 0);
+                } else {
+                    constexpr int g = f - NPV;
+                    if constexpr (g % KS == 0) {
+                        f32x16_t z;
 #pragma unroll
-    for (int f = 0; f < PF; ++f) frag[f] = read_v(&sm.V[1][v_frag], f);
-    float psum = 0.f;
-    int j = 0;
-    // Inner loop = steady state.  It is left when a row sum shows that m must be raised; the outer
-    // loop does that and re-enters.
-    for (;;) {
-    bool finished = false, raise;
-    do {
-        lsum += psum;
-        if (j == nt) { finished = true; break; }
-        const bf16_t* Kn = &sm.K[(j + 1) & 3][k_frag];
-        const bf16_t* Vp = &sm.V[(j + 1) & 1][v_frag];
-        const bf16_t* Vn = &sm.V[j & 1][v_frag];
-        bf16_t* Kw = &sm.K[(j + 2) & 3][st_k];
-        bf16_t* Vw = &sm.V[j & 1][st_v];
-        const float mneg = -m;
-        float wt[8];                               // weights on their way into P
-        ps0 = ps1 = 0.f;
-        constexpr int NEXP = NPV + KS - 1;         // products over which the exponentials are spread
-        constexpr int BAR = NPV + KS / 2;
-        static_for<N>([&](auto F) __attribute__((always_inline)) {
-            constexpr int f = F;
-            // matrix cores: O += V P(j-1), then S(j+1) = K Q^T
-            const bf16x8_t fr = frag[f % PF];
-            if constexpr (f < NPV) {
-                o[f % DVB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr, __builtin_bit_cast(bf16x8_t, P[f / DVB]), o[f % DVB], 0, 0, 0);
-            } else {
-                constexpr int g = f - NPV;
-                if constexpr (g % KS == 0) {
-                    f32x16_t z;
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) z[i] = 0.f;
-                    s[g / KS] = z;
+                        for (int i = 0; i < 16; ++i) z[i] = 0.f;
+                        s[g / KS] = z;
+                    }
+                    s[g / KS] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr, qf[g % KS], s[g / KS], 0, 0, 0);
                 }
-                s[g / KS] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr, qf[g % KS], s[g / KS], 0, 0, 0);
-            }
-            // LDS: the fragment of product f + PF
-            if constexpr (f + PF < NPV) frag[f % PF] = read_v(Vp, f + PF);
-            else if constexpr (f + PF < N) frag[f % PF] = read_k(Kn, f + PF - NPV);
-            else frag[f % PF] = read_v(Vn, f + PF - N);
-            // vector ALU: weights of tile j
-            constexpr int e0 = f < NEXP ? 32 * f / NEXP : 32, e1 = f < NEXP ? 32 * (f + 1) / NEXP : 32;
-            static_for<e1 - e0>([&](auto E) __attribute__((always_inline)) {
-                constexpr int e = e0 + E;
-                float w = __builtin_amdgcn_exp2f(fmaf(s[e >> 4][e & 15], c2, mneg));
-                asm volatile("" : "+v"(w));       // computed here, next to the matrix products
-                wt[e & 7] = w;
-            });
-            static_for<8>([&](auto Q) __attribute__((always_inline)) {
-                // weights q are ready, and the products with the P register they replace are issued
-                constexpr int q = Q, fe = ((q + 1) * 4 * NEXP + 31) / 32 - 1, fp = (q / 2 + 1) * DVB;
-                if constexpr (f == (fe > fp ? fe : fp))
-                    pack4(wt[(4 * q) & 7], wt[(4 * q + 1) & 7], wt[(4 * q + 2) & 7], wt[(4 * q + 3) & 7], q);
-            });
-            // staging: K(j+2), V(j) to LDS, then the loads of K(j+3), V(j+1)
-            if constexpr (f >= 2 && f < 2 + LD)
-                *reinterpret_cast<u32x4_native*>(Kw + (f - 2) * RPP * KROW) = kreg[f - 2];
-            if constexpr (f >= 2 + LD && f < 2 + 2 * LD)
-                *reinterpret_cast<u32x4_native*>(Vw + (f - 2 - LD) * RPP * VROW) = vreg[f - 2 - LD];
-            if constexpr (f == 2 + 2 * LD) step_tile();
-            if constexpr (f >= 2 + 2 * LD && f < 2 + 3 * LD) {
-                load_rows(kreg[f - 2 - 2 * LD], kbase, pos_k, nv_k, f - 2 - 2 * LD);
-                load_rows(vreg[f - 2 - 2 * LD], vbase, pos_v, nv_v, f - 2 - 2 * LD);
-            }
-            if constexpr (f == BAR) {
-                // K(j+2), V(j) are visible past this point: this wavefront's stores are done (seven
-                // or more later LDS accesses are behind them, LDS serves them in order), and every
-                // other one's too
+                // LDS: the fragment of product f + PF
+                if constexpr (f + PF < NPV) frag[f % PF] = read_v(Vp, f + PF);
+                else if constexpr (f + PF < N) frag[f % PF] = read_k(Kn, f + PF - NPV);
+                else frag[f % PF] = read_v(Vn, f + PF - N);
+                // vector ALU: weights of tile j
+                constexpr int e0 = f < NEXP ? 32 * f / NEXP : 32, e1 = f < NEXP ? 32 * (f + 1) / NEXP : 32;
+                static_for<e1 - e0>([&](auto E) __attribute__((always_inline)) {
+                    constexpr int e = e0 + E;
+                    float w = __builtin_amdgcn_exp2f(fmaf(s[e >> 4][e & 15], c2, mneg));
+                    asm volatile("" : "+v"(w));       // computed here, next to the matrix products
+                    wt[e & 7] = w;
+                });
+                static_for<8>([&](auto Q) __attribute__((always_inline)) {
+                    // weights q are ready, and the products with the P register they replace are issued
+                    constexpr int q = Q, fe = ((q + 1) * 4 * NEXP + 31) / 32 - 1, fp = (q / 2 + 1) * DVB;
+                    if constexpr (f == (fe > fp ? fe : fp))
+                        pack4(wt[(4 * q) & 7], wt[(4 * q + 1) & 7], wt[(4 * q + 2) & 7], wt[(4 * q + 3) & 7], q);
+                });
+                // staging: K(j+2), V(j) to LDS, then the loads of K(j+3), V(j+1)
+                if constexpr (f >= 2 && f < 2 + LD)
+                    *reinterpret_cast<u32x4_native*>(Kw + (f - 2) * RPP * KROW) = kreg[f - 2];
+                if constexpr (f >= 2 + LD && f < 2 + 2 * LD)
+                    *reinterpret_cast<u32x4_native*>(Vw + (f - 2 - LD) * RPP * VROW) = vreg[f - 2 - LD];
+                if constexpr (f == 2 + 2 * LD) step_tile();
+                if constexpr (f >= 2 + 2 * LD && f < 2 + 3 * LD) {
+                    load_rows(kreg[f - 2 - 2 * LD], kbase, pos_k, nv_k, f - 2 - 2 * LD);
+                    load_rows(vreg[f - 2 - 2 * LD], vbase, pos_v, nv_v, f - 2 - 2 * LD);
+                }
+                if constexpr (f == BAR) {
+                    // K(j+2), V(j) are visible past this point: this wavefront's stores are done (seven
+                    // or more later LDS accesses are behind them, LDS serves them in order), and every
+                    // other one's too
+                    __builtin_amdgcn_sched_barrier(0);
+                    __builtin_amdgcn_s_waitcnt(0xC67F);      // lgkmcnt(6)
+                    asm volatile("" ::: "memory");
+                    __builtin_amdgcn_s_barrier();
+                    asm volatile("" ::: "memory");
+                }
                 __builtin_amdgcn_sched_barrier(0);
-                __builtin_amdgcn_s_waitcnt(0xC67F);      // lgkmcnt(6)
-                asm volatile("" ::: "memory");
-                __builtin_amdgcn_s_barrier();
-                asm volatile("" ::: "memory");
+            });
+            psum = ps0 + ps1;
+            if (nv_next < BK) mask_tail(s, nv_next);
+            nv_prev = nv_cur;
+            nv_cur = nv_next;
+            nv_next = nv_q1;          // of tile j + 2
+            ++j;
+            raise = __any(psum > kTooBig);
+        } while (!raise);
+        if (finished) break;
+        {
+            // S of the tile just weighted again, its true row maximum, O and l to the new scale (the
+            // products so far are in the old one), its weights anew
+            f32x16_t x[2];
+            qk(&sm.K[(j - 1) & 3][k_frag], x);
+            if (nv_prev < BK) mask_tail(x, nv_prev);
+            float v = fmaxf(x[0][0], x[1][0]);
+#pragma unroll
+            for (int i = 1; i < 16; ++i) v = fmaxf(v, fmaxf(x[0][i], x[1][i]));
+            v = fmaxf(v, __shfl_xor(v, 32, FC_WAVE));
+            const float mnew = fmaxf(m, v * c2);
+            const float alpha = __builtin_amdgcn_exp2f(m - mnew);
+            m = mnew;
+            lsum *= alpha;
+#pragma unroll
+            for (int dv = 0; dv < DVB; ++dv) o[dv] *= alpha;
+            ps0 = ps1 = 0.f;
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const int kb = q >> 2, i = (q & 3) * 4;
+                pack4(__builtin_amdgcn_exp2f(fmaf(x[kb][i], c2, -m)), __builtin_amdgcn_exp2f(fmaf(x[kb][i + 1], c2, -m)),
+                      __builtin_amdgcn_exp2f(fmaf(x[kb][i + 2], c2, -m)), __builtin_amdgcn_exp2f(fmaf(x[kb][i + 3], c2, -m)), q);
             }
-            __builtin_amdgcn_sched_barrier(0);
-        });
-        psum = ps0 + ps1;
-        if (nv_next < BK) mask_tail(s, nv_next);
-        nv_prev = nv_cur;
-        nv_cur = nv_next;
-        nv_next = nv_q1;          // of tile j + 2
-        ++j;
-        raise = __any(psum > kTooBig);
-    } while (!raise);
-    if (finished) break;
-    {
-        // S of the tile just weighted again, its true row maximum, O and l to the new scale (the
-        // products so far are in the old one), its weights anew
-        f32x16_t x[2];
-        qk(&sm.K[(j - 1) & 3][k_frag], x);
-        if (nv_prev < BK) mask_tail(x, nv_prev);
-        float v = fmaxf(x[0][0], x[1][0]);
-#pragma unroll
-        for (int i = 1; i < 16; ++i) v = fmaxf(v, fmaxf(x[0][i], x[1][i]));
-        v = fmaxf(v, __shfl_xor(v, 32, FC_WAVE));
-        const float mnew = fmaxf(m, v * c2);
-        const float alpha = __builtin_amdgcn_exp2f(m - mnew);
-        m = mnew;
-        lsum *= alpha;
-#pragma unroll
-        for (int dv = 0; dv < DVB; ++dv) o[dv] *= alpha;
-        ps0 = ps1 = 0.f;
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int kb = q >> 2, i = (q & 3) * 4;
-            pack4(__builtin_amdgcn_exp2f(fmaf(x[kb][i], c2, -m)), __builtin_amdgcn_exp2f(fmaf(x[kb][i + 1], c2, -m)),
-                  __builtin_amdgcn_exp2f(fmaf(x[kb][i + 2], c2, -m)), __builtin_amdgcn_exp2f(fmaf(x[kb][i + 3], c2, -m)), q);
+            psum = ps0 + ps1;
         }
-        psum = ps0 + ps1;
-    }
-    }
-    // ---- drain: O += V P of the last tile
-    const bf16_t* Vl = &sm.V[(nt - 1) & 1][v_frag];
+        }
+        // ---- drain: O += V P of the last tile
+        const bf16_t* Vl = &sm.V[(nt - 1) & 1][v_frag];
 #pragma unroll
-    for (int f = 0; f < NPV; ++f)
-        o[f % DVB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f < PF ? frag[f] : read_v(Vl, f), __builtin_bit_cast(bf16x8_t, P[f / DVB]), o[f % DVB], 0, 0, 0);
+        for (int f = 0; f < NPV; ++f)
+            o[f % DVB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f < PF ? frag[f] : read_v(Vl, f), __builtin_bit_cast(bf16x8_t, P[f / DVB]), o[f % DVB], 0, 0, 0);
+    }
 
-    // ---- epilogue: normalise, store O (bf16) and the row log-sum-exp
+    // ---- epilogue: normalise, store O (bf16) and the row log-sum-exp; or leave the partial
     {
         const float ltot = lsum + __shfl_xor(lsum, 32, FC_WAVE);
+        if (wi.S > 1) {
+            const int64_t part = (wi.unit * (BQ / kUnitRows) + wave) * wi.S + wi.s;   // 32 rows each
+            float* po = parts + (part * kUnitRows + l32) * D;
+#pragma unroll
+            for (int dv = 0; dv < DVB; ++dv)
+#pragma unroll
+                for (int g = 0; g < 4; ++g)
+                    store_out(po + dv * 32 + g * 8 + hh * 4, o[dv][4 * g], o[dv][4 * g + 1], o[dv][4 * g + 2],
+                              o[dv][4 * g + 3]);
+            if (hh == 0) {
+                float* ml = parts + (int64_t)p.parts * kUnitRows * D + part * 2 * kUnitRows;
+                ml[l32] = m;
+                ml[kUnitRows + l32] = ltot;
+            }
+            return;
+        }
         const float inv = 1.0f / ltot;
         if (row_in_chunk < a.L_c) {
             const int64_t row = (int64_t)r * a.L_c + row_in_chunk;
@@ -406,12 +432,8 @@ __global__ __launch_bounds__(NT) void attend_bf16_kernel(FcAttendArgs a, int til
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
                     const int e0 = dv * 32 + g * 8 + hh * 4;
-                    uint2 pk;
-                    pk.x = (uint32_t)f32_to_bf16(o[dv][4 * g] * inv) |
-                           ((uint32_t)f32_to_bf16(o[dv][4 * g + 1] * inv) << 16);
-                    pk.y = (uint32_t)f32_to_bf16(o[dv][4 * g + 2] * inv) |
-                           ((uint32_t)f32_to_bf16(o[dv][4 * g + 3] * inv) << 16);
-                    *reinterpret_cast<uint2*>(op + e0) = pk;
+                    store_out(op + e0, o[dv][4 * g] * inv, o[dv][4 * g + 1] * inv, o[dv][4 * g + 2] * inv,
+                              o[dv][4 * g + 3] * inv);
                 }
             if (a.lse && hh == 0)
                 a.lse[(int64_t)h * a.A * a.L_c + row] =
@@ -420,19 +442,217 @@ __global__ __launch_bounds__(NT) void attend_bf16_kernel(FcAttendArgs a, int til
     }
 }
 
+// ---- few query rows ---------------------------------------------------------------------
+// 32 query rows per block; its 8 wavefronts take every 8th 32-key tile of the range and never meet
+// before the end, where their partials are merged through LDS.  Each stages its own tile in LDS
+// (coalesced loads one tile ahead; K read straight into registers in the operand's layout, 32
+// bytes of 32 rows per load, took twice as long) and follows the row maximum at a distance of
+// 2^8.  A tile costs a wavefront about 1.9 us, most of it the 16 KB that nothing shares with the
+// other wavefronts; that is why launches with enough rows take the 256-row body, where 8
+// wavefronts share every tile.
+template <int D>
+struct NarrowSmem {
+    static constexpr int KROW = D + 8, VROW = D + 32, OROW = D + 4;   // padded rows, as in WideSmem
+    __attribute__((aligned(16))) union {
+        struct { bf16_t k[kSplitWaves][32 * KROW], v[kSplitWaves][32 * VROW]; } t;   // one tile per wavefront
+        float o[kSplitWaves * kUnitRows * OROW];        // partial O at the end
+    };
+    float m_s[kSplitWaves * kUnitRows], l_s[kSplitWaves * kUnitRows];
+    Segments sg;
+};
+
+template <int D>
+__device__ __forceinline__ void attend_narrow(const FcAttendArgs& a, const FcAttendPlan& p, uint32_t valid,
+                                              NarrowSmem<D>& sm, float* parts) {
+    constexpr int KS = D / 16;           // contraction steps of Q K^T
+    constexpr int DVB = D / 32;          // 32-wide blocks of the value dimension
+    constexpr int KROW = NarrowSmem<D>::KROW, VROW = NarrowSmem<D>::VROW, OROW = NarrowSmem<D>::OROW;
+    constexpr int VPR = D / 8;           // 16-byte vectors per row
+    constexpr int LD = 32 * VPR / FC_WAVE;
+    constexpr float kSlack = 8.0f;       // the exponents' reference follows the row maximum at this distance (log2)
+    Segments& sg = sm.sg;
+    float *m_s = sm.m_s, *l_s = sm.l_s;
+
+    const SplitItem it = split_item(a, p, valid, blockIdx.x);
+    if (!it.ok) return;
+    const int hk = it.h / (a.H_q / a.H_k);
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int l32 = lane & 31, hh = lane >> 5;
+    const float c2 = a.scale * 1.4426950408889634f;
+    if (tid == 0) list_segments(a, it.c, sg);
+
+    // B operand of S^T = K Q^T: lane holds Q[q = l32][16 step + 8 hh .. + 8)
+    bf16x8_t qf[KS];
+    {
+        int rc = it.tile * kUnitRows + l32;
+        if (rc > a.L_c - 1) rc = a.L_c - 1;
+        const bf16_t* qp = (const bf16_t*)a.q + (((int64_t)it.r * a.L_c + rc) * a.H_q + it.h) * D + 8 * hh;
+#pragma unroll
+        for (int st = 0; st < KS; ++st) qf[st] = *reinterpret_cast<const bf16x8_t*>(qp + 16 * st);
+    }
+    __syncthreads();
+    const bf16_t* kbase = (const bf16_t*)a.k_cache + (int64_t)hk * a.head_stride;
+    const bf16_t* vbase = (const bf16_t*)a.v_cache + (int64_t)hk * a.head_stride;
+    const uint32_t ts = (uint32_t)a.tok_stride;
+    const int nt = __builtin_amdgcn_readfirstlane(sg.tile0[sg.n]);
+    const int t_end = (int)((int64_t)nt * (it.s + 1) / it.S);
+    int t = (int)((int64_t)nt * it.s / it.S) + wave;
+
+    f32x16_t o[DVB];
+#pragma unroll
+    for (int b = 0; b < DVB; ++b)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) o[b][i] = 0.f;
+    float m = kNegBig, l = 0.f;
+
+    u32x4_native kr[LD], vr[LD];
+    int seg = 0, nvalid = 0;
+    const int ld_row = lane / VPR, ld_col = lane % VPR;
+    // tile tt -> registers, by rows; a row past the end of its segment re-reads the last one
+    auto fetch = [&](int tt) {
+        while (tt >= __builtin_amdgcn_readfirstlane(sg.tile0[seg + 1])) ++seg;
+        const int off = (tt - __builtin_amdgcn_readfirstlane(sg.tile0[seg])) * 32;
+        const int left = __builtin_amdgcn_readfirstlane(sg.len[seg]) - off;
+        const int64_t pos = (int64_t)(__builtin_amdgcn_readfirstlane(sg.start[seg]) + off) * a.tok_stride;
+        nvalid = left < 32 ? left : 32;
+        const char* kt = reinterpret_cast<const char*>(kbase + pos);
+        const char* vt = reinterpret_cast<const char*>(vbase + pos);
+#pragma unroll
+        for (int i = 0; i < LD; ++i) {
+            int row = i * (FC_WAVE / VPR) + ld_row;
+            row = row < nvalid ? row : nvalid - 1;
+            const uint32_t at = ((uint32_t)row * ts + 8u * (uint32_t)ld_col) * 2u;
+            kr[i] = *reinterpret_cast<const u32x4_native*>(kt + at);
+            vr[i] = *reinterpret_cast<const u32x4_native*>(vt + at);
+        }
+    };
+    const int l16 = lane & 15;
+    bf16_t *kw = sm.t.k[wave], *vw = sm.t.v[wave];
+    const bf16_t* v_frag = vw + (hh * 4 + (l16 >> 2)) * VROW + ((lane >> 4) & 1) * 16 + (l16 & 3) * 4;
+    if (t < t_end) fetch(t);
+    while (t < t_end) {
+        // the wavefront's own tile: its LDS accesses are served in order, no barrier is needed
+#pragma unroll
+        for (int i = 0; i < LD; ++i) {
+            const int row = i * (FC_WAVE / VPR) + ld_row;
+            *reinterpret_cast<u32x4_native*>(&kw[row * KROW + ld_col * 8]) = kr[i];
+            *reinterpret_cast<u32x4_native*>(&vw[row * VROW + ld_col * 8]) = vr[i];
+        }
+        const int nv = nvalid;
+        t += kSplitWaves;
+        if (t < t_end) fetch(t);                        // the next tile, behind all of this one
+        f32x16_t s;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s[i] = 0.f;
+#pragma unroll
+        for (int st = 0; st < KS; ++st) {
+            const bf16x8_t kf = *reinterpret_cast<const bf16x8_t*>(&kw[l32 * KROW + 16 * st + 8 * hh]);
+            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[st], s, 0, 0, 0);
+        }
+        if (nv < 32) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+                if ((i >> 2) * 8 + hh * 4 + (i & 3) >= nv) s[i] = kNegBig;
+        }
+        float mx = s[0];
+#pragma unroll
+        for (int i = 1; i < 16; ++i) mx = fmaxf(mx, s[i]);
+        mx = fmaxf(mx, __shfl_xor(mx, 32, FC_WAVE)) * c2;
+        if (__any(mx > m + kSlack)) {
+            const float mn = fmaxf(m, mx);
+            const float alpha = __builtin_amdgcn_exp2f(m - mn);
+            m = mn;
+            l *= alpha;
+#pragma unroll
+            for (int b = 0; b < DVB; ++b) o[b] *= alpha;
+        }
+        const float mneg = -m;
+        const bf16x2_t ones = {(__bf16)1.0f, (__bf16)1.0f};
+        bf16x8_t pf[2];
+        float l0 = 0.f, l1 = 0.f;
+#pragma unroll
+        for (int i = 0; i < 16; i += 4) {
+            const float p0 = __builtin_amdgcn_exp2f(fmaf(s[i], c2, mneg));
+            const float p1 = __builtin_amdgcn_exp2f(fmaf(s[i + 1], c2, mneg));
+            const float p2 = __builtin_amdgcn_exp2f(fmaf(s[i + 2], c2, mneg));
+            const float p3 = __builtin_amdgcn_exp2f(fmaf(s[i + 3], c2, mneg));
+            const bf16x2_t lo = {(__bf16)p0, (__bf16)p1}, hi = {(__bf16)p2, (__bf16)p3};
+            // the sums run over the rounded weights, the ones V is multiplied with
+            l0 = __builtin_amdgcn_fdot2_f32_bf16(lo, ones, l0, false);
+            l1 = __builtin_amdgcn_fdot2_f32_bf16(hi, ones, l1, false);
+            pf[i >> 3][i & 7] = lo[0];
+            pf[i >> 3][(i & 7) + 1] = lo[1];
+            pf[i >> 3][(i & 7) + 2] = hi[0];
+            pf[i >> 3][(i & 7) + 3] = hi[1];
+        }
+        l += l0 + l1;
+#pragma unroll
+        for (int tt = 0; tt < 2; ++tt)
+#pragma unroll
+            for (int b = 0; b < DVB; ++b) {
+                const bf16_t* vp = v_frag + tt * 16 * VROW + b * 32;
+                const s16x4_t lo = lds_read_tr(vp), hi = lds_read_tr(vp + 8 * VROW);
+                const bf16x8_t vf = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+                o[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[tt], o[b], 0, 0, 0);
+            }
+    }
+    l += __shfl_xor(l, 32, FC_WAVE);
+    __syncthreads();                                    // every wavefront is done with its V tile
+    if (hh == 0) { m_s[wave * kUnitRows + l32] = m; l_s[wave * kUnitRows + l32] = l; }
+#pragma unroll
+    for (int b = 0; b < DVB; ++b)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+            *reinterpret_cast<f32x4_t*>(&sm.o[(wave * kUnitRows + l32) * OROW + b * 32 + g * 8 + hh * 4]) =
+                f32x4_t{o[b][4 * g], o[b][4 * g + 1], o[b][4 * g + 2], o[b][4 * g + 3]};
+    __syncthreads();
+    finish_unit<bf16_t, D, OROW>(a, p, it, sm.o, m_s, l_s, parts);
+}
+
+// WIDE and NARROW say which of the two bodies some recompute count of this launch asks for.
+template <int D, bool WIDE, bool NARROW>
+__global__ __launch_bounds__(NT) void attend_bf16_kernel(FcAttendArgs a, FcAttendPlan p, float* parts) {
+    static_assert(NT == kSplitThreads, "both bodies run on the same block");
+    const uint32_t valid = valid_blocks(a);
+    const int R = __popc(valid);
+    if (R == 0) return;
+    union Smem {
+        WideSmem<WIDE ? D : 64> w;
+        NarrowSmem<NARROW ? D : 64> n;
+    };
+    __shared__ __attribute__((aligned(16))) char raw[WIDE && NARROW ? sizeof(Smem) : WIDE ? sizeof(WideSmem<D>) : sizeof(NarrowSmem<D>)];
+    if (WIDE && (!NARROW || !p.narrow[R - 1]))
+        attend_wide<D>(a, p, valid, *reinterpret_cast<WideSmem<D>*>(raw), parts);
+    else if (NARROW)
+        attend_narrow<D>(a, p, valid, *reinterpret_cast<NarrowSmem<D>*>(raw), parts);
+}
+
+template <int D>
+int launch_bf16(const FcAttendArgs& a, hipStream_t s) {
+    FcAttendPlan p = fc_attend_plan_bf16(a.A, a.L_c, a.L_clean, a.H_q, D, true);
+    if (p.parts > 0 && (!a.ws || a.ws_bytes < (size_t)p.parts * fc_split_part_bytes(D)))
+        p = fc_attend_plan_bf16(a.A, a.L_c, a.L_clean, a.H_q, D, false);    // no room for partials
+    bool wide = false, narrow = false;
+    for (int R = 0; R < a.A; ++R) (p.narrow[R] ? narrow : wide) = true;
+    if (!narrow)
+        attend_bf16_kernel<D, true, false><<<p.grid, NT, 0, s>>>(a, p, (float*)a.ws);
+    else if (!wide)
+        attend_bf16_kernel<D, false, true><<<p.grid, NT, 0, s>>>(a, p, (float*)a.ws);
+    else
+        attend_bf16_kernel<D, true, true><<<p.grid, NT, 0, s>>>(a, p, (float*)a.ws);
+    FC_LAUNCH_CHECK();
+    if (p.merge_grid > 0) {
+        attend_merge_kernel<bf16_t, D><<<p.merge_grid, 256, 0, s>>>(a, p, (const float*)a.ws);
+        FC_LAUNCH_CHECK();
+    }
+    return FC_OK;
+}
+
 }  // namespace
 
 int fc_launch_attend_bf16(const FcAttendArgs& a, hipStream_t s) {
-    const int tiles = (a.L_c + BQ - 1) / BQ;
-    const int items = a.H_q * tiles;
-    const int per = (items + NXCD - 1) / NXCD;
-    const dim3 grid((unsigned)(NXCD * per * a.A));
-    if (a.d == 128)
-        attend_bf16_kernel<128><<<grid, NT, 0, s>>>(a, tiles, per);
-    else if (a.d == 64)
-        attend_bf16_kernel<64><<<grid, NT, 0, s>>>(a, tiles, per);
-    else
-        return FC_UNSUPPORTED;
-    FC_LAUNCH_CHECK();
-    return FC_OK;
+    if (a.d == 128) return launch_bf16<128>(a, s);
+    if (a.d == 64) return launch_bf16<64>(a, s);
+    return FC_UNSUPPORTED;
 }

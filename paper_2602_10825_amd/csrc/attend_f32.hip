@@ -48,7 +48,7 @@ template <> struct VecF<4> { typedef float type __attribute__((ext_vector_type(4
 template <> struct VecF<2> { typedef float type __attribute__((ext_vector_type(2))); };
 
 template <int D>
-__global__ __launch_bounds__(kSplitThreads) void attend_f32_kernel(FcAttendArgs a, FcSplitPlan p, float* parts) {
+__global__ __launch_bounds__(kSplitThreads) void attend_f32_kernel(FcAttendArgs a, FcAttendPlan p, float* parts) {
     constexpr int NB = D / 32;           // 32-wide blocks of the value dimension
     constexpr int ROW = D + 4;           // padded LDS rows (floats): 16-byte reads of 32 rows spread over the banks
     typedef float f32x4_t __attribute__((ext_vector_type(4)));
@@ -57,7 +57,7 @@ __global__ __launch_bounds__(kSplitThreads) void attend_f32_kernel(FcAttendArgs 
     __shared__ float m_s[kSplitWaves * kUnitRows], l_s[kSplitWaves * kUnitRows];
     __shared__ Segments sg;
 
-    const SplitItem it = split_item(a, p, blockIdx.x);
+    const SplitItem it = split_item(a, p, valid_blocks(a), blockIdx.x);
     if (!it.ok) return;
     const int hk = it.h / (a.H_q / a.H_k);
     const int tid = threadIdx.x;
@@ -179,13 +179,11 @@ __global__ __launch_bounds__(kSplitThreads) void attend_f32_kernel(FcAttendArgs 
     finish_unit<float, D, ROW>(a, p, it, buf, m_s, l_s, parts);
 }
 
-constexpr int kF32BlockCost = 8;   // in 32-key tiles: one per wavefront
-
 template <int D>
 int launch_f32(const FcAttendArgs& a, hipStream_t s) {
-    FcSplitPlan p = fc_split_plan(a.A, a.L_c, a.L_clean, a.H_q, kF32BlockCost, true);
+    FcAttendPlan p = fc_attend_plan_f32(a.A, a.L_c, a.L_clean, a.H_q, true);
     if (p.parts > 0 && (!a.ws || a.ws_bytes < (size_t)p.parts * fc_split_part_bytes(D)))
-        p = fc_split_plan(a.A, a.L_c, a.L_clean, a.H_q, kF32BlockCost, false);    // no room for partials
+        p = fc_attend_plan_f32(a.A, a.L_c, a.L_clean, a.H_q, false);    // no room for partials
     attend_f32_kernel<D><<<p.grid, kSplitThreads, 0, s>>>(a, p, (float*)a.ws);
     FC_LAUNCH_CHECK();
     if (p.merge_grid > 0) {

@@ -18,60 +18,136 @@ constexpr int kMaxSplits = 32;
 constexpr int kCus = 256;
 constexpr float kNegBig = -1.0e30f;
 
-struct FcSplitPlan {
+constexpr int kWideRows = 256;        // query rows per block of the wide bf16 kernel
+
+struct FcAttendPlan {
     int tiles;                           // 32-row tiles per chunk
     int grid;                            // blocks of the attention launch
     int merge_grid;                      // blocks of the merge launch (0: never needed)
-    int parts;                           // partials the workspace has to hold
-    uint8_t splits[FC_MAX_ACTIVE];       // S for R = 1 .. A
+    int parts;                           // 32-row partials the workspace has to hold
+    uint8_t narrow[FC_MAX_ACTIVE];       // for R = 1 .. A: 32-row blocks (else 256-row blocks)
+    uint8_t splits[FC_MAX_ACTIVE];       // and the number of key ranges S
 };
 
-// S minimises rounds of one block per compute unit, times the key tiles of a round.  A block also
-// costs `block_cost` key tiles of prologue and merging, and the merge launch twice that; a range
-// has at least `block_cost` tiles, and no launch is split into more than four blocks per compute
-// unit (so the partials stay within 18 MB).
-inline int fc_choose_splits(int64_t units, int key_tiles, int block_cost) {
-    int cap = key_tiles / block_cost;
+// Cost of a launch of 32-row blocks, one per compute unit at a time, in the time of one key tile
+// (32 keys, one of the block's 8 wavefronts): rounds of blocks times the tiles of a range.  A
+// block also costs `block_cost` tiles of prologue and merging, and the merge launch twice that; a
+// range has at least 8 tiles, and no launch is split into more than four blocks per compute unit
+// (so the partials stay within 18 MB).
+inline double fc_narrow_cost(int64_t units, int key_tiles, int block_cost, bool may_split, int* splits) {
+    int cap = may_split ? key_tiles / kSplitWaves : 1;
     cap = cap < 1 ? 1 : (cap > kMaxSplits ? kMaxSplits : cap);
-    int best = 1;
     double best_cost = 0.0;
     for (int s = 1; s <= cap; ++s) {
         if (s > 1 && units * s > 4 * kCus) break;
         const double rounds = (double)((units * s + kCus - 1) / kCus);
-        const double cost = rounds * ((double)key_tiles / s + block_cost) + (s > 1 ? 2 * block_cost : 0);
-        if (s == 1 || cost < 0.97 * best_cost) { best = s; best_cost = cost; }
+        const int per_wave = ((key_tiles + s - 1) / s + kSplitWaves - 1) / kSplitWaves;
+        const double cost = rounds * (per_wave * kSplitWaves + block_cost) + (s > 1 ? 2 * block_cost : 0);
+        if (s == 1 || cost < 0.97 * best_cost) { *splits = s; best_cost = cost; }
     }
-    return best;
+    return best_cost;
 }
 
-inline FcSplitPlan fc_split_plan(int A, int L_c, int L_clean, int H_q, int block_cost, bool may_split) {
-    FcSplitPlan p{};
+inline void fc_plan_add(FcAttendPlan& p, int R, int64_t blocks, int64_t merge_units, int S) {
+    p.splits[R - 1] = (uint8_t)S;
+    const int n = (int)((blocks + 7) / 8 * 8);
+    if (n > p.grid) p.grid = n;
+    if (S > 1) {
+        if (merge_units > p.merge_grid) p.merge_grid = (int)merge_units;
+        if (merge_units * S > p.parts) p.parts = (int)(merge_units * S);
+    }
+}
+
+inline FcAttendPlan fc_attend_plan_f32(int A, int L_c, int L_clean, int H_q, bool may_split) {
+    constexpr int kBlockCost = 8;
+    FcAttendPlan p{};
     p.tiles = (L_c + kUnitRows - 1) / kUnitRows;
     const int key_tiles = (int)(((int64_t)L_clean + (int64_t)A * L_c + 31) / 32);
     for (int R = 1; R <= A; ++R) {
         const int64_t units = (int64_t)R * H_q * p.tiles;
-        const int S = may_split ? fc_choose_splits(units, key_tiles, block_cost) : 1;
-        p.splits[R - 1] = (uint8_t)S;
-        const int n = (int)((units * S + 7) / 8 * 8);
-        if (n > p.grid) p.grid = n;
-        if (S > 1) {
-            if (units > p.merge_grid) p.merge_grid = (int)units;
-            if (units * S > p.parts) p.parts = (int)(units * S);
+        int S = 1;
+        fc_narrow_cost(units, key_tiles, kBlockCost, may_split, &S);
+        p.narrow[R - 1] = 1;
+        fc_plan_add(p, R, units * S, units, S);
+    }
+    return p;
+}
+
+// Wide launch: U = R * H_q * ceil(L_c / 256) units.  With fewer units than compute units all of them
+// are split S ways; otherwise only those of the last, partly filled round (per XCD: the units
+// past the last multiple of 32).
+struct FcWideShape { int per, n, full, rem; };   // per XCD: units of one chunk, of all, unsplit, split
+__host__ __device__ inline FcWideShape fc_wide_shape(int R, int items, int S) {
+    FcWideShape w;
+    w.per = (items + 7) / 8;
+    w.n = R * w.per;
+    w.full = S > 1 ? w.n / (kCus / 8) * (kCus / 8) : w.n;
+    w.rem = w.n - w.full;
+    return w;
+}
+
+inline FcAttendPlan fc_attend_plan_bf16(int A, int L_c, int L_clean, int H_q, int d, bool may_split) {
+    // Microseconds, from kernel traces of both forms with forced S (12 x 128: 600 rows on 5200 keys
+    // narrow 40 / wide 50 with S = 4; 1200 rows 91 / 57; 1500 rows on 51689 keys 1040 / 470): a wide
+    // block's 64-key tile, its fixed cost, the merge launch, and a split block's further cost
+    // (short pipeline, writing and merging its partial); an eighth of the time in which a narrow
+    // block's 8 wavefronts take one 32-key tile each, and its fixed cost in those.
+    const double w_tile = d == 128 ? 1.75 : 1.15, w_block = 5.0, w_merge = 5.0, w_parts = d == 128 ? 14.0 : 8.0;
+    const double n_tile = d == 128 ? 0.235 : 0.17;
+    constexpr int kNarrowBlockCost = 11;
+    FcAttendPlan p{};
+    p.tiles = (L_c + kUnitRows - 1) / kUnitRows;
+    const int64_t keys = (int64_t)L_clean + (int64_t)A * L_c;
+    const int items = H_q * ((L_c + kWideRows - 1) / kWideRows);
+    for (int R = 1; R <= A; ++R) {
+        int Sn = 1, Sw = 1;
+        const int64_t units = (int64_t)R * H_q * p.tiles;
+        const double narrow = n_tile * fc_narrow_cost(units, (int)((keys + 31) / 32), kNarrowBlockCost, may_split, &Sn);
+        double wide = 0.0;
+        const int64_t T = (keys + 63) / 64;
+        for (int S = 1; S <= kMaxSplits && (S == 1 || (may_split && T >= 2 * S)); ++S) {
+            const FcWideShape w = fc_wide_shape(R, items, S);
+            const bool flat = S > 1 && w.full == 0;
+            const int64_t split = flat ? (int64_t)R * items * S : (int64_t)8 * w.rem * S;   // blocks of split units
+            if (S > 1 && (split == 0 || split > 2 * kCus)) break;
+            const double rounds_full = (w.full + kCus / 8 - 1) / (kCus / 8);
+            const double rounds = (double)((split + kCus - 1) / kCus);
+            const double cost = rounds_full * (T * w_tile + w_block) +
+                                (S > 1 ? rounds * ((double)T / S * w_tile + w_block + w_parts) + w_merge : 0.0);
+            if (S == 1 || cost < 0.97 * wide) { wide = cost; Sw = S; }
+        }
+        if (narrow < wide) {
+            p.narrow[R - 1] = 1;
+            fc_plan_add(p, R, units * Sn, units, Sn);
+        } else {
+            const FcWideShape w = fc_wide_shape(R, items, Sw);
+            const bool flat = Sw > 1 && w.full == 0;
+            const int64_t split_units = Sw == 1 ? 0 : flat ? (int64_t)R * items : (int64_t)8 * w.rem;
+            fc_plan_add(p, R, flat ? split_units * Sw : (int64_t)8 * w.full + split_units * Sw,
+                        split_units * (kWideRows / kUnitRows), Sw);
         }
     }
     return p;
 }
-// Most partials a launch with these shapes can need, whatever the number of keys.
-inline int fc_split_parts_bound(int A, int L_c, int H_q) {
+
+// Most 32-row partials a launch with these shapes can need, whatever the number of keys.
+inline int64_t fc_split_parts_bound(int A, int L_c, int H_q) {
     const int64_t tiles = (L_c + kUnitRows - 1) / kUnitRows;
+    const int64_t items = (int64_t)H_q * ((L_c + kWideRows - 1) / kWideRows);
     int64_t most = 0;
     for (int R = 1; R <= A; ++R) {
         const int64_t units = (int64_t)R * H_q * tiles;
         int64_t s = 4 * kCus / units;
         if (s > kMaxSplits) s = kMaxSplits;
         if (s > 1 && units * s > most) most = units * s;
+        for (int S = 2; S <= kMaxSplits; ++S) {
+            const FcWideShape w = fc_wide_shape(R, (int)items, S);
+            const int64_t split = w.full == 0 ? (int64_t)R * items * S : (int64_t)8 * w.rem * S;
+            if (split > 2 * kCus) break;
+            if (split * (kWideRows / kUnitRows) > most) most = split * (kWideRows / kUnitRows);
+        }
     }
-    return (int)most;
+    return most;
 }
 // bytes per partial: O [32][d], then m [32] and l [32]
 inline size_t fc_split_part_bytes(int d) { return (size_t)kUnitRows * (d + 2) * sizeof(float); }
@@ -94,17 +170,17 @@ __device__ __forceinline__ int block_of_rank(uint32_t mask, int rank) {
 
 struct SplitItem { int R, S, r, c, h, tile, s; int64_t part; bool ok; };
 
-// Block -> (head, chunk, key range, row tile).  Consecutive blocks go round the 8 XCDs, so item
-// numbers are dealt to them in contiguous runs: the row tiles that read the same keys run on
-// one XCD and share its L2.
-__device__ __forceinline__ SplitItem split_item(const FcAttendArgs& a, const FcSplitPlan& p, int bid) {
+// Block -> (head, chunk, key range, row tile) of a launch of 32-row blocks.  Consecutive blocks go
+// round the 8 XCDs, so item numbers are dealt to them in contiguous runs: the row tiles that read
+// the same keys run on one XCD and share its L2.
+__device__ __forceinline__ SplitItem split_item(const FcAttendArgs& a, const FcAttendPlan& p, uint32_t valid, int bid) {
     SplitItem it;
+    const int R = __popc(valid);
     it.ok = false;
-    const uint32_t valid = valid_blocks(a);
-    it.R = __popc(valid);
-    if (it.R == 0) return it;
-    it.S = p.splits[it.R - 1];
-    const int n = it.R * a.H_q * p.tiles * it.S;
+    if (R == 0) return it;
+    it.R = R;
+    it.S = p.splits[R - 1];
+    const int n = R * a.H_q * p.tiles * it.S;
     const int per = (n + 7) / 8;
     const int slot = bid >> 3;
     const int item = (bid & 7) * per + slot;
@@ -113,13 +189,58 @@ __device__ __forceinline__ SplitItem split_item(const FcAttendArgs& a, const FcS
     int rest = item / p.tiles;
     it.s = rest % it.S;
     rest /= it.S;
-    const int rank = rest % it.R;
-    it.h = rest / it.R;
-    it.part = (int64_t)((it.h * it.R + rank) * p.tiles + it.tile) * it.S + it.s;
+    const int rank = rest % R;
+    it.h = rest / R;
+    it.part = (int64_t)((it.h * R + rank) * p.tiles + it.tile) * it.S + it.s;
     it.r = block_of_rank(valid, rank);
     it.c = a.rec_idx[it.r];
     it.ok = true;
     return it;
+}
+
+// The same for 256-row blocks.  The 32 compute units of an XCD work on the same head and chunk at
+// the same time and share the K/V stream through its L2; heaviest chunk first.  `unit` numbers the
+// split units.
+struct WideItem { int r, h, tile, s, S; int64_t unit; bool ok; };
+__device__ __forceinline__ WideItem wide_unit(const FcAttendArgs& a, uint32_t valid, int items, int rank, int item) {
+    WideItem wi;
+    const int tiles = (a.L_c + kWideRows - 1) / kWideRows;
+    wi.ok = item < items;
+    wi.r = block_of_rank(valid, rank);
+    wi.h = item / tiles;
+    wi.tile = item % tiles;
+    return wi;
+}
+__device__ __forceinline__ WideItem wide_item(const FcAttendArgs& a, const FcAttendPlan& p, uint32_t valid, int bid) {
+    WideItem wi;
+    const int R = __popc(valid);
+    wi.ok = false;
+    const int items = a.H_q * ((a.L_c + kWideRows - 1) / kWideRows);
+    const int S = p.splits[R - 1];
+    const FcWideShape w = fc_wide_shape(R, items, S);
+    const int xcd = bid & 7, slot = bid >> 3;
+    if (S > 1 && w.full == 0) {
+        // all units split: range-major, so that the row tiles of a head that read one range are neighbours
+        const int U = R * items, n = U * S, per = (n + 7) / 8;
+        const int e = xcd * per + slot;
+        if (slot >= per || e >= n) return wi;
+        const int u = e % U;
+        wi = wide_unit(a, valid, items, u / items, u % items);
+        wi.s = e / U; wi.S = S; wi.unit = u;
+        return wi;
+    }
+    int j = slot;
+    if (slot >= w.full) {
+        const int b = slot - w.full;
+        if (S == 1 || b >= w.rem * S) return wi;
+        j = w.full + b % w.rem;
+        wi = wide_unit(a, valid, items, j / w.per, xcd * w.per + j % w.per);
+        wi.s = b / w.rem; wi.S = S; wi.unit = xcd * w.rem + b % w.rem;
+        return wi;
+    }
+    wi = wide_unit(a, valid, items, j / w.per, xcd * w.per + j % w.per);
+    wi.s = 0; wi.S = 1; wi.unit = 0;
+    return wi;
 }
 
 // Visible key segments of chunk c (clean region, then active chunks 0..c; adjacent ones merged)
@@ -158,7 +279,7 @@ __device__ __forceinline__ void store_out(bf16_t* p, float v0, float v1, float v
 // End of a block: the 8 wavefronts' partials (O in LDS, rows of OROW floats; m and l per row)
 // are put together; one thread per 16th of a row.  Writes the result (S = 1) or the partial.
 template <typename T, int D, int OROW>
-__device__ __forceinline__ void finish_unit(const FcAttendArgs& a, const FcSplitPlan& p, const SplitItem& it,
+__device__ __forceinline__ void finish_unit(const FcAttendArgs& a, const FcAttendPlan& p, const SplitItem& it,
                                             const float* o_s, const float* m_s, const float* l_s,
                                             float* parts) {
     constexpr int PER = D / 16;
@@ -201,16 +322,39 @@ __device__ __forceinline__ void finish_unit(const FcAttendArgs& a, const FcSplit
 
 // The S partials of every unit -> out and lse.  One block per unit, 8 threads per row.
 template <typename T, int D>
-__global__ __launch_bounds__(256) void attend_merge_kernel(FcAttendArgs a, FcSplitPlan p, const float* parts) {
+__global__ __launch_bounds__(256) void attend_merge_kernel(FcAttendArgs a, FcAttendPlan p, const float* parts) {
     constexpr int PER = D / 8;
     const uint32_t valid = valid_blocks(a);
     const int R = __popc(valid);
     if (R == 0) return;
     const int S = p.splits[R - 1];
+    if (S == 1) return;
     const int unit = blockIdx.x;
-    if (S == 1 || unit >= R * a.H_q * p.tiles) return;
-    const int tile = unit % p.tiles;
-    const int r = block_of_rank(valid, (unit / p.tiles) % R), h = unit / (p.tiles * R);
+    int tile, r, h;
+    if (p.narrow[R - 1]) {
+        if (unit >= R * a.H_q * p.tiles) return;
+        tile = unit % p.tiles;
+        r = block_of_rank(valid, (unit / p.tiles) % R);
+        h = unit / (p.tiles * R);
+    } else {
+        constexpr int SUB = kWideRows / kUnitRows;
+        const int items = a.H_q * ((a.L_c + kWideRows - 1) / kWideRows);
+        const FcWideShape w = fc_wide_shape(R, items, S);
+        const int u = unit / SUB;
+        WideItem wi;
+        if (w.full == 0) {
+            if (u >= R * items) return;
+            wi = wide_unit(a, valid, items, u / items, u % items);
+        } else {
+            if (u >= 8 * w.rem) return;
+            const int j = w.full + u % w.rem;
+            wi = wide_unit(a, valid, items, j / w.per, (u / w.rem) * w.per + j % w.per);
+        }
+        if (!wi.ok) return;
+        tile = wi.tile * SUB + unit % SUB;
+        r = wi.r;
+        h = wi.h;
+    }
     const int row = threadIdx.x >> 3, c0 = (threadIdx.x & 7) * PER;
     const int row_in_chunk = tile * kUnitRows + row;
     if (row_in_chunk >= a.L_c) return;

@@ -21,11 +21,13 @@ SHAPES = [
     (4, 2, 64, 2, 65, 1025, [1]),             # two ranges and more
     (1, 1, 128, 2, 5, 9000, [0, 1]),          # few rows, long context: the most ranges
     (3, 1, 64, 16, 40, 700, [0, 3, 15]),      # ranges over many segments
-    (8, 8, 128, 4, 321, 64, [0, 1, 2, 3]),    # enough rows that nothing is split over blocks
+    (8, 8, 128, 4, 321, 64, [0, 1, 2, 3]),    # enough rows that fp32 splits nothing over blocks
+    (12, 12, 64, 2, 513, 3000, [0, 1]),       # 256-row units, all of them split (bf16)
+    (24, 24, 64, 2, 1400, 700, [0, 1]),       # more 256-row units than compute units: the last round split
 ]
 
 
-@pytest.mark.parametrize("dtype", ["f32"])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("H_q,H_k,d,A,L_c,L_clean,rec", SHAPES)
 def test_attend_split_edges(dtype, H_q, H_k, d, A, L_c, L_clean, rec):
     wl = synth.Workload("split", dtype, H_q, H_k, d, A, L_c, L_clean, 1)
@@ -34,7 +36,7 @@ def test_attend_split_edges(dtype, H_q, H_k, d, A, L_c, L_clean, rec):
     check_attend(wl, got, ref, res, ref_lse, len(rec))
 
 
-@pytest.mark.parametrize("dtype", ["f32"])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_attend_without_room_for_partials(dtype):
     """A workspace too small for the partials (or none) leaves the keys of a unit in one block."""
     wl = synth.Workload("split", dtype, 2, 2, 64, 2, 48, 4000, 1)
