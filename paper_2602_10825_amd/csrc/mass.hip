@@ -15,8 +15,9 @@
 // merged once per block); cols forms S = Q K^T (one key per lane, the 64 padded rows in
 // registers: the key's sum over rows is in-lane).  fp32: one thread per key with its key in
 // registers, fp32 FMA.
-// Rows are processed in groups of at most 64; groups accumulate into mass in launch
-// order, so the result is deterministic.  No atomics.
+// Rows are processed in groups of 64.  With one group the passes are bound by the reads of K; with
+// more (kernels of their own, further down) by the arithmetic.  fp32 groups accumulate into mass in
+// launch order.  Every sum has a fixed order: the result is deterministic.  No atomics.
 #include "fc_common.hpp"
 
 namespace {
@@ -185,15 +186,15 @@ struct __attribute__((aligned(16))) MassSmem {
 };
 
 template <int D>
-__device__ __forceinline__ void stage_q_bf16(const FcMassArgs& a, int64_t row0, int w0, int nw, int h,
+__device__ __forceinline__ void stage_q_bf16(const FcMassArgs& a, int64_t row0, int h,
                                              bf16_t (*qs)[D + 8]) {
     constexpr int PR = D / 8;   // 16-byte pieces per row
     for (int i = threadIdx.x; i < kRowGroup * PR; i += kNT) {
         const int w = i / PR, c = i % PR;
         uint4 v = make_uint4(0, 0, 0, 0);
-        if (w < nw)
+        if (w < a.W)
             v = *reinterpret_cast<const uint4*>((const bf16_t*)a.q_base +
-                                                ((row0 + w0 + w) * a.H_q + h) * D + c * 8);
+                                                ((row0 + w) * a.H_q + h) * D + c * 8);
         *reinterpret_cast<uint4*>(&qs[w][c * 8]) = v;
     }
 }
@@ -271,7 +272,7 @@ __device__ __forceinline__ void tile_scores_t(const MassSmem<D>& sm, int wave, i
 
 // Pass 1: per observation row, max and sum of exp2 over this block's span of keys.
 template <int D>
-__global__ __launch_bounds__(kNT, 2) void mass_stats_bf16_kernel(FcMassArgs a, int nrg, int np, int tpb,
+__global__ __launch_bounds__(kNT, 2) void mass_stats_bf16_kernel(FcMassArgs a, int np, int tpb,
                                                               float* __restrict__ pm,
                                                               float* __restrict__ pl) {
     int64_t row0;
@@ -287,15 +288,9 @@ __global__ __launch_bounds__(kNT, 2) void mass_stats_bf16_kernel(FcMassArgs a, i
     const int left = a.mass_len - jb;
     const int nt = left >= span ? tpb : (left + kTile - 1) / kTile;
     const float c2 = a.scale * kLog2e;
-    // row groups of 64 observation rows, one after the other: the block re-reads its own key
-    // span (resident in L2 / Infinity Cache after the first group) instead of the whole K
-    for (int rg = 0; rg < nrg; ++rg) {
-    const int w0 = rg * kRowGroup;
-    const int nw = (a.W - w0 < kRowGroup) ? a.W - w0 : kRowGroup;
-    __syncthreads();
     u32x4_native kr[D / 16];
     fetch_ktile<D>(a, kh, jb, kr);             // on its way while the rows are staged
-    stage_q_bf16<D>(a, row0, w0, nw, h, sm.q);
+    stage_q_bf16<D>(a, row0, h, sm.q);
     float m[2] = {kNegBig, kNegBig}, l[2] = {0.f, 0.f};   // of row rb*32 + n over this lane's keys
     for (int t = 0; t < nt; ++t) {
         __syncthreads();
@@ -355,10 +350,9 @@ __global__ __launch_bounds__(kNT, 2) void mass_stats_bf16_kernel(FcMassArgs a, i
         float sum = 0.f;
 #pragma unroll
         for (int i = 0; i < 8; ++i) sum += lp[i] * __builtin_amdgcn_exp2f(mp[i] - mx);
-        pm[(((int64_t)h * nrg + rg) * kRowGroup + q) * np + blockIdx.x] = mx;
-        pl[(((int64_t)h * nrg + rg) * kRowGroup + q) * np + blockIdx.x] = sum;
+        pm[((int64_t)h * kRowGroup + q) * np + blockIdx.x] = mx;
+        pl[((int64_t)h * kRowGroup + q) * np + blockIdx.x] = sum;
     }
-    }   // row groups
 }
 
 // Between the passes: log2-sum-exp of every observation row over all keys, from the blocks'
@@ -405,7 +399,7 @@ __global__ __launch_bounds__(kNT) void mass_lse_bf16_kernel(const float* __restr
 }
 
 template <int D>
-__global__ __launch_bounds__(kNT, 2) void mass_cols_bf16_kernel(FcMassArgs a, int nrg, int tpb,
+__global__ __launch_bounds__(kNT, 2) void mass_cols_bf16_kernel(FcMassArgs a, int tpb,
                                                              const float* __restrict__ lse2) {
     const int hk = gridDim.y - 1 - blockIdx.y;   // the first pass read the last heads last: they may still be cached
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
@@ -425,16 +419,13 @@ __global__ __launch_bounds__(kNT, 2) void mass_cols_bf16_kernel(FcMassArgs a, in
     const int nt = (nkeys + kTile - 1) / kTile;
     const float c2 = a.scale * kLog2e;
     for (int i = tid; i < kSpan; i += kNT) sm.acc[i] = 0.f;
-    for (int rg = 0; rg < nrg; ++rg)
     for (int g = 0; g < G; ++g) {
         const int h = hk * G + g;
-        const int w0 = rg * kRowGroup;
-        const int nw = (a.W - w0 < kRowGroup) ? a.W - w0 : kRowGroup;
         __syncthreads();
         u32x4_native kr[D / 16];
         fetch_ktile<D>(a, kh, jb, kr);         // on its way while the rows are staged
-        stage_q_bf16<D>(a, row0, w0, nw, h, sm.q);
-        if (tid < kRowGroup) sm.lse[tid] = lse2[((int64_t)h * nrg + rg) * kRowGroup + tid];
+        stage_q_bf16<D>(a, row0, h, sm.q);
+        if (tid < kRowGroup) sm.lse[tid] = lse2[h * kRowGroup + tid];
         __syncthreads();
         float lr[2][16];
 #pragma unroll
@@ -466,269 +457,378 @@ __global__ __launch_bounds__(kNT, 2) void mass_cols_bf16_kernel(FcMassArgs a, in
 }
 
 // ---- bf16, more than one group of 64 observation rows (frame-level queries, App. D.2.1) ------
-// With many row groups the product S = Q K^T is real matrix work, and the two kernels above would
-// stage every key tile again for every row group.  Here the loop order is: chunks of kNR row
-// groups, inside them the key tiles of the block's span, inside a tile the row groups of the
-// chunk.  A key tile is staged once per chunk and its MFMA fragments stay in registers across the
-// chunk's row groups; the row groups' queries pass through a double buffer in LDS (the next group
-// is on its way from L2 while the current one is multiplied; asking two groups ahead gained
-// nothing), one barrier per (tile, row group).
-// Both passes form S^T = K Q^T (one observation row per lane): pass 1 keeps the running (max,
-// sum) of the chunk's row groups in registers, pass 2 adds exp2(s - lse) over the chunk's row
-// groups per lane and reduces over the 32 rows of the lanes once per tile and chunk.
-constexpr int kNR = 4;
+// With many row groups the product S^T = K Q^T is real matrix work.  One operand stays in a
+// wavefront's registers for the whole kernel (64 rows x D), the other passes through LDS in tiles
+// of 64 rows that all wavefronts of the block read:
+//   stats  64 observation rows stay, a range of keys passes: per lane one row's running sum
+//   cols   64 keys stay, the rows of all the head's groups pass: per lane 32 keys' running sums
+// Bound: the vector ALU, 24 cycles per 64 scores and pass (fma, exp2, add: 1.0 ms for 24 heads,
+// 1872 rows, 74880 keys) against 16 of matrix products.  So each score costs nothing but those
+// three instructions -- no running maximum: the reference point m of a lane is raised only when a
+// sum of 16 terms exceeds 2^40 -- and the products of a 32-row step are issued between the
+// exponentials of the step before, one set of accumulators filled while the other is read.  Each
+// fragment read from LDS serves two products.  (Key tiles staged once per four row groups, the
+// queries double-buffered in LDS with a barrier per tile and group, a running maximum in pass 1, the
+// products and the vector work of a tile one after the other, before / this, whole call, us: 24 x 128,
+// 1872 rows on 74880 keys 2833 / 1681 (passes 880 and 935); 2 heads on 1, 700 rows on 60000 keys 180
+// / 87; 4 x 128, 2040 rows on 700 keys 459 / 72; 24 x 64, 130 rows on 84240 keys 235 / 212.)
+constexpr int kStream = 64;             // rows of a tile that passes
+constexpr int kRing = 3;                // tiles in LDS: read, complete, being written
+constexpr float kTooBig = 1.0995116e12f;   // 2^40
 
 template <int D>
 struct __attribute__((aligned(16))) MassWideSmem {
-    __attribute__((aligned(16))) bf16_t q[2][kRowGroup][D + 8];
-    union __attribute__((aligned(16))) {
-        __attribute__((aligned(16))) bf16_t k[kTile][D + 8];
-        float merge[2][32][17];
-    };
-    float lse[kNR][kRowGroup];
-    float acc[kSpan];
+    // padded like MassSmem::k
+    __attribute__((aligned(16))) bf16_t x[kRing][kStream][D + 8];
+    float lse[kRing][kStream];          // cols: the rows' normalisers
 };
 
-template <int D>
-__device__ __forceinline__ void fetch_q_wide(const FcMassArgs& a, int64_t row0, int rg, int h,
-                                             u32x4_native (&qr)[kRowGroup * (D / 8) / kNT]) {
-    constexpr int PR = D / 8;
-    const int w0 = rg * kRowGroup;
-    const int nw = (a.W - w0 < kRowGroup) ? a.W - w0 : kRowGroup;
-#pragma unroll
-    for (int i = 0; i < kRowGroup * PR / kNT; ++i) {
-        const int p = threadIdx.x + kNT * i;
-        const int w = p / PR, c = p % PR;
-        const int wc = w < nw ? w : 0;     // padding rows: a valid row is read, zeros are stored
-        u32x4_native v = *reinterpret_cast<const u32x4_native*>(
-            (const bf16_t*)a.q_base + ((row0 + w0 + wc) * a.H_q + h) * D + c * 8);
-        if (w >= nw) v = u32x4_native{0u, 0u, 0u, 0u};
-        qr[i] = v;
-    }
-}
-template <int D>
-__device__ __forceinline__ void store_q_wide(bf16_t (*qs)[D + 8], const u32x4_native (&qr)[kRowGroup * (D / 8) / kNT]) {
-    constexpr int PR = D / 8;
-#pragma unroll
-    for (int i = 0; i < kRowGroup * PR / kNT; ++i) {
-        const int p = threadIdx.x + kNT * i;
-        *reinterpret_cast<u32x4_native*>(&qs[p / PR][(p % PR) * 8]) = qr[i];
-    }
+// A block's barrier that orders LDS accesses only (the loads of the next tile stay in flight).
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(0xC07F);      // lgkmcnt(0)
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
 }
 
-// S^T[key][row] of this wavefront's 32 keys (fragments kf, in registers) and the 64 staged rows:
-// st[rb][r] = key (r/4)*8 + (lane/32)*4 + r%4 of the wavefront's 32, row rb*32 + lane%32.
-template <int D>
-__device__ __forceinline__ void scores_t_wide(const bf16x8_t (&kf)[D / 16], const bf16_t (*qs)[D + 8],
-                                              int lane, f32x16_t (&st)[2]) {
-    const int n = lane & 31, half = lane >> 5;
+// One step: nxt = products of the 32 rows whose fragments start at `cur`, sums += exponentials of
+// `prev`.  `frag` holds the first kAhead fragments of the step on entry and of the next one (at `after`)
+// on exit.  COLS: the resident operand is K and sums[b][r] one key each; else it is Q and sums[b][0..1]
+// are two halves of the sum of row b.  neg[b]: what the exponents are lowered by.
+constexpr int kAhead = 4;
+template <int D, bool COLS, int NS>
+__device__ __forceinline__ void mass_step(f32x16_t (&nxt)[2], const f32x16_t (&prev)[2], const bf16x8_t (&stay)[2][D / 16],
+                                          bf16x8_t (&frag)[kAhead], const bf16_t* cur, const bf16_t* after, float c2,
+                                          const float (&neg)[2], float (&sums)[2][NS]) {
+    constexpr int KS = D / 16, E = 32 / (2 * KS);   // exponentials beside each product
+    f32x16_t zero;
 #pragma unroll
-    for (int rb = 0; rb < 2; ++rb) {
-        f32x16_t c = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+    for (int i = 0; i < 16; ++i) zero[i] = 0.f;
 #pragma unroll
-        for (int kb = 0; kb < D / 16; ++kb) {
-            const bf16x8_t qf = *reinterpret_cast<const bf16x8_t*>(&qs[rb * 32 + n][kb * 16 + half * 8]);
-            c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kb], qf, c, 0, 0, 0);
+    for (int kb = 0; kb < KS; ++kb) {
+        const bf16x8_t fr = frag[kb % kAhead];
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            if constexpr (COLS)
+                nxt[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(stay[b][kb], fr, kb ? nxt[b] : zero, 0, 0, 0);
+            else
+                nxt[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr, stay[b][kb], kb ? nxt[b] : zero, 0, 0, 0);
+            if (b == 1)
+                frag[kb % kAhead] = *reinterpret_cast<const bf16x8_t*>(
+                    kb + kAhead < KS ? cur + (kb + kAhead) * 16 : after + (kb + kAhead - KS) * 16);
+#pragma unroll
+            for (int i = 0; i < E; ++i) {
+                const int e = (2 * kb + b) * E + i, q = e >> 4, r = e & 15;
+                float w = __builtin_amdgcn_exp2f(fmaf(prev[q][r], c2, neg[q]));
+                float& sum = sums[q][COLS ? r : r & 1];
+                sum += w;
+                asm volatile("" : "+v"(sum));       // computed here, next to the matrix products
+            }
+            __builtin_amdgcn_sched_barrier(0);
         }
-        st[rb] = c;
     }
 }
 
-template <int D>
-__global__ __launch_bounds__(kNT, 2) void mass_stats_wide_kernel(FcMassArgs a, int nrg, int np, int tpb,
-                                                              float* __restrict__ pm,
-                                                              float* __restrict__ pl) {
+// The sums of step `prev` (32 keys from `key0` on, of which those below `end` count) once more, from a
+// reference point that fits them: taken for the first keys, ragged ends and sums that became too big.
+__device__ __forceinline__ void stats_raise(const f32x16_t (&prev)[2], int key0, int end, float c2, float (&m)[2],
+                                            float (&l)[2]) {
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+        float tm = kNegBig;
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            if (key0 + (r >> 2) * 8 + (r & 3) < end) tm = fmaxf(tm, prev[b][r] * c2);
+        const float mn = fmaxf(m[b], tm);
+        float acc = 0.f;
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            if (key0 + (r >> 2) * 8 + (r & 3) < end) acc += __builtin_amdgcn_exp2f(fmaf(prev[b][r], c2, -mn));
+        // no real key yet (m and mn both at the floor): keep l = 0
+        l[b] = (mn > kNegBig) ? fmaf(l[b], __builtin_amdgcn_exp2f(m[b] - mn), acc) : 0.f;
+        m[b] = mn;
+    }
+}
+
+// Pass 1.  A block has NW wavefronts of 64 rows and one of S ranges of the keys; consecutive blocks
+// of an XCD share the range (its L2 serves all but the first).
+template <int D, int NW>
+__global__ __launch_bounds__(NW * 64, 2) void mass_stats_wide_kernel(FcMassArgs a, int nrg, int S, float* __restrict__ pm,
+                                                                    float* __restrict__ pl) {
+    constexpr int KS = D / 16, PR = D / 8, NT = NW * 64, LD = kStream * PR / NT;
     int64_t row0;
     if (!resolve_rows(a, row0)) return;
     __shared__ __attribute__((aligned(16))) MassWideSmem<D> sm;
-    const int h = blockIdx.y;
+    const int RB = (nrg + NW - 1) / NW;
+    const int n_items = a.H_q * S * RB, per = (n_items + 7) / 8;
+    const int item = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
+    if ((int)(blockIdx.x >> 3) >= per || item >= n_items) return;
+    const int s = (item / RB) % S, h = item / RB / S;
     const int hk = h / (a.H_q / a.H_k);
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int n = lane & 31, half = lane >> 5;
+    const int rg = (item % RB) * NW + wave;
+    const bool active = rg < nrg;                 // a wavefront without rows only helps to load
     const bf16_t* kh = (const bf16_t*)a.k_cache + (int64_t)hk * a.head_stride;
-    const int span = tpb * kTile;
-    const int jb = blockIdx.x * span;
-    const int left = a.mass_len - jb;
-    const int nt = left >= span ? tpb : (left + kTile - 1) / kTile;
+    const int T = (a.mass_len + kStream - 1) / kStream;
+    const int t_lo = (int)((int64_t)T * s / S), nt = (int)((int64_t)T * (s + 1) / S) - t_lo;
     const float c2 = a.scale * kLog2e;
-    for (int rc = 0; rc < nrg; rc += kNR) {
-        const int ncr = nrg - rc < kNR ? nrg - rc : kNR;
-        float m[kNR][2], l[kNR][2];
+
+    bf16x8_t stay[2][KS];
 #pragma unroll
-        for (int g = 0; g < kNR; ++g) { m[g][0] = m[g][1] = kNegBig; l[g][0] = l[g][1] = 0.f; }
-        u32x4_native kr[D / 16];
-        u32x4_native qr[kRowGroup * (D / 8) / kNT];
-        fetch_ktile<D>(a, kh, jb, kr);
-        fetch_q_wide<D>(a, row0, rc, h, qr);
-        bf16x8_t kf[D / 16];
-        for (int t = 0; t < nt; ++t) {
-            __syncthreads();                       // the last tile's fragments are in registers everywhere
-            store_ktile<D>(sm.k, kr);
-            if (t + 1 < nt) fetch_ktile<D>(a, kh, jb + (t + 1) * kTile, kr);
-            const int key0 = jb + t * kTile + wave * 32 + half * 4;   // + (r/4)*8 + r%4
-            const bool full = key0 - half * 4 + 32 <= a.mass_len;
+    for (int b = 0; b < 2; ++b) {
+        const int w = rg * kRowGroup + b * 32 + n;
+        const bf16_t* qp = (const bf16_t*)a.q_base + ((row0 + (w < a.W ? w : 0)) * a.H_q + h) * D + half * 8;
 #pragma unroll
-            for (int g = 0; g < kNR; ++g) {
-                if (g < ncr) {                     // uniform over the block
-                    const int buf = (t * ncr + g) & 1;
-                    store_q_wide<D>(sm.q[buf], qr);
-                    __syncthreads();
-                    if (g == 0) {
-#pragma unroll
-                        for (int kb = 0; kb < D / 16; ++kb)
-                            kf[kb] = *reinterpret_cast<const bf16x8_t*>(&sm.k[wave * 32 + n][kb * 16 + half * 8]);
-                    }
-                    if (!(t == nt - 1 && g == ncr - 1))     // the next pair's queries, on their way from L2
-                        fetch_q_wide<D>(a, row0, rc + (g + 1) % ncr, h, qr);
-                    f32x16_t st[2];
-                    scores_t_wide<D>(kf, sm.q[buf], lane, st);
-                    if (full) {                    // all 32 keys of this wavefront are real
-#pragma unroll
-                        for (int rb = 0; rb < 2; ++rb) {
-                            float tm = st[rb][0];
-#pragma unroll
-                            for (int r = 1; r < 16; ++r) tm = fmaxf(tm, st[rb][r]);
-                            const float mn = fmaxf(m[g][rb], tm * c2);
-                            float acc = 0.f;
-#pragma unroll
-                            for (int r = 0; r < 16; ++r) acc += __builtin_amdgcn_exp2f(fmaf(st[rb][r], c2, -mn));
-                            l[g][rb] = fmaf(l[g][rb], __builtin_amdgcn_exp2f(m[g][rb] - mn), acc);
-                            m[g][rb] = mn;
-                        }
-                    } else {                       // the ragged end of the scored range
-#pragma unroll
-                        for (int rb = 0; rb < 2; ++rb) {
-                            float tm = kNegBig;
-#pragma unroll
-                            for (int r = 0; r < 16; ++r)
-                                if (key0 + (r >> 2) * 8 + (r & 3) < a.mass_len) tm = fmaxf(tm, st[rb][r] * c2);
-                            const float mn = fmaxf(m[g][rb], tm);
-                            float acc = 0.f;
-#pragma unroll
-                            for (int r = 0; r < 16; ++r)
-                                if (key0 + (r >> 2) * 8 + (r & 3) < a.mass_len)
-                                    acc += __builtin_amdgcn_exp2f(fmaf(st[rb][r], c2, -mn));
-                            // no real key yet (m and mn both at the floor): keep l = 0
-                            l[g][rb] = (mn > kNegBig) ? fmaf(l[g][rb], __builtin_amdgcn_exp2f(m[g][rb] - mn), acc) : 0.f;
-                            m[g][rb] = mn;
-                        }
-                    }
-                }
-            }
+        for (int kb = 0; kb < KS; ++kb) {
+            u32x4_native v = *reinterpret_cast<const u32x4_native*>(qp + kb * 16);
+            if (w >= a.W) v = u32x4_native{0u, 0u, 0u, 0u};
+            stay[b][kb] = __builtin_bit_cast(bf16x8_t, v);
         }
-        // merge the 8 partials of every row (4 wavefronts x 2 lane halves), in a fixed order
+    }
+    u32x4_native kr[LD];
+    auto fetch = [&](int t) {                     // rows past the end re-read the last one and are masked
+        const int j0 = (t_lo + (t < nt ? t : nt - 1)) * kStream;
 #pragma unroll
-        for (int g = 0; g < kNR; ++g) {
-            if (g < ncr) {
-                __syncthreads();
-#pragma unroll
-                for (int rb = 0; rb < 2; ++rb) {
-                    sm.merge[0][rb * 16 + (n >> 1)][(n & 1) * 8 + wave * 2 + half] = m[g][rb];
-                    sm.merge[1][rb * 16 + (n >> 1)][(n & 1) * 8 + wave * 2 + half] = l[g][rb];
-                }
-                __syncthreads();
-                if (tid < kRowGroup) {
-                    const int q = tid;   // rb*32 + n
-                    const float* mp = &sm.merge[0][(q >> 5) * 16 + ((q & 31) >> 1)][(q & 1) * 8];
-                    const float* lp = &sm.merge[1][(q >> 5) * 16 + ((q & 31) >> 1)][(q & 1) * 8];
-                    float mx = kNegBig;
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) mx = fmaxf(mx, mp[i]);
-                    float sum = 0.f;
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) sum += lp[i] * __builtin_amdgcn_exp2f(mp[i] - mx);
-                    pm[(((int64_t)h * nrg + rc + g) * kRowGroup + q) * np + blockIdx.x] = mx;
-                    pl[(((int64_t)h * nrg + rc + g) * kRowGroup + q) * np + blockIdx.x] = sum;
-                }
-            }
+        for (int i = 0; i < LD; ++i) {
+            const int p = tid + NT * i;
+            const int j = j0 + p / PR < a.mass_len ? j0 + p / PR : a.mass_len - 1;
+            kr[i] = *reinterpret_cast<const u32x4_native*>(kh + (int64_t)j * a.tok_stride + (p % PR) * 8);
         }
-        __syncthreads();     // the merge area is the key tile of the next chunk
+    };
+    auto store = [&](int buf) {
+#pragma unroll
+        for (int i = 0; i < LD; ++i) {
+            const int p = tid + NT * i;
+            *reinterpret_cast<u32x4_native*>(&sm.x[buf][p / PR][(p % PR) * 8]) = kr[i];
+        }
+    };
+    fetch(0);
+    store(0);
+    fetch(1);
+    __syncthreads();
+    bf16x8_t frag[kAhead];
+#pragma unroll
+    for (int f = 0; f < kAhead; ++f) frag[f] = *reinterpret_cast<const bf16x8_t*>(&sm.x[0][n][f * 16 + half * 8]);
+    f32x16_t sa[2], sb[2];
+    float m[2] = {kNegBig, kNegBig}, l[2] = {0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < 16; ++i) sb[0][i] = sb[1][i] = 0.f;
+    // after a step: its sums, of the 32 keys of subtile u (counted from the start of the range)
+    auto take = [&](const f32x16_t (&prev)[2], const float (&sums)[2][2], int u) {
+        const float s0 = sums[0][0] + sums[0][1], s1 = sums[1][0] + sums[1][1];
+        const int first = t_lo * kStream + u * 32;
+        if (first + 32 > a.mass_len || __any(!(s0 <= kTooBig) || !(s1 <= kTooBig)))
+            stats_raise(prev, first + half * 4, a.mass_len, c2, m, l);
+        else {
+            l[0] += s0;
+            l[1] += s1;
+        }
+    };
+    int buf = 0;
+    for (int t = 0; t < nt; ++t) {
+        const int nbuf = buf + 1 == kRing ? 0 : buf + 1;
+        // Tile t + 1 goes where tile t - 2 was: the barrier in the middle of t - 1 is behind every
+        // wavefront's last read of that one.  Visible past this tile's barrier, read after it.
+        store(nbuf);
+        fetch(t + 2);
+        const bf16_t* x0 = &sm.x[buf][n][half * 8];
+        const bf16_t* x1 = &sm.x[buf][32 + n][half * 8];
+        if (active) {
+            float sums[2][2] = {{0.f, 0.f}, {0.f, 0.f}};
+            const float neg[2] = {-m[0], -m[1]};
+            mass_step<D, false, 2>(sa, sb, stay, frag, x0, x1, c2, neg, sums);
+            if (t > 0) take(sb, sums, 2 * t - 1);
+        }
+        lds_barrier();
+        if (active) {
+            float sums[2][2] = {{0.f, 0.f}, {0.f, 0.f}};
+            const float neg[2] = {-m[0], -m[1]};
+            mass_step<D, false, 2>(sb, sa, stay, frag, x1, &sm.x[nbuf][n][half * 8], c2, neg, sums);
+            take(sa, sums, 2 * t);
+        }
+        buf = nbuf;
+    }
+    if (!active) return;
+    stats_raise(sb, (t_lo + nt) * kStream - 32 + half * 4, a.mass_len, c2, m, l);
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+        // the two lane halves saw different keys of the same rows
+        const float mo = __shfl_xor(m[b], 32, FC_WAVE), lo = __shfl_xor(l[b], 32, FC_WAVE);
+        const float mx = fmaxf(m[b], mo);
+        const float sum = fmaf(lo, __builtin_amdgcn_exp2f(mo - mx), l[b] * __builtin_amdgcn_exp2f(m[b] - mx));
+        if (half == 0) {
+            const int64_t at = (((int64_t)h * nrg + rg) * kRowGroup + b * 32 + n) * S + s;
+            pm[at] = mx;
+            pl[at] = sum;
+        }
     }
 }
 
-template <int D>
-__global__ __launch_bounds__(kNT, 2) void mass_cols_wide_kernel(FcMassArgs a, int nrg, int tpb,
-                                                             const float* __restrict__ lse2) {
+// Pass 2.  A block has NW wavefronts of 64 keys of one key head.
+template <int D, int NW>
+__global__ __launch_bounds__(NW * 64, 2) void mass_cols_wide_kernel(FcMassArgs a, int nrg, const float* __restrict__ lse2) {
+    constexpr int KS = D / 16, PR = D / 8, NT = NW * 64, LD = kStream * PR / NT;
     const int hk = gridDim.y - 1 - blockIdx.y;   // the first pass read the last heads last
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int n = lane & 31, half = lane >> 5;
-    const int span = tpb * kTile;
-    const int jb = blockIdx.x * span;
-    const int left = a.mass_len - jb;
-    const int nkeys = left >= span ? span : left;
+    const int jb = blockIdx.x * NT;
     int64_t row0;
     if (!resolve_rows(a, row0)) {
-        for (int i = tid; i < nkeys; i += kNT)
-            a.mass[(int64_t)hk * a.mass_len + jb + i] = __uint_as_float(0x7fc00000u);
+        if (jb + tid < a.mass_len) a.mass[(int64_t)hk * a.mass_len + jb + tid] = __uint_as_float(0x7fc00000u);
         return;
     }
     __shared__ __attribute__((aligned(16))) MassWideSmem<D> sm;
     const int G = a.H_q / a.H_k;
     const bf16_t* kh = (const bf16_t*)a.k_cache + (int64_t)hk * a.head_stride;
-    const int nt = (nkeys + kTile - 1) / kTile;
     const float c2 = a.scale * kLog2e;
-    for (int i = tid; i < kSpan; i += kNT) sm.acc[i] = 0.f;
-    for (int gq = 0; gq < G; ++gq) {
-        const int h = hk * G + gq;
-        for (int rc = 0; rc < nrg; rc += kNR) {
-            const int ncr = nrg - rc < kNR ? nrg - rc : kNR;
-            __syncthreads();                       // the previous chunk's normalisers are no longer read
-            for (int i = tid; i < ncr * kRowGroup; i += kNT)
-                sm.lse[i / kRowGroup][i % kRowGroup] = lse2[((int64_t)h * nrg + rc) * kRowGroup + i];
-            u32x4_native kr[D / 16];
-            u32x4_native qr[kRowGroup * (D / 8) / kNT];
-            fetch_ktile<D>(a, kh, jb, kr);
-            fetch_q_wide<D>(a, row0, rc, h, qr);
-            bf16x8_t kf[D / 16];
-            for (int t = 0; t < nt; ++t) {
-                __syncthreads();
-                store_ktile<D>(sm.k, kr);
-                if (t + 1 < nt) fetch_ktile<D>(a, kh, jb + (t + 1) * kTile, kr);
-                float ka[16];                      // this lane's rows' share of the 16 keys it sees
+    const int key0 = jb + wave * 64;
+    const bool active = key0 < a.mass_len;
+
+    bf16x8_t stay[2][KS];
 #pragma unroll
-                for (int r = 0; r < 16; ++r) ka[r] = 0.f;
+    for (int b = 0; b < 2; ++b) {
+        const int j = key0 + b * 32 + n < a.mass_len ? key0 + b * 32 + n : a.mass_len - 1;
 #pragma unroll
-                for (int g = 0; g < kNR; ++g) {
-                    if (g < ncr) {
-                        const int buf = (t * ncr + g) & 1;
-                        store_q_wide<D>(sm.q[buf], qr);
-                        __syncthreads();
-                        if (g == 0) {
+        for (int kb = 0; kb < KS; ++kb)
+            stay[b][kb] = *reinterpret_cast<const bf16x8_t*>(kh + (int64_t)j * a.tok_stride + kb * 16 + half * 8);
+    }
+    const int nt = G * nrg;                       // tiles of 64 rows: query head g = t / nrg, group t % nrg
+    int ft = 0, fg = 0, frg = 0;                  // the tile that is fetched next
+    u32x4_native qr[LD];
+    float lr = 0.f;
+    auto fetch = [&]() {                          // padding rows: a valid row is read, zeros are stored
+        const int h = hk * G + fg;
 #pragma unroll
-                            for (int kb = 0; kb < D / 16; ++kb)
-                                kf[kb] = *reinterpret_cast<const bf16x8_t*>(&sm.k[wave * 32 + n][kb * 16 + half * 8]);
-                        }
-                        if (!(t == nt - 1 && g == ncr - 1))
-                            fetch_q_wide<D>(a, row0, rc + (g + 1) % ncr, h, qr);
-                        f32x16_t st[2];
-                        scores_t_wide<D>(kf, sm.q[buf], lane, st);
+        for (int i = 0; i < LD; ++i) {
+            const int p = tid + NT * i, w = frg * kRowGroup + p / PR;
+            u32x4_native v = *reinterpret_cast<const u32x4_native*>(
+                (const bf16_t*)a.q_base + ((row0 + (w < a.W ? w : 0)) * a.H_q + h) * D + (p % PR) * 8);
+            if (w >= a.W) v = u32x4_native{0u, 0u, 0u, 0u};
+            qr[i] = v;
+        }
+        if (tid < kRowGroup) lr = lse2[((int64_t)h * nrg + frg) * kRowGroup + tid];
+        if (++ft < nt && ++frg == nrg) { frg = 0; ++fg; }      // past the last tile: that one again
+    };
+    auto store = [&](int buf) {
 #pragma unroll
-                        for (int rb = 0; rb < 2; ++rb) {
-                            const float ls = sm.lse[g][rb * 32 + n];   // padding rows: huge, their terms vanish
+        for (int i = 0; i < LD; ++i) {
+            const int p = tid + NT * i;
+            *reinterpret_cast<u32x4_native*>(&sm.x[buf][p / PR][(p % PR) * 8]) = qr[i];
+        }
+        if (tid < kRowGroup) sm.lse[buf][tid] = lr;
+    };
+    fetch();
+    store(0);
+    fetch();
+    __syncthreads();
+    bf16x8_t frag[kAhead];
 #pragma unroll
-                            for (int r = 0; r < 16; ++r) ka[r] += __builtin_amdgcn_exp2f(fmaf(st[rb][r], c2, -ls));
-                        }
-                    }
-                }
-                // over the 32 rows of the lanes (fixed exchange pattern), then one owner per key
+    for (int f = 0; f < kAhead; ++f) frag[f] = *reinterpret_cast<const bf16x8_t*>(&sm.x[0][n][f * 16 + half * 8]);
+    f32x16_t sa[2], sb[2];
+    float sums[2][16];
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    float v = ka[r];
+    for (int i = 0; i < 16; ++i) { sb[0][i] = sb[1][i] = 0.f; sums[0][i] = sums[1][i] = 0.f; }
+    float neg_b = -kPosBig;                       // of the rows in sb: none yet, their terms vanish
+    int buf = 0;
+    for (int t = 0; t < nt; ++t) {
+        const int nbuf = buf + 1 == kRing ? 0 : buf + 1;
+        store(nbuf);                              // as in pass 1
+        fetch();
+        const bf16_t* x0 = &sm.x[buf][n][half * 8];
+        const bf16_t* x1 = &sm.x[buf][32 + n][half * 8];
+        const float neg_a = -sm.lse[buf][n], neg_next = -sm.lse[buf][32 + n];   // padding rows: huge
+        if (active) {
+            const float neg[2] = {neg_b, neg_b};
+            mass_step<D, true, 16>(sa, sb, stay, frag, x0, x1, c2, neg, sums);
+        }
+        lds_barrier();
+        if (active) {
+            const float neg[2] = {neg_a, neg_a};
+            mass_step<D, true, 16>(sb, sa, stay, frag, x1, &sm.x[nbuf][n][half * 8], c2, neg, sums);
+        }
+        neg_b = neg_next;
+        buf = nbuf;
+    }
+    if (!active) return;
+    const float inv = 1.0f / (float)(a.W * G);
 #pragma unroll
-                    for (int o = 1; o < 32; o <<= 1) v += __shfl_xor(v, o, FC_WAVE);
-                    ka[r] = v;
-                }
-                if (n == 0) {
+    for (int b = 0; b < 2; ++b) {
+        float v[16];
 #pragma unroll
-                    for (int r = 0; r < 16; ++r)
-                        sm.acc[t * kTile + wave * 32 + (r >> 2) * 8 + half * 4 + (r & 3)] += ka[r];
-                }
+        for (int r = 0; r < 16; ++r) v[r] = sums[b][r] + __builtin_amdgcn_exp2f(fmaf(sb[b][r], c2, neg_b));
+        // over the 32 rows of the lanes: in the step for lane bit k a lane keeps the half of its
+        // values whose index has bit k like its own; lane u of 16 ends with value u
+#pragma unroll
+        for (int k = 1; k < 16; k <<= 1) {
+            const bool up = n & k;
+#pragma unroll
+            for (int i = 0; i < 8 / k; ++i) {
+                const float keep = up ? v[2 * i + 1] : v[2 * i], give = up ? v[2 * i] : v[2 * i + 1];
+                v[i] = keep + __shfl_xor(give, k, FC_WAVE);
             }
         }
+        const float tot = v[0] + __shfl_xor(v[0], 16, FC_WAVE);
+        const int r = n & 15, j = key0 + b * 32 + (r >> 2) * 8 + half * 4 + (r & 3);
+        if (n < 16 && j < a.mass_len) a.mass[(int64_t)hk * a.mass_len + j] = tot * inv;
     }
-    __syncthreads();
-    const float inv = 1.0f / (float)(a.W * G);
-    for (int i = tid; i < nkeys; i += kNT) a.mass[(int64_t)hk * a.mass_len + jb + i] = sm.acc[i] * inv;
+}
+
+// Wavefronts per block of the two passes and key ranges of the first.  Pass 1: as many wavefronts
+// as there are row groups (a block of 8 fills a compute unit's registers, of two of 2 its LDS holds
+// three), then the number of ranges whose last round of blocks is fullest, a block's prologue and
+// the merge of its partial counted as 8 tiles.  A range has at least 8 tiles: the partials fit the
+// workspace, which has room for one per 512 keys.  Pass 2: the widest block that still leaves two
+// per compute unit.
+struct MassWidePlan { int nw1, S, nw2; };
+inline MassWidePlan mass_wide_plan(int H_q, int H_k, int nrg, int mass_len) {
+    MassWidePlan p;
+    p.nw1 = nrg > 4 ? 8 : (nrg > 2 ? 4 : 2);
+    const int64_t slots = 256 * (p.nw1 == 8 ? 1 : (p.nw1 == 4 ? 2 : 3));
+    const int64_t units = (int64_t)H_q * ((nrg + p.nw1 - 1) / p.nw1);
+    const int T = (mass_len + kStream - 1) / kStream;
+    p.S = 1;
+    double best = 0.0;
+    for (int S = 1; S == 1 || (S <= 128 && T >= 8 * S); ++S) {
+        const double cost = (double)((units * S + slots - 1) / slots) * ((double)((T + S - 1) / S) + 8.0);
+        if (S == 1 || cost < 0.99 * best) { best = cost; p.S = S; }
+    }
+    p.nw2 = 8;
+    while (p.nw2 > 2 && (int64_t)H_k * ((mass_len + p.nw2 * 64 - 1) / (p.nw2 * 64)) < 512) p.nw2 /= 2;
+    return p;
+}
+
+template <int D, int NW>
+int launch_stats_wide(const FcMassArgs& a, int nrg, int S, float* pm, float* pl, hipStream_t s) {
+    const int64_t items = (int64_t)a.H_q * S * ((nrg + NW - 1) / NW);
+    mass_stats_wide_kernel<D, NW><<<(unsigned)((items + 7) / 8 * 8), NW * 64, 0, s>>>(a, nrg, S, pm, pl);
+    FC_LAUNCH_CHECK();
+    return FC_OK;
+}
+template <int D, int NW>
+int launch_cols_wide(const FcMassArgs& a, int nrg, const float* lse2, hipStream_t s) {
+    mass_cols_wide_kernel<D, NW><<<dim3((a.mass_len + NW * 64 - 1) / (NW * 64), a.H_k), NW * 64, 0, s>>>(a, nrg, lse2);
+    FC_LAUNCH_CHECK();
+    return FC_OK;
+}
+template <int D>
+int launch_wide(const FcMassArgs& a, hipStream_t s) {
+    const int nrg = (a.W + kRowGroup - 1) / kRowGroup;
+    const MassWidePlan p = mass_wide_plan(a.H_q, a.H_k, nrg, a.mass_len);
+    float* pm = reinterpret_cast<float*>(a.ws);
+    float* pl = pm + (size_t)a.H_q * nrg * kRowGroup * p.S;
+    float* lse2 = pl + (size_t)a.H_q * nrg * kRowGroup * p.S;
+    int st = p.nw1 == 8   ? launch_stats_wide<D, 8>(a, nrg, p.S, pm, pl, s)
+             : p.nw1 == 4 ? launch_stats_wide<D, 4>(a, nrg, p.S, pm, pl, s)
+                          : launch_stats_wide<D, 2>(a, nrg, p.S, pm, pl, s);
+    if (st != FC_OK) return st;
+    mass_lse_bf16_kernel<<<dim3(nrg, a.H_q), kNT, 0, s>>>(pm, pl, nrg, p.S, a.W, lse2);
+    FC_LAUNCH_CHECK();
+    return p.nw2 == 8   ? launch_cols_wide<D, 8>(a, nrg, lse2, s)
+           : p.nw2 == 4 ? launch_cols_wide<D, 4>(a, nrg, lse2, s)
+                        : launch_cols_wide<D, 2>(a, nrg, lse2, s);
 }
 
 // Tiles per block, 4 to 8: blocks of one launch take about the same time, so they run in rounds
@@ -750,23 +850,17 @@ inline int mass_tiles_per_block(int mass_len, int heads) {
 
 template <int D>
 int launch_bf16(const FcMassArgs& a, hipStream_t s) {
+    if (a.W > kRowGroup) return launch_wide<D>(a, s);
     const int tpb = mass_tiles_per_block(a.mass_len, a.H_q);
     const int np = (a.mass_len + tpb * kTile - 1) / (tpb * kTile);
-    const int nrg = (a.W + kRowGroup - 1) / kRowGroup;
     float* pm = reinterpret_cast<float*>(a.ws);
-    float* pl = pm + (size_t)a.H_q * nrg * kRowGroup * np;
-    float* lse2 = pl + (size_t)a.H_q * nrg * kRowGroup * np;
-    if (nrg > 1)
-        mass_stats_wide_kernel<D><<<dim3(np, a.H_q), kNT, 0, s>>>(a, nrg, np, tpb, pm, pl);
-    else
-        mass_stats_bf16_kernel<D><<<dim3(np, a.H_q), kNT, 0, s>>>(a, nrg, np, tpb, pm, pl);
+    float* pl = pm + (size_t)a.H_q * kRowGroup * np;
+    float* lse2 = pl + (size_t)a.H_q * kRowGroup * np;
+    mass_stats_bf16_kernel<D><<<dim3(np, a.H_q), kNT, 0, s>>>(a, np, tpb, pm, pl);
     FC_LAUNCH_CHECK();
-    mass_lse_bf16_kernel<<<dim3(nrg, a.H_q), kNT, 0, s>>>(pm, pl, nrg, np, a.W, lse2);
+    mass_lse_bf16_kernel<<<dim3(1, a.H_q), kNT, 0, s>>>(pm, pl, 1, np, a.W, lse2);
     FC_LAUNCH_CHECK();
-    if (nrg > 1)
-        mass_cols_wide_kernel<D><<<dim3(np, a.H_k), kNT, 0, s>>>(a, nrg, tpb, lse2);
-    else
-        mass_cols_bf16_kernel<D><<<dim3(np, a.H_k), kNT, 0, s>>>(a, nrg, tpb, lse2);
+    mass_cols_bf16_kernel<D><<<dim3(np, a.H_k), kNT, 0, s>>>(a, tpb, lse2);
     FC_LAUNCH_CHECK();
     return FC_OK;
 }
