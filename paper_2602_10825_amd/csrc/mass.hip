@@ -5,47 +5,28 @@
 //                  softmax_j(q_w . k_j * scale), the softmax running over j < mass_len only.
 //
 // Two passes over the keys (the softmax normaliser of a row is known only after all keys):
-//   stats  per-row running (max, sum-exp) per block of keys             -> partials
+//   stats  per-row (reference point, sum of exp2 above it) per range of keys -> partials
 //   lse    (between them) per row: the partials merged, fixed order     -> log2-sum-exp
 //   cols   per key: sum over rows of exp2(s - lse), fixed order         -> mass
-// bf16: both passes use v_mfma_f32_32x32x16_bf16 on 128-key tiles staged through LDS by
-// coalesced 16-byte loads (the passes are bound by the two reads of K), each in the
+// Both passes run on the matrix cores.  bf16 with one group of 64 rows: 128-key tiles staged through
+// LDS by coalesced 16-byte loads (the passes are bound by the two reads of K), each in the
 // orientation that makes its reduction in-lane: stats forms S^T = K Q^T (one row per lane,
 // its keys in registers: the row's max and sum need no exchange, 8 partials per row are
 // merged once per block); cols forms S = Q K^T (one key per lane, the 64 padded rows in
-// registers: the key's sum over rows is in-lane).  fp32: one thread per key with its key in
-// registers, fp32 FMA.
-// Rows are processed in groups of 64.  With one group the passes are bound by the reads of K; with
-// more (kernels of their own, further down) by the arithmetic.  fp32 groups accumulate into mass in
-// launch order.  Every sum has a fixed order: the result is deterministic.  No atomics.
+// registers: the key's sum over rows is in-lane).  bf16 with more rows, and fp32, are bound by
+// arithmetic and have kernels of their own.  Every sum has a fixed order: the result is
+// deterministic.  No atomics.
 #include "fc_common.hpp"
 
 namespace {
 
-constexpr int kKeys = 256;   // keys (threads) per block
 constexpr int kRowGroup = 64;
+constexpr int kNT = 256;
+constexpr float kPosBig = 1.0e30f;
 constexpr float kNegBig = -1.0e30f;
 constexpr float kLog2e = 1.4426950408889634f;
 
-template <typename T, int D>
-__device__ __forceinline__ void load_key(const T* kp, float (&k)[D]) {
-    constexpr int V = Elem<T>::kVec;
-    const uint4* p = reinterpret_cast<const uint4*>(kp);
-#pragma unroll
-    for (int e = 0; e < D / V; ++e) {
-        float f[V];
-        unpack16(p[e], f, T());
-#pragma unroll
-        for (int u = 0; u < V; ++u) k[e * V + u] = f[u];
-    }
-}
-
-// Row w of the current group, head h -> pointer; handles the "tail of the last compact
-// block" addressing when n_rec is given.
-struct RowSrc {
-    const void* q; int64_t row0; int H_q; int D;
-};
-
+// First observation row; handles the "tail of the last compact block" addressing when n_rec is given.
 __device__ __forceinline__ bool resolve_rows(const FcMassArgs& a, int64_t& row0) {
     if (a.n_rec) {
         const int R = *a.n_rec;
@@ -57,120 +38,212 @@ __device__ __forceinline__ bool resolve_rows(const FcMassArgs& a, int64_t& row0)
     return true;
 }
 
-template <typename T, int D>
-__device__ __forceinline__ void stage_rows(const FcMassArgs& a, int64_t row0, int w0, int nw,
-                                           int h, float (*qs)[D]) {
-    for (int i = threadIdx.x; i < nw * D; i += kKeys) {
-        const int w = i / D, e = i % D;
-        const T* src = (const T*)a.q_base + ((row0 + w0 + w) * a.H_q + h) * D + e;
-        qs[w][e] = Elem<T>::to_f32(*src);
-    }
+// ---- fp32: on the fp32 matrix cores --------------------------------------------------
+// v_mfma_f32_32x32x2_f32, operands read straight into registers in their own layout: lane (half, n)
+// holds elements 8 j + 4 half .. + 4 of row n, and the product of step (j, i) contracts over the
+// two elements 8 j + i and 8 j + 4 + i.  Both passes form S^T = K Q^T, one observation row per lane.
+// A wavefront keeps 32 rows (pass 1) or 32 keys (pass 2) and passes over the others.  Bound by the
+// matrix cores (64 cycles a product) in large calls and by latency in small ones, where one thread per
+// key with a wavefront reduction per row was a serial chain of all the rows.  Whole call, us before /
+// now: four query heads on one x 64, 50 rows on 512 keys 132 / 18; 12 x 128, 50 rows on 4000 keys 135 /
+// 54; 2 x 128, 600 rows on 9000 keys 1723 / 122; 4 x 128, 2040 rows on 700 keys 4826 / 88; one x 64, 64
+// rows on 40000 keys 266 / 31.
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+typedef float f32x16_t __attribute__((ext_vector_type(16)));
+constexpr int kF32Waves = 8;
+
+template <int D>
+__device__ __forceinline__ void load_rows_f32(const float* row, int half, f32x4_t (&f)[D / 8]) {
+#pragma unroll
+    for (int j = 0; j < D / 8; ++j) f[j] = *reinterpret_cast<const f32x4_t*>(row + 8 * j + 4 * half);
+}
+template <int D>
+__device__ __forceinline__ f32x16_t scores_f32(const f32x4_t (&k)[D / 8], const f32x4_t (&q)[D / 8]) {
+    f32x16_t s;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) s[i] = 0.f;
+#pragma unroll
+    for (int j = 0; j < D / 8; ++j)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) s = __builtin_amdgcn_mfma_f32_32x32x2f32(k[j][i], q[j][i], s, 0, 0, 0);
+    return s;
 }
 
-template <typename T, int D>
-__global__ __launch_bounds__(kKeys) void mass_stats_kernel(FcMassArgs a, int w0, int nw, int np,
-                                                           float* __restrict__ pm,
-                                                           float* __restrict__ pl) {
+// Pass 1: a block is 32 rows of one head and one of S key ranges; its wavefronts take every eighth 32-key
+// tile and are merged through LDS.
+template <int D>
+__global__ __launch_bounds__(kF32Waves * 64, 2) void mass_stats_f32_kernel(FcMassArgs a, int nrg, int S, float* __restrict__ pm,
+                                                                          float* __restrict__ pl) {
     int64_t row0;
     if (!resolve_rows(a, row0)) return;
-    const int h = blockIdx.y;
+    const int s = blockIdx.x, rt = blockIdx.y, h = blockIdx.z;
     const int hk = h / (a.H_q / a.H_k);
-    const int tid = threadIdx.x;
-    const int j = blockIdx.x * kKeys + tid;
-    const bool ok = j < a.mass_len;
-    __shared__ float qs[kRowGroup][D];
-    stage_rows<T, D>(a, row0, w0, nw, h, qs);
-    float k[D];
-    load_key<T, D>((const T*)a.k_cache + (int64_t)hk * a.head_stride +
-                       (int64_t)(ok ? j : a.mass_len - 1) * a.tok_stride, k);
-    __syncthreads();
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int n = lane & 31, half = lane >> 5;
+    const float* kh = (const float*)a.k_cache + (int64_t)hk * a.head_stride;
     const float c2 = a.scale * kLog2e;
-    const int wave = tid / FC_WAVE, lane = tid % FC_WAVE;
-    const int slot = blockIdx.x * (kKeys / FC_WAVE) + wave;
-    for (int w = 0; w < nw; ++w) {
-        float s = 0.f;
+    const int T = (a.mass_len + 31) / 32;
+    const int t_end = (int)((int64_t)T * (s + 1) / S);
+    const int w = rt * 32 + n < a.W ? rt * 32 + n : a.W - 1;     // padding rows: computed, not used
+    f32x4_t q[D / 8], k[D / 8];
+    auto load_k = [&](int t) {
+        const int j = t * 32 + n < a.mass_len ? t * 32 + n : a.mass_len - 1;
+        load_rows_f32<D>(kh + (int64_t)j * a.tok_stride, half, k);
+    };
+    int t = (int)((int64_t)T * s / S) + wave;
+    if (t < t_end) load_k(t);
+    load_rows_f32<D>((const float*)a.q_base + ((row0 + w) * a.H_q + h) * D, half, q);
+    float m = kNegBig, l = 0.f;
+    for (; t < t_end; t += kF32Waves) {
+        const f32x16_t st = scores_f32<D>(k, q);
+        if (t + kF32Waves < t_end) load_k(t + kF32Waves);
+        const int key0 = t * 32 + half * 4;
+        const bool full = t * 32 + 32 <= a.mass_len;
+        float tm = kNegBig;
 #pragma unroll
-        for (int e = 0; e < D; ++e) s = fmaf(k[e], qs[w][e], s);
-        s = ok ? s * c2 : kNegBig;
-        const float mx = wave_max_all(s);
-        const float sum = wave_sum_all(__builtin_amdgcn_exp2f(s - mx));
-        if (lane == 0) {
-            pm[((int64_t)h * kRowGroup + w) * np + slot] = mx;
-            pl[((int64_t)h * kRowGroup + w) * np + slot] = sum;
+        for (int r = 0; r < 16; ++r)
+            if (full || key0 + (r >> 2) * 8 + (r & 3) < a.mass_len) tm = fmaxf(tm, st[r] * c2);
+        const float mn = fmaxf(m, tm);
+        float acc = 0.f;
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            if (full || key0 + (r >> 2) * 8 + (r & 3) < a.mass_len) acc += __builtin_amdgcn_exp2f(fmaf(st[r], c2, -mn));
+        // no real key yet (m and mn both at the floor): keep l = 0
+        l = (mn > kNegBig) ? fmaf(l, __builtin_amdgcn_exp2f(m - mn), acc) : 0.f;
+        m = mn;
+    }
+    __shared__ float merge[2][2 * kF32Waves][32];
+    merge[0][wave * 2 + half][n] = m;
+    merge[1][wave * 2 + half][n] = l;
+    __syncthreads();
+    if (tid < 32) {
+        float mx = kNegBig, sum = 0.f;
+#pragma unroll
+        for (int i = 0; i < 2 * kF32Waves; ++i) mx = fmaxf(mx, merge[0][i][tid]);
+#pragma unroll
+        for (int i = 0; i < 2 * kF32Waves; ++i) sum = fmaf(merge[1][i][tid], __builtin_amdgcn_exp2f(merge[0][i][tid] - mx), sum);
+        const int64_t at = ((int64_t)h * nrg * kRowGroup + rt * 32 + tid) * S + s;
+        pm[at] = mx;
+        pl[at] = sum;
+    }
+}
+
+// Sums over the 32 lanes n of 16 values each: in the step for lane bit k a lane keeps the half of
+// its values whose index has bit k like its own; lane n ends with the sum of value n % 16.
+__device__ __forceinline__ float lanes_sum_scatter(float (&v)[16], int n) {
+#pragma unroll
+    for (int k = 1; k < 16; k <<= 1) {
+        const bool up = n & k;
+#pragma unroll
+        for (int i = 0; i < 8 / k; ++i) {
+            const float keep = up ? v[2 * i + 1] : v[2 * i], give = up ? v[2 * i] : v[2 * i + 1];
+            v[i] = keep + __shfl_xor(give, k, FC_WAVE);
         }
     }
+    return v[0] + __shfl_xor(v[0], 16, FC_WAVE);
 }
 
-__global__ __launch_bounds__(kRowGroup) void mass_lse_kernel(const float* __restrict__ pm,
-                                                             const float* __restrict__ pl, int nw,
-                                                             int np, float* __restrict__ lse2,
-                                                             const int32_t* n_rec,
-                                                             const int32_t* rec_idx, int A) {
-    if (n_rec) {
-        const int R = *n_rec;
-        if (R <= 0 || R > A || rec_idx[R - 1] != A - 1) return;
-    }
-    const int h = blockIdx.x, w = threadIdx.x;
-    if (w >= nw) return;
-    const float* m = pm + ((int64_t)h * kRowGroup + w) * np;
-    const float* l = pl + ((int64_t)h * kRowGroup + w) * np;
-    float mx = kNegBig;
-    for (int i = 0; i < np; ++i) mx = fmaxf(mx, m[i]);
-    float sum = 0.f;
-    for (int i = 0; i < np; ++i) sum += l[i] * __builtin_amdgcn_exp2f(m[i] - mx);
-    lse2[h * kRowGroup + w] = mx + __builtin_amdgcn_logf(sum);
-}
-
-template <typename T, int D>
-__global__ __launch_bounds__(kKeys) void mass_cols_kernel(FcMassArgs a, int w0, int nw,
-                                                          const float* __restrict__ lse2,
-                                                          int first) {
-    const int hk = blockIdx.y;
-    const int tid = threadIdx.x;
-    const int j = blockIdx.x * kKeys + tid;
-    const bool ok = j < a.mass_len;
+// Pass 2: a wavefront keeps 32 keys; `parts` wavefronts of a block share the 32-row tiles of the head's
+// groups (every parts-th each) and are added up in order.
+template <int D>
+__global__ __launch_bounds__(kF32Waves * 64, 2) void mass_cols_f32_kernel(FcMassArgs a, int nrg, int parts,
+                                                                         const float* __restrict__ lse2) {
+    const int hk = blockIdx.y, kb = kF32Waves / parts;             // key blocks of 32 per block
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int n = lane & 31, half = lane >> 5;
+    const int jb = blockIdx.x * kb * 32;
     int64_t row0;
     if (!resolve_rows(a, row0)) {
-        if (ok) a.mass[(int64_t)hk * a.mass_len + j] = __uint_as_float(0x7fc00000u);
+        if (tid < kb * 32 && jb + tid < a.mass_len) a.mass[(int64_t)hk * a.mass_len + jb + tid] = __uint_as_float(0x7fc00000u);
         return;
     }
+    __shared__ float merge[kF32Waves][32];
     const int G = a.H_q / a.H_k;
-    __shared__ float qs[kRowGroup][D];
-    float k[D];
-    load_key<T, D>((const T*)a.k_cache + (int64_t)hk * a.head_stride +
-                       (int64_t)(ok ? j : a.mass_len - 1) * a.tok_stride, k);
+    const int part = wave / kb, key0 = jb + (wave % kb) * 32;
     const float c2 = a.scale * kLog2e;
-    float acc = 0.f;
-    for (int g = 0; g < G; ++g) {
-        const int h = hk * G + g;
-        __syncthreads();
-        stage_rows<T, D>(a, row0, w0, nw, h, qs);
-        __syncthreads();
-        for (int w = 0; w < nw; ++w) {
-            float s = 0.f;
+    const int per = (a.W + 31) / 32, nt = G * per;                 // tiles of 32 rows: query head t / per
+    float sums[16];
 #pragma unroll
-            for (int e = 0; e < D; ++e) s = fmaf(k[e], qs[w][e], s);
-            acc += __builtin_amdgcn_exp2f(s * c2 - lse2[h * kRowGroup + w]);
-        }
+    for (int r = 0; r < 16; ++r) sums[r] = 0.f;
+    f32x4_t k[D / 8], q[D / 8];
+    float ls = 0.f;
+    auto load_q = [&](int t) {
+        const int h = hk * G + t / per, w = t % per * 32 + n;
+        load_rows_f32<D>((const float*)a.q_base + ((row0 + (w < a.W ? w : a.W - 1)) * a.H_q + h) * D, half, q);
+        ls = lse2[(int64_t)h * nrg * kRowGroup + w];               // padding rows: huge, their terms vanish
+    };
+    if (part < nt) load_q(part);
+    {
+        const int j = key0 + n < a.mass_len ? key0 + n : a.mass_len - 1;
+        load_rows_f32<D>((const float*)a.k_cache + (int64_t)hk * a.head_stride + (int64_t)j * a.tok_stride, half, k);
     }
-    if (ok) {
-        const float contrib = acc / (float)(a.W * G);
-        float* dst = a.mass + (int64_t)hk * a.mass_len + j;
-        *dst = first ? contrib : *dst + contrib;
+    for (int t = part; t < nt; t += parts) {
+        const f32x16_t st = scores_f32<D>(k, q);
+        const float neg = -ls;
+        if (t + parts < nt) load_q(t + parts);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sums[r] += __builtin_amdgcn_exp2f(fmaf(st[r], c2, neg));
+    }
+    const float v = lanes_sum_scatter(sums, n);
+    if (n < 16) merge[wave][(n >> 2) * 8 + half * 4 + (n & 3)] = v;
+    __syncthreads();
+    if (tid < kb * 32 && jb + tid < a.mass_len) {
+        float tot = 0.f;
+        for (int p = 0; p < parts; ++p) tot += merge[p * kb + (tid >> 5)][tid & 31];
+        a.mass[(int64_t)hk * a.mass_len + jb + tid] = tot / (float)(a.W * G);
     }
 }
 
+// Between the passes: log2-sum-exp of every observation row over all keys, from the blocks'
+// partials.  One block per (row group, query head); four lanes per row take every fourth
+// partial (loads batched four deep) and merge in a fixed order.  Padding rows get a huge
+// normaliser: their terms vanish.
+__global__ __launch_bounds__(kNT) void mass_lse_kernel(const float* __restrict__ pm,
+                                                            const float* __restrict__ pl, int nrg, int np,
+                                                            int W, float* __restrict__ lse2) {
+    const int rg = blockIdx.x, h = blockIdx.y, tid = threadIdx.x;
+    const int w0 = rg * kRowGroup;
+    const int nw = (W - w0 < kRowGroup) ? W - w0 : kRowGroup;
+    const int row = tid >> 2, part = tid & 3;
+    const float* m = pm + (((int64_t)h * nrg + rg) * kRowGroup + row) * np;
+    const float* l = pl + (((int64_t)h * nrg + rg) * kRowGroup + row) * np;
+    float mx = kNegBig, sum = 0.f;
+    for (int i0 = part; i0 < np; i0 += 16) {
+        float mi[4], li[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int i = i0 + 4 * u;
+            mi[u] = i < np ? m[i] : kNegBig;
+            li[u] = i < np ? l[i] : 0.f;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const float mn = fmaxf(mx, mi[u]);
+            sum = sum * __builtin_amdgcn_exp2f(mx - mn) + li[u] * __builtin_amdgcn_exp2f(mi[u] - mn);
+            mx = mn;
+        }
+    }
+#pragma unroll
+    for (int o = 1; o < 4; o <<= 1) {
+        const float mo = __shfl_xor(mx, o, FC_WAVE), so = __shfl_xor(sum, o, FC_WAVE);
+        const float mn = fmaxf(mx, mo);
+        // the lower lane's term first on both sides, so partners agree bit for bit
+        const float lo = (part & o) ? so * __builtin_amdgcn_exp2f(mo - mn) : sum * __builtin_amdgcn_exp2f(mx - mn);
+        const float hi = (part & o) ? sum * __builtin_amdgcn_exp2f(mx - mn) : so * __builtin_amdgcn_exp2f(mo - mn);
+        sum = lo + hi;
+        mx = mn;
+    }
+    if (part == 0)
+        lse2[((int64_t)h * nrg + rg) * kRowGroup + row] = row < nw ? mx + __builtin_amdgcn_logf(sum) : kPosBig;
+}
 
 // ---- bf16: matrix-core passes -------------------------------------------------------
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef float f32x16_t __attribute__((ext_vector_type(16)));
 
 constexpr int kTile = 128;            // keys per tile: 4 wavefronts x 32 keys
 constexpr int kTilesPerBlock = 8;      // at most
 constexpr int kMinTilesPerBlock = 4;
 constexpr int kSpan = kTile * kTilesPerBlock;
-constexpr int kNT = 256;
-constexpr float kPosBig = 1.0e30f;
 
 template <int D>
 struct __attribute__((aligned(16))) MassSmem {
@@ -353,49 +426,6 @@ __global__ __launch_bounds__(kNT, 2) void mass_stats_bf16_kernel(FcMassArgs a, i
         pm[((int64_t)h * kRowGroup + q) * np + blockIdx.x] = mx;
         pl[((int64_t)h * kRowGroup + q) * np + blockIdx.x] = sum;
     }
-}
-
-// Between the passes: log2-sum-exp of every observation row over all keys, from the blocks'
-// partials.  One block per (row group, query head); four lanes per row take every fourth
-// partial (loads batched four deep) and merge in a fixed order.  Padding rows get a huge
-// normaliser: their terms vanish.
-__global__ __launch_bounds__(kNT) void mass_lse_bf16_kernel(const float* __restrict__ pm,
-                                                            const float* __restrict__ pl, int nrg, int np,
-                                                            int W, float* __restrict__ lse2) {
-    const int rg = blockIdx.x, h = blockIdx.y, tid = threadIdx.x;
-    const int w0 = rg * kRowGroup;
-    const int nw = (W - w0 < kRowGroup) ? W - w0 : kRowGroup;
-    const int row = tid >> 2, part = tid & 3;
-    const float* m = pm + (((int64_t)h * nrg + rg) * kRowGroup + row) * np;
-    const float* l = pl + (((int64_t)h * nrg + rg) * kRowGroup + row) * np;
-    float mx = kNegBig, sum = 0.f;
-    for (int i0 = part; i0 < np; i0 += 16) {
-        float mi[4], li[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int i = i0 + 4 * u;
-            mi[u] = i < np ? m[i] : kNegBig;
-            li[u] = i < np ? l[i] : 0.f;
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const float mn = fmaxf(mx, mi[u]);
-            sum = sum * __builtin_amdgcn_exp2f(mx - mn) + li[u] * __builtin_amdgcn_exp2f(mi[u] - mn);
-            mx = mn;
-        }
-    }
-#pragma unroll
-    for (int o = 1; o < 4; o <<= 1) {
-        const float mo = __shfl_xor(mx, o, FC_WAVE), so = __shfl_xor(sum, o, FC_WAVE);
-        const float mn = fmaxf(mx, mo);
-        // the lower lane's term first on both sides, so partners agree bit for bit
-        const float lo = (part & o) ? so * __builtin_amdgcn_exp2f(mo - mn) : sum * __builtin_amdgcn_exp2f(mx - mn);
-        const float hi = (part & o) ? sum * __builtin_amdgcn_exp2f(mx - mn) : so * __builtin_amdgcn_exp2f(mo - mn);
-        sum = lo + hi;
-        mx = mn;
-    }
-    if (part == 0)
-        lse2[((int64_t)h * nrg + rg) * kRowGroup + row] = row < nw ? mx + __builtin_amdgcn_logf(sum) : kPosBig;
 }
 
 template <int D>
@@ -759,18 +789,7 @@ __global__ __launch_bounds__(NW * 64, 2) void mass_cols_wide_kernel(FcMassArgs a
         float v[16];
 #pragma unroll
         for (int r = 0; r < 16; ++r) v[r] = sums[b][r] + __builtin_amdgcn_exp2f(fmaf(sb[b][r], c2, neg_b));
-        // over the 32 rows of the lanes: in the step for lane bit k a lane keeps the half of its
-        // values whose index has bit k like its own; lane u of 16 ends with value u
-#pragma unroll
-        for (int k = 1; k < 16; k <<= 1) {
-            const bool up = n & k;
-#pragma unroll
-            for (int i = 0; i < 8 / k; ++i) {
-                const float keep = up ? v[2 * i + 1] : v[2 * i], give = up ? v[2 * i] : v[2 * i + 1];
-                v[i] = keep + __shfl_xor(give, k, FC_WAVE);
-            }
-        }
-        const float tot = v[0] + __shfl_xor(v[0], 16, FC_WAVE);
+        const float tot = lanes_sum_scatter(v, n);
         const int r = n & 15, j = key0 + b * 32 + (r >> 2) * 8 + half * 4 + (r & 3);
         if (n < 16 && j < a.mass_len) a.mass[(int64_t)hk * a.mass_len + j] = tot * inv;
     }
@@ -824,7 +843,7 @@ int launch_wide(const FcMassArgs& a, hipStream_t s) {
              : p.nw1 == 4 ? launch_stats_wide<D, 4>(a, nrg, p.S, pm, pl, s)
                           : launch_stats_wide<D, 2>(a, nrg, p.S, pm, pl, s);
     if (st != FC_OK) return st;
-    mass_lse_bf16_kernel<<<dim3(nrg, a.H_q), kNT, 0, s>>>(pm, pl, nrg, p.S, a.W, lse2);
+    mass_lse_kernel<<<dim3(nrg, a.H_q), kNT, 0, s>>>(pm, pl, nrg, p.S, a.W, lse2);
     FC_LAUNCH_CHECK();
     return p.nw2 == 8   ? launch_cols_wide<D, 8>(a, nrg, lse2, s)
            : p.nw2 == 4 ? launch_cols_wide<D, 4>(a, nrg, lse2, s)
@@ -858,44 +877,52 @@ int launch_bf16(const FcMassArgs& a, hipStream_t s) {
     float* lse2 = pl + (size_t)a.H_q * kRowGroup * np;
     mass_stats_bf16_kernel<D><<<dim3(np, a.H_q), kNT, 0, s>>>(a, np, tpb, pm, pl);
     FC_LAUNCH_CHECK();
-    mass_lse_bf16_kernel<<<dim3(1, a.H_q), kNT, 0, s>>>(pm, pl, 1, np, a.W, lse2);
+    mass_lse_kernel<<<dim3(1, a.H_q), kNT, 0, s>>>(pm, pl, 1, np, a.W, lse2);
     FC_LAUNCH_CHECK();
     mass_cols_bf16_kernel<D><<<dim3(np, a.H_k), kNT, 0, s>>>(a, tpb, lse2);
     FC_LAUNCH_CHECK();
     return FC_OK;
 }
 
-template <typename T, int D>
-int launch_typed(const FcMassArgs& a, hipStream_t s) {
-    const int nkb = (a.mass_len + kKeys - 1) / kKeys;
-    const int np = nkb * (kKeys / FC_WAVE);
+// Key ranges of pass 1: enough for two blocks per compute unit, a range at least one 32-key tile per
+// wavefront, and no more partials than the workspace holds (per row group one per 512 keys; one
+// group alone has room for one per 64).  Pass 2: as few wavefronts on the same keys as still give two
+// blocks per compute unit, never more than there are row tiles.
+template <int D>
+int launch_f32(const FcMassArgs& a, hipStream_t s) {
+    const int nrg = (a.W + kRowGroup - 1) / kRowGroup, rt = (a.W + 31) / 32;
+    const int most = nrg == 1 ? a.mass_len / 256 : a.mass_len / 512;
+    const int64_t units = (int64_t)a.H_q * rt;
+    int S = (int)((511 + units) / units);
+    S = S < most ? S : most;
+    S = S < 1 ? 1 : S;
     float* pm = reinterpret_cast<float*>(a.ws);
-    float* pl = pm + (size_t)a.H_q * kRowGroup * np;
-    float* lse2 = pl + (size_t)a.H_q * kRowGroup * np;
-    for (int w0 = 0; w0 < a.W; w0 += kRowGroup) {
-        const int nw = (a.W - w0 < kRowGroup) ? a.W - w0 : kRowGroup;
-        mass_stats_kernel<T, D><<<dim3(nkb, a.H_q), kKeys, 0, s>>>(a, w0, nw, np, pm, pl);
-        FC_LAUNCH_CHECK();
-        mass_lse_kernel<<<a.H_q, kRowGroup, 0, s>>>(pm, pl, nw, np, lse2, a.n_rec, a.rec_idx, a.A);
-        FC_LAUNCH_CHECK();
-        mass_cols_kernel<T, D><<<dim3(nkb, a.H_k), kKeys, 0, s>>>(a, w0, nw, lse2, w0 == 0 ? 1 : 0);
-        FC_LAUNCH_CHECK();
-    }
+    float* pl = pm + (size_t)a.H_q * nrg * kRowGroup * S;
+    float* lse2 = pl + (size_t)a.H_q * nrg * kRowGroup * S;
+    mass_stats_f32_kernel<D><<<dim3(S, rt, a.H_q), kF32Waves * 64, 0, s>>>(a, nrg, S, pm, pl);
+    FC_LAUNCH_CHECK();
+    mass_lse_kernel<<<dim3(nrg, a.H_q), kNT, 0, s>>>(pm, pl, nrg, S, a.W, lse2);
+    FC_LAUNCH_CHECK();
+    const int nt = a.H_q / a.H_k * rt;
+    auto blocks = [&](int parts) { const int keys = kF32Waves / parts * 32; return (a.mass_len + keys - 1) / keys; };
+    int parts = 1;
+    while (parts < kF32Waves && 2 * parts <= nt && (int64_t)a.H_k * blocks(parts) < 512) parts *= 2;
+    mass_cols_f32_kernel<D><<<dim3(blocks(parts), a.H_k), kF32Waves * 64, 0, s>>>(a, nrg, parts, lse2);
+    FC_LAUNCH_CHECK();
     return FC_OK;
 }
 
 }  // namespace
 
 size_t fc_mass_workspace(int W, int H_q, int mass_len) {
-    // fp32 path: one row group at a time, a partial per wavefront of 64 keys
-    const size_t nkb = ((size_t)mass_len + kKeys - 1) / kKeys;
-    const size_t np = nkb * (kKeys / FC_WAVE);
-    const size_t f32 = ((size_t)2 * H_q * kRowGroup * np + (size_t)H_q * kRowGroup) * sizeof(float);
-    // bf16 path: all row groups in one launch, a partial per block span of keys
+    // one row group: a partial per 64 keys and row
+    const size_t np = ((size_t)mass_len + 255) / 256 * 4;
+    const size_t one = ((size_t)2 * H_q * kRowGroup * np + (size_t)H_q * kRowGroup) * sizeof(float);
+    // more: all of them in one launch, a partial per 512 keys and row
     const size_t nrg = ((size_t)(W > 0 ? W : 1) + kRowGroup - 1) / kRowGroup;
     const size_t nps = ((size_t)mass_len + kMinTilesPerBlock * kTile - 1) / (kMinTilesPerBlock * kTile);
-    const size_t bf16 = ((size_t)2 * H_q * nrg * kRowGroup * nps + (size_t)H_q * nrg * kRowGroup) * sizeof(float);
-    return fc_align_up(f32 > bf16 ? f32 : bf16);
+    const size_t many = ((size_t)2 * H_q * nrg * kRowGroup * nps + (size_t)H_q * nrg * kRowGroup) * sizeof(float);
+    return fc_align_up(one > many ? one : many);
 }
 
 int fc_launch_mass(const FcMassArgs& a, hipStream_t s) {
@@ -903,8 +930,8 @@ int fc_launch_mass(const FcMassArgs& a, hipStream_t s) {
         if (a.d == 128) return launch_bf16<128>(a, s);
         if (a.d == 64) return launch_bf16<64>(a, s);
     } else {
-        if (a.d == 128) return launch_typed<float, 128>(a, s);
-        if (a.d == 64) return launch_typed<float, 64>(a, s);
+        if (a.d == 128) return launch_f32<128>(a, s);
+        if (a.d == 64) return launch_f32<64>(a, s);
     }
     return FC_UNSUPPORTED;
 }
