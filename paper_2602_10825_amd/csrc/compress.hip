@@ -9,18 +9,16 @@
 //                  r_j = (k^_j . s - k^_j . k^_j) / L, the linear-time form of the
 //                  diagonal-zeroed column mean of Eq. (11); writes e_j = exp(r_j) and block
 //                  partial sums of e.  (The softmax of Eq. (11) is shift-invariant and
-//                  |r_j| <= 1 + 1/L, so no max is subtracted.)  Also per block the smallest
-//                  and largest e and importance value: the bounds score_keys starts from.
+//                  |r_j| <= 1 + 1/L, so no max is subtracted.)
 //   score_keys     Red_j = e_j / sum e (Eq. (11)), max-pooled importance (Eq. (10)), score
-//                  (Eq. (12)) -> order-preserving 64-bit keys; and the histogram of the first
-//                  11 bits below the bits that all keys of the head share, which it knows
-//                  before it has the keys: the score is monotone in e and in the importance,
-//                  rounding included, so the same operations on their extremes bound it
-//   select         per head: radix select of the budget-th largest key: a few blocks gather
-//                  the chosen bin's keys in parallel, the last one to finish ends the select
-//                  on them in LDS
+//                  (Eq. (12)) -> order-preserving 64-bit keys; and a histogram of the keys whose
+//                  bins are spread over a bracket of the wanted key that a sample of the head's
+//                  keys gives
+//   select         per head: the bin that holds the budget-th largest key; a few blocks gather its
+//                  keys in parallel, the last one to finish ends the select on them in LDS
 //   write_kept     ordered compaction of the kept positions (ties: lower position wins;
 //                  output ascending); blocks exchange their counts through one word each
+//   select_small   the three above in one launch of one block per head, for heads whose keys fit in LDS
 //   compact_rows   move the kept K and V rows to positions [0, budget) IN PLACE, one pass of
 //                  64-row tiles drawn from a ticket counter; a tile stores only after the
 //                  lower tiles that read from its rows have loaded them
@@ -40,6 +38,15 @@ constexpr int kTokBlk = kThreads * kItems;   // tokens per block in the per-toke
 constexpr int kDigitBits = 11;
 constexpr int kBins = 1 << kDigitBits;
 constexpr int kCand = 4096;   // candidates resolved in LDS
+constexpr int kRank = 256;    // candidates resolved by comparing each with each
+// bins of the first digit, which every block of a head adds to in global memory: more bins cost
+// score_keys what they save the select (24 heads of 74880 keys, the two together with 256, 512 and 2048
+// bins: 42, 43 and 44 us)
+constexpr int kFirstBits = 9;
+constexpr int kFirstBins = 1 << kFirstBits;
+constexpr int kSample = 128;  // keys that the first digit's bracket is taken from
+constexpr int kSampleWide = 28;   // the bracket's half width in ranks of the sample: five deviations
+constexpr int kSmallL = kSelThreads * 4;   // heads up to this length are selected by one block
 constexpr int kUnroll = 8;    // independent loads in flight per thread in the selection scans
 
 // ---- bookkeeping of the in-place compaction (kernels further down) ----------------------
@@ -251,19 +258,18 @@ __global__ __launch_bounds__(kThreads) void key_stats_kernel(
 // Pass 2: r_j = (k^_j . s - k^_j . k^_j) / L for every token, e_j = exp(r_j) and the block's
 // partial sum of e.  Every block first adds up the head's few block partials of pass 1 itself,
 // in block order (s = sum_i k^_i; the same bits in every block), which saves a launch.
-template <typename T, int D, int R, typename MT>
+template <typename T, int D, int R>
 __global__ __launch_bounds__(kThreads) void mean_sim_kernel(
     const T* __restrict__ k_cache, int64_t head_stride, int64_t tok_stride, int L,
     const double* __restrict__ psum, int npart,
-    double* __restrict__ e_out, double* __restrict__ pz, const MT* __restrict__ mass_all,
-    double* __restrict__ pstat, uint32_t* __restrict__ hist_all) {
+    double* __restrict__ e_out, double* __restrict__ pz, uint32_t* __restrict__ hist_all) {
     typedef Slice<T, D> S;
     constexpr int EL = S::EL;
     const int h = gridDim.y - 1 - blockIdx.y;   // pass 1 read the last heads last: they may still be cached
     const int g = threadIdx.x / 16, u = threadIdx.x % 16;
     const T* base = k_cache + (int64_t)h * head_stride;
-    if (blockIdx.x == 0)   // the first-digit histogram that score_keys adds to
-        for (int i = threadIdx.x; i < kBins; i += kThreads) hist_all[(int64_t)h * kBins + i] = 0u;
+    if (hist_all && blockIdx.x == 0)   // the first-digit histogram that score_keys adds to
+        for (int i = threadIdx.x; i < kFirstBins; i += kThreads) hist_all[(int64_t)h * kFirstBins + i] = 0u;
     __shared__ double sh_s[D];
     if (threadIdx.x < D) {
         const double* p = psum + (int64_t)h * npart * D + threadIdx.x;
@@ -285,24 +291,6 @@ __global__ __launch_bounds__(kThreads) void mean_sim_kernel(
     for (int e = 0; e < EL; ++e) s[e] = sh_s[u * EL + e];
     const double dL = (double)L;
     double zsum = 0.0;
-    // Bounds for score_keys (which needs the range of the scores before it has the scores):
-    // smallest and largest e of this block's tokens and smallest and largest importance of a
-    // slice of the head; `odd` notes a value that is not finite.
-    const double kInf = __longlong_as_double(0x7ff0000000000000LL);
-    double emin = kInf, emax = -kInf, mmin = kInf, mmax = -kInf;
-    bool odd = false;
-    // this block's share of the head's importance values: requested now, looked at after the
-    // pass over the rows, so that their latency is not a prologue in front of it
-    constexpr int MP = 12;
-    const MT* mass = mass_all + (int64_t)h * L;
-    const int mj0 = blockIdx.x * kThreads + threadIdx.x, mstride = gridDim.x * kThreads;
-    MT mv[MP];
-#pragma unroll
-    for (int q = 0; q < MP; ++q) {
-        const int j = mj0 + q * mstride;
-        mv[q] = mass[j < L ? j : L - 1];
-    }
-    __builtin_amdgcn_sched_barrier(0);
     const int stride = gridDim.x * kGroups * R;
     for (int j0 = (blockIdx.x * kGroups + g) * R; j0 < L; j0 += stride) {
         typename S::raw_t raw[R];
@@ -329,61 +317,16 @@ __global__ __launch_bounds__(kThreads) void mean_sim_kernel(
             const double ej = exp((mine * ti.x - ti.y) / dL);
             e_out[(int64_t)h * L + j0 + u] = ej;
             zsum += ej;
-            odd = odd || !(ej - ej == 0.0);
-            emin = ej < emin ? ej : emin;
-            emax = ej > emax ? ej : emax;
         }
-    }
-#pragma unroll
-    for (int q = 0; q < MP; ++q) {
-        if (mj0 + q * mstride < L) {
-            const double m = (double)mv[q];
-            odd = odd || !(m - m == 0.0);
-            mmin = m < mmin ? m : mmin;
-            mmax = m > mmax ? m : mmax;
-        }
-    }
-    for (int j = mj0 + MP * mstride; j < L; j += mstride) {   // long heads: the rest
-        const double m = (double)mass[j];
-        odd = odd || !(m - m == 0.0);
-        mmin = m < mmin ? m : mmin;
-        mmax = m > mmax ? m : mmax;
     }
     __shared__ double shz[kThreads];
-    __shared__ double shb[kThreads / FC_WAVE][4];
-    __shared__ int sh_odd;
-    if (threadIdx.x == 0) sh_odd = 0;
     shz[threadIdx.x] = zsum;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {   // minima and maxima: any order gives the same value
-        emin = fmin(emin, __shfl_xor(emin, o, FC_WAVE));
-        emax = fmax(emax, __shfl_xor(emax, o, FC_WAVE));
-        mmin = fmin(mmin, __shfl_xor(mmin, o, FC_WAVE));
-        mmax = fmax(mmax, __shfl_xor(mmax, o, FC_WAVE));
-    }
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) {
-        double* b = shb[threadIdx.x / FC_WAVE];
-        b[0] = emin; b[1] = emax; b[2] = mmin; b[3] = mmax;
-    }
-    if (odd) sh_odd = 1;
     __syncthreads();
     if (threadIdx.x < 64) {   // fixed order: four strided terms per lane, then the lanes in order
         double z = (shz[threadIdx.x] + shz[threadIdx.x + 64]) + (shz[threadIdx.x + 128] + shz[threadIdx.x + 192]);
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) z += __shfl_down(z, o, FC_WAVE);
-        if (threadIdx.x == 0) {
-            pz[(int64_t)h * gridDim.x + blockIdx.x] = z;
-            double* st = pstat + ((int64_t)h * gridDim.x + blockIdx.x) * 4;
-            double v[4] = {shb[0][0], shb[0][1], shb[0][2], shb[0][3]};
-            for (int w = 1; w < kThreads / FC_WAVE; ++w) {
-                v[0] = fmin(v[0], shb[w][0]); v[1] = fmax(v[1], shb[w][1]);
-                v[2] = fmin(v[2], shb[w][2]); v[3] = fmax(v[3], shb[w][3]);
-            }
-            // a value that is not finite anywhere in the block: the record says so with a NaN
-            st[0] = sh_odd ? __longlong_as_double(0x7ff8000000000000LL) : v[0];
-            st[1] = v[1]; st[2] = v[2]; st[3] = v[3];
-        }
+        if (threadIdx.x == 0) pz[(int64_t)h * gridDim.x + blockIdx.x] = z;
     }
 }
 
@@ -398,21 +341,6 @@ __device__ __forceinline__ double block_sum_fixed(double v, double* sh) {
         __syncthreads();
     }
     return sh[0];
-}
-
-template <int NT>
-__device__ __forceinline__ uint64_t block_reduce_u64(uint64_t v, bool want_max, uint64_t* sh) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const uint64_t w = (uint64_t)__shfl_xor((long long)v, o, FC_WAVE);
-        v = want_max ? (w > v ? w : v) : (w < v ? w : v);
-    }
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x / FC_WAVE] = v;
-    __syncthreads();
-    uint64_t m = sh[0];
-    for (int k = 1; k < NT / FC_WAVE; ++k) m = want_max ? (sh[k] > m ? sh[k] : m) : (sh[k] < m ? sh[k] : m);
-    return m;
 }
 
 // Histogram increment that survives skew: the digits most lanes of a wavefront share are
@@ -437,12 +365,37 @@ __device__ __forceinline__ uint64_t score_key(double score) {
     return (b >> 63) ? ~b : (b | 0x8000000000000000ull);
 }
 
+// Eq. (11) and (12) of one token: e = exp(r), the pooled importance, z = sum of e over the head
+__device__ __forceinline__ uint64_t token_key(double e, double pooled, double z, double lambda) {
+    const double red = e / z;
+    const double a = lambda * pooled;
+    const double b = (1.0 - lambda) * red;
+    return score_key(a - b);
+}
+
+// The first digit: keys in [lo, hi] by their distance from lo, kFirstBins - 2 bins at most; one bin below
+// and one above.
+__device__ __forceinline__ int bracket_shift(uint64_t lo, uint64_t hi) {
+    const int bits = hi > lo ? 64 - __clzll((long long)(hi - lo)) : 0;
+    int sh = bits > kFirstBits - 1 ? bits - (kFirstBits - 1) : 0;
+    if (sh > 0 && ((hi - lo) >> (sh - 1)) <= (uint64_t)(kFirstBins - 3)) --sh;
+    return sh;
+}
+__device__ __forceinline__ uint32_t bracket_digit(uint64_t k, uint64_t lo, uint64_t hi, int sh) {
+    return k < lo ? 0u : (k > hi ? (uint32_t)(kFirstBins - 1) : 1u + (uint32_t)((k - lo) >> sh));
+}
 
 // ---- keys: Eq. (10)-(12) per token, fully parallel ------------------------------------
+// Where the first digit's bins lie decides how many keys the select has to look at again.  The top
+// bits of the keys are mostly sign and exponent: with heavy-tailed importance half of the head fell
+// into one bin and one block read the whole head three times over (12 heads of 51000 keys: select 62
+// us, 24 of 74880: 93 us; with the bracket 10 and 14 us).  So every block takes the same 128 keys
+// of the head, finds those some ranks above and below the wanted one, and spreads the bins between
+// them, whatever the distribution; a wanted key outside the bracket (5 deviations) costs time only.
 template <typename MT>   // importance as given (float) or pooled over a key group (double)
 __global__ __launch_bounds__(kThreads) void score_keys_kernel(
     const double* __restrict__ e_all, const MT* __restrict__ mass_all,
-    const double* __restrict__ pz_all, const double* __restrict__ pstat_all, int nblkz, int L, int pool_k,
+    const double* __restrict__ pz_all, int nblkz, int L, int budget, int pool_k,
     double lambda, uint64_t* __restrict__ keys_all, uint64_t* __restrict__ krange,
     uint32_t* __restrict__ hist_all, uint32_t* __restrict__ sync, int ntile, uint32_t* __restrict__ selsync,
     uint64_t* __restrict__ agg_all) {
@@ -451,9 +404,21 @@ __global__ __launch_bounds__(kThreads) void score_keys_kernel(
     const MT* mass = mass_all + (int64_t)h * L;
     uint64_t* keys = keys_all + (int64_t)h * L;
     __shared__ double shd[kThreads];
-    __shared__ double sh_bound[4];
-    __shared__ int sh_odd;
-    __shared__ uint32_t hist[kBins];
+    __shared__ uint64_t sample[kSample];
+    __shared__ uint64_t sh_lo, sh_hi;
+    __shared__ uint32_t hist[kFirstBins];
+    const int half = pool_k / 2;
+    // The sample: one token of each 128th of the head (L >= kSample), not always the same one of it.
+    // Threads 2q and 2q + 1 both take token q; everything is requested before the sums that z needs.
+    const int sq = tid >> 1, slen = L / kSample;
+    const int sj = (int)((int64_t)sq * L / kSample) + (int)(((uint32_t)sq * 2654435761u >> 12) % (uint32_t)slen);
+    const double se = e[sj];
+    MT simp = mass[sj];
+    for (int d = 1; d <= half; ++d) {
+        const MT lo = mass[sj - d >= 0 ? sj - d : 0], hi = mass[sj + d < L ? sj + d : L - 1];
+        const MT nb = lo > hi ? lo : hi;
+        simp = simp > nb ? simp : nb;
+    }
     if (blockIdx.x == 0) {   // state later kernels of this call start from: tile flags, tickets
         uint32_t* flags = sync_flags(sync, gridDim.y, ntile, h);
         for (int i = tid; i < ntile; i += kThreads) flags[i] = 0u;
@@ -462,53 +427,7 @@ __global__ __launch_bounds__(kThreads) void score_keys_kernel(
         if (tid < 3) selsync[h * 64 + tid] = 0u;
         for (int i = tid; i < (int)gridDim.x; i += kThreads) agg_all[(int64_t)h * gridDim.x + i] = 0ull;
     }
-    // Z = sum_j e_j: the block partials of the pass that wrote e, in a fixed order
-    double z = 0.0;
-    for (int i = tid; i < nblkz; i += kThreads) z += pz_all[(int64_t)h * nblkz + i];
-    z = block_sum_fixed<kThreads>(z, shd);
-    // The range of the head's scores, before any score: e and the pooled importance of every
-    // token lie between the head's smallest and largest, and every operation from there to the
-    // score is monotone, rounding included, so the same operations on the extremes bound the
-    // scores from both sides.  All keys of the head then agree in the bits above the first in
-    // which the keys of the two bounds differ; the 11 bits below are counted here.
-    if (tid < FC_WAVE) {
-        const double kInf = __longlong_as_double(0x7ff0000000000000LL);
-        double v[4] = {kInf, -kInf, kInf, -kInf};
-        bool odd = false;
-        for (int i = tid; i < nblkz; i += FC_WAVE) {
-            const double* st = pstat_all + ((int64_t)h * nblkz + i) * 4;
-            odd = odd || (st[0] != st[0]);
-            v[0] = fmin(v[0], st[0]); v[1] = fmax(v[1], st[1]);
-            v[2] = fmin(v[2], st[2]); v[3] = fmax(v[3], st[3]);
-        }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            v[0] = fmin(v[0], __shfl_xor(v[0], o, FC_WAVE)); v[1] = fmax(v[1], __shfl_xor(v[1], o, FC_WAVE));
-            v[2] = fmin(v[2], __shfl_xor(v[2], o, FC_WAVE)); v[3] = fmax(v[3], __shfl_xor(v[3], o, FC_WAVE));
-        }
-        const bool any_odd = __ballot(odd) != 0ull;
-        if (tid == 0) {
-            sh_bound[0] = v[0]; sh_bound[1] = v[1]; sh_bound[2] = v[2]; sh_bound[3] = v[3];
-            sh_odd = any_odd ? 1 : 0;
-        }
-    }
-    __syncthreads();
-    uint64_t klo = 0ull, khi = ~0ull;   // a value that is not finite somewhere: no common bits assumed
-    if (!sh_odd && z - z == 0.0) {
-        const double a_lo = lambda * sh_bound[2], a_hi = lambda * sh_bound[3];
-        const double b_lo = (1.0 - lambda) * (sh_bound[0] / z), b_hi = (1.0 - lambda) * (sh_bound[1] / z);
-        klo = score_key(a_lo - b_hi);
-        khi = score_key(a_hi - b_lo);
-    }
-    const uint64_t kdiff = klo ^ khi;
-    const int rem = kdiff ? 64 - __clzll((long long)kdiff) : 0;
-    const int wbits = rem < kDigitBits ? rem : kDigitBits;
-    const int shift = rem - wbits;
-    if (blockIdx.x == 0 && tid == 0) { krange[2 * h] = klo; krange[2 * h + 1] = khi; }
-    for (int i = tid; i < kBins; i += kThreads) hist[i] = 0u;
-    __syncthreads();
-
-    const int half = pool_k / 2;
+    for (int i = tid; i < kFirstBins; i += kThreads) hist[i] = 0u;
     const int j0 = blockIdx.x * kTokBlk;
     double ev[kItems];
     MT imp[kItems];
@@ -518,6 +437,33 @@ __global__ __launch_bounds__(kThreads) void score_keys_kernel(
         ev[i] = (j < L) ? e[j] : 0.0;
         imp[i] = (j < L) ? mass[j] : (MT)0;
     }
+    // Z = sum_j e_j: the block partials of the pass that wrote e, in a fixed order
+    double z = 0.0;
+    for (int i = tid; i < nblkz; i += kThreads) z += pz_all[(int64_t)h * nblkz + i];
+    z = block_sum_fixed<kThreads>(z, shd);
+    const uint64_t sk = token_key(se, (double)simp, z, lambda);
+    if (!(tid & 1)) sample[sq] = sk;
+    __syncthreads();
+    {   // rank of each sampled key from the top (ties by index); the two threads count half each
+        uint32_t above = 0;
+        const int c0 = (tid & 1) * (kSample / 2);
+#pragma unroll 8
+        for (int i = c0; i < c0 + kSample / 2; ++i) {
+            const uint64_t o = sample[i];
+            above += (o > sk || (o == sk && i < sq)) ? 1u : 0u;
+        }
+        above += __shfl_xor(above, 1, FC_WAVE);
+        const int want = (int)((int64_t)budget * kSample / L);
+        const int r_hi = want > kSampleWide ? want - kSampleWide : 0;
+        const int r_lo = want + kSampleWide < kSample - 1 ? want + kSampleWide : kSample - 1;
+        if (!(tid & 1) && (int)above == r_hi) sh_hi = sk;
+        if (!(tid & 1) && (int)above == r_lo) sh_lo = sk;
+    }
+    __syncthreads();
+    const uint64_t klo = sh_lo, khi = sh_hi;
+    const int shift = bracket_shift(klo, khi);
+    if (blockIdx.x == 0 && tid == 0) { krange[2 * h] = klo; krange[2 * h + 1] = khi; }
+
     for (int d = 1; d <= half; ++d) {   // Eq. (10): window max, -inf outside [0, L)
 #pragma unroll
         for (int i = 0; i < kItems; ++i) {
@@ -536,20 +482,27 @@ __global__ __launch_bounds__(kThreads) void score_keys_kernel(
         const int j = j0 + i * kThreads + tid;
         kv[i] = 0ull;
         if (j < L) {
-            const double red = ev[i] / z;                    // Eq. (11)
-            const double a = lambda * (double)imp[i];
-            const double b = (1.0 - lambda) * red;
-            kv[i] = score_key(a - b);                        // Eq. (12)
+            kv[i] = token_key(ev[i], (double)imp[i], z, lambda);
             keys[j] = kv[i];
         }
     }
-    if (rem == 0) return;   // every score of the head is the same: nothing to count
+    // the two outer bins hold most of the keys: counted by the wavefront; the others are spread
+    uint32_t below = 0, above = 0;
 #pragma unroll
-    for (int i = 0; i < kItems; ++i)
-        hist_add(hist, j0 + i * kThreads + tid < L, (uint32_t)(kv[i] >> shift) & ((1u << wbits) - 1u));
+    for (int i = 0; i < kItems; ++i) {
+        const bool in = j0 + i * kThreads + tid < L;
+        const uint32_t dgt = bracket_digit(kv[i], klo, khi, shift);
+        below += __popcll(__ballot(in && dgt == 0u));
+        above += __popcll(__ballot(in && dgt == (uint32_t)(kFirstBins - 1)));
+        if (in && dgt != 0u && dgt != (uint32_t)(kFirstBins - 1)) atomicAdd(&hist[dgt], 1u);
+    }
+    if ((tid & 63) == 0) {
+        atomicAdd(&hist[0], below);
+        atomicAdd(&hist[kFirstBins - 1], above);
+    }
     __syncthreads();
-    for (int i = tid; i < kBins; i += kThreads)
-        if (hist[i]) atomicAdd(&hist_all[(int64_t)h * kBins + i], hist[i]);
+    for (int i = tid; i < kFirstBins; i += kThreads)
+        if (hist[i]) atomicAdd(&hist_all[(int64_t)h * kFirstBins + i], hist[i]);
 }
 
 // From a histogram of `nb` <= 2048 bins (counts of the current candidates by digit), find the
@@ -600,14 +553,30 @@ __device__ __forceinline__ void list_append(uint64_t* list, uint32_t* counter, b
     if (take) list[base + __popcll(m & ((1ull << lane) - 1ull))] = k;
 }
 
-// ---- per head: finish the radix select -> threshold key and the number of its copies kept.
+// The `need`-th largest of n <= kRank keys: every key is compared with every other one.
+__device__ __forceinline__ void rank_select(const uint64_t* cand, uint32_t n, uint32_t need, uint64_t* out_key,
+                                            uint32_t* out_need) {
+    if (threadIdx.x < n) {
+        const uint64_t k = cand[threadIdx.x];
+        uint32_t gt = 0, eq = 0;
+        for (uint32_t i = 0; i < n; ++i) {
+            const uint64_t o = cand[i];
+            gt += o > k ? 1u : 0u;
+            eq += o == k ? 1u : 0u;
+        }
+        if (gt < need && need <= gt + eq) { *out_key = k; *out_need = need - gt; }   // equal keys write the same
+    }
+}
+
+// ---- per head: finish the select -> threshold key and the number of its copies kept.
 // A few blocks per head.  Every block reads the first-digit histogram and picks the same bin.
 // If that bin holds at most kCand keys (the usual case), the blocks scan the head's keys in
 // parallel and append the bin's keys to a list in global memory; the block that finishes last
 // (an integer count, nobody waits) pulls the list into LDS and finishes the select there.
-// Otherwise -- many equal or nearly equal scores -- block 0 goes on alone with further
-// histogram passes over global memory.  The list is written and read with agent-scope
-// accesses: its writers may sit on other XCDs, whose L2 this block does not see.
+// Otherwise -- many equal or nearly equal scores, or a wanted key outside the bracket -- block 0 goes
+// on alone with further histogram passes over global memory.  The list is written and read with
+// agent-scope accesses: its writers may sit on other XCDs, whose L2 this block does not see.
+// A candidate is a key k with k - base <= limit, and k - base is what the further digits are of.
 // selsync[h * 64 + 0] = length of the list, [+1] = blocks done, [+2] = ticket of write_kept.
 __global__ __launch_bounds__(kSelThreads) void select_kernel(
     const uint64_t* __restrict__ keys_all, const uint64_t* __restrict__ krange,
@@ -616,53 +585,58 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
     const int h = blockIdx.y, part = blockIdx.x, nparts = gridDim.x;
     const int tid = threadIdx.x;
     const uint64_t* keys = keys_all + (int64_t)h * L;
-    __shared__ uint64_t shu[kSelThreads / FC_WAVE];
     __shared__ uint32_t hist[kBins];
     __shared__ uint64_t cand[kCand];
+    __shared__ uint64_t few[kRank];
     __shared__ uint32_t wtot[kSelThreads / FC_WAVE];
-    __shared__ uint64_t sh_prefix, sh_thr;
+    __shared__ uint64_t sh_prefix;
     __shared__ uint32_t sh_need, sh_count, sh_ncand;
     __shared__ int sh_last;
 
-    const uint64_t kmin = krange[2 * h], kmax = krange[2 * h + 1];   // bounds on the head's keys
-    uint32_t need = (uint32_t)budget;
-    const uint64_t diff = kmin ^ kmax;
-    if (diff == 0) {   // every score is the same: keep the first `budget` positions
-        if (part == 0 && tid == 0) { sel[2 * h] = kmax; sel[2 * h + 1] = need; }
-        return;
+    const uint64_t klo = krange[2 * h], khi = krange[2 * h + 1];
+    if (tid < kFirstBins) hist[tid] = hist_all[(int64_t)h * kFirstBins + tid];
+    __syncthreads();
+    pick_bin_parallel(hist, kFirstBins, (uint32_t)budget, wtot, 0ull, 0, &sh_prefix, &sh_need, &sh_count);
+    __syncthreads();
+    const uint32_t bin = (uint32_t)sh_prefix;
+    uint32_t need = sh_need;
+    uint32_t count = sh_count;        // keys in the bin chosen last
+    uint64_t base, limit;
+    if (bin == 0u) {                  // below the bracket
+        base = 0ull;
+        limit = klo - 1ull;
+    } else if (bin == (uint32_t)(kFirstBins - 1)) {   // above it
+        base = khi + 1ull;
+        limit = ~0ull - base;
+    } else {
+        const int sh = bracket_shift(klo, khi);
+        base = klo + ((uint64_t)(bin - 1u) << sh);
+        const uint64_t width = (1ull << sh) - 1ull;
+        limit = khi - base < width ? khi - base : width;
     }
-    int rem = 64 - __clzll((long long)diff);                   // undecided low bits
-    uint64_t prefix = (rem == 64) ? 0ull : (kmax >> rem) << rem;
-    {   // first digit: counted by score_keys_kernel
-        const int w = rem < kDigitBits ? rem : kDigitBits;
-        const int shift = rem - w;
-        const int nb = 1 << w;
-        for (int i = tid; i < nb; i += kSelThreads) hist[i] = hist_all[(int64_t)h * kBins + i];
-        __syncthreads();
-        pick_bin_parallel(hist, nb, need, wtot, prefix, shift, &sh_prefix, &sh_need, &sh_count);
-        __syncthreads();
-        prefix = sh_prefix;
-        need = sh_need;
-        rem = shift;
+    int rem = limit ? 64 - __clzll((long long)limit) : 0;      // undecided low bits
+    uint64_t prefix = 0ull;
+    if (rem == 0) {
+        if (part == 0 && tid == 0) { sel[2 * h] = base; sel[2 * h + 1] = need; }
+        return;
     }
     bool in_lds = false;
     uint32_t ncand = 0;
-    uint32_t count = sh_count;        // keys in the bin chosen last
-    if (rem > 0 && count <= (uint32_t)kCand) {
+    __syncthreads();
+    if (count <= (uint32_t)kCand) {
         uint64_t* cand_g = cand_all + (int64_t)h * kCand;
         uint32_t* cnt = &selsync[h * 64];
-        const uint64_t hm = ~0ull << rem;
         const int lane = tid & 63;
-        for (int base = part * kSelThreads * kUnroll; base < L; base += nparts * kSelThreads * kUnroll) {
+        for (int b0 = part * kSelThreads * kUnroll; b0 < L; b0 += nparts * kSelThreads * kUnroll) {
             uint64_t kv[kUnroll];
 #pragma unroll
             for (int u = 0; u < kUnroll; ++u) {
-                const int j = base + u * kSelThreads + tid;
-                kv[u] = (j < L) ? keys[j] : 0ull;
+                const int j = b0 + u * kSelThreads + tid;
+                kv[u] = keys[j < L ? j : L - 1] - base;
             }
 #pragma unroll
             for (int u = 0; u < kUnroll; ++u) {
-                const bool take = (kv[u] & hm) == prefix && base + u * kSelThreads + tid < L;
+                const bool take = kv[u] <= limit && b0 + u * kSelThreads + tid < L;
                 const uint64_t m = __ballot(take);
                 if (m == 0) continue;
                 const int leader = __ffsll((long long)m) - 1;
@@ -691,44 +665,47 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
         __syncthreads();
         in_lds = true;
     } else if (part != 0) {
-        return;       // threshold already decided, or too many candidates: block 0 goes on alone
+        return;       // too many candidates: block 0 goes on alone
     }
     for (;;) {
+        const uint64_t himask = (rem >= 64) ? 0ull : (~0ull << rem);
         // few candidates left and still in global memory: pull them into LDS and finish there
-        if (!in_lds && rem > 0 && count <= (uint32_t)kCand) {
+        if (!in_lds && count <= (uint32_t)kCand) {
             if (tid == 0) sh_ncand = 0;
             __syncthreads();
-            const uint64_t hm = ~0ull << rem;
-            for (int base = 0; base < L; base += kSelThreads * kUnroll) {
+            for (int b0 = 0; b0 < L; b0 += kSelThreads * kUnroll) {
                 uint64_t kv[kUnroll];
 #pragma unroll
                 for (int u = 0; u < kUnroll; ++u) {
-                    const int j = base + u * kSelThreads + tid;
-                    kv[u] = (j < L) ? keys[j] : 0ull;
+                    const int j = b0 + u * kSelThreads + tid;
+                    kv[u] = keys[j < L ? j : L - 1] - base;
                 }
 #pragma unroll
                 for (int u = 0; u < kUnroll; ++u)
                     list_append(cand, &sh_ncand,
-                                (kv[u] & hm) == prefix && base + u * kSelThreads + tid < L, kv[u]);
+                                kv[u] <= limit && (kv[u] & himask) == prefix && b0 + u * kSelThreads + tid < L, kv[u]);
             }
             __syncthreads();
             ncand = sh_ncand;
             in_lds = true;
         }
-        // one candidate left in the chosen bin: it is the threshold, whatever its low bits
-        if (in_lds && rem > 0 && count == 1u) {
-            const uint64_t hm = ~0ull << rem;
-            for (uint32_t i = tid; i < ncand; i += kSelThreads)
-                if ((cand[i] & hm) == prefix) sh_thr = cand[i];
+        if (in_lds && count <= (uint32_t)kRank) {   // very few: no more digits
+            if (tid == 0) sh_ncand = 0;
             __syncthreads();
-            prefix = sh_thr;
-            rem = 0;
+            for (uint32_t i0 = 0; i0 < ncand; i0 += kSelThreads) {
+                const uint64_t k = (i0 + tid < ncand) ? cand[i0 + tid] : 0ull;
+                list_append(few, &sh_ncand, i0 + tid < ncand && (k & himask) == prefix, k);
+            }
+            __syncthreads();
+            rank_select(few, sh_ncand, need, &sh_prefix, &sh_need);
+            __syncthreads();
+            prefix = sh_prefix;
+            need = sh_need;
+            break;
         }
-        if (rem == 0) break;
         const int w = in_lds ? (rem < 8 ? rem : 8) : (rem < kDigitBits ? rem : kDigitBits);
         const int shift = rem - w;
         const int nb = 1 << w;
-        const uint64_t himask = (rem == 64) ? 0ull : (~0ull << rem);
         for (int i = tid; i < nb; i += kSelThreads) hist[i] = 0;
         __syncthreads();
         if (in_lds) {
@@ -738,16 +715,16 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
                 hist_add(hist, i < ncand && (k & himask) == prefix, (uint32_t)(k >> shift) & (nb - 1));
             }
         } else {
-            for (int base = 0; base < L; base += kSelThreads * kUnroll) {
+            for (int b0 = 0; b0 < L; b0 += kSelThreads * kUnroll) {
                 uint64_t kv[kUnroll];
 #pragma unroll
                 for (int u = 0; u < kUnroll; ++u) {
-                    const int j = base + u * kSelThreads + tid;
-                    kv[u] = (j < L) ? keys[j] : 0ull;
+                    const int j = b0 + u * kSelThreads + tid;
+                    kv[u] = keys[j < L ? j : L - 1] - base;
                 }
 #pragma unroll
                 for (int u = 0; u < kUnroll; ++u)
-                    hist_add(hist, (kv[u] & himask) == prefix && base + u * kSelThreads + tid < L,
+                    hist_add(hist, kv[u] <= limit && (kv[u] & himask) == prefix && b0 + u * kSelThreads + tid < L,
                              (uint32_t)(kv[u] >> shift) & (nb - 1));
             }
         }
@@ -758,9 +735,10 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
         need = sh_need;
         count = sh_count;
         rem = shift;
+        if (rem == 0) break;
     }
     if (tid == 0) {
-        sel[2 * h] = prefix;
+        sel[2 * h] = base + prefix;
         sel[2 * h + 1] = need;
     }
 }
@@ -857,6 +835,157 @@ __global__ __launch_bounds__(kThreads) void write_kept_kernel(const uint64_t* __
         }
         gt_before += g ? 1u : 0u;
         eq_before += e ? 1u : 0u;
+    }
+}
+
+// ---- a head of at most kSmallL keys: scores, select and kept positions by one block.  Such a call is
+// bound by its launches, each a chain of dependent round trips (4 heads of 1312 keys: the three
+// kernels above 25 us of the call's 44, this one 14).  Same operations per token, same order of the
+// sum of e, so the same keys.
+template <typename MT>
+__global__ __launch_bounds__(kSelThreads) void select_small_kernel(
+    const double* __restrict__ e_all, const MT* __restrict__ mass_all, const double* __restrict__ pz_all, int nblkz,
+    int L, int budget, int pool_k, double lambda, int32_t* __restrict__ kept_all, uint32_t* __restrict__ sync, int ntile) {
+    constexpr int PER = kSmallL / kSelThreads;
+    const int h = blockIdx.x, tid = threadIdx.x, wave = tid / FC_WAVE, lane = tid & 63;
+    const double* e = e_all + (int64_t)h * L;
+    const MT* mass = mass_all + (int64_t)h * L;
+    int32_t* kept = kept_all + (int64_t)h * budget;
+    int32_t* tile_last = sync_tile_last(sync, gridDim.x, ntile, h);
+    __shared__ MT ms[kSmallL];
+    __shared__ uint64_t keys[kSmallL];
+    __shared__ double shd[kSelThreads];
+    __shared__ uint32_t hist[kBins];
+    __shared__ uint64_t few[kRank];
+    __shared__ uint64_t red[2][kSelThreads / FC_WAVE];
+    __shared__ uint32_t wtot[2][kSelThreads / FC_WAVE];
+    __shared__ uint64_t sh_prefix;
+    __shared__ uint32_t sh_need, sh_count, sh_n;
+
+    double ev[PER];
+    MT imp[PER];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const int j = i * kSelThreads + tid;
+        ev[i] = e[j < L ? j : L - 1];
+        imp[i] = mass[j < L ? j : L - 1];
+    }
+    double z = 0.0;   // the order of score_keys: the first kThreads threads, the tree adds zeros besides
+    if (tid < kThreads)
+        for (int i = tid; i < nblkz; i += kThreads) z += pz_all[(int64_t)h * nblkz + i];
+    {   // what the compaction starts from
+        uint32_t* flags = sync_flags(sync, gridDim.x, ntile, h);
+        for (int i = tid; i < ntile; i += kSelThreads) flags[i] = 0u;
+        if (tid == 0) sync[64 * (h + 1)] = 0u;
+        if (h == 0 && tid == 0) sync[0] = 0u;
+    }
+#pragma unroll
+    for (int i = 0; i < PER; ++i) ms[i * kSelThreads + tid] = imp[i];
+    if (tid == 0) sh_n = 0u;
+    z = block_sum_fixed<kSelThreads>(z, shd);   // its barriers publish ms too
+    const int half = pool_k / 2;
+    for (int d = 1; d <= half; ++d) {
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const int j = i * kSelThreads + tid;
+            if (j < L) {
+                const MT lo = (j - d >= 0) ? ms[j - d] : imp[i];
+                const MT hi = (j + d < L) ? ms[j + d] : imp[i];
+                const MT nb = lo > hi ? lo : hi;
+                imp[i] = imp[i] > nb ? imp[i] : nb;
+            }
+        }
+    }
+    uint64_t kv[PER], kmin = ~0ull, kmax = 0ull;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const int j = i * kSelThreads + tid;
+        kv[i] = 0ull;
+        if (j < L) {
+            kv[i] = token_key(ev[i], (double)imp[i], z, lambda);
+            kmin = kv[i] < kmin ? kv[i] : kmin;
+            kmax = kv[i] > kmax ? kv[i] : kmax;
+            keys[j] = kv[i];
+        }
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        const uint64_t a = (uint64_t)__shfl_xor((long long)kmin, o, FC_WAVE), b = (uint64_t)__shfl_xor((long long)kmax, o, FC_WAVE);
+        kmin = a < kmin ? a : kmin;
+        kmax = b > kmax ? b : kmax;
+    }
+    if (lane == 0) { red[0][wave] = kmin; red[1][wave] = kmax; }
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kSelThreads / FC_WAVE; ++w) {
+        kmin = red[0][w] < kmin ? red[0][w] : kmin;
+        kmax = red[1][w] > kmax ? red[1][w] : kmax;
+    }
+    // digits of the distance from the smallest key, until few candidates are left
+    uint32_t need = (uint32_t)budget, count = (uint32_t)L;
+    uint64_t prefix = 0ull;
+    int rem = kmax > kmin ? 64 - __clzll((long long)(kmax - kmin)) : 0;
+    while (rem > 0) {
+        const uint64_t himask = (rem >= 64) ? 0ull : (~0ull << rem);
+        if (count <= (uint32_t)kRank) {
+#pragma unroll
+            for (int i = 0; i < PER; ++i)
+                list_append(few, &sh_n, i * kSelThreads + tid < L && ((kv[i] - kmin) & himask) == prefix, kv[i] - kmin);
+            __syncthreads();
+            rank_select(few, sh_n, need, &sh_prefix, &sh_need);
+            __syncthreads();
+            prefix = sh_prefix;
+            need = sh_need;
+            break;
+        }
+        const int w = rem < kDigitBits ? rem : kDigitBits, shift = rem - w, nb = 1 << w;
+        for (int i = tid; i < nb; i += kSelThreads) hist[i] = 0u;
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < PER; ++i)
+            hist_add(hist, i * kSelThreads + tid < L && ((kv[i] - kmin) & himask) == prefix,
+                     (uint32_t)((kv[i] - kmin) >> shift) & (uint32_t)(nb - 1));
+        __syncthreads();
+        pick_bin_parallel(hist, nb, need, wtot[0], prefix, shift, &sh_prefix, &sh_need, &sh_count);
+        __syncthreads();
+        prefix = sh_prefix;
+        need = sh_need;
+        count = sh_count;
+        rem = shift;
+    }
+    const uint64_t thr = kmin + prefix;
+    // kept positions in order: #greater before + min(#equal before, need)
+    const int j0 = tid * PER;
+    uint32_t fgt = 0, feq = 0;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        if (j0 + i < L) {
+            fgt |= (keys[j0 + i] > thr) ? (1u << i) : 0u;
+            feq |= (keys[j0 + i] == thr) ? (1u << i) : 0u;
+        }
+    }
+    const uint32_t cg = __popc(fgt), ce = __popc(feq);
+    uint32_t sg = cg, se = ce;
+#pragma unroll
+    for (int o = 1; o < FC_WAVE; o <<= 1) {
+        const uint32_t tg = __shfl_up(sg, o, FC_WAVE), te = __shfl_up(se, o, FC_WAVE);
+        if (lane >= o) { sg += tg; se += te; }
+    }
+    __syncthreads();
+    if (lane == 63) { wtot[0][wave] = sg; wtot[1][wave] = se; }
+    __syncthreads();
+    uint32_t gt_before = sg - cg, eq_before = se - ce;
+    for (int w = 0; w < wave; ++w) { gt_before += wtot[0][w]; eq_before += wtot[1][w]; }
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const bool g = (fgt >> i) & 1u, q = (feq >> i) & 1u;
+        if (g || (q && eq_before < need)) {
+            const uint32_t pos = gt_before + (eq_before < need ? eq_before : need);
+            kept[pos] = j0 + i;
+            if ((pos + 1) % kTileRows == 0 || (int)pos == budget - 1) tile_last[pos / kTileRows] = j0 + i;
+        }
+        gt_before += g ? 1u : 0u;
+        eq_before += q ? 1u : 0u;
     }
 }
 
@@ -1024,7 +1153,7 @@ unsigned compact_grid(int ntile, int H) {
 }
 
 struct WsLayout {
-    size_t e, keys, psum, pz, pstat, krange, hist, sel, cand, selsync, agg, sync, total;
+    size_t e, keys, psum, pz, krange, hist, sel, cand, selsync, agg, sync, total;
     int nblk, nb2, ntile;
 };
 
@@ -1045,9 +1174,8 @@ WsLayout layout(int H, int L, int d, int budget, fc_dtype dtype) {
     w.keys = off;    off += fc_align_up((size_t)H * L * 8);
     w.psum = off;    off += fc_align_up((size_t)H * nblk * d * 8);
     w.pz = off;      off += fc_align_up((size_t)H * nblk * 8);
-    w.pstat = off;   off += fc_align_up((size_t)H * nblk * 32);
     w.krange = off;  off += fc_align_up((size_t)H * 16);
-    w.hist = off;    off += fc_align_up((size_t)H * kBins * 4);
+    w.hist = off;    off += fc_align_up((size_t)H * kFirstBins * 4);
     w.sel = off;     off += fc_align_up((size_t)H * 16);
     w.cand = off;    off += fc_align_up((size_t)H * kCand * 8);
     w.selsync = off; off += fc_align_up((size_t)H * 64 * 4);
@@ -1081,7 +1209,6 @@ int launch_typed(const FcCompressArgs& a, const MT* mass, hipStream_t s, bool co
     uint64_t* keys = reinterpret_cast<uint64_t*>(ws + w.keys);
     double* psum = reinterpret_cast<double*>(ws + w.psum);
     double* pz = reinterpret_cast<double*>(ws + w.pz);
-    double* pstat = reinterpret_cast<double*>(ws + w.pstat);
     uint64_t* krange = reinterpret_cast<uint64_t*>(ws + w.krange);
     uint32_t* hist = reinterpret_cast<uint32_t*>(ws + w.hist);
     uint64_t* sel = reinterpret_cast<uint64_t*>(ws + w.sel);
@@ -1096,20 +1223,29 @@ int launch_typed(const FcCompressArgs& a, const MT* mass, hipStream_t s, bool co
     key_stats_kernel<T, D, R><<<dim3(w.nblk, a.H_k), kThreads, 0, s>>>(kc, a.head_stride, a.tok_stride,
                                                                       a.L_k, psum);
     FC_LAUNCH_CHECK();
-    mean_sim_kernel<T, D, R, MT><<<dim3(w.nblk, a.H_k), kThreads, 0, s>>>(
-        kc, a.head_stride, a.tok_stride, a.L_k, psum, w.nblk, e, pz, mass, pstat, hist);
+    const bool small = a.L_k <= kSmallL;
+    mean_sim_kernel<T, D, R><<<dim3(w.nblk, a.H_k), kThreads, 0, s>>>(
+        kc, a.head_stride, a.tok_stride, a.L_k, psum, w.nblk, e, pz, small ? nullptr : hist);
     FC_LAUNCH_CHECK();
-    score_keys_kernel<MT><<<dim3(w.nb2, a.H_k), kThreads, 0, s>>>(e, mass, pz, pstat, w.nblk, a.L_k, a.pool_k,
-                                                              a.lambda, keys, krange, hist, sync, w.ntile,
-                                                              selsync, agg);
-    FC_LAUNCH_CHECK();
-    const int nparts = w.nb2 < 8 ? w.nb2 : 8;     // blocks per head that scan for the candidates
-    select_kernel<<<dim3(nparts, a.H_k), kSelThreads, 0, s>>>(keys, krange, hist, a.L_k, a.budget, sel, cand,
-                                                             selsync);
-    FC_LAUNCH_CHECK();
-    write_kept_kernel<<<dim3(w.nb2, a.H_k), kThreads, 0, s>>>(keys, sel, a.L_k, a.budget, a.kept, sync, w.ntile,
-                                                              selsync, agg);
-    FC_LAUNCH_CHECK();
+    if (small) {
+        select_small_kernel<MT><<<a.H_k, kSelThreads, 0, s>>>(e, mass, pz, w.nblk, a.L_k, a.budget, a.pool_k, a.lambda,
+                                                              a.kept, sync, w.ntile);
+        FC_LAUNCH_CHECK();
+    } else {
+        score_keys_kernel<MT><<<dim3(w.nb2, a.H_k), kThreads, 0, s>>>(e, mass, pz, w.nblk, a.L_k, a.budget, a.pool_k,
+                                                                  a.lambda, keys, krange, hist, sync, w.ntile,
+                                                                  selsync, agg);
+        FC_LAUNCH_CHECK();
+        // blocks per head that scan for the candidates: one batch of loads each, up to 131072 keys
+        constexpr int kBatch = kSelThreads * kUnroll;
+        const int nparts = a.L_k <= 16 * kBatch ? (a.L_k + kBatch - 1) / kBatch : 16;
+        select_kernel<<<dim3(nparts, a.H_k), kSelThreads, 0, s>>>(keys, krange, hist, a.L_k, a.budget, sel, cand,
+                                                                 selsync);
+        FC_LAUNCH_CHECK();
+        write_kept_kernel<<<dim3(w.nb2, a.H_k), kThreads, 0, s>>>(keys, sel, a.L_k, a.budget, a.kept, sync, w.ntile,
+                                                                  selsync, agg);
+        FC_LAUNCH_CHECK();
+    }
     if (!compact || a.phase == 1) return FC_OK;   // scoring and selection only
     if constexpr (sizeof(T) <= 4) {
         constexpr int VPR = D * (int)sizeof(T) / 16;

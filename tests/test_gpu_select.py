@@ -1,0 +1,69 @@
+"""Selection of the top-B keys: heads up to 4096 keys go to one block, longer ones to a histogram over a
+bracket taken from 128 sampled keys, with a list of at most 4096 candidates and, in LDS, comparison of at
+most 256.  Lengths and budgets sit at those edges.  With lambda = 1 and no pooling the score is the
+importance itself, so the cases can put the wanted key where they like: inside the bracket, below or
+above it (the sampled positions hold the other values), among ties.  Whole
+numbers: exact against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import flowcache_oracle as O
+from paper_2602_10825_amd import binding as B
+from paper_2602_10825_amd import synth
+from tests.test_gpu_parity import DEV, dev
+
+pytestmark = pytest.mark.gpu
+
+
+def sampled(L):
+    q = np.arange(128, dtype=np.uint64)
+    jitter = ((q * 2654435761) & 0xFFFFFFFF) >> 12
+    return (q * L // 128 + jitter % (L // 128)).astype(np.int64)
+
+
+def importance(kind, L, rng):
+    if kind == "even":
+        return rng.random(L)
+    if kind == "skewed":
+        return np.exp(12.0 * rng.standard_normal(L))
+    if kind == "plateaus":                  # eleven values
+        return rng.integers(0, 11, L) / 11.0
+    if kind == "equal":
+        return np.full(L, 0.25)
+    m = rng.random(L)
+    m[sampled(L)] = (2.0 if kind == "below" else -2.0) + rng.random(128)
+    return m
+
+
+@pytest.mark.parametrize("kind,L,budget", [
+    ("even", 2, 1), ("even", 257, 256), ("even", 1312, 984), ("even", 4096, 4095), ("even", 4096, 1),
+    ("skewed", 4095, 2000), ("plateaus", 4096, 1234), ("equal", 3000, 77),
+    ("even", 4097, 4096), ("even", 4097, 1), ("skewed", 20001, 15000), ("skewed", 50000, 100),
+    ("plateaus", 20000, 9000), ("plateaus", 4100, 300), ("equal", 20000, 12345),
+    ("below", 20001, 10000), ("above", 20001, 10000),     # more candidates outside than the list holds
+    ("below", 4200, 4150), ("above", 4200, 40),           # few enough for it
+])
+def test_selection_by_importance_alone(kind, L, budget):
+    rng = np.random.default_rng(L + budget)
+    k = synth.to_storage(rng.standard_normal((2, L, 64)).astype(np.float32), "bf16")
+    mass = np.stack([importance(kind, L, rng) for _ in range(2)]).astype(np.float32)
+    kept = B.flowcache_kv_select(dev(k, "bf16"), L, budget, torch.from_numpy(mass).to(DEV), 1, 1.0)
+    ref = np.stack([O.select_top_b(m.astype(np.float64), budget) for m in mass])
+    assert np.array_equal(kept.cpu().numpy(), ref)
+
+
+@pytest.mark.parametrize("dtype,d,L,budget,pool_k", [
+    ("bf16", 128, 4096, 3000, 7), ("bf16", 128, 4097, 3000, 7), ("f32", 64, 700, 350, 9), ("f32", 128, 9000, 4500, 3),
+])
+def test_selection_with_redundancy(dtype, d, L, budget, pool_k):
+    rng = np.random.default_rng(L)
+    k = synth.to_storage(rng.standard_normal((2, L, d)).astype(np.float32), dtype)
+    v = synth.to_storage(rng.standard_normal((2, L, d)).astype(np.float32), dtype)
+    mass = (rng.exponential(size=(2, L)) ** 2).astype(np.float32)
+    mass /= mass.sum(1, keepdims=True)
+    kc, vc = dev(k, dtype), dev(v, dtype)
+    kept = B.flowcache_kv_compress(kc, vc, L, budget, torch.from_numpy(mass).to(DEV), pool_k, 0.07)
+    rk, rk_k, rk_v, _ = O.kv_compress(k, v, L, budget, mass, pool_k, 0.07)
+    assert np.array_equal(kept.cpu().numpy(), rk)
+    assert np.array_equal(B.to_host(kc), rk_k) and np.array_equal(B.to_host(vc), rk_v)
