@@ -50,7 +50,9 @@ constexpr int kSmallL = kSelThreads * 4;   // heads up to this length are select
 constexpr int kUnroll = 8;    // independent loads in flight per thread in the selection scans
 
 // ---- bookkeeping of the in-place compaction (kernels further down) ----------------------
-constexpr int kTileRows = 64;
+// Rows per tile of the compaction: 16 KB or more of each cache.  (128-byte rows in tiles of 64 were bound
+// by what each tile costs: 24 heads of 84000 -> 40000 rows 187 us, in tiles of 128 108.)
+__host__ __device__ constexpr int tile_rows(int row_bytes) { return row_bytes <= 128 ? 128 : 64; }
 constexpr uint32_t kSpinLimit = 1u << 24;
 
 // Words of the sync area (uint32), all reset earlier in the call:
@@ -752,7 +754,7 @@ __global__ __launch_bounds__(kThreads) void write_kept_kernel(const uint64_t* __
                                                               const uint64_t* __restrict__ sel, int L,
                                                               int budget, int32_t* __restrict__ kept_all,
                                                               uint32_t* __restrict__ sync, int ntile,
-                                                              uint32_t* __restrict__ selsync,
+                                                              int trows, uint32_t* __restrict__ selsync,
                                                               uint64_t* __restrict__ agg_all) {
     const int h = blockIdx.y, tid = threadIdx.x;
     const int wave = tid / FC_WAVE, lane = tid & 63;
@@ -831,7 +833,7 @@ __global__ __launch_bounds__(kThreads) void write_kept_kernel(const uint64_t* __
         if (g || (e && eq_before < need)) {
             const uint32_t pos = gt_before + (eq_before < need ? eq_before : need);
             kept[pos] = j0 + i;
-            if ((pos + 1) % kTileRows == 0 || (int)pos == budget - 1) tile_last[pos / kTileRows] = j0 + i;
+            if ((pos + 1) % (uint32_t)trows == 0 || (int)pos == budget - 1) tile_last[pos / (uint32_t)trows] = j0 + i;
         }
         gt_before += g ? 1u : 0u;
         eq_before += e ? 1u : 0u;
@@ -845,7 +847,8 @@ __global__ __launch_bounds__(kThreads) void write_kept_kernel(const uint64_t* __
 template <typename MT>
 __global__ __launch_bounds__(kSelThreads) void select_small_kernel(
     const double* __restrict__ e_all, const MT* __restrict__ mass_all, const double* __restrict__ pz_all, int nblkz,
-    int L, int budget, int pool_k, double lambda, int32_t* __restrict__ kept_all, uint32_t* __restrict__ sync, int ntile) {
+    int L, int budget, int pool_k, double lambda, int32_t* __restrict__ kept_all, uint32_t* __restrict__ sync, int ntile,
+    int trows) {
     constexpr int PER = kSmallL / kSelThreads;
     const int h = blockIdx.x, tid = threadIdx.x, wave = tid / FC_WAVE, lane = tid & 63;
     const double* e = e_all + (int64_t)h * L;
@@ -982,7 +985,7 @@ __global__ __launch_bounds__(kSelThreads) void select_small_kernel(
         if (g || (q && eq_before < need)) {
             const uint32_t pos = gt_before + (eq_before < need ? eq_before : need);
             kept[pos] = j0 + i;
-            if ((pos + 1) % kTileRows == 0 || (int)pos == budget - 1) tile_last[pos / kTileRows] = j0 + i;
+            if ((pos + 1) % (uint32_t)trows == 0 || (int)pos == budget - 1) tile_last[pos / (uint32_t)trows] = j0 + i;
         }
         gt_before += g ? 1u : 0u;
         eq_before += q ? 1u : 0u;
@@ -995,17 +998,20 @@ __global__ void iota_kernel(int32_t* kept, int H, int n) {
 }
 
 // ---- in-place compaction ---------------------------------------------------------------
-// Rows are VPR 16-byte vectors; a tile is 64 destination rows of one head.  The launch is a
+// Rows are VPR 16-byte vectors; a tile is tile_rows() destination rows of one head.  The launch is a
 // fixed number of blocks that draw tiles from ONE ticket counter until it runs out: ticket g is
 // tile g / H of head g % H, so a head's tiles are drawn in ascending order while consecutive
 // tickets -- the tiles in flight at any moment -- are spread over all heads and seldom depend
 // on one another.  Tile t may overwrite rows that a lower tile of its head still has to read
 // (sources never lie below their destination): it stores only after every lower tile whose
 // last source row reaches into its rows has published "read".
-// A block works on its tiles in a two-stage pipeline: while the rows of the current tile are
-// on their way it draws the next ticket, and it requests the next tile's row indices and what
-// it needs to know about that tile's predecessors (their last source row, their flag) before it
-// waits and stores the current one.  Every wait ends: a tile waits only for tiles of lower
+// A block works on its tiles in a two-stage pipeline: before it waits for the current tile's predecessors
+// and stores it, it draws the next ticket and requests that tile's row indices, what it needs to
+// know about the tile's predecessors (their last source row, their flag) and the rows themselves.
+// (Rows loaded early are safe: no tile is stored before the lower tiles that read from it say so, and
+// higher ones never do.  With the rows requested only after the stores, a block that waited had nothing
+// in flight: 12 heads of 51000 -> 40800 rows 126 us, now 112; of 20000 -> 18000 65, now 60; 24 of 74880 ->
+// 37440, where few tiles wait, 190 and 192.)  Every wait ends: a tile waits only for tiles of lower
 // tickets; such a tile is held by a running block either as its current tile (published as soon
 // as its rows have arrived, before that block waits for anything) or as its next tile, which
 // becomes current once that block's current tile -- drawn earlier still -- is done; following
@@ -1015,6 +1021,7 @@ __global__ __launch_bounds__(kThreads) void compact_rows_kernel(
     uint4* __restrict__ k_cache, uint4* __restrict__ v_cache, int64_t head_stride_v,
     int64_t tok_stride_v, int H, int L, int budget, int ntile, const int32_t* __restrict__ kept_all,
     uint32_t* __restrict__ sync) {
+    constexpr int kTileRows = tile_rows(VPR * 16);
     constexpr int LDN = kTileRows * VPR / kThreads;   // vectors per thread per matrix
     constexpr int RPP = kThreads / VPR;               // rows per pass
     __shared__ uint32_t sh_ticket;
@@ -1049,32 +1056,39 @@ __global__ __launch_bounds__(kThreads) void compact_rows_kernel(
         }
     };
 
+    struct Rows { u32x4_native k[LDN], v[LDN]; };   // native vectors: the arrays stay in registers
+    auto load_rows = [&](Tile& T, Rows& R) {
+        const uint4* kh = k_cache + T.h * head_stride_v;
+        const uint4* vh = v_cache + T.h * head_stride_v;
+#pragma unroll
+        for (int p = 0; p < LDN; ++p) {
+            const int s = T.tile * kTileRows + p * RPP + lrow;
+            if (T.src[p] >= L) T.src[p] = -1;   // never read outside the compressed range
+            if (T.src[p] == s) T.src[p] = -1;   // already in place
+            // branch-free: a row that is not moved loads row 0 instead (in range, value unused),
+            // so that all loads of the tile are in flight together
+            const int64_t a = (int64_t)(T.src[p] >= 0 ? T.src[p] : 0) * tok_stride_v + lcol;
+            R.k[p] = *reinterpret_cast<const u32x4_native*>(kh + a);
+            R.v[p] = *reinterpret_cast<const u32x4_native*>(vh + a);
+        }
+    };
+
     if (tid == 0) sh_ticket = atomicAdd(ticket, 1u);
     __syncthreads();
     uint32_t g = sh_ticket;
     if (g >= total) return;
     Tile cur;
+    Rows rows;
     request(g, cur);
+    load_rows(cur, rows);
+    uint32_t g_next = 0;
+    if (tid == 0) g_next = atomicAdd(ticket, 1u);               // travels with the rows
     for (;;) {
         const int row0 = cur.tile * kTileRows;
         uint4* kh = k_cache + cur.h * head_stride_v;
         uint4* vh = v_cache + cur.h * head_stride_v;
         uint32_t* flags = sync_flags(sync, H, ntile, cur.h);
         const int32_t* tile_last = sync_tile_last(sync, H, ntile, cur.h);
-        u32x4_native kr[LDN], vr[LDN];   // native vectors: the arrays stay in registers
-#pragma unroll
-        for (int p = 0; p < LDN; ++p) {
-            const int s = row0 + p * RPP + lrow;
-            if (cur.src[p] >= L) cur.src[p] = -1;   // never read outside the compressed range
-            if (cur.src[p] == s) cur.src[p] = -1;   // already in place
-            // branch-free: a row that is not moved loads row 0 instead (in range, value unused),
-            // so that all loads of the tile are in flight together
-            const int64_t a = (int64_t)(cur.src[p] >= 0 ? cur.src[p] : 0) * tok_stride_v + lcol;
-            kr[p] = *reinterpret_cast<const u32x4_native*>(kh + a);
-            vr[p] = *reinterpret_cast<const u32x4_native*>(vh + a);
-        }
-        uint32_t g_next = 0;
-        if (tid == 0) g_next = atomicAdd(ticket, 1u);           // travels with the rows
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");        // the rows are in registers
         if (tid == 0) sh_ticket = g_next;
         __syncthreads();
@@ -1082,10 +1096,15 @@ __global__ __launch_bounds__(kThreads) void compact_rows_kernel(
         // loaded, then flag" matters, and the loads have returned.  (A release fence here would
         // write back the whole L2 of this XCD, once per tile.)
         if (tid == 0) __hip_atomic_fetch_or(&flags[cur.tile], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        g_next = sh_ticket;
-        const bool more = g_next < total;
+        g = sh_ticket;
+        const bool more = g < total;
         Tile nxt;
-        if (more) request(g_next, nxt);       // on its way while this tile waits and stores
+        Rows nrows;
+        if (more) {                           // on its way while this tile waits and stores
+            request(g, nxt);
+            load_rows(nxt, nrows);
+            if (tid == 0) g_next = atomicAdd(ticket, 1u);
+        }
         // Lower tiles whose last (= largest) source row is >= row0 read from this tile's rows.
         // The last source rows ascend with the tile, so each thread walks down from its nearest
         // tile and stops at the first one that ends below row0.
@@ -1115,12 +1134,13 @@ __global__ __launch_bounds__(kThreads) void compact_rows_kernel(
                 // streaming stores: written the ordinary way, up to a cache's worth of these rows
                 // stays behind as dirty lines and is written back during whichever kernel runs
                 // next (a following pass over 460 MB of cold keys: 118 us instead of 90)
-                __builtin_nontemporal_store(kr[p], reinterpret_cast<u32x4_native*>(kh + a));
-                __builtin_nontemporal_store(vr[p], reinterpret_cast<u32x4_native*>(vh + a));
+                __builtin_nontemporal_store(rows.k[p], reinterpret_cast<u32x4_native*>(kh + a));
+                __builtin_nontemporal_store(rows.v[p], reinterpret_cast<u32x4_native*>(vh + a));
             }
         }
         if (!more) break;
         cur = nxt;
+        rows = nrows;
     }
 }
 
@@ -1128,25 +1148,24 @@ __global__ __launch_bounds__(kThreads) void compact_rows_kernel(
 // flags and status word, and every tile's last source row.  grid = (blocks, H).
 __global__ __launch_bounds__(kThreads) void prep_compact_kernel(uint32_t* __restrict__ sync, int H, int ntile,
                                                                 const int32_t* __restrict__ kept_all,
-                                                                int budget, int L) {
+                                                                int budget, int trows) {
     const int h = blockIdx.y;
     uint32_t* flags = sync_flags(sync, H, ntile, h);
     int32_t* tile_last = sync_tile_last(sync, H, ntile, h);
     for (int t = blockIdx.x * kThreads + threadIdx.x; t < ntile; t += gridDim.x * kThreads) {
         flags[t] = 0u;
-        const int e = ((t + 1) * kTileRows < budget ? (t + 1) * kTileRows : budget) - 1;
+        const int e = ((t + 1) * trows < budget ? (t + 1) * trows : budget) - 1;
         tile_last[t] = kept_all[(int64_t)h * budget + e];
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         sync[64 * (h + 1)] = 0u;
         if (h == 0) sync[0] = 0u;
     }
-    (void)L;
 }
 
-// Blocks of the compaction: two per compute unit, never more than there are tiles.  Measured on
-// the MAGI-1-like cache (24 x 37440 rows of 256 bytes moved): 2048 blocks 215 us, 1024 200 us,
-// 512 186 us, 256 197 us -- fewer streams in flight keep more of each open DRAM page in use.
+// Blocks of the compaction: two per compute unit, never more than there are tiles.  Measured (12 heads
+// of 51000 -> 40800 rows of 256 bytes / 24 of 74880 -> 37440): 256 blocks 119 / 215 us, 384 116 / 201, 512 112
+// / 193, 640 116 / 195 -- more streams in flight keep less of each open DRAM page in use.
 unsigned compact_grid(int ntile, int H) {
     const int64_t tiles = (int64_t)ntile * H;
     return (unsigned)(tiles < 512 ? tiles : 512);
@@ -1180,9 +1199,9 @@ WsLayout layout(int H, int L, int d, int budget, fc_dtype dtype) {
     w.cand = off;    off += fc_align_up((size_t)H * kCand * 8);
     w.selsync = off; off += fc_align_up((size_t)H * 64 * 4);
     w.agg = off;     off += fc_align_up((size_t)H * w.nb2 * 8);
-    w.ntile = (((budget < L) ? budget : L) + kTileRows - 1) / kTileRows;
+    const int trows = tile_rows(d * (int)esz);
+    w.ntile = (((budget < L) ? budget : L) + trows - 1) / trows;
     w.sync = off;    off += fc_align_up(sync_words(H, w.ntile) * 4);
-    (void)esz;
     w.total = off;
     return w;
 }
@@ -1190,11 +1209,13 @@ WsLayout layout(int H, int L, int d, int budget, fc_dtype dtype) {
 template <typename T, int D, typename MT>
 int launch_typed(const FcCompressArgs& a, const MT* mass, hipStream_t s, bool compact = true) {
     const WsLayout w = layout(a.H_k, a.L_k, a.d, a.budget, a.dtype);
+    // (the float64 instantiation moves no rows: its layout has the tiles of four-byte rows)
+    constexpr int TR = tile_rows(D * (int)(sizeof(T) == 8 ? 4 : sizeof(T)));
     if constexpr (sizeof(T) <= 4) {   // (the float64 instantiation scores pooled keys: no rows to move)
         if (a.phase == 2) {           // rows only: the kept list is the caller's
             uint32_t* sync2 = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(a.ws) + w.sync);
             prep_compact_kernel<<<dim3((w.ntile + kThreads - 1) / kThreads, a.H_k), kThreads, 0, s>>>(
-                sync2, a.H_k, w.ntile, a.kept, a.budget, a.L_k);
+                sync2, a.H_k, w.ntile, a.kept, a.budget, TR);
             FC_LAUNCH_CHECK();
             constexpr int VPR2 = D * (int)sizeof(T) / 16;
             const int64_t hs2 = a.head_stride * (int64_t)sizeof(T) / 16, ts2 = a.tok_stride * (int64_t)sizeof(T) / 16;
@@ -1229,7 +1250,7 @@ int launch_typed(const FcCompressArgs& a, const MT* mass, hipStream_t s, bool co
     FC_LAUNCH_CHECK();
     if (small) {
         select_small_kernel<MT><<<a.H_k, kSelThreads, 0, s>>>(e, mass, pz, w.nblk, a.L_k, a.budget, a.pool_k, a.lambda,
-                                                              a.kept, sync, w.ntile);
+                                                              a.kept, sync, w.ntile, TR);
         FC_LAUNCH_CHECK();
     } else {
         score_keys_kernel<MT><<<dim3(w.nb2, a.H_k), kThreads, 0, s>>>(e, mass, pz, w.nblk, a.L_k, a.budget, a.pool_k,
@@ -1242,7 +1263,7 @@ int launch_typed(const FcCompressArgs& a, const MT* mass, hipStream_t s, bool co
         select_kernel<<<dim3(nparts, a.H_k), kSelThreads, 0, s>>>(keys, krange, hist, a.L_k, a.budget, sel, cand,
                                                                  selsync);
         FC_LAUNCH_CHECK();
-        write_kept_kernel<<<dim3(w.nb2, a.H_k), kThreads, 0, s>>>(keys, sel, a.L_k, a.budget, a.kept, sync, w.ntile,
+        write_kept_kernel<<<dim3(w.nb2, a.H_k), kThreads, 0, s>>>(keys, sel, a.L_k, a.budget, a.kept, sync, w.ntile, TR,
                                                                   selsync, agg);
         FC_LAUNCH_CHECK();
     }
@@ -1306,14 +1327,14 @@ __global__ __launch_bounds__(kThreads) void expand_groups_kernel(
 
 struct GroupedLayout {
     size_t k_pooled, mass_pooled, kept_groups, inner, sync, total;
-    int G, Bg, ntile;
+    int G, Bg, ntile;      // (64-row tiles; longer ones need less of the sync area)
 };
 
 GroupedLayout grouped_layout(int H, int L, int d, int budget, int group) {
     GroupedLayout w;
     w.G = L / group;
     w.Bg = budget / group;
-    w.ntile = (budget + kTileRows - 1) / kTileRows;
+    w.ntile = (budget + 63) / 64;
     size_t off = 0;
     w.k_pooled = off;    off += fc_align_up((size_t)H * w.G * d * 8);
     w.mass_pooled = off; off += fc_align_up((size_t)H * w.G * 8);
@@ -1348,13 +1369,14 @@ int launch_grouped(const FcCompressArgs& a, hipStream_t s) {
     gx = gx < 1 ? 1 : (gx > 256 ? 256 : gx);
     expand_groups_kernel<<<dim3(gx, a.H_k), kThreads, 0, s>>>(kept_groups, w.Bg, a.group, a.kept);
     FC_LAUNCH_CHECK();
-    prep_compact_kernel<<<dim3((w.ntile + kThreads - 1) / kThreads, a.H_k), kThreads, 0, s>>>(
-        sync, a.H_k, w.ntile, a.kept, a.budget, a.L_k);
+    constexpr int VPR = D * (int)sizeof(T) / 16, TR = tile_rows(VPR * 16);
+    const int ntile = (a.budget + TR - 1) / TR;
+    prep_compact_kernel<<<dim3((ntile + kThreads - 1) / kThreads, a.H_k), kThreads, 0, s>>>(
+        sync, a.H_k, ntile, a.kept, a.budget, TR);
     FC_LAUNCH_CHECK();
-    constexpr int VPR = D * (int)sizeof(T) / 16;
     const int64_t hs = a.head_stride * (int64_t)sizeof(T) / 16, ts = a.tok_stride * (int64_t)sizeof(T) / 16;
-    compact_rows_kernel<VPR><<<dim3(compact_grid(w.ntile, a.H_k)), kThreads, 0, s>>>(
-        (uint4*)a.k_cache, (uint4*)a.v_cache, hs, ts, a.H_k, a.L_k, a.budget, w.ntile, a.kept, sync);
+    compact_rows_kernel<VPR><<<dim3(compact_grid(ntile, a.H_k)), kThreads, 0, s>>>(
+        (uint4*)a.k_cache, (uint4*)a.v_cache, hs, ts, a.H_k, a.L_k, a.budget, ntile, a.kept, sync);
     FC_LAUNCH_CHECK();
     return FC_OK;
 }
