@@ -194,6 +194,81 @@ __global__ __launch_bounds__(kF32Waves * 64, 2) void mass_cols_f32_kernel(FcMass
     }
 }
 
+// At most kFewRows rows per key head: one thread per key, its key in registers, the rows broadcast
+// from LDS.  Bound by the two reads of K.
+constexpr int kFewRows = 2;
+
+template <int D>
+__device__ __forceinline__ void load_key_f32(const FcMassArgs& a, int hk, int j, f32x4_t (&k)[D / 4]) {
+    const float* p = (const float*)a.k_cache + (int64_t)hk * a.head_stride + (int64_t)(j < a.mass_len ? j : a.mass_len - 1) * a.tok_stride;
+#pragma unroll
+    for (int e = 0; e < D / 4; ++e) k[e] = *reinterpret_cast<const f32x4_t*>(p + 4 * e);
+}
+template <int D>
+__device__ __forceinline__ float dot_f32(const f32x4_t (&k)[D / 4], const float* q) {
+    float s = 0.f;
+#pragma unroll
+    for (int e = 0; e < D; ++e) s = fmaf(k[e / 4][e % 4], q[e], s);
+    return s;
+}
+__device__ __forceinline__ void stage_rows_f32(const FcMassArgs& a, int64_t row0, int h, int D, float* qs) {
+    for (int i = threadIdx.x; i < a.W * D; i += kNT) {
+        const int w = i / D, e = i % D;
+        qs[i] = ((const float*)a.q_base)[((row0 + w) * a.H_q + h) * D + e];
+    }
+}
+
+template <int D>
+__global__ __launch_bounds__(kNT) void mass_stats_f32_few_kernel(FcMassArgs a, int np, float* __restrict__ pm,
+                                                                float* __restrict__ pl) {
+    int64_t row0;
+    if (!resolve_rows(a, row0)) return;
+    const int h = blockIdx.y, tid = threadIdx.x;
+    const int j = blockIdx.x * kNT + tid;
+    __shared__ __attribute__((aligned(16))) float qs[kFewRows * D];
+    stage_rows_f32(a, row0, h, D, qs);
+    f32x4_t k[D / 4];
+    load_key_f32<D>(a, h / (a.H_q / a.H_k), j, k);
+    __syncthreads();
+    const float c2 = a.scale * kLog2e;
+    const int slot = blockIdx.x * (kNT / FC_WAVE) + tid / FC_WAVE;
+    for (int w = 0; w < a.W; ++w) {
+        const float s = j < a.mass_len ? dot_f32<D>(k, qs + w * D) * c2 : kNegBig;
+        const float mx = wave_max_all(s);
+        const float sum = wave_sum_all(__builtin_amdgcn_exp2f(s - mx));
+        if (tid % FC_WAVE == 0) {
+            pm[((int64_t)h * kRowGroup + w) * np + slot] = mx;
+            pl[((int64_t)h * kRowGroup + w) * np + slot] = sum;
+        }
+    }
+}
+
+template <int D>
+__global__ __launch_bounds__(kNT) void mass_cols_f32_few_kernel(FcMassArgs a, const float* __restrict__ lse2) {
+    const int hk = blockIdx.y, tid = threadIdx.x;
+    const int j = blockIdx.x * kNT + tid;
+    int64_t row0;
+    if (!resolve_rows(a, row0)) {
+        if (j < a.mass_len) a.mass[(int64_t)hk * a.mass_len + j] = __uint_as_float(0x7fc00000u);
+        return;
+    }
+    const int G = a.H_q / a.H_k;
+    __shared__ __attribute__((aligned(16))) float qs[kFewRows * D];
+    f32x4_t k[D / 4];
+    load_key_f32<D>(a, hk, j, k);
+    const float c2 = a.scale * kLog2e;
+    float acc = 0.f;
+    for (int g = 0; g < G; ++g) {
+        const int h = hk * G + g;
+        __syncthreads();
+        stage_rows_f32(a, row0, h, D, qs);
+        __syncthreads();
+        for (int w = 0; w < a.W; ++w)
+            acc += __builtin_amdgcn_exp2f(dot_f32<D>(k, qs + w * D) * c2 - lse2[h * kRowGroup + w]);
+    }
+    if (j < a.mass_len) a.mass[(int64_t)hk * a.mass_len + j] = acc / (float)(a.W * G);
+}
+
 // Between the passes: log2-sum-exp of every observation row over all keys, from the blocks'
 // partials.  One block per (row group, query head); four lanes per row take every fourth
 // partial (loads batched four deep) and merge in a fixed order.  Padding rows get a huge
@@ -233,8 +308,15 @@ __global__ __launch_bounds__(kNT) void mass_lse_kernel(const float* __restrict__
         sum = lo + hi;
         mx = mn;
     }
-    if (part == 0)
-        lse2[((int64_t)h * nrg + rg) * kRowGroup + row] = row < nw ? mx + __builtin_amdgcn_logf(sum) : kPosBig;
+    if (part == 0) {
+        // log2(sum) = e + log2(f), 1/2 <= f < 1, so that the logarithm's own error (one of its last
+        // place) stays below the one rounding of the total: mx + e in two terms.  (mx + log2(sum) as
+        // it stands made every entry of the importance wrong by up to 3e-7, now 1e-7.)
+        const float e = (float)__builtin_amdgcn_frexp_expf(sum), f = __builtin_amdgcn_frexp_mantf(sum);
+        const float hi = mx + e, b = hi - mx;
+        const float lo = (mx - (hi - b)) + (e - b);
+        lse2[((int64_t)h * nrg + rg) * kRowGroup + row] = row < nw ? hi + (lo + __builtin_amdgcn_logf(f)) : kPosBig;
+    }
 }
 
 // ---- bf16: matrix-core passes -------------------------------------------------------
@@ -888,8 +970,27 @@ int launch_bf16(const FcMassArgs& a, hipStream_t s) {
 // wavefront, and no more partials than the workspace holds (per row group one per 512 keys; one
 // group alone has room for one per 64).  Pass 2: as few wavefronts on the same keys as still give two
 // blocks per compute unit, never more than there are row tiles.
+// With one or two rows per key head nothing is left for the matrix cores to do: the kernels of one
+// thread per key (12 x 128, one row on 3000 keys 22 us against 27; 24 x 128 on 12000 keys 78 against 106;
+// with four heads on one key head 35 against 26).
+template <int D>
+int launch_f32_few(const FcMassArgs& a, hipStream_t s) {
+    const int nkb = (a.mass_len + kNT - 1) / kNT, np = nkb * (kNT / FC_WAVE);
+    float* pm = reinterpret_cast<float*>(a.ws);
+    float* pl = pm + (size_t)a.H_q * kRowGroup * np;
+    float* lse2 = pl + (size_t)a.H_q * kRowGroup * np;
+    mass_stats_f32_few_kernel<D><<<dim3(nkb, a.H_q), kNT, 0, s>>>(a, np, pm, pl);
+    FC_LAUNCH_CHECK();
+    mass_lse_kernel<<<dim3(1, a.H_q), kNT, 0, s>>>(pm, pl, 1, np, a.W, lse2);
+    FC_LAUNCH_CHECK();
+    mass_cols_f32_few_kernel<D><<<dim3(nkb, a.H_k), kNT, 0, s>>>(a, lse2);
+    FC_LAUNCH_CHECK();
+    return FC_OK;
+}
+
 template <int D>
 int launch_f32(const FcMassArgs& a, hipStream_t s) {
+    if (a.W * (a.H_q / a.H_k) <= kFewRows && a.W <= kFewRows) return launch_f32_few<D>(a, s);
     const int nrg = (a.W + kRowGroup - 1) / kRowGroup, rt = (a.W + 31) / 32;
     const int most = nrg == 1 ? a.mass_len / 256 : a.mass_len / 512;
     const int64_t units = (int64_t)a.H_q * rt;

@@ -1,7 +1,7 @@
 """fp32 importance mass on the matrix cores: 32 rows (pass 1) or 32 keys (pass 2) stay in a wavefront, eight
 wavefronts to a block, key ranges over blocks.  Sizes at the edges: one row and one key, a tile of rows or
 keys more or less, fewer key tiles than wavefronts, several ranges, one to eight wavefronts on the same
-keys; against the float64 oracle at its usual bars."""
+keys, and the one-thread-per-key kernels for one or two rows; against the float64 oracle at its usual bars."""
 import numpy as np
 import pytest
 
@@ -22,6 +22,8 @@ pytestmark = pytest.mark.gpu
     (128, 2, 1, 130, 1100, 4.0),      # scores that grow along the keys
     (64, 24, 24, 20, 6000, 4.0),      # enough key blocks that no two wavefronts share one
     (128, 1, 1, 300, 3000, 1.0),
+    (128, 3, 3, 1, 1000, 1.0), (64, 2, 1, 1, 257, 4.0), (64, 1, 1, 2, 3000, 4.0),   # one thread per key
+    (64, 3, 1, 1, 257, 1.0), (128, 2, 2, 3, 257, 1.0),                              # and just past it
 ])
 def test_mass_f32(d, H_q, H_k, W, L, grow):
     rng = np.random.default_rng(L + W)
