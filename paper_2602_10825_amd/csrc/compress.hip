@@ -44,6 +44,7 @@ constexpr int kRank = 256;    // candidates resolved by comparing each with each
 // bins: 42, 43 and 44 us)
 constexpr int kFirstBits = 9;
 constexpr int kFirstBins = 1 << kFirstBits;
+constexpr int kHalo = 64;     // importance beside a block's tokens that score_keys keeps in LDS
 constexpr int kSample = 128;  // keys that the first digit's bracket is taken from
 constexpr int kSampleWide = 28;   // the bracket's half width in ranks of the sample: five deviations
 constexpr int kSmallL = kSelThreads * 4;   // heads up to this length are selected by one block
@@ -332,17 +333,21 @@ __global__ __launch_bounds__(kThreads) void mean_sim_kernel(
     }
 }
 
-// fixed-shape tree over the block: deterministic, and identical in every block that runs it
-template <int NT>
-__device__ __forceinline__ double block_sum_fixed(double v, double* sh) {
+// Sum over the first kThreads threads of a block, along a fixed tree (distances 128, 64, ..., 1): the same
+// bits in every block that runs it.  A block of more threads passes anything in the others.
+__device__ __forceinline__ double block_sum_fixed(double v, double* sh) {   // sh: kThreads + 1
+    static_assert(kThreads == 256, "four terms per lane");
+    const int t = threadIdx.x;
+    if (t < kThreads) sh[t] = v;
     __syncthreads();
-    sh[threadIdx.x] = v;
-    __syncthreads();
-    for (int s = NT / 2; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) sh[threadIdx.x] += sh[threadIdx.x + s];
-        __syncthreads();
+    if (t < FC_WAVE) {
+        double z = (sh[t] + sh[t + 128]) + (sh[t + 64] + sh[t + 192]);
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) z += __shfl_down(z, o, FC_WAVE);
+        if (t == 0) sh[kThreads] = z;
     }
-    return sh[0];
+    __syncthreads();
+    return sh[kThreads];
 }
 
 // Histogram increment that survives skew: the digits most lanes of a wavefront share are
@@ -405,7 +410,8 @@ __global__ __launch_bounds__(kThreads) void score_keys_kernel(
     const double* e = e_all + (int64_t)h * L;
     const MT* mass = mass_all + (int64_t)h * L;
     uint64_t* keys = keys_all + (int64_t)h * L;
-    __shared__ double shd[kThreads];
+    __shared__ double shd[kThreads + 1];
+    __shared__ MT ms[kTokBlk + 2 * kHalo];
     __shared__ uint64_t sample[kSample];
     __shared__ uint64_t sh_lo, sh_hi;
     __shared__ uint32_t hist[kFirstBins];
@@ -416,10 +422,19 @@ __global__ __launch_bounds__(kThreads) void score_keys_kernel(
     const int sj = (int)((int64_t)sq * L / kSample) + (int)(((uint32_t)sq * 2654435761u >> 12) % (uint32_t)slen);
     const double se = e[sj];
     MT simp = mass[sj];
-    for (int d = 1; d <= half; ++d) {
-        const MT lo = mass[sj - d >= 0 ? sj - d : 0], hi = mass[sj + d < L ? sj + d : L - 1];
-        const MT nb = lo > hi ? lo : hi;
-        simp = simp > nb ? simp : nb;
+    for (int d0 = 1; d0 <= half; d0 += 4) {       // four distances of the window in flight at a time
+        MT lo[4], hi[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int d = d0 + i < half ? d0 + i : half;
+            lo[i] = mass[sj - d >= 0 ? sj - d : 0];
+            hi[i] = mass[sj + d < L ? sj + d : L - 1];
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const MT nb = lo[i] > hi[i] ? lo[i] : hi[i];
+            simp = simp > nb ? simp : nb;
+        }
     }
     if (blockIdx.x == 0) {   // state later kernels of this call start from: tile flags, tickets
         uint32_t* flags = sync_flags(sync, gridDim.y, ntile, h);
@@ -439,10 +454,21 @@ __global__ __launch_bounds__(kThreads) void score_keys_kernel(
         ev[i] = (j < L) ? e[j] : 0.0;
         imp[i] = (j < L) ? mass[j] : (MT)0;
     }
+    const bool staged = half <= kHalo;            // the window comes from LDS
+    if (staged) {
+        MT edge = (MT)0;
+        const int lj = j0 - 1 - tid, rj = j0 + kTokBlk + tid - kHalo;
+        if (tid < kHalo) edge = mass[lj >= 0 ? lj : 0];
+        else if (tid < 2 * kHalo) edge = mass[rj < L ? rj : L - 1];
+#pragma unroll
+        for (int i = 0; i < kItems; ++i) ms[kHalo + i * kThreads + tid] = imp[i];
+        if (tid < kHalo) ms[kHalo - 1 - tid] = edge;
+        else if (tid < 2 * kHalo) ms[kTokBlk + tid] = edge;
+    }
     // Z = sum_j e_j: the block partials of the pass that wrote e, in a fixed order
     double z = 0.0;
     for (int i = tid; i < nblkz; i += kThreads) z += pz_all[(int64_t)h * nblkz + i];
-    z = block_sum_fixed<kThreads>(z, shd);
+    z = block_sum_fixed(z, shd);   // its barriers publish ms too
     const uint64_t sk = token_key(se, (double)simp, z, lambda);
     if (!(tid & 1)) sample[sq] = sk;
     __syncthreads();
@@ -466,18 +492,22 @@ __global__ __launch_bounds__(kThreads) void score_keys_kernel(
     const int shift = bracket_shift(klo, khi);
     if (blockIdx.x == 0 && tid == 0) { krange[2 * h] = klo; krange[2 * h + 1] = khi; }
 
-    for (int d = 1; d <= half; ++d) {   // Eq. (10): window max, -inf outside [0, L)
+    auto pool = [&](auto at) {   // Eq. (10): window max, -inf outside [0, L)
+        for (int d = 1; d <= half; ++d) {
 #pragma unroll
-        for (int i = 0; i < kItems; ++i) {
-            const int j = j0 + i * kThreads + tid;
-            if (j < L) {
-                const MT lo = (j - d >= 0) ? mass[j - d] : imp[i];
-                const MT hi = (j + d < L) ? mass[j + d] : imp[i];
-                const MT nb = lo > hi ? lo : hi;
-                imp[i] = imp[i] > nb ? imp[i] : nb;
+            for (int i = 0; i < kItems; ++i) {
+                const int j = j0 + i * kThreads + tid;
+                if (j < L) {
+                    const MT lo = (j - d >= 0) ? at(j - d) : imp[i];
+                    const MT hi = (j + d < L) ? at(j + d) : imp[i];
+                    const MT nb = lo > hi ? lo : hi;
+                    imp[i] = imp[i] > nb ? imp[i] : nb;
+                }
             }
         }
-    }
+    };
+    if (staged) pool([&](int j) { return ms[j - j0 + kHalo]; });
+    else pool([&](int j) { return mass[j]; });
     uint64_t kv[kItems];
 #pragma unroll
     for (int i = 0; i < kItems; ++i) {
@@ -857,7 +887,7 @@ __global__ __launch_bounds__(kSelThreads) void select_small_kernel(
     int32_t* tile_last = sync_tile_last(sync, gridDim.x, ntile, h);
     __shared__ MT ms[kSmallL];
     __shared__ uint64_t keys[kSmallL];
-    __shared__ double shd[kSelThreads];
+    __shared__ double shd[kThreads + 1];
     __shared__ uint32_t hist[kBins];
     __shared__ uint64_t few[kRank];
     __shared__ uint64_t red[2][kSelThreads / FC_WAVE];
@@ -873,7 +903,7 @@ __global__ __launch_bounds__(kSelThreads) void select_small_kernel(
         ev[i] = e[j < L ? j : L - 1];
         imp[i] = mass[j < L ? j : L - 1];
     }
-    double z = 0.0;   // the order of score_keys: the first kThreads threads, the tree adds zeros besides
+    double z = 0.0;   // the order of score_keys
     if (tid < kThreads)
         for (int i = tid; i < nblkz; i += kThreads) z += pz_all[(int64_t)h * nblkz + i];
     {   // what the compaction starts from
@@ -885,7 +915,7 @@ __global__ __launch_bounds__(kSelThreads) void select_small_kernel(
 #pragma unroll
     for (int i = 0; i < PER; ++i) ms[i * kSelThreads + tid] = imp[i];
     if (tid == 0) sh_n = 0u;
-    z = block_sum_fixed<kSelThreads>(z, shd);   // its barriers publish ms too
+    z = block_sum_fixed(z, shd);   // its barriers publish ms too
     const int half = pool_k / 2;
     for (int d = 1; d <= half; ++d) {
 #pragma unroll
@@ -1301,12 +1331,12 @@ __global__ __launch_bounds__(kThreads) void group_pool_kernel(
         for (int e = 0; e < EL; ++e) acc[e] += x[e];
     }
     __shared__ double sh[kGroups][D];
-    __shared__ double shm[kThreads];
+    __shared__ double shm[kThreads + 1];
 #pragma unroll
     for (int e = 0; e < EL; ++e) sh[r0][u * EL + e] = acc[e];
     double m = 0.0;
     for (int r = threadIdx.x; r < group; r += kThreads) m += (double)mass[(int64_t)h * L + (int64_t)g * group + r];
-    m = block_sum_fixed<kThreads>(m, shm);   // includes the barrier that publishes sh
+    m = block_sum_fixed(m, shm);   // includes the barrier that publishes sh
     if (threadIdx.x < D) {
         double t = 0.0;
 #pragma unroll
