@@ -20,7 +20,7 @@
 //                  output ascending); blocks exchange their counts through one word each
 //   select_small   the three above in one launch of one block per head, for heads whose keys fit in LDS
 //   compact_rows   move the kept K and V rows to positions [0, budget) IN PLACE, one pass of
-//                  64-row tiles drawn from a ticket counter; a tile stores only after the
+//                  tiles drawn from a ticket counter; a tile stores only after the
 //                  lower tiles that read from its rows have loaded them
 // A 16-lane group owns one token row in the two passes over K (16-byte loads, a full
 // row per group), so a token's values never depend on where it sits in the launch.
