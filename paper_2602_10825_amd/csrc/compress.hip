@@ -622,10 +622,12 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
     __shared__ uint64_t few[kRank];
     __shared__ uint32_t wtot[kSelThreads / FC_WAVE];
     __shared__ uint64_t sh_prefix;
-    __shared__ uint32_t sh_need, sh_count, sh_ncand;
+    __shared__ uint32_t sh_need, sh_count, sh_ncand, sh_nfew;   // lengths of cand and few: a counter each,
+                                                                // zeroed barriers before anyone adds to it
     __shared__ int sh_last;
 
     const uint64_t klo = krange[2 * h], khi = krange[2 * h + 1];
+    if (tid == 0) sh_ncand = sh_nfew = 0u;
     if (tid < kFirstBins) hist[tid] = hist_all[(int64_t)h * kFirstBins + tid];
     __syncthreads();
     pick_bin_parallel(hist, kFirstBins, (uint32_t)budget, wtot, 0ull, 0, &sh_prefix, &sh_need, &sh_count);
@@ -703,8 +705,6 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
         const uint64_t himask = (rem >= 64) ? 0ull : (~0ull << rem);
         // few candidates left and still in global memory: pull them into LDS and finish there
         if (!in_lds && count <= (uint32_t)kCand) {
-            if (tid == 0) sh_ncand = 0;
-            __syncthreads();
             for (int b0 = 0; b0 < L; b0 += kSelThreads * kUnroll) {
                 uint64_t kv[kUnroll];
 #pragma unroll
@@ -722,14 +722,12 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
             in_lds = true;
         }
         if (in_lds && count <= (uint32_t)kRank) {   // very few: no more digits
-            if (tid == 0) sh_ncand = 0;
-            __syncthreads();
             for (uint32_t i0 = 0; i0 < ncand; i0 += kSelThreads) {
                 const uint64_t k = (i0 + tid < ncand) ? cand[i0 + tid] : 0ull;
-                list_append(few, &sh_ncand, i0 + tid < ncand && (k & himask) == prefix, k);
+                list_append(few, &sh_nfew, i0 + tid < ncand && (k & himask) == prefix, k);
             }
             __syncthreads();
-            rank_select(few, sh_ncand, need, &sh_prefix, &sh_need);
+            rank_select(few, sh_nfew, need, &sh_prefix, &sh_need);
             __syncthreads();
             prefix = sh_prefix;
             need = sh_need;

@@ -31,9 +31,27 @@ def importance(kind, L, rng):
         return rng.integers(0, 11, L) / 11.0
     if kind == "equal":
         return np.full(L, 0.25)
+    if kind == "signed":                    # a bracket with zero inside: its bins are octaves wide
+        return rng.standard_normal(L)
     m = rng.random(L)
     m[sampled(L)] = (2.0 if kind == "below" else -2.0) + rng.random(128)
     return m
+
+
+def candidates(score, budget):
+    """Keys that share the first digit of the wanted one (a model of the bracket's bins on the host)."""
+    bits = (score + 0.0).view(np.uint64)
+    key = [int(k) for k in np.where(bits >> np.uint64(63), ~bits, bits | np.uint64(1 << 63))]
+    L = len(key)
+    top = sorted((key[i] for i in sampled(L)), reverse=True)
+    want = budget * 128 // L
+    hi, lo = top[max(want - 28, 0)], top[min(want + 28, 127)]
+    shift = max((hi - lo).bit_length() - 8, 0)
+    if shift and (hi - lo) >> (shift - 1) <= 509:
+        shift -= 1
+    digit = lambda k: -1 if k < lo else 512 if k > hi else (k - lo) >> shift
+    wanted = digit(sorted(key, reverse=True)[budget - 1])
+    return sum(digit(k) == wanted for k in key)
 
 
 @pytest.mark.parametrize("kind,L,budget", [
@@ -43,6 +61,7 @@ def importance(kind, L, rng):
     ("plateaus", 20000, 9000), ("plateaus", 4100, 300), ("equal", 20000, 12345),
     ("below", 20001, 10000), ("above", 20001, 10000),     # more candidates outside than the list holds
     ("below", 4200, 4150), ("above", 4200, 40),           # few enough for it
+    ("signed", 50000, 20000), ("signed", 50000, 24000), ("signed", 50000, 25000),
 ])
 def test_selection_by_importance_alone(kind, L, budget):
     rng = np.random.default_rng(L + budget)
@@ -69,3 +88,20 @@ def test_selection_with_redundancy(dtype, d, L, budget, pool_k):
     rk, rk_k, rk_v, _ = O.kv_compress(k, v, L, budget, mass, pool_k, 0.07)
     assert np.array_equal(kept.cpu().numpy(), rk)
     assert np.array_equal(B.to_host(kc), rk_k) and np.array_equal(B.to_host(vc), rk_v)
+
+
+@pytest.mark.parametrize("L,budget,lam", [(51000, 25500, 0.2), (51000, 25500, 0.3), (51000, 40800, 0.5),
+                                          (51000, 40800, 0.7), (20001, 16000, 0.7)])
+def test_selection_with_scores_of_both_signs(L, budget, lam):
+    """The wanted score close to zero, where importance and redundancy balance: more keys share its first
+    digit than the list holds, and one more digit leaves few enough to be compared with each other."""
+    rng = np.random.default_rng(5)
+    k = synth.to_storage(rng.standard_normal((2, L, 64)).astype(np.float32), "bf16")
+    mass = (rng.exponential(size=(2, L)) ** 2).astype(np.float32)
+    mass /= mass.sum(1, keepdims=True)
+    score = [O.selection_scores(O.widen(k[h]), mass[h], 7, lam) for h in range(2)]
+    assert max(candidates(x, budget) for x in score) > 4096
+    ref = np.stack([O.select_top_b(x, budget) for x in score])
+    for _ in range(3):
+        kept = B.flowcache_kv_select(dev(k, "bf16"), L, budget, torch.from_numpy(mass).to(DEV), 7, lam)
+        assert np.array_equal(kept.cpu().numpy(), ref)
