@@ -1052,7 +1052,8 @@ __global__ __launch_bounds__(kThreads) void compact_rows_kernel(
     constexpr int kTileRows = tile_rows(VPR * 16);
     constexpr int LDN = kTileRows * VPR / kThreads;   // vectors per thread per matrix
     constexpr int RPP = kThreads / VPR;               // rows per pass
-    __shared__ uint32_t sh_ticket;
+    // (the first ticket has a word of its own: no barrier lies between its reads and the store of the second)
+    __shared__ uint32_t sh_first, sh_ticket;
     const int tid = threadIdx.x;
     const int lrow = tid / VPR, lcol = tid % VPR;
     const uint32_t total = (uint32_t)ntile * (uint32_t)H;
@@ -1101,9 +1102,9 @@ __global__ __launch_bounds__(kThreads) void compact_rows_kernel(
         }
     };
 
-    if (tid == 0) sh_ticket = atomicAdd(ticket, 1u);
+    if (tid == 0) sh_first = atomicAdd(ticket, 1u);
     __syncthreads();
-    uint32_t g = sh_ticket;
+    uint32_t g = sh_first;
     if (g >= total) return;
     Tile cur;
     Rows rows;

@@ -105,3 +105,20 @@ def test_selection_with_scores_of_both_signs(L, budget, lam):
     for _ in range(3):
         kept = B.flowcache_kv_select(dev(k, "bf16"), L, budget, torch.from_numpy(mass).to(DEV), 7, lam)
         assert np.array_equal(kept.cpu().numpy(), ref)
+
+
+@pytest.mark.parametrize("H,d,L,budget", [(1, 64, 200, 100),          # one tile: the second ticket is past the end
+                                          (8, 128, 5000, 4096),       # 512 tiles: one ticket per block
+                                          (9, 128, 4200, 4096),       # 576: some blocks draw a second tile
+                                          (3, 64, 40000, 39000)])     # 915 of 128 rows, nearly all of them waiting
+def test_compaction_draws_every_tile_once(H, d, L, budget):
+    """All wavefronts of a block work on the block's first ticket, whatever the second one is."""
+    g = torch.Generator(device=DEV).manual_seed(L)
+    k0, v0 = (torch.randn((H, L + 64, d), generator=g, device=DEV).to(torch.bfloat16) for _ in range(2))
+    kept = torch.stack([torch.randperm(L, generator=g, device=DEV)[:budget].sort().values for _ in range(H)]).int()
+    rows = kept.long()[..., None].expand(H, budget, d)
+    for _ in range(10):
+        k, v = k0.clone(), v0.clone()
+        B.flowcache_kv_compact(k, v, L, budget, kept, check_status=True)
+        for x, x0 in ((k, k0), (v, v0)):
+            assert torch.equal(x[:, :budget], x0.gather(1, rows)) and torch.equal(x[:, budget:], x0[:, budget:])
