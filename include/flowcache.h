@@ -47,7 +47,7 @@
  *  - The recompute list (recompute_idx, n_recompute) lives on the device, so the host
  *    cannot check it: the kernels do.  A count above A is cut to A and an entry outside
  *    [0, A) is skipped (nothing is read or written for it); no out-of-range access follows
- *    from a bad list.
+ *    from a bad list.  Entries from *n_recompute on are not read.
  *  - Decisions (reuse masks) and kept-token indices are taken in float64 and are meant to
  *    be bit-reproducible run to run: no floating-point atomics are used anywhere.
  */

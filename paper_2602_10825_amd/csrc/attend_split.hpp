@@ -154,13 +154,17 @@ inline size_t fc_split_part_bytes(int d) { return (size_t)kUnitRows * (d + 2) * 
 
 // ---- device side ---------------------------------------------------------------------------
 // The recompute list is the device's: a count above A is cut to A and an entry outside [0, A) is
-// skipped (nothing is read or written for it).  Bit r of the mask = row block r holds a chunk; R =
-// the number of such blocks, so that a malformed list is planned like the well-formed one.
+// skipped (nothing is read or written for it).  The list may end after *n_rec entries: what lies
+// beyond is not read.  The chunk of row block i, or -1:
+__host__ __device__ inline int fc_listed_chunk(const int32_t* rec_idx, int n_rec, int A, int i) {
+    if (i >= n_rec || i >= A) return -1;
+    const int c = rec_idx[i];
+    return (unsigned)c < (unsigned)A ? c : -1;
+}
+// Bit r of the mask = row block r holds a chunk; R = the number of such blocks, so that a malformed
+// list is planned like the well-formed one.
 __device__ __forceinline__ uint32_t valid_blocks(const FcAttendArgs& a) {
-    const int lane = threadIdx.x & (FC_WAVE - 1);
-    const int c = a.rec_idx[lane < a.A ? lane : 0];
-    const uint32_t mask = (uint32_t)__ballot(lane < min(*a.n_rec, a.A) && (unsigned)c < (unsigned)a.A);
-    return mask;
+    return (uint32_t)__ballot(fc_listed_chunk(a.rec_idx, *a.n_rec, a.A, threadIdx.x & (FC_WAVE - 1)) >= 0);
 }
 // the row block with `rank` valid ones above it: latest (heaviest) chunk first
 __device__ __forceinline__ int block_of_rank(uint32_t mask, int rank) {

@@ -1,0 +1,57 @@
+"""Host code of the attention launch (attend_split.hpp), compiled for the CPU: no GPU needed."""
+import ctypes
+import os
+import subprocess
+import sys
+
+import pytest
+
+from paper_2602_10825_amd import build
+
+DRIVER = r"""
+#include "attend_split.hpp"
+extern "C" {
+__attribute__((visibility("default"))) int listed_chunk(const int32_t* rec, int n, int A, int i) {
+    return fc_listed_chunk(rec, n, A, i);
+}
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def driver(tmp_path_factory):
+    d = tmp_path_factory.mktemp("plan")
+    src, so = d / "plan.hip", d / "plan.so"
+    src.write_text(DRIVER)
+    subprocess.run([build.HIPCC, "--offload-host-only", *build.FLAGS, "-shared", str(src), "-o", str(so)], check=True)
+    return str(so)
+
+
+def read_lists(so):
+    """Every list ends at the last byte before a page that must not be touched."""
+    libc = ctypes.CDLL(None, use_errno=True)
+    libc.mmap.restype = ctypes.c_void_p
+    libc.mmap.argtypes = [ctypes.c_void_p, ctypes.c_size_t, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_long]
+    libc.mprotect.argtypes = [ctypes.c_void_p, ctypes.c_size_t, ctypes.c_int]
+    page = os.sysconf("SC_PAGE_SIZE")
+    base = libc.mmap(None, 2 * page, 3, 0x22, -1, 0)             # read | write, private | anonymous
+    assert base and base != ctypes.c_void_p(-1).value
+    assert libc.mprotect(base + page, page, 0) == 0
+    f = ctypes.CDLL(so).listed_chunk
+    f.argtypes = [ctypes.c_void_p, ctypes.c_int, ctypes.c_int, ctypes.c_int]
+    for A in (1, 3, 16):
+        for entries in ([], [0], [A - 1], [0, A, -1][:A], list(range(A))):
+            at = base + page - 4 * len(entries)
+            (ctypes.c_int32 * len(entries)).from_address(at)[:] = entries
+            got = [f(at, len(entries), A, lane) for lane in range(64)]
+            assert got == [c if 0 <= c < A else -1 for c in entries] + [-1] * (64 - len(entries))
+    assert [f(base, -3, 4, lane) for lane in range(64)] == [-1] * 64
+    full = (ctypes.c_int32 * 16)(*range(16))                     # a count above A is cut to A
+    assert [f(ctypes.addressof(full), 99, 16, lane) for lane in range(64)] == list(range(16)) + [-1] * 48
+
+
+def test_recompute_list_is_not_read_past_its_count(driver):
+    """A list of exactly *n_rec entries: 64 lanes look at it, none touches what lies behind."""
+    r = subprocess.run([sys.executable, "-c", "import sys; sys.path.insert(0, %r); "
+                        "from tests.test_attend_plan import read_lists; read_lists(%r)" % (build.ROOT, driver)])
+    assert r.returncode == 0
