@@ -213,6 +213,13 @@ int flowcache_residual_apply(const void* x_cur, const void* y_compact, void* res
  *                  H_q/H_k query heads of each key head, of softmax restricted to those
  *                  positions.  That block must hold the last active chunk (A-1); if it
  *                  does not, mass is filled with NaN.
+ *   workspace [dev] flowcache_attend_workspace() bytes, overwritten: a launch that does not fill
+ *                  the chip divides the keys of a block over several and leaves their partial
+ *                  results there.  A smaller one is accepted -- NULL too when mass is NULL, with
+ *                  mass 256 bytes more than flowcache_attention_mass_workspace() of the window.
+ *                  Where the partial results find no room in it the keys are not divided: the same
+ *                  outputs up to rounding, for few query rows on long contexts up to ten times
+ *                  slower.
  * Supported: d in {64, 128}; H_q % H_k == 0; A <= FC_MAX_ACTIVE; FC_BF16 needs d == 128 or 64.
  */
 int flowcache_attend(const void* q, const void* k_new, const void* v_new, void* k_cache,

@@ -188,16 +188,21 @@ int flowcache_scatter_kv(const void* k_new, const void* v_new, void* k_cache, vo
 }
 
 // ------------------------------------------------------------------ attend
+namespace {
+// what the call cannot do without; room to divide the keys comes on top
+size_t attend_least_workspace(int L_c, int H_q, int mass_len, int obs_window) {
+    if (mass_len <= 0) return 0;
+    const int W = (obs_window <= 0 || obs_window > L_c) ? L_c : obs_window;
+    return 256 + fc_mass_workspace(W, H_q, mass_len);
+}
+}  // namespace
+
 size_t flowcache_attend_workspace(int A, int L_c, int H_q, int H_k, int d, int mass_len,
                                   int obs_window) {
     (void)H_k;
     if (A < 1 || A > FC_MAX_ACTIVE || L_c < 1 || H_q < 1) return 0;
-    size_t need = 256 + fc_attend_split_workspace(A, L_c, H_q, d);
-    if (mass_len > 0) {
-        const int W = (obs_window <= 0 || obs_window > L_c) ? L_c : obs_window;
-        need += fc_mass_workspace(W, H_q, mass_len);
-    }
-    return need;
+    const size_t least = attend_least_workspace(L_c, H_q, mass_len, obs_window);
+    return (least ? least : 256) + fc_attend_split_workspace(A, L_c, H_q, d);
 }
 
 int flowcache_attend(const void* q, const void* k_new, const void* v_new, void* k_cache,
@@ -225,8 +230,7 @@ int flowcache_attend(const void* q, const void* k_new, const void* v_new, void* 
         if (mass_len < 1 || mass_len > capacity || obs_window < 0 || !workspace)
             return FC_INVALID_ARGUMENT;
     }
-    if (workspace_bytes < flowcache_attend_workspace(A, L_c, H_q, H_k, d, mass ? mass_len : 0, obs_window) &&
-        mass)
+    if (workspace_bytes < attend_least_workspace(L_c, H_q, mass ? mass_len : 0, obs_window))
         return FC_WORKSPACE_TOO_SMALL;
     const float scale = softmax_scale > 0.f ? softmax_scale : 1.0f / std::sqrt((float)d);
     hipStream_t s = (hipStream_t)stream;

@@ -55,3 +55,30 @@ def test_attend_without_room_for_partials(dtype):
     tol = 1e-5 if dtype == "f32" else 1e-2
     for x, y in zip(*outs):
         assert np.linalg.norm(x - y) <= tol * np.linalg.norm(y)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_importance_needs_no_room_for_partials(dtype):
+    """With mass the workspace has to hold what the importance needs and no more: one sized for other
+    lengths (shorter chunks may ask for more partials) is not refused."""
+    wl = synth.Workload("split", dtype, 2, 2, 64, 2, 48, 4000, 1)
+    a = synth.attend_inputs(wl, seed=4)
+    idx = torch.tensor([0, 1], dtype=torch.int32, device=DEV)
+    n = torch.tensor([2], dtype=torch.int32, device=DEV)
+    q, k, v = dev(a["q"], dtype), dev(a["k_cache"], dtype), dev(a["v_cache"], dtype)
+    L = B.lib()
+    least = 256 + L.flowcache_attention_mass_workspace(40, wl.H_q, wl.H_k, wl.d, 4000)
+    full = L.flowcache_attend_workspace(wl.A, wl.L_c, wl.H_q, wl.H_k, wl.d, 4000, 40)
+    assert least < full
+    outs = []
+    for nbytes in (full, least):
+        ws = torch.empty(nbytes, dtype=torch.uint8, device=DEV)
+        r = B.flowcache_attend(q, None, None, k, v, wl.L_c, wl.L_clean, a["active_off"], idx, n, mass_len=4000,
+                               obs_window=40, workspace=ws)
+        outs.append((r["out"].float().cpu().numpy(), r["mass"].cpu().numpy()))
+    assert np.array_equal(outs[0][1], outs[1][1])
+    tol = 1e-5 if dtype == "f32" else 1e-2        # as above
+    assert np.linalg.norm(outs[0][0] - outs[1][0]) <= tol * np.linalg.norm(outs[0][0])
+    with pytest.raises(B.FlowCacheError):
+        B.flowcache_attend(q, None, None, k, v, wl.L_c, wl.L_clean, a["active_off"], idx, n, mass_len=4000,
+                           obs_window=40, workspace=torch.empty(least - 1, dtype=torch.uint8, device=DEV))
