@@ -631,8 +631,8 @@ __global__ __launch_bounds__(NT) void attend_bf16_kernel(FcAttendArgs a, FcAtten
 template <int D>
 int launch_bf16(const FcAttendArgs& a, hipStream_t s) {
     FcAttendPlan p = fc_attend_plan_bf16(a.A, a.L_c, a.L_clean, a.H_q, D, true);
-    if (p.parts > 0 && (!a.ws || a.ws_bytes < (size_t)p.parts * fc_split_part_bytes(D)))
-        p = fc_attend_plan_bf16(a.A, a.L_c, a.L_clean, a.H_q, D, false);    // no room for partials
+    if (!fc_room_for_partials(a.ws, a.ws_bytes, p.parts, D))
+        p = fc_attend_plan_bf16(a.A, a.L_c, a.L_clean, a.H_q, D, false);
     bool wide = false, narrow = false;
     for (int R = 0; R < a.A; ++R) (p.narrow[R] ? narrow : wide) = true;
     if (!narrow)

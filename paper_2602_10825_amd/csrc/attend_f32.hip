@@ -182,8 +182,8 @@ __global__ __launch_bounds__(kSplitThreads) void attend_f32_kernel(FcAttendArgs 
 template <int D>
 int launch_f32(const FcAttendArgs& a, hipStream_t s) {
     FcAttendPlan p = fc_attend_plan_f32(a.A, a.L_c, a.L_clean, a.H_q, true);
-    if (p.parts > 0 && (!a.ws || a.ws_bytes < (size_t)p.parts * fc_split_part_bytes(D)))
-        p = fc_attend_plan_f32(a.A, a.L_c, a.L_clean, a.H_q, false);    // no room for partials
+    if (!fc_room_for_partials(a.ws, a.ws_bytes, p.parts, D))
+        p = fc_attend_plan_f32(a.A, a.L_c, a.L_clean, a.H_q, false);
     attend_f32_kernel<D><<<p.grid, kSplitThreads, 0, s>>>(a, p, (float*)a.ws);
     FC_LAUNCH_CHECK();
     if (p.merge_grid > 0) {

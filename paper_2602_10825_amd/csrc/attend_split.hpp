@@ -152,6 +152,12 @@ inline int64_t fc_split_parts_bound(int A, int L_c, int H_q) {
 // bytes per partial: O [32][d], then m [32] and l [32]
 inline size_t fc_split_part_bytes(int d) { return (size_t)kUnitRows * (d + 2) * sizeof(float); }
 
+// Room for the plan's partials?  They are written and read 16 bytes at a time; a pointer that does not
+// allow that is no room.
+inline bool fc_room_for_partials(const void* ws, size_t ws_bytes, int parts, int d) {
+    return parts == 0 || (ws && ((uintptr_t)ws & 15u) == 0 && ws_bytes >= (size_t)parts * fc_split_part_bytes(d));
+}
+
 // ---- device side ---------------------------------------------------------------------------
 // The recompute list is the device's: a count above A is cut to A and an entry outside [0, A) is
 // skipped (nothing is read or written for it).  The list may end after *n_rec entries: what lies

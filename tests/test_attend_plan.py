@@ -14,6 +14,9 @@ extern "C" {
 __attribute__((visibility("default"))) int listed_chunk(const int32_t* rec, int n, int A, int i) {
     return fc_listed_chunk(rec, n, A, i);
 }
+__attribute__((visibility("default"))) int room(const void* ws, size_t bytes, int parts, int d) {
+    return fc_room_for_partials(ws, bytes, parts, d);
+}
 }
 """
 
@@ -55,3 +58,12 @@ def test_recompute_list_is_not_read_past_its_count(driver):
     r = subprocess.run([sys.executable, "-c", "import sys; sys.path.insert(0, %r); "
                         "from tests.test_attend_plan import read_lists; read_lists(%r)" % (build.ROOT, driver)])
     assert r.returncode == 0
+
+
+def test_room_for_partials(driver):
+    f = ctypes.CDLL(driver).room
+    f.argtypes = [ctypes.c_void_p, ctypes.c_size_t, ctypes.c_int, ctypes.c_int]
+    need = 3 * 32 * 66 * 4
+    assert f(None, 0, 0, 64) and f(0x1000, need, 3, 64)
+    assert not f(None, need, 3, 64) and not f(0x1000, need - 1, 3, 64)
+    assert not any(f(0x1000 + off, need, 3, 64) for off in range(1, 16)) and f(0x1010, need, 3, 64)

@@ -38,7 +38,8 @@ def test_attend_split_edges(dtype, H_q, H_k, d, A, L_c, L_clean, rec):
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_attend_without_room_for_partials(dtype):
-    """A workspace too small for the partials (or none) leaves the keys of a unit in one block."""
+    """A workspace too small for the partials, or not aligned for them, leaves the keys of a unit in one
+    block."""
     wl = synth.Workload("split", dtype, 2, 2, 64, 2, 48, 4000, 1)
     a = synth.attend_inputs(wl, seed=3)
     idx = torch.tensor([1, -1], dtype=torch.int32, device=DEV)
@@ -46,15 +47,17 @@ def test_attend_without_room_for_partials(dtype):
     q, k, v = dev(a["q"], dtype), dev(a["k_cache"], dtype), dev(a["v_cache"], dtype)
     need = B.lib().flowcache_attend_workspace(wl.A, wl.L_c, wl.H_q, wl.H_k, wl.d, 0, 50)
     outs = []
-    for nbytes in (need, 256):
-        ws = torch.empty(nbytes, dtype=torch.uint8, device=DEV)
+    for ws in (torch.empty(need, dtype=torch.uint8, device=DEV), torch.empty(256, dtype=torch.uint8, device=DEV),
+               torch.empty(need + 8, dtype=torch.uint8, device=DEV)[8:], torch.empty(need + 1, dtype=torch.uint8, device=DEV)[1:]):
         r = B.flowcache_attend(q, None, None, k, v, wl.L_c, wl.L_clean, a["active_off"], idx, n, workspace=ws)
         outs.append((r["out"][:wl.L_c].float().cpu().numpy(), r["lse"][:, :wl.L_c].cpu().numpy()))
     # the same products summed in another grouping: fp32 sums of at most 4096 terms, and for bf16 one
     # rounding of weights and outputs each
     tol = 1e-5 if dtype == "f32" else 1e-2
-    for x, y in zip(*outs):
+    for x, y in zip(outs[0], outs[1]):
         assert np.linalg.norm(x - y) <= tol * np.linalg.norm(y)
+    for other in outs[2:]:
+        assert all(np.array_equal(x, y) for x, y in zip(other, outs[1]))
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
