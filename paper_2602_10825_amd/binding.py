@@ -146,7 +146,13 @@ def _stream(stream) -> ctypes.c_void_p:
     return ctypes.c_void_p(s.cuda_stream)
 
 
-def _workspace(nbytes: int, device) -> torch.Tensor:
+def _workspace(nbytes: int, device, stream=None) -> torch.Tensor:
+    """A call's own scratch, given back when the call returns.  It is allocated for the stream that the
+    call's work is enqueued on and reused in that stream's order; one of the current stream could be
+    handed out again, for work on the current stream, before `stream` is done with it."""
+    if isinstance(stream, torch.cuda.Stream):
+        with torch.cuda.stream(stream):
+            return _workspace(nbytes, device)
     return torch.empty(max(int(nbytes), 256), dtype=torch.uint8, device=device)
 
 
@@ -170,7 +176,7 @@ def flowcache_chunk_decide(x_cur: torch.Tensor, x_prev: torch.Tensor, step_idx: 
         x_compact = torch.empty_like(x_cur)
     L = lib()
     if workspace is None:
-        workspace = _workspace(L.flowcache_chunk_decide_workspace(A, chunk_elems), dev)
+        workspace = _workspace(L.flowcache_chunk_decide_workspace(A, chunk_elems), dev, stream)
     st = L.flowcache_chunk_decide(_ptr(x_cur), _ptr(x_prev), _dtype_code(x_cur), A, chunk_elems,
                                   _ptr(step_idx), int(warmup_m), float(eps), _ptr(acc), _ptr(l1rel),
                                   _ptr(mask), _ptr(idx), _ptr(n_rec), _ptr(x_compact),
@@ -214,7 +220,7 @@ def flowcache_uniform_decide(x_cur: torch.Tensor, x_prev: torch.Tensor, step_idx
         x_compact = torch.empty_like(x_cur)
     L = lib()
     if workspace is None:
-        workspace = _workspace(L.flowcache_chunk_decide_workspace(A, chunk_elems), dev)
+        workspace = _workspace(L.flowcache_chunk_decide_workspace(A, chunk_elems), dev, stream)
     st = L.flowcache_uniform_decide(_ptr(x_cur), _ptr(x_prev), _dtype_code(x_cur), A, chunk_elems,
                                     _ptr(step_idx), int(warmup_m), float(eps), _ptr(acc_global),
                                     _ptr(l1rel), _ptr(mask), _ptr(idx), _ptr(n_rec), _ptr(x_compact),
@@ -265,7 +271,7 @@ def flowcache_attend(q: torch.Tensor, k_new: Optional[torch.Tensor], v_new: Opti
     off = (ctypes.c_int32 * A)(*[int(x) for x in active_off])
     L = lib()
     if workspace is None:
-        workspace = _workspace(L.flowcache_attend_workspace(A, L_c, H_q, H_k, d, mass_len, obs_window), dev)
+        workspace = _workspace(L.flowcache_attend_workspace(A, L_c, H_q, H_k, d, mass_len, obs_window), dev, stream)
     st = L.flowcache_attend(_ptr(q), _ptr(k_new), _ptr(v_new), _ptr(k_cache), _ptr(v_cache),
                             k_cache.stride(0), k_cache.stride(1), capacity, _dtype_code(q), H_q, H_k,
                             d, int(L_c), int(L_clean), A, ctypes.cast(off, ctypes.c_void_p),
@@ -304,7 +310,7 @@ def flowcache_attention_mass(q_obs: torch.Tensor, k_cache: torch.Tensor, mass_le
     mass = torch.empty((H_k, mass_len), dtype=torch.float32, device=dev)
     L = lib()
     if workspace is None:
-        workspace = _workspace(L.flowcache_attention_mass_workspace(W, H_q, H_k, d, mass_len), dev)
+        workspace = _workspace(L.flowcache_attention_mass_workspace(W, H_q, H_k, d, mass_len), dev, stream)
     st = L.flowcache_attention_mass(_ptr(q_obs), W, _ptr(k_cache), k_cache.stride(0),
                                     k_cache.stride(1), _dtype_code(q_obs), H_q, H_k, d, int(mass_len),
                                     float(softmax_scale), _ptr(mass), _ptr(workspace),
@@ -332,7 +338,7 @@ def flowcache_kv_compress(k_cache: torch.Tensor, v_cache: torch.Tensor, L_k: int
     L = lib()
     code = _dtype_code(k_cache)
     if workspace is None:
-        workspace = _workspace(L.flowcache_kv_compress_workspace(H_k, L_k, d, budget, code), dev)
+        workspace = _workspace(L.flowcache_kv_compress_workspace(H_k, L_k, d, budget, code), dev, stream)
     st = L.flowcache_kv_compress(_ptr(k_cache), _ptr(v_cache), k_cache.stride(0), k_cache.stride(1),
                                  code, H_k, d, int(L_k), int(budget), _ptr(mass), int(pool_k),
                                  float(lam), _ptr(kept_idx), _ptr(workspace), workspace.numel(),
@@ -357,7 +363,7 @@ def flowcache_kv_select(k_cache: torch.Tensor, L_k: int, budget: int, mass: torc
     L = lib()
     code = _dtype_code(k_cache)
     if workspace is None:
-        workspace = _workspace(L.flowcache_kv_compress_workspace(H_k, L_k, d, budget, code), dev)
+        workspace = _workspace(L.flowcache_kv_compress_workspace(H_k, L_k, d, budget, code), dev, stream)
     st = L.flowcache_kv_select(_ptr(k_cache), k_cache.stride(0), k_cache.stride(1), code, H_k, d,
                                int(L_k), int(budget), _ptr(mass), int(pool_k), float(lam),
                                _ptr(kept_idx), _ptr(workspace), workspace.numel(), _stream(stream))
@@ -377,7 +383,7 @@ def flowcache_kv_compact(k_cache: torch.Tensor, v_cache: torch.Tensor, L_k: int,
     L = lib()
     code = _dtype_code(k_cache)
     if workspace is None:
-        workspace = _workspace(L.flowcache_kv_compress_workspace(H_k, L_k, d, budget, code), dev)
+        workspace = _workspace(L.flowcache_kv_compress_workspace(H_k, L_k, d, budget, code), dev, stream)
     st = L.flowcache_kv_compact(_ptr(k_cache), _ptr(v_cache), k_cache.stride(0), k_cache.stride(1),
                                 code, H_k, d, int(L_k), int(budget), _ptr(kept_idx), _ptr(workspace),
                                 workspace.numel(), _stream(stream))
@@ -403,7 +409,7 @@ def flowcache_kv_compress_grouped(k_cache: torch.Tensor, v_cache: torch.Tensor, 
     L = lib()
     code = _dtype_code(k_cache)
     if workspace is None:
-        workspace = _workspace(L.flowcache_kv_compress_grouped_workspace(H_k, L_k, d, budget, group, code), dev)
+        workspace = _workspace(L.flowcache_kv_compress_grouped_workspace(H_k, L_k, d, budget, group, code), dev, stream)
     st = L.flowcache_kv_compress_grouped(_ptr(k_cache), _ptr(v_cache), k_cache.stride(0), k_cache.stride(1),
                                          code, H_k, d, int(L_k), int(budget), int(group), _ptr(mass),
                                          int(pool_k), float(lam), _ptr(kept_idx), _ptr(workspace),
