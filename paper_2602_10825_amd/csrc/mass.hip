@@ -76,7 +76,7 @@ __global__ __launch_bounds__(kF32Waves * 64, 2) void mass_stats_f32_kernel(FcMas
                                                                           float* __restrict__ pl) {
     int64_t row0;
     if (!resolve_rows(a, row0)) return;
-    const int s = blockIdx.x, rt = blockIdx.y, h = blockIdx.z;
+    const int s = blockIdx.x % S, rt = blockIdx.x / S, h = blockIdx.y;   // (only grid.x takes any number of rows)
     const int hk = h / (a.H_q / a.H_k);
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int n = lane & 31, half = lane >> 5;
@@ -1000,7 +1000,7 @@ int launch_f32(const FcMassArgs& a, hipStream_t s) {
     float* pm = reinterpret_cast<float*>(a.ws);
     float* pl = pm + (size_t)a.H_q * nrg * kRowGroup * S;
     float* lse2 = pl + (size_t)a.H_q * nrg * kRowGroup * S;
-    mass_stats_f32_kernel<D><<<dim3(S, rt, a.H_q), kF32Waves * 64, 0, s>>>(a, nrg, S, pm, pl);
+    mass_stats_f32_kernel<D><<<dim3(S * rt, a.H_q), kF32Waves * 64, 0, s>>>(a, nrg, S, pm, pl);
     FC_LAUNCH_CHECK();
     mass_lse_kernel<<<dim3(nrg, a.H_q), kNT, 0, s>>>(pm, pl, nrg, S, a.W, lse2);
     FC_LAUNCH_CHECK();

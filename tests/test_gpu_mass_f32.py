@@ -4,11 +4,12 @@ keys more or less, fewer key tiles than wavefronts, several ranges, one to eight
 keys, and the one-thread-per-key kernels for one or two rows; against the float64 oracle at its usual bars."""
 import numpy as np
 import pytest
+import torch
 
 from oracle import flowcache_oracle as O
 from paper_2602_10825_amd import binding as B
 from tests._checks import assert_mass_close
-from tests.test_gpu_parity import dev
+from tests.test_gpu_parity import DEV, dev
 
 pytestmark = pytest.mark.gpu
 
@@ -33,3 +34,16 @@ def test_mass_f32(d, H_q, H_k, W, L, grow):
     k[:, L:] *= 100.0                 # past the scored range: must not count
     got = B.flowcache_attention_mass(dev(q, "f32"), dev(k, "f32"), L).cpu().numpy().astype(np.float64)
     assert_mass_close(got, O.attention_mass(q, k, L), "f32", f"W={W} L={L}")
+
+
+def test_mass_f32_of_more_rows_than_a_grid_dimension_has_blocks():
+    """65536 tiles of 32 rows and one row more; the reference in float64 on the device."""
+    W, L, d = 65536 * 32 + 1, 8, 64
+    g = torch.Generator(device=DEV).manual_seed(1)
+    q = torch.randn((W, 1, d), generator=g, device=DEV)
+    k = torch.randn((1, L, d), generator=g, device=DEV)
+    got = B.flowcache_attention_mass(q, k, L).double()
+    ref = sum(torch.softmax(x[:, 0].double() @ k[0].double().T * d ** -0.5, 1).sum(0) for x in q.split(1 << 18)) / W
+    # a lane adds W / 32 / 8 terms one after the other: at most that many roundings of 2^-24, far fewer as
+    # they go both ways; a tenth of that bound
+    assert float((got[0] - ref).abs().max() / ref.min()) <= 0.1 * (W / 256) * 2.0 ** -24
