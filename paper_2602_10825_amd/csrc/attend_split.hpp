@@ -32,8 +32,9 @@ struct FcAttendPlan {
 // Cost of a launch of 32-row blocks, one per compute unit at a time, in the time of one key tile
 // (32 keys, one of the block's 8 wavefronts): rounds of blocks times the tiles of a range.  A
 // block also costs `block_cost` tiles of prologue and merging, and the merge launch twice that; a
-// range has at least 8 tiles, and no launch is split into more than four blocks per compute unit
-// (so the partials stay within 18 MB).
+// range has at least 8 tiles, and no launch is split into more than four blocks per compute unit.
+// The partials of such a launch are at most 17 MB, those of split 256-row blocks (two per compute
+// unit, eight partials each) at most 68.
 inline double fc_narrow_cost(int64_t units, int key_tiles, int block_cost, bool may_split, int* splits) {
     int cap = may_split ? key_tiles / kSplitWaves : 1;
     cap = cap < 1 ? 1 : (cap > kMaxSplits ? kMaxSplits : cap);
@@ -130,7 +131,10 @@ inline FcAttendPlan fc_attend_plan_bf16(int A, int L_c, int L_clean, int H_q, in
     return p;
 }
 
-// Most 32-row partials a launch with these shapes can need, whatever the number of keys.
+// Most 32-row partials a launch with these shapes can need, whatever the number of keys.  The wide
+// plan takes S only where it costs less than every smaller S' does.  Both costs are a + b T in the number of
+// tiles T and a never falls with S (more rounds of blocks, a merge), so b, the rounds of blocks with a split
+// one counted as 1 / S, has to be smaller.
 inline int64_t fc_split_parts_bound(int A, int L_c, int H_q) {
     const int64_t tiles = (L_c + kUnitRows - 1) / kUnitRows;
     const int64_t items = (int64_t)H_q * ((L_c + kWideRows - 1) / kWideRows);
@@ -140,10 +144,14 @@ inline int64_t fc_split_parts_bound(int A, int L_c, int H_q) {
         int64_t s = 4 * kCus / units;
         if (s > kMaxSplits) s = kMaxSplits;
         if (s > 1 && units * s > most) most = units * s;
+        double least = (double)((fc_wide_shape(R, (int)items, 1).full + kCus / 8 - 1) / (kCus / 8));
         for (int S = 2; S <= kMaxSplits; ++S) {
             const FcWideShape w = fc_wide_shape(R, (int)items, S);
             const int64_t split = w.full == 0 ? (int64_t)R * items * S : (int64_t)8 * w.rem * S;
-            if (split > 2 * kCus) break;
+            if (split == 0 || split > 2 * kCus) break;
+            const double b = (double)(w.full / (kCus / 8)) + (double)((split + kCus - 1) / kCus) / S;
+            if (b >= least) continue;
+            least = b;
             if (split * (kWideRows / kUnitRows) > most) most = split * (kWideRows / kUnitRows);
         }
     }

@@ -1,6 +1,7 @@
 """Host code of the attention launch (attend_split.hpp), compiled for the CPU: no GPU needed."""
 import ctypes
 import os
+import random
 import subprocess
 import sys
 
@@ -17,6 +18,17 @@ __attribute__((visibility("default"))) int listed_chunk(const int32_t* rec, int 
 __attribute__((visibility("default"))) int room(const void* ws, size_t bytes, int parts, int d) {
     return fc_room_for_partials(ws, bytes, parts, d);
 }
+// partials that the plans ask for, the most over key counts from 0 to 2^17
+__attribute__((visibility("default"))) int parts(int A, int L_c, int H_q, int d) {
+    int most = 0;
+    for (int clean = 0; clean < 1 << 17; clean += 1 + clean / 7) {
+        const int b = fc_attend_plan_bf16(A, L_c, clean, H_q, d, true).parts, f = fc_attend_plan_f32(A, L_c, clean, H_q, true).parts;
+        most = most > b ? most : b;
+        most = most > f ? most : f;
+    }
+    return most;
+}
+__attribute__((visibility("default"))) int bound(int A, int L_c, int H_q) { return (int)fc_split_parts_bound(A, L_c, H_q); }
 }
 """
 
@@ -67,3 +79,20 @@ def test_room_for_partials(driver):
     assert f(None, 0, 0, 64) and f(0x1000, need, 3, 64)
     assert not f(None, need, 3, 64) and not f(0x1000, need - 1, 3, 64)
     assert not any(f(0x1000 + off, need, 3, 64) for off in range(1, 16)) and f(0x1010, need, 3, 64)
+
+
+def test_workspace_holds_what_any_number_of_keys_can_ask_for(driver):
+    so = ctypes.CDLL(driver)
+    rng = random.Random(1)
+    for _ in range(4000):
+        A, H, d = rng.randint(1, 16), rng.choice((1, 2, 3, 8, 12, 24, 40, 64)), rng.choice((64, 128))
+        L_c = int(2 ** rng.uniform(0, 14))
+        assert so.parts(A, L_c, H, d) <= so.bound(A, L_c, H), (A, L_c, H, d)
+
+
+@pytest.mark.parametrize("A,L_c,H,most", [(2, 10200, 12, 0),              # SkyReels-V2-1.3B-like layer: never split
+                                          (4, 9360, 24, 8 * 8 * 15 * 2),  # MAGI-1-like: one chunk, the last round in two
+                                          (3, 328, 8, 2048)])
+def test_workspace_of_known_layers(driver, A, L_c, H, most):
+    """No room for splits that no plan takes: 60 and 64 MB of them on the two layers."""
+    assert ctypes.CDLL(driver).bound(A, L_c, H) == most
