@@ -25,6 +25,7 @@
 // A 16-lane group owns one token row in the two passes over K (16-byte loads, a full
 // row per group), so a token's values never depend on where it sits in the launch.
 #include "fc_common.hpp"
+#include "select_bins.hpp"
 
 #pragma clang fp contract(off)
 
@@ -39,14 +40,7 @@ constexpr int kDigitBits = 11;
 constexpr int kBins = 1 << kDigitBits;
 constexpr int kCand = 4096;   // candidates resolved in LDS
 constexpr int kRank = 256;    // candidates resolved by comparing each with each
-// bins of the first digit, which every block of a head adds to in global memory: more bins cost
-// score_keys what they save the select (24 heads of 74880 keys, the two together with 256, 512 and 2048
-// bins: 42, 43 and 44 us)
-constexpr int kFirstBits = 9;
-constexpr int kFirstBins = 1 << kFirstBits;
 constexpr int kHalo = 64;     // importance beside a block's tokens that score_keys keeps in LDS
-constexpr int kSample = 128;  // keys that the first digit's bracket is taken from
-constexpr int kSampleWide = 28;   // the bracket's half width in ranks of the sample: five deviations
 constexpr int kSmallL = kSelThreads * 4;   // heads up to this length are selected by one block
 constexpr int kUnroll = 8;    // independent loads in flight per thread in the selection scans
 
@@ -380,30 +374,21 @@ __device__ __forceinline__ uint64_t token_key(double e, double pooled, double z,
     return score_key(a - b);
 }
 
-// The first digit: keys in [lo, hi] by their distance from lo, kFirstBins - 2 bins at most; one bin below
-// and one above.
-__device__ __forceinline__ int bracket_shift(uint64_t lo, uint64_t hi) {
-    const int bits = hi > lo ? 64 - __clzll((long long)(hi - lo)) : 0;
-    int sh = bits > kFirstBits - 1 ? bits - (kFirstBits - 1) : 0;
-    if (sh > 0 && ((hi - lo) >> (sh - 1)) <= (uint64_t)(kFirstBins - 3)) --sh;
-    return sh;
-}
-__device__ __forceinline__ uint32_t bracket_digit(uint64_t k, uint64_t lo, uint64_t hi, int sh) {
-    return k < lo ? 0u : (k > hi ? (uint32_t)(kFirstBins - 1) : 1u + (uint32_t)((k - lo) >> sh));
+// fc_first_digit's choice of bins: the same in every wavefront that looks at the same edges
+__device__ __forceinline__ int first_digit_shift(const uint64_t* edge, int n) {
+    const int sh = __builtin_amdgcn_readfirstlane(fc_even_shift(edge, n));
+    return __any(fc_crowded(edge, n, sh, threadIdx.x & (FC_WAVE - 1))) ? -1 : sh;
 }
 
 // ---- keys: Eq. (10)-(12) per token, fully parallel ------------------------------------
-// Where the first digit's bins lie decides how many keys the select has to look at again.  The top
-// bits of the keys are mostly sign and exponent: with heavy-tailed importance half of the head fell
-// into one bin and one block read the whole head three times over (12 heads of 51000 keys: select 62
-// us, 24 of 74880: 93 us; with the bracket 10 and 14 us).  So every block takes the same 128 keys
-// of the head, finds those some ranks above and below the wanted one, and spreads the bins between
-// them, whatever the distribution; a wanted key outside the bracket (5 deviations) costs time only.
+// Where the first digit's bins lie decides how many keys the select has to look at again: every block
+// takes the same 128 keys of the head and lays the bins between those some ranks above and below the
+// wanted one (select_bins.hpp).  A wanted key outside (5 deviations) costs time only.
 template <typename MT>   // importance as given (float) or pooled over a key group (double)
 __global__ __launch_bounds__(kThreads) void score_keys_kernel(
     const double* __restrict__ e_all, const MT* __restrict__ mass_all,
     const double* __restrict__ pz_all, int nblkz, int L, int budget, int pool_k,
-    double lambda, uint64_t* __restrict__ keys_all, uint64_t* __restrict__ krange,
+    double lambda, uint64_t* __restrict__ keys_all, uint64_t* __restrict__ edge_all,
     uint32_t* __restrict__ hist_all, uint32_t* __restrict__ sync, int ntile, uint32_t* __restrict__ selsync,
     uint64_t* __restrict__ agg_all) {
     const int h = blockIdx.y, tid = threadIdx.x;
@@ -413,9 +398,11 @@ __global__ __launch_bounds__(kThreads) void score_keys_kernel(
     __shared__ double shd[kThreads + 1];
     __shared__ MT ms[kTokBlk + 2 * kHalo];
     __shared__ uint64_t sample[kSample];
-    __shared__ uint64_t sh_lo, sh_hi;
+    __shared__ uint64_t edge[kEdges];
     __shared__ uint32_t hist[kFirstBins];
     const int half = pool_k / 2;
+    const FcBracket br = fc_bracket(budget, L);
+    const int n_int = br.bottom - br.top;
     // The sample: one token of each 128th of the head (L >= kSample), not always the same one of it.
     // Threads 2q and 2q + 1 both take token q; everything is requested before the sums that z needs.
     const int sq = tid >> 1, slen = L / kSample;
@@ -445,6 +432,7 @@ __global__ __launch_bounds__(kThreads) void score_keys_kernel(
         for (int i = tid; i < (int)gridDim.x; i += kThreads) agg_all[(int64_t)h * gridDim.x + i] = 0ull;
     }
     for (int i = tid; i < kFirstBins; i += kThreads) hist[i] = 0u;
+    if (tid < kEdges) edge[tid] = ~0ull;
     const int j0 = blockIdx.x * kTokBlk;
     double ev[kItems];
     MT imp[kItems];
@@ -481,16 +469,11 @@ __global__ __launch_bounds__(kThreads) void score_keys_kernel(
             above += (o > sk || (o == sk && i < sq)) ? 1u : 0u;
         }
         above += __shfl_xor(above, 1, FC_WAVE);
-        const int want = (int)((int64_t)budget * kSample / L);
-        const int r_hi = want > kSampleWide ? want - kSampleWide : 0;
-        const int r_lo = want + kSampleWide < kSample - 1 ? want + kSampleWide : kSample - 1;
-        if (!(tid & 1) && (int)above == r_hi) sh_hi = sk;
-        if (!(tid & 1) && (int)above == r_lo) sh_lo = sk;
+        if (!(tid & 1) && (int)above >= br.top && (int)above <= br.bottom) edge[br.bottom - (int)above] = sk;
     }
     __syncthreads();
-    const uint64_t klo = sh_lo, khi = sh_hi;
-    const int shift = bracket_shift(klo, khi);
-    if (blockIdx.x == 0 && tid == 0) { krange[2 * h] = klo; krange[2 * h + 1] = khi; }
+    if (blockIdx.x == 0 && tid < kEdges) edge_all[(int64_t)h * kEdges + tid] = edge[tid];
+    const int even_sh = first_digit_shift(edge, n_int);
 
     auto pool = [&](auto at) {   // Eq. (10): window max, -inf outside [0, L)
         for (int d = 1; d <= half; ++d) {
@@ -523,7 +506,7 @@ __global__ __launch_bounds__(kThreads) void score_keys_kernel(
 #pragma unroll
     for (int i = 0; i < kItems; ++i) {
         const bool in = j0 + i * kThreads + tid < L;
-        const uint32_t dgt = bracket_digit(kv[i], klo, khi, shift);
+        const uint32_t dgt = fc_first_digit(kv[i], edge, n_int, even_sh);
         below += __popcll(__ballot(in && dgt == 0u));
         above += __popcll(__ballot(in && dgt == (uint32_t)(kFirstBins - 1)));
         if (in && dgt != 0u && dgt != (uint32_t)(kFirstBins - 1)) atomicAdd(&hist[dgt], 1u);
@@ -611,7 +594,7 @@ __device__ __forceinline__ void rank_select(const uint64_t* cand, uint32_t n, ui
 // A candidate is a key k with k - base <= limit, and k - base is what the further digits are of.
 // selsync[h * 64 + 0] = length of the list, [+1] = blocks done, [+2] = ticket of write_kept.
 __global__ __launch_bounds__(kSelThreads) void select_kernel(
-    const uint64_t* __restrict__ keys_all, const uint64_t* __restrict__ krange,
+    const uint64_t* __restrict__ keys_all, const uint64_t* __restrict__ edge_all,
     const uint32_t* __restrict__ hist_all, int L, int budget, uint64_t* __restrict__ sel,
     uint64_t* __restrict__ cand_all, uint32_t* __restrict__ selsync) {
     const int h = blockIdx.y, part = blockIdx.x, nparts = gridDim.x;
@@ -626,28 +609,18 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
                                                                 // zeroed barriers before anyone adds to it
     __shared__ int sh_last;
 
-    const uint64_t klo = krange[2 * h], khi = krange[2 * h + 1];
+    __shared__ uint64_t edge[kEdges];
+    const FcBracket br = fc_bracket(budget, L);
+    if (tid < kEdges) edge[tid] = edge_all[(int64_t)h * kEdges + tid];
     if (tid == 0) sh_ncand = sh_nfew = 0u;
     if (tid < kFirstBins) hist[tid] = hist_all[(int64_t)h * kFirstBins + tid];
     __syncthreads();
     pick_bin_parallel(hist, kFirstBins, (uint32_t)budget, wtot, 0ull, 0, &sh_prefix, &sh_need, &sh_count);
     __syncthreads();
-    const uint32_t bin = (uint32_t)sh_prefix;
     uint32_t need = sh_need;
     uint32_t count = sh_count;        // keys in the bin chosen last
     uint64_t base, limit;
-    if (bin == 0u) {                  // below the bracket
-        base = 0ull;
-        limit = klo - 1ull;
-    } else if (bin == (uint32_t)(kFirstBins - 1)) {   // above it
-        base = khi + 1ull;
-        limit = ~0ull - base;
-    } else {
-        const int sh = bracket_shift(klo, khi);
-        base = klo + ((uint64_t)(bin - 1u) << sh);
-        const uint64_t width = (1ull << sh) - 1ull;
-        limit = khi - base < width ? khi - base : width;
-    }
+    fc_bin_keys((uint32_t)sh_prefix, edge, br.bottom - br.top, first_digit_shift(edge, br.bottom - br.top), &base, &limit);
     int rem = limit ? 64 - __clzll((long long)limit) : 0;      // undecided low bits
     uint64_t prefix = 0ull;
     if (rem == 0) {
@@ -1201,7 +1174,7 @@ unsigned compact_grid(int ntile, int H) {
 }
 
 struct WsLayout {
-    size_t e, keys, psum, pz, krange, hist, sel, cand, selsync, agg, sync, total;
+    size_t e, keys, psum, pz, edge, hist, sel, cand, selsync, agg, sync, total;
     int nblk, nb2, ntile;
 };
 
@@ -1222,7 +1195,7 @@ WsLayout layout(int H, int L, int d, int budget, fc_dtype dtype) {
     w.keys = off;    off += fc_align_up((size_t)H * L * 8);
     w.psum = off;    off += fc_align_up((size_t)H * nblk * d * 8);
     w.pz = off;      off += fc_align_up((size_t)H * nblk * 8);
-    w.krange = off;  off += fc_align_up((size_t)H * 16);
+    w.edge = off;    off += fc_align_up((size_t)H * kEdges * 8);
     w.hist = off;    off += fc_align_up((size_t)H * kFirstBins * 4);
     w.sel = off;     off += fc_align_up((size_t)H * 16);
     w.cand = off;    off += fc_align_up((size_t)H * kCand * 8);
@@ -1259,7 +1232,7 @@ int launch_typed(const FcCompressArgs& a, const MT* mass, hipStream_t s, bool co
     uint64_t* keys = reinterpret_cast<uint64_t*>(ws + w.keys);
     double* psum = reinterpret_cast<double*>(ws + w.psum);
     double* pz = reinterpret_cast<double*>(ws + w.pz);
-    uint64_t* krange = reinterpret_cast<uint64_t*>(ws + w.krange);
+    uint64_t* edge = reinterpret_cast<uint64_t*>(ws + w.edge);
     uint32_t* hist = reinterpret_cast<uint32_t*>(ws + w.hist);
     uint64_t* sel = reinterpret_cast<uint64_t*>(ws + w.sel);
     uint64_t* cand = reinterpret_cast<uint64_t*>(ws + w.cand);
@@ -1283,13 +1256,13 @@ int launch_typed(const FcCompressArgs& a, const MT* mass, hipStream_t s, bool co
         FC_LAUNCH_CHECK();
     } else {
         score_keys_kernel<MT><<<dim3(w.nb2, a.H_k), kThreads, 0, s>>>(e, mass, pz, w.nblk, a.L_k, a.budget, a.pool_k,
-                                                                  a.lambda, keys, krange, hist, sync, w.ntile,
+                                                                  a.lambda, keys, edge, hist, sync, w.ntile,
                                                                   selsync, agg);
         FC_LAUNCH_CHECK();
         // blocks per head that scan for the candidates: one batch of loads each, up to 131072 keys
         constexpr int kBatch = kSelThreads * kUnroll;
         const int nparts = a.L_k <= 16 * kBatch ? (a.L_k + kBatch - 1) / kBatch : 16;
-        select_kernel<<<dim3(nparts, a.H_k), kSelThreads, 0, s>>>(keys, krange, hist, a.L_k, a.budget, sel, cand,
+        select_kernel<<<dim3(nparts, a.H_k), kSelThreads, 0, s>>>(keys, edge, hist, a.L_k, a.budget, sel, cand,
                                                                  selsync);
         FC_LAUNCH_CHECK();
         write_kept_kernel<<<dim3(w.nb2, a.H_k), kThreads, 0, s>>>(keys, sel, a.L_k, a.budget, a.kept, sync, w.ntile, TR,
