@@ -24,6 +24,8 @@
 //                  lower tiles that read from its rows have loaded them
 // A 16-lane group owns one token row in the two passes over K (16-byte loads, a full
 // row per group), so a token's values never depend on where it sits in the launch.
+#include <type_traits>
+
 #include "fc_common.hpp"
 #include "select_bins.hpp"
 
@@ -40,7 +42,7 @@ constexpr int kDigitBits = 11;
 constexpr int kBins = 1 << kDigitBits;
 constexpr int kCand = 4096;   // candidates resolved in LDS
 constexpr int kRank = 256;    // candidates resolved by comparing each with each
-constexpr int kHalo = 64;     // importance beside a block's tokens that score_keys keeps in LDS
+constexpr int kHalo = 192;    // importance beside a block's tokens that score_keys can keep in LDS
 constexpr int kSmallL = kSelThreads * 4;   // heads up to this length are selected by one block
 constexpr int kUnroll = 8;    // independent loads in flight per thread in the selection scans
 
@@ -404,24 +406,33 @@ __global__ __launch_bounds__(kThreads) void score_keys_kernel(
     const FcBracket br = fc_bracket(budget, L);
     const int n_int = br.bottom - br.top;
     // The sample: one token of each 128th of the head (L >= kSample), not always the same one of it.
-    // Threads 2q and 2q + 1 both take token q; everything is requested before the sums that z needs.
+    // Threads 2q and 2q + 1 take token q, every other distance of its importance window each; everything
+    // is requested before the sums that z needs.
     const int sq = tid >> 1, slen = L / kSample;
     const int sj = (int)((int64_t)sq * L / kSample) + (int)(((uint32_t)sq * 2654435761u >> 12) % (uint32_t)slen);
     const double se = e[sj];
     MT simp = mass[sj];
-    for (int d0 = 1; d0 <= half; d0 += 4) {       // four distances of the window in flight at a time
-        MT lo[4], hi[4];
+    auto window = [&](auto n, int d0) {           // every other distance from d0 on, n of them in flight together
+        constexpr int N = decltype(n)::value;
+        MT lo[N], hi[N];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int d = d0 + i < half ? d0 + i : half;
+        for (int i = 0; i < N; ++i) {
+            const int d = d0 + 2 * i < half ? d0 + 2 * i : half;
             lo[i] = mass[sj - d >= 0 ? sj - d : 0];
             hi[i] = mass[sj + d < L ? sj + d : L - 1];
         }
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < N; ++i) {
             const MT nb = lo[i] > hi[i] ? lo[i] : hi[i];
             simp = simp > nb ? simp : nb;
         }
+    };
+    int d0 = 1 + (tid & 1);
+    for (; d0 + 23 < half; d0 += 32) window(std::integral_constant<int, 16>(), d0);
+    for (; d0 <= half; d0 += 4) window(std::integral_constant<int, 2>(), d0);
+    {
+        const MT nb = __shfl_xor(simp, 1, FC_WAVE);
+        simp = simp > nb ? simp : nb;
     }
     if (blockIdx.x == 0) {   // state later kernels of this call start from: tile flags, tickets
         uint32_t* flags = sync_flags(sync, gridDim.y, ntile, h);
@@ -444,14 +455,16 @@ __global__ __launch_bounds__(kThreads) void score_keys_kernel(
     }
     const bool staged = half <= kHalo;            // the window comes from LDS
     if (staged) {
-        MT edge = (MT)0;
-        const int lj = j0 - 1 - tid, rj = j0 + kTokBlk + tid - kHalo;
-        if (tid < kHalo) edge = mass[lj >= 0 ? lj : 0];
-        else if (tid < 2 * kHalo) edge = mass[rj < L ? rj : L - 1];
+        auto beside = [&](int i) {                // i < 2 half: the tokens to the left, then those to the right
+            const int j = i < half ? j0 - 1 - i : j0 + kTokBlk + i - half;
+            return mass[j < 0 ? 0 : (j < L ? j : L - 1)];
+        };
+        auto slot = [&](int i) { return i < half ? kHalo - 1 - i : kHalo + kTokBlk + i - half; };
+        const MT first = tid < 2 * half ? beside(tid) : (MT)0;
 #pragma unroll
         for (int i = 0; i < kItems; ++i) ms[kHalo + i * kThreads + tid] = imp[i];
-        if (tid < kHalo) ms[kHalo - 1 - tid] = edge;
-        else if (tid < 2 * kHalo) ms[kTokBlk + tid] = edge;
+        if (tid < 2 * half) ms[slot(tid)] = first;
+        for (int i = tid + kThreads; i < 2 * half; i += kThreads) ms[slot(i)] = beside(i);
     }
     // Z = sum_j e_j: the block partials of the pass that wrote e, in a fixed order
     double z = 0.0;

@@ -58,7 +58,8 @@ def test_selection_by_importance_alone(kind, L, budget):
 
 @pytest.mark.parametrize("dtype,d,L,budget,pool_k", [
     ("bf16", 128, 4096, 3000, 7), ("bf16", 128, 4097, 3000, 7), ("f32", 64, 700, 350, 9), ("f32", 128, 9000, 4500, 3),
-    ("bf16", 64, 5000, 2500, 141),        # a window wider than what LDS holds beside a block's tokens
+    ("bf16", 64, 5000, 2500, 141), ("bf16", 64, 5000, 2500, 385), ("f32", 64, 4200, 900, 257),
+    ("bf16", 64, 5000, 2500, 387),        # a window wider than what LDS holds beside a block's tokens
     ("bf16", 64, 129, 128, 7), ("bf16", 64, 700, 385, 7), ("bf16", 64, 9001, 8000, 7),   # tiles of 128 rows
 ])
 def test_selection_with_redundancy(dtype, d, L, budget, pool_k):
