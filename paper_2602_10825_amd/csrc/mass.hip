@@ -69,22 +69,31 @@ __device__ __forceinline__ f32x16_t scores_f32(const f32x4_t (&k)[D / 8], const 
     return s;
 }
 
-// Pass 1: a block is 32 rows of one head and one of S key ranges; its wavefronts take every eighth 32-key
-// tile and are merged through LDS.
+// A tile of rows is 32 of the W * G that use one key head: with a tile of its own for every query head,
+// 24 x 128 with four heads on one, two rows each, took 367 us on 16384 keys (one tile for the eight: 135).
+struct F32Row { int h, w; bool ok; };
+__device__ __forceinline__ F32Row f32_row(const FcMassArgs& a, int hk, int r) {
+    const int G = a.H_q / a.H_k;
+    const bool ok = r < a.W * G;
+    const int g = ok ? r / a.W : 0;
+    return F32Row{hk * G + g, ok ? r - g * a.W : 0, ok};
+}
+
+// Pass 1: a block is 32 rows of one key head and one of S key ranges; its wavefronts take every eighth
+// 32-key tile and are merged through LDS.
 template <int D>
 __global__ __launch_bounds__(kF32Waves * 64, 2) void mass_stats_f32_kernel(FcMassArgs a, int nrg, int S, float* __restrict__ pm,
                                                                           float* __restrict__ pl) {
     int64_t row0;
     if (!resolve_rows(a, row0)) return;
-    const int s = blockIdx.x % S, rt = blockIdx.x / S, h = blockIdx.y;   // (only grid.x takes any number of rows)
-    const int hk = h / (a.H_q / a.H_k);
+    const int s = blockIdx.x % S, rt = blockIdx.x / S, hk = blockIdx.y;   // (only grid.x takes any number of rows)
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int n = lane & 31, half = lane >> 5;
     const float* kh = (const float*)a.k_cache + (int64_t)hk * a.head_stride;
     const float c2 = a.scale * kLog2e;
     const int T = (a.mass_len + 31) / 32;
     const int t_end = (int)((int64_t)T * (s + 1) / S);
-    const int w = rt * 32 + n < a.W ? rt * 32 + n : a.W - 1;     // padding rows: computed, not used
+    const F32Row row = f32_row(a, hk, rt * 32 + n);               // padding rows: computed, not used
     f32x4_t q[D / 8], k[D / 8];
     auto load_k = [&](int t) {
         const int j = t * 32 + n < a.mass_len ? t * 32 + n : a.mass_len - 1;
@@ -92,7 +101,7 @@ __global__ __launch_bounds__(kF32Waves * 64, 2) void mass_stats_f32_kernel(FcMas
     };
     int t = (int)((int64_t)T * s / S) + wave;
     if (t < t_end) load_k(t);
-    load_rows_f32<D>((const float*)a.q_base + ((row0 + w) * a.H_q + h) * D, half, q);
+    load_rows_f32<D>((const float*)a.q_base + ((row0 + row.w) * a.H_q + row.h) * D, half, q);
     float m = kNegBig, l = 0.f;
     for (; t < t_end; t += kF32Waves) {
         const f32x16_t st = scores_f32<D>(k, q);
@@ -116,13 +125,13 @@ __global__ __launch_bounds__(kF32Waves * 64, 2) void mass_stats_f32_kernel(FcMas
     merge[0][wave * 2 + half][n] = m;
     merge[1][wave * 2 + half][n] = l;
     __syncthreads();
-    if (tid < 32) {
+    if (tid < 32 && row.ok) {                                     // (lane n of the first wavefront: its own row)
         float mx = kNegBig, sum = 0.f;
 #pragma unroll
         for (int i = 0; i < 2 * kF32Waves; ++i) mx = fmaxf(mx, merge[0][i][tid]);
 #pragma unroll
         for (int i = 0; i < 2 * kF32Waves; ++i) sum = fmaf(merge[1][i][tid], __builtin_amdgcn_exp2f(merge[0][i][tid] - mx), sum);
-        const int64_t at = ((int64_t)h * nrg * kRowGroup + rt * 32 + tid) * S + s;
+        const int64_t at = ((int64_t)row.h * nrg * kRowGroup + row.w) * S + s;
         pm[at] = mx;
         pl[at] = sum;
     }
@@ -143,8 +152,8 @@ __device__ __forceinline__ float lanes_sum_scatter(float (&v)[16], int n) {
     return v[0] + __shfl_xor(v[0], 16, FC_WAVE);
 }
 
-// Pass 2: a wavefront keeps 32 keys; `parts` wavefronts of a block share the 32-row tiles of the head's
-// groups (every parts-th each) and are added up in order.
+// Pass 2: a wavefront keeps 32 keys; `parts` wavefronts of a block share the 32-row tiles of the key head
+// (every parts-th each) and are added up in order.
 template <int D>
 __global__ __launch_bounds__(kF32Waves * 64, 2) void mass_cols_f32_kernel(FcMassArgs a, int nrg, int parts,
                                                                          const float* __restrict__ lse2) {
@@ -161,16 +170,16 @@ __global__ __launch_bounds__(kF32Waves * 64, 2) void mass_cols_f32_kernel(FcMass
     const int G = a.H_q / a.H_k;
     const int part = wave / kb, key0 = jb + (wave % kb) * 32;
     const float c2 = a.scale * kLog2e;
-    const int per = (a.W + 31) / 32, nt = G * per;                 // tiles of 32 rows: query head t / per
+    const int nt = (int)(((int64_t)a.W * G + 31) / 32);            // tiles of 32 rows
     float sums[16];
 #pragma unroll
     for (int r = 0; r < 16; ++r) sums[r] = 0.f;
     f32x4_t k[D / 8], q[D / 8];
     float ls = 0.f;
     auto load_q = [&](int t) {
-        const int h = hk * G + t / per, w = t % per * 32 + n;
-        load_rows_f32<D>((const float*)a.q_base + ((row0 + (w < a.W ? w : a.W - 1)) * a.H_q + h) * D, half, q);
-        ls = lse2[(int64_t)h * nrg * kRowGroup + w];               // padding rows: huge, their terms vanish
+        const F32Row row = f32_row(a, hk, t * 32 + n);
+        load_rows_f32<D>((const float*)a.q_base + ((row0 + row.w) * a.H_q + row.h) * D, half, q);
+        ls = row.ok ? lse2[(int64_t)row.h * nrg * kRowGroup + row.w] : kPosBig;   // padding rows: their terms vanish
     };
     if (part < nt) load_q(part);
     {
@@ -194,9 +203,9 @@ __global__ __launch_bounds__(kF32Waves * 64, 2) void mass_cols_f32_kernel(FcMass
     }
 }
 
-// At most kFewRows rows per key head: one thread per key, its key in registers, the rows broadcast
+// Few rows per key head, W * G <= kFewRows: one thread per key, its key in registers, the rows broadcast
 // from LDS.  Bound by the two reads of K.
-constexpr int kFewRows = 2;
+constexpr int kFewRows = 8;
 
 template <int D>
 __device__ __forceinline__ void load_key_f32(const FcMassArgs& a, int hk, int j, f32x4_t (&k)[D / 4]) {
@@ -211,10 +220,10 @@ __device__ __forceinline__ float dot_f32(const f32x4_t (&k)[D / 4], const float*
     for (int e = 0; e < D; ++e) s = fmaf(k[e / 4][e % 4], q[e], s);
     return s;
 }
-__device__ __forceinline__ void stage_rows_f32(const FcMassArgs& a, int64_t row0, int h, int D, float* qs) {
-    for (int i = threadIdx.x; i < a.W * D; i += kNT) {
-        const int w = i / D, e = i % D;
-        qs[i] = ((const float*)a.q_base)[((row0 + w) * a.H_q + h) * D + e];
+__device__ __forceinline__ void stage_rows_f32(const FcMassArgs& a, int64_t row0, int hk, int rows, int D, float* qs) {
+    for (int i = threadIdx.x; i < rows * D; i += kNT) {
+        const F32Row row = f32_row(a, hk, i / D);
+        qs[i] = ((const float*)a.q_base)[((row0 + row.w) * a.H_q + row.h) * D + i % D];
     }
 }
 
@@ -223,23 +232,25 @@ __global__ __launch_bounds__(kNT) void mass_stats_f32_few_kernel(FcMassArgs a, i
                                                                 float* __restrict__ pl) {
     int64_t row0;
     if (!resolve_rows(a, row0)) return;
-    const int h = blockIdx.y, tid = threadIdx.x;
+    const int hk = blockIdx.y, tid = threadIdx.x, rows = a.W * (a.H_q / a.H_k);
     const int j = blockIdx.x * kNT + tid;
     __shared__ __attribute__((aligned(16))) float qs[kFewRows * D];
-    stage_rows_f32(a, row0, h, D, qs);
+    stage_rows_f32(a, row0, hk, rows, D, qs);
     f32x4_t k[D / 4];
-    load_key_f32<D>(a, h / (a.H_q / a.H_k), j, k);
+    load_key_f32<D>(a, hk, j, k);
     __syncthreads();
     const float c2 = a.scale * kLog2e;
     const int slot = blockIdx.x * (kNT / FC_WAVE) + tid / FC_WAVE;
-    for (int w = 0; w < a.W; ++w) {
-        const float s = j < a.mass_len ? dot_f32<D>(k, qs + w * D) * c2 : kNegBig;
+    int at = hk * (a.H_q / a.H_k) * kRowGroup;        // of the row's partials; the head's rows are a.W of kRowGroup
+    for (int r = 0, w = 0; r < rows; ++r) {
+        const float s = j < a.mass_len ? dot_f32<D>(k, qs + r * D) * c2 : kNegBig;
         const float mx = wave_max_all(s);
         const float sum = wave_sum_all(__builtin_amdgcn_exp2f(s - mx));
         if (tid % FC_WAVE == 0) {
-            pm[((int64_t)h * kRowGroup + w) * np + slot] = mx;
-            pl[((int64_t)h * kRowGroup + w) * np + slot] = sum;
+            pm[(int64_t)(at + w) * np + slot] = mx;
+            pl[(int64_t)(at + w) * np + slot] = sum;
         }
+        if (++w == a.W) { w = 0; at += kRowGroup; }
     }
 }
 
@@ -252,21 +263,20 @@ __global__ __launch_bounds__(kNT) void mass_cols_f32_few_kernel(FcMassArgs a, co
         if (j < a.mass_len) a.mass[(int64_t)hk * a.mass_len + j] = __uint_as_float(0x7fc00000u);
         return;
     }
-    const int G = a.H_q / a.H_k;
+    const int rows = a.W * (a.H_q / a.H_k);
     __shared__ __attribute__((aligned(16))) float qs[kFewRows * D];
+    stage_rows_f32(a, row0, hk, rows, D, qs);
     f32x4_t k[D / 4];
     load_key_f32<D>(a, hk, j, k);
+    __syncthreads();
     const float c2 = a.scale * kLog2e;
     float acc = 0.f;
-    for (int g = 0; g < G; ++g) {
-        const int h = hk * G + g;
-        __syncthreads();
-        stage_rows_f32(a, row0, h, D, qs);
-        __syncthreads();
-        for (int w = 0; w < a.W; ++w)
-            acc += __builtin_amdgcn_exp2f(dot_f32<D>(k, qs + w * D) * c2 - lse2[h * kRowGroup + w]);
+    const float* ls = lse2 + hk * (a.H_q / a.H_k) * kRowGroup;
+    for (int r = 0, w = 0; r < rows; ++r) {
+        acc += __builtin_amdgcn_exp2f(dot_f32<D>(k, qs + r * D) * c2 - ls[w]);
+        if (++w == a.W) { w = 0; ls += kRowGroup; }
     }
-    if (j < a.mass_len) a.mass[(int64_t)hk * a.mass_len + j] = acc / (float)(a.W * G);
+    if (j < a.mass_len) a.mass[(int64_t)hk * a.mass_len + j] = acc / (float)rows;
 }
 
 // Between the passes: log2-sum-exp of every observation row over all keys, from the blocks'
@@ -966,20 +976,23 @@ int launch_bf16(const FcMassArgs& a, hipStream_t s) {
     return FC_OK;
 }
 
-// Key ranges of pass 1: enough for two blocks per compute unit, a range at least one 32-key tile per
-// wavefront, and no more partials than the workspace holds (per row group one per 512 keys; one
-// group alone has room for one per 64).  Pass 2: as few wavefronts on the same keys as still give two
-// blocks per compute unit, never more than there are row tiles.
-// With one or two rows per key head nothing is left for the matrix cores to do: the kernels of one
-// thread per key (12 x 128, one row on 3000 keys 22 us against 27; 24 x 128 on 12000 keys 78 against 106;
-// with four heads on one key head 35 against 26).
+// With few rows the matrix cores work on padding, and one thread per key is faster (a x b keys: a heads of
+// b; head dimension 64 / 128; one thread per key against matrix cores): one row, 24 x 16384 45 against 65 / 73
+// against 134; four, 24 x 16384 48 : 66 / 79 : 134, 12 x 1024 16 : 16 / 20 : 24, 1 x 16384 20 : 16 / 26 : 26;
+// eight, 24 x 4096 25 : 25 / 38 : 45, 12 x 4096 21 : 16 / 30 : 26.  Few long heads leave most threads' chains of
+// loads uncovered.
+inline bool f32_one_thread_per_key(int64_t rows, int H_k, int mass_len) {
+    if (rows <= 2) return true;
+    if (rows <= 4) return H_k >= 8 || mass_len < 8192;
+    return rows <= kFewRows && H_k >= 8 && (int64_t)H_k * mass_len >= 24 * 4096;
+}
 template <int D>
 int launch_f32_few(const FcMassArgs& a, hipStream_t s) {
     const int nkb = (a.mass_len + kNT - 1) / kNT, np = nkb * (kNT / FC_WAVE);
     float* pm = reinterpret_cast<float*>(a.ws);
     float* pl = pm + (size_t)a.H_q * kRowGroup * np;
     float* lse2 = pl + (size_t)a.H_q * kRowGroup * np;
-    mass_stats_f32_few_kernel<D><<<dim3(nkb, a.H_q), kNT, 0, s>>>(a, np, pm, pl);
+    mass_stats_f32_few_kernel<D><<<dim3(nkb, a.H_k), kNT, 0, s>>>(a, np, pm, pl);
     FC_LAUNCH_CHECK();
     mass_lse_kernel<<<dim3(1, a.H_q), kNT, 0, s>>>(pm, pl, 1, np, a.W, lse2);
     FC_LAUNCH_CHECK();
@@ -988,26 +1001,30 @@ int launch_f32_few(const FcMassArgs& a, hipStream_t s) {
     return FC_OK;
 }
 
+// Key ranges of pass 1: enough for two blocks per compute unit, a range at least one 32-key tile per
+// wavefront, and no more partials than the workspace holds (per row group one per 512 keys; one
+// group alone has room for one per 64).  Pass 2: as few wavefronts on the same keys as still give two
+// blocks per compute unit, never more than there are row tiles.
 template <int D>
 int launch_f32(const FcMassArgs& a, hipStream_t s) {
-    if (a.W * (a.H_q / a.H_k) <= kFewRows && a.W <= kFewRows) return launch_f32_few<D>(a, s);
-    const int nrg = (a.W + kRowGroup - 1) / kRowGroup, rt = (a.W + 31) / 32;
+    const int64_t rows = (int64_t)a.W * (a.H_q / a.H_k);
+    if (f32_one_thread_per_key(rows, a.H_k, a.mass_len)) return launch_f32_few<D>(a, s);
+    const int nrg = (a.W + kRowGroup - 1) / kRowGroup, rt = (int)((rows + 31) / 32);
     const int most = nrg == 1 ? a.mass_len / 256 : a.mass_len / 512;
-    const int64_t units = (int64_t)a.H_q * rt;
+    const int64_t units = (int64_t)a.H_k * rt;
     int S = (int)((511 + units) / units);
     S = S < most ? S : most;
     S = S < 1 ? 1 : S;
     float* pm = reinterpret_cast<float*>(a.ws);
     float* pl = pm + (size_t)a.H_q * nrg * kRowGroup * S;
     float* lse2 = pl + (size_t)a.H_q * nrg * kRowGroup * S;
-    mass_stats_f32_kernel<D><<<dim3(S * rt, a.H_q), kF32Waves * 64, 0, s>>>(a, nrg, S, pm, pl);
+    mass_stats_f32_kernel<D><<<dim3(S * rt, a.H_k), kF32Waves * 64, 0, s>>>(a, nrg, S, pm, pl);
     FC_LAUNCH_CHECK();
     mass_lse_kernel<<<dim3(nrg, a.H_q), kNT, 0, s>>>(pm, pl, nrg, S, a.W, lse2);
     FC_LAUNCH_CHECK();
-    const int nt = a.H_q / a.H_k * rt;
     auto blocks = [&](int parts) { const int keys = kF32Waves / parts * 32; return (a.mass_len + keys - 1) / keys; };
     int parts = 1;
-    while (parts < kF32Waves && 2 * parts <= nt && (int64_t)a.H_k * blocks(parts) < 512) parts *= 2;
+    while (parts < kF32Waves && 2 * parts <= rt && (int64_t)a.H_k * blocks(parts) < 512) parts *= 2;
     mass_cols_f32_kernel<D><<<dim3(blocks(parts), a.H_k), kF32Waves * 64, 0, s>>>(a, nrg, parts, lse2);
     FC_LAUNCH_CHECK();
     return FC_OK;

@@ -24,7 +24,11 @@ pytestmark = pytest.mark.gpu
     (64, 24, 24, 20, 6000, 4.0),      # enough key blocks that no two wavefronts share one
     (128, 1, 1, 300, 3000, 1.0),
     (128, 3, 3, 1, 1000, 1.0), (64, 2, 1, 1, 257, 4.0), (64, 1, 1, 2, 3000, 4.0),   # one thread per key
-    (64, 3, 1, 1, 257, 1.0), (128, 2, 2, 3, 257, 1.0),                              # and just past it
+    (64, 3, 1, 1, 257, 1.0), (128, 2, 2, 3, 257, 1.0),
+    (64, 16, 4, 1, 8191, 1.0), (64, 16, 4, 1, 8192, 1.0),   # four rows of four heads: the last length of that
+    (128, 8, 8, 4, 8200, 1.0), (64, 16, 8, 4, 12289, 4.0),  # four and eight rows, long
+    (64, 16, 8, 4, 12287, 1.0), (128, 16, 8, 5, 600, 1.0),  # tiles that hold rows of several heads of one key head
+    (64, 12, 3, 9, 1100, 1.0), (128, 8, 2, 65, 300, 1.0), (64, 6, 2, 11, 40, 1.0),
 ])
 def test_mass_f32(d, H_q, H_k, W, L, grow):
     rng = np.random.default_rng(L + W)
