@@ -1020,12 +1020,15 @@ __global__ void iota_kernel(int32_t* kept, int H, int n) {
 // (sources never lie below their destination): it stores only after every lower tile whose
 // last source row reaches into its rows has published "read".
 // A block works on its tiles in a two-stage pipeline: before it waits for the current tile's predecessors
-// and stores it, it draws the next ticket and requests that tile's row indices, what it needs to
-// know about the tile's predecessors (their last source row, their flag) and the rows themselves.
+// and stores it, it requests the next tile's row indices, what it needs to know about the tile's
+// predecessors (their last source row, their flag) and, in launches of many tiles per block, the rows
+// themselves.
 // (Rows loaded early are safe: no tile is stored before the lower tiles that read from it say so, and
-// higher ones never do.  With the rows requested only after the stores, a block that waited had nothing
-// in flight: 12 heads of 51000 -> 40800 rows 126 us, now 112; of 20000 -> 18000 65, now 60; 24 of 74880 ->
-// 37440, where few tiles wait, 190 and 192.)  Every wait ends: a tile waits only for tiles of lower
+// higher ones never do.  They pay where a block has many tiles: with the rows requested only after the stores, a
+// block that waited had nothing in flight: 12 heads of 51000 -> 40800 rows, 15 tiles per block, 126 us, now 112;
+// of 20000 -> 18000, 7, 65 and 60; 24 of 74880 -> 37440, where few tiles wait, 190 and 192.  With few tiles the
+// stores, behind the wait for the row indices, come too late: 12 of 4494 -> 4036, 1.5, 24.1 early 26.1; 24 of
+// 6761 -> 5804, 4.3, 40.4 and 43.6.)  Every wait ends: a tile waits only for tiles of lower
 // tickets; such a tile is held by a running block either as its current tile (published as soon
 // as its rows have arrived, before that block waits for anything) or as its next tile, which
 // becomes current once that block's current tile -- drawn earlier still -- is done; following
@@ -1043,6 +1046,7 @@ __global__ __launch_bounds__(kThreads) void compact_rows_kernel(
     const int tid = threadIdx.x;
     const int lrow = tid / VPR, lcol = tid % VPR;
     const uint32_t total = (uint32_t)ntile * (uint32_t)H;
+    const bool early = total >= 5u * gridDim.x;       // the next tile's rows before this one waits, see above
     uint32_t* ticket = &sync[64];
 
     // what a tile needs before its rows can be requested
@@ -1115,11 +1119,12 @@ __global__ __launch_bounds__(kThreads) void compact_rows_kernel(
         const bool more = g < total;
         Tile nxt;
         Rows nrows;
-        if (more) {                           // on its way while this tile waits and stores
-            request(g, nxt);
+        auto next_rows = [&]() {
             load_rows(nxt, nrows);
             if (tid == 0) g_next = atomicAdd(ticket, 1u);
-        }
+        };
+        if (more) request(g, nxt);            // on its way while this tile waits and stores
+        if (more && early) next_rows();
         // Lower tiles whose last (= largest) source row is >= row0 read from this tile's rows.
         // The last source rows ascend with the tile, so each thread walks down from its nearest
         // tile and stops at the first one that ends below row0.
@@ -1154,6 +1159,7 @@ __global__ __launch_bounds__(kThreads) void compact_rows_kernel(
             }
         }
         if (!more) break;
+        if (!early) next_rows();
         cur = nxt;
         rows = nrows;
     }

@@ -92,7 +92,9 @@ def test_selection_with_scores_of_both_signs(L, budget, lam):
 @pytest.mark.parametrize("H,d,L,budget", [(1, 64, 200, 100),          # one tile: the second ticket is past the end
                                           (8, 128, 5000, 4096),       # 512 tiles: one ticket per block
                                           (9, 128, 4200, 4096),       # 576: some blocks draw a second tile
-                                          (3, 64, 40000, 39000)])     # 915 of 128 rows, nearly all of them waiting
+                                          (3, 64, 40000, 39000),      # 915 of 128 rows, nearly all of them waiting
+                                          (10, 128, 17000, 16384),    # 2560: five per block, rows requested early
+                                          (24, 64, 16000, 13500)])    # 2544: not
 def test_compaction_draws_every_tile_once(H, d, L, budget):
     """All wavefronts of a block work on the block's first ticket, whatever the second one is."""
     g = torch.Generator(device=DEV).manual_seed(L)
