@@ -28,6 +28,13 @@ __attribute__((visibility("default"))) int parts(int A, int L_c, int H_q, int d)
     }
     return most;
 }
+// what a bf16 launch of R chunks runs: 32-row blocks (0), 256-row units whole (1), all split (2), the last round split (3)
+__attribute__((visibility("default"))) int form(int A, int L_c, int L_clean, int H_q, int d, int R) {
+    const FcAttendPlan p = fc_attend_plan_bf16(A, L_c, L_clean, H_q, d, true);
+    if (p.narrow[R - 1]) return 0;
+    const int S = p.splits[R - 1];
+    return S == 1 ? 1 : fc_wide_shape(R, H_q * ((L_c + kWideRows - 1) / kWideRows), S).full == 0 ? 2 : 3;
+}
 __attribute__((visibility("default"))) int bound(int A, int L_c, int H_q) { return (int)fc_split_parts_bound(A, L_c, H_q); }
 }
 """

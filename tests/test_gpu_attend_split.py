@@ -2,12 +2,16 @@
 query rows, over several blocks: row tiles of 32, key tiles of 32, key ranges per block.  The sizes
 sit at the edges of those (one row, one key, a tile more or less, fewer tiles than wavefronts,
 ranges that split inside a segment), against the float64 oracle at the bars of the parity tests."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
 
+from oracle import flowcache_oracle as O
 from paper_2602_10825_amd import binding as B
 from paper_2602_10825_amd import synth
+from tests.test_attend_plan import driver  # noqa: F401  (fixture: the launch plan, compiled for the CPU)
 from tests.test_gpu_parity import DEV, check_attend, dev, run_attend
 
 pytestmark = pytest.mark.gpu
@@ -85,3 +89,32 @@ def test_importance_needs_no_room_for_partials(dtype):
     with pytest.raises(B.FlowCacheError):
         B.flowcache_attend(q, None, None, k, v, wl.L_c, wl.L_clean, a["active_off"], idx, n, mass_len=4000,
                            obs_window=40, workspace=torch.empty(least - 1, dtype=torch.uint8, device=DEV))
+
+
+NARROW, WHOLE, ALL_SPLIT, LAST_SPLIT = range(4)
+
+
+@pytest.mark.parametrize("H_q,H_k,d,A,L_c,L_clean,form", [
+    (4, 2, 128, 3, 328, 1000, NARROW), (2, 2, 64, 2, 70, 3000, NARROW),
+    (24, 24, 128, 3, 450, 601, WHOLE), (24, 4, 64, 4, 330, 333, WHOLE),
+    (12, 12, 64, 2, 513, 3000, ALL_SPLIT), (12, 3, 128, 2, 600, 3001, ALL_SPLIT),
+    (24, 24, 64, 2, 1400, 700, LAST_SPLIT), (24, 6, 128, 2, 1300, 701, LAST_SPLIT),
+])
+def test_every_form_when_later_keys_dwarf_earlier_ones(driver, H_q, H_k, d, A, L_c, L_clean, form):
+    """Scores that grow along the keys by far more than 2^40, in the clean region and again in the active
+    chunks, so that the exponents' reference is raised in the middle of a run, in every form of the bf16
+    launch; the slots lie in reverse order, so every segment ends in its own ragged tile.  The plan is
+    asked for the form, so that a change of its costs cannot take a case elsewhere unseen."""
+    assert ctypes.CDLL(driver).form(A, L_c, L_clean, H_q, d, A) == form
+    wl = synth.Workload("grow", "bf16", H_q, H_k, d, A, L_c, L_clean, 1)
+    a = synth.attend_inputs(wl, seed=L_c)
+    a["active_off"] = a["active_off"][::-1]
+    ramp = np.linspace(0.05, 30.0, wl.capacity)[None, :, None]
+    a["k_cache"] = synth.to_storage((O.widen(a["k_cache"]) * ramp).astype(np.float32), "bf16")
+    grow = np.linspace(20.0, 60.0, A * L_c)[:, None, None]
+    a["k_new"] = synth.to_storage((O.widen(a["k_new"]) * grow).astype(np.float32), "bf16")
+    got, ref, res, ref_lse, *_ = run_attend(wl, a, list(range(A)))
+    err = np.abs(got - ref)                      # outputs are O(1), a few keys dominate each row: relative bars
+    assert np.sqrt((err ** 2).sum()) / np.sqrt((ref ** 2).sum()) <= 1e-2
+    assert err.max() <= 2e-2 * max(1.0, np.abs(ref).max())
+    assert np.abs(res["lse"].cpu().numpy()[:, :A * L_c] - ref_lse).max() <= 2e-2 * np.abs(ref_lse).max()
