@@ -1021,14 +1021,15 @@ __global__ void iota_kernel(int32_t* kept, int H, int n) {
 // last source row reaches into its rows has published "read".
 // A block works on its tiles in a two-stage pipeline: before it waits for the current tile's predecessors
 // and stores it, it requests the next tile's row indices, what it needs to know about the tile's
-// predecessors (their last source row, their flag) and, in launches of many tiles per block, the rows
-// themselves.
+// predecessors (their last source row, their flag) and, in launches of many tiles per block or per head,
+// the rows themselves.
 // (Rows loaded early are safe: no tile is stored before the lower tiles that read from it say so, and
-// higher ones never do.  They pay where a block has many tiles: with the rows requested only after the stores, a
-// block that waited had nothing in flight: 12 heads of 51000 -> 40800 rows, 15 tiles per block, 126 us, now 112;
-// of 20000 -> 18000, 7, 65 and 60; 24 of 74880 -> 37440, where few tiles wait, 190 and 192.  With few tiles the
-// stores, behind the wait for the row indices, come too late: 12 of 4494 -> 4036, 1.5, 24.1 early 26.1; 24 of
-// 6761 -> 5804, 4.3, 40.4 and 43.6.)  Every wait ends: a tile waits only for tiles of lower
+// higher ones never do.  They pay where a block has many tiles or heads are long: with the rows requested only after
+// the stores, a block that waited had nothing in flight: 12 heads of 51000 -> 40800 rows, 15 tiles per block, 126
+// us, now 112; of 20000 -> 18000, 7, 65 and 60; 4 of 46900 -> 37353 float rows, 5 and 584 tiles per head, the call
+// 108 and 104; 24 of 74880 -> 37440, where few tiles wait, 190 and 192.  Elsewhere the stores, behind the wait
+// for the row indices, come too late: 12 of 4494 -> 4036, 1.5 tiles per block and 64 per head, 24.1, early 26.1; 24
+// of 6761 -> 5804, 4.3 and 91, 40.4 and 43.6.)  Every wait ends: a tile waits only for tiles of lower
 // tickets; such a tile is held by a running block either as its current tile (published as soon
 // as its rows have arrived, before that block waits for anything) or as its next tile, which
 // becomes current once that block's current tile -- drawn earlier still -- is done; following
@@ -1046,7 +1047,7 @@ __global__ __launch_bounds__(kThreads) void compact_rows_kernel(
     const int tid = threadIdx.x;
     const int lrow = tid / VPR, lcol = tid % VPR;
     const uint32_t total = (uint32_t)ntile * (uint32_t)H;
-    const bool early = total >= 5u * gridDim.x;       // the next tile's rows before this one waits, see above
+    const bool early = total >= 5u * gridDim.x || ntile >= 160;   // the next tile's rows before this one waits, see above
     uint32_t* ticket = &sync[64];
 
     // what a tile needs before its rows can be requested

@@ -94,7 +94,8 @@ def test_selection_with_scores_of_both_signs(L, budget, lam):
                                           (9, 128, 4200, 4096),       # 576: some blocks draw a second tile
                                           (3, 64, 40000, 39000),      # 915 of 128 rows, nearly all of them waiting
                                           (10, 128, 17000, 16384),    # 2560: five per block, rows requested early
-                                          (24, 64, 16000, 13500)])    # 2544: not
+                                          (24, 64, 16000, 13500),     # 2544: not
+                                          (4, 128, 12000, 10240)])    # 160 per head: early again
 def test_compaction_draws_every_tile_once(H, d, L, budget):
     """All wavefronts of a block work on the block's first ticket, whatever the second one is."""
     g = torch.Generator(device=DEV).manual_seed(L)
