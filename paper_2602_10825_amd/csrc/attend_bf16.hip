@@ -61,7 +61,6 @@ constexpr int BQ = kWideRows;   // query rows per workgroup
 constexpr int BK = 64;       // keys per tile
 
 typedef short s16x4_t __attribute__((ext_vector_type(4)));
-typedef short s16x8_t __attribute__((ext_vector_type(8)));
 
 // Transposing LDS load: within each group of 16 lanes, lane s passes the address of 4
 // consecutive bf16; lane i receives element (i % 4) of the data addressed by lanes

@@ -1,7 +1,7 @@
 """fp32 importance mass on the matrix cores: 32 rows (pass 1) or 32 keys (pass 2) stay in a wavefront, eight
 wavefronts to a block, key ranges over blocks.  Sizes at the edges: one row and one key, a tile of rows or
 keys more or less, fewer key tiles than wavefronts, several ranges, one to eight wavefronts on the same
-keys, and the one-thread-per-key kernels for one or two rows; against the float64 oracle at its usual bars."""
+keys, tiles with rows of several query heads, and the one-thread-per-key kernels for few rows; against the float64 oracle at its usual bars."""
 import numpy as np
 import pytest
 import torch
