@@ -2,6 +2,7 @@
 // attention kernel (Sec. 3.3; softmax(q K^T d^-1/2) V with a chunk-granular causal mask).
 //
 #include "attend_split.hpp"
+#include "f32_split.hpp"
 
 namespace {
 
@@ -29,32 +30,40 @@ __global__ __launch_bounds__(256) void scatter_kv_kernel(
 }
 
 // ------------------------------------------------------------------ fp32 attention
-// Bound by the fp32 matrix cores (v_mfma_f32_32x32x2_f32, 157 TFLOP/s; a library product of two
-// 8192 matrices reaches 153).  A block is 32 query rows; its 8 wavefronts take every 8th 32-key
-// tile, read K and V straight into registers in the operands' own layout and never meet before
-// the end, where their partials are merged through LDS: at 64 matrix-core cycles per product
-// there is time for the uncoalesced K reads, nothing has to be shared through LDS except Q, and a
-// launch of few rows still occupies eight wavefronts per 32 rows.
+// On the f16 matrix cores, every operand in two f16 parts (f32_split.hpp).  A block is 32 query rows; its 8
+// wavefronts take every 8th 32-key tile and never meet before the end, where their partials are merged
+// through LDS; a launch of few rows still occupies eight wavefronts per 32 rows.  Bound by the vector
+// ALU: about 600 instructions a tile and wavefront, two thirds of them splitting K and V, against 48
+// products of 32 cycles.
 //   S^T = K Q^T  puts one query per lane, so maximum and sum are in-lane but for one exchange,
 //   and the accumulators of S^T already are the B operand of  O^T += V^T P^T.
-// 12 heads x 128, 2 chunks of 1021 rows on 4083 clean keys: 642 us, 110 TFLOP/s (one row per
-// thread on the vector ALU: 18.8 ms, 3.7); 4 query heads on 1 x 64, 2 x 128 rows on 512: 19 us
-// (1136 us).  Splitting over blocks as well (us without / with): 8 heads x 128, 448 rows on 33682
-// keys 1217 / 592; 1 head, 68 rows on 30068 keys 1066 / 72; 12 heads, 1021 rows on 6125: 451 / 365.
-typedef float f32x16_t __attribute__((ext_vector_type(16)));
-
+//   Q is split once, a scale per row; K a scale per key, read as rows and turned to the operand's layout
+//   in LDS (read straight into that layout, 32 bytes of 32 rows a load: 357 -> 379 us below); V one scale
+//   that follows the largest entry the wavefront has seen; the weights none, their range is the choice
+//   of the reference.
+// 12 heads x 128, 2 chunks of 1021 rows on 4083 clean keys: 650 us on the fp32 matrix cores (69 % busy, no
+// vector instruction beside them), now 357; 24 x 128, 460 rows on 4890 keys 237 / 130; 12 x 64, 2 x 174 rows on
+// 18580 keys 246 / 163; 4 query heads on 1 x 64, 2 x 128 rows on 512: 19 / 14.  Relative error against float64
+// 3.4e-7 .. 6.3e-7 before, 2.9e-7 .. 4.2e-7 now; at twice the logits 8e-7 .. 16e-7 and 5e-7 .. 7e-7.
 template <int N> struct VecF;
 template <> struct VecF<4> { typedef float type __attribute__((ext_vector_type(4))); };
 template <> struct VecF<2> { typedef float type __attribute__((ext_vector_type(2))); };
 
 template <int D>
 __global__ __launch_bounds__(kSplitThreads) void attend_f32_kernel(FcAttendArgs a, FcAttendPlan p, float* parts) {
+    constexpr int KS = D / 16;           // contraction steps of Q K^T
     constexpr int NB = D / 32;           // 32-wide blocks of the value dimension
-    constexpr int ROW = D + 4;           // padded LDS rows (floats): 16-byte reads of 32 rows spread over the banks
-    typedef float f32x4_t __attribute__((ext_vector_type(4)));
+    constexpr int ROW = D + 4;           // padded rows of K tiles and of the partial O (floats),
+    constexpr int QROW = D + 8;          // and of Q's parts (f16): 16-byte reads of 32 rows spread over the banks
+    // The exponents' reference follows the row maximum at a distance: weights are at most 2^15, and those
+    // above 2^-13 of the largest so far (2^-2) are split without loss.
+    constexpr float kTop = 15.0f, kStart = 12.0f;
     typedef typename VecF<NB>::type vrow_t;
-    __shared__ __attribute__((aligned(16))) float buf[kSplitWaves * kUnitRows * ROW];   // Q first, partial O at the end
+    __shared__ __attribute__((aligned(16))) float buf[kSplitWaves * kUnitRows * ROW];   // a K tile per wavefront, partial O at the end
+    __shared__ __attribute__((aligned(16))) bf16_t q_s[2 * kUnitRows * QROW];            // Q's two parts
     __shared__ float m_s[kSplitWaves * kUnitRows], l_s[kSplitWaves * kUnitRows];
+    __shared__ __attribute__((aligned(16))) float k_scale[kSplitWaves][32];
+    __shared__ float q_scale[kUnitRows];
     __shared__ Segments sg;
 
     const SplitItem it = split_item(a, p, valid_blocks(a), blockIdx.x);
@@ -66,13 +75,23 @@ __global__ __launch_bounds__(kSplitThreads) void attend_f32_kernel(FcAttendArgs 
     const float c2 = a.scale * 1.4426950408889634f;   // fold log2(e): exp(x) = exp2(x*log2 e)
 
     if (tid == 0) list_segments(a, it.c, sg);
-    for (int i = tid; i < kUnitRows * (D / 4); i += kSplitThreads) {
-        const int row = i / (D / 4), e = i % (D / 4);
+    if (tid < kUnitRows * (D / 8)) {
+        const int row = tid / (D / 8), e = tid % (D / 8);
         int rc = it.tile * kUnitRows + row;
         if (rc > a.L_c - 1) rc = a.L_c - 1;
-        f32x4_t v = *reinterpret_cast<const f32x4_t*>(
-            (const float*)a.q + (((int64_t)it.r * a.L_c + rc) * a.H_q + it.h) * D + 4 * e);
-        *reinterpret_cast<f32x4_t*>(&buf[row * ROW + 4 * e]) = v * c2;
+        const float* qp = (const float*)a.q + (((int64_t)it.r * a.L_c + rc) * a.H_q + it.h) * D + 8 * e;
+        const f32x4_t v0 = *reinterpret_cast<const f32x4_t*>(qp) * c2, v1 = *reinterpret_cast<const f32x4_t*>(qp + 4) * c2;
+        float most = max_abs4(max_abs4(0.f, v0), v1);
+#pragma unroll
+        for (int x = 1; x < D / 8; x <<= 1) most = fmaxf(most, __shfl_xor(most, x, FC_WAVE));
+        float inv;
+        const float sc = split_scale(most, inv);
+        if (e == 0) q_scale[row] = inv;
+        Split8 s;
+        split_pair(s, 0, v0[0], v0[1], sc); split_pair(s, 1, v0[2], v0[3], sc);
+        split_pair(s, 2, v1[0], v1[1], sc); split_pair(s, 3, v1[2], v1[3], sc);
+        *reinterpret_cast<u32x4_native*>(q_s + row * QROW + 8 * e) = s.h;
+        *reinterpret_cast<u32x4_native*>(q_s + (kUnitRows + row) * QROW + 8 * e) = s.l;
     }
     __syncthreads();
 
@@ -88,9 +107,11 @@ __global__ __launch_bounds__(kSplitThreads) void attend_f32_kernel(FcAttendArgs 
 #pragma unroll
         for (int i = 0; i < 16; ++i) o[b][i] = 0.f;
     float m = kNegBig, l = 0.f;
+    const float qs = q_scale[l32];
+    float v_most = 0.f, v_sc = 1.f, v_inv = 1.f;      // V's scale, the wavefront's: it fits entries of up to v_most
     const uint32_t ts = (uint32_t)a.tok_stride;
 
-    f32x4_t kf[D / 8];
+    f32x4_t kf[2 * KS];
     vrow_t vf[16];
     int seg = 0, pos = 0, nvalid = 0;
     auto locate = [&](int tt) {
@@ -100,47 +121,99 @@ __global__ __launch_bounds__(kSplitThreads) void attend_f32_kernel(FcAttendArgs 
         pos = __builtin_amdgcn_readfirstlane(sg.start[seg]) + off;
         nvalid = left < 32 ? left : 32;
     };
-    // A operand of S^T = K Q^T: lane (hh, l32) holds K[l32][8 j + 4 hh .. + 4); the MFMA of step
-    // (j, i) contracts over the two elements 8 j + i and 8 j + 4 + i
+    // Whole rows at a time; A operand of S^T = K Q^T: lane (hh, l32) holds K[l32][16 st + 8 hh .. + 8)
+    constexpr int LPR = D / 4, RPL = FC_WAVE / LPR;     // lanes per row, rows per load
+    const int ld_row = lane / LPR, ld_col = 4 * (lane % LPR);
+    const uint32_t k_off = ((uint32_t)ld_row * ts + (uint32_t)ld_col) * 4u, v_off = ((uint32_t)hh * 4u * ts + (uint32_t)(NB * l32)) * 4u;
+    float* const k_tile = buf + wave * 32 * ROW;
     auto load_k = [&]() {
-        const int kr = l32 < nvalid ? l32 : nvalid - 1;
         const char* kt = reinterpret_cast<const char*>(kbase + (int64_t)pos * a.tok_stride);   // scalar
-        const uint32_t off = ((uint32_t)kr * ts + 4u * (uint32_t)hh) * 4u;
+        const uint32_t last = (uint32_t)(nvalid - 1) * ts * 4u + (uint32_t)ld_col * 4u;   // rows past the end: the last one again
+        uint32_t off = k_off;
+        asm volatile("" : "+v"(off));                  // (computed here each time: sixteen offsets kept in registers spill)
 #pragma unroll
-        for (int j = 0; j < D / 8; ++j) kf[j] = *reinterpret_cast<const f32x4_t*>(kt + off + 32 * j);
+        for (int j = 0; j < 2 * KS; ++j) {
+            kf[j] = *reinterpret_cast<const f32x4_t*>(kt + (off < last ? off : last));
+            off += (uint32_t)RPL * ts * 4u;
+        }
     };
+    auto turn_k = [&]() {                // the wavefront's own tile: LDS serves its accesses in order, no barrier is needed
+#pragma unroll
+        for (int j = 0; j < 2 * KS; ++j) *reinterpret_cast<f32x4_t*>(k_tile + (j * RPL + ld_row) * ROW + ld_col) = kf[j];
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int j = 0; j < 2 * KS; ++j) kf[j] = *reinterpret_cast<const f32x4_t*>(k_tile + l32 * ROW + 16 * (j >> 1) + 8 * hh + 4 * (j & 1));
+    };
+    // A operand of O^T += V^T P^T: row l32 of block b is value column NB * l32 + b, so one wide load
+    // per key serves all blocks; step tt contracts over the 16 keys of accumulators 8 tt .. 8 tt + 7
+    // of both lane halves
+    auto load_v = [&](int tt, int vpos, int nv) {
+        const char* vt = reinterpret_cast<const char*>(vbase + (int64_t)vpos * a.tok_stride);   // scalar
+        const uint32_t last = ((uint32_t)(nv - 1) * ts + (uint32_t)(NB * l32)) * 4u;
+        uint32_t off0 = v_off + (uint32_t)tt * 16u * ts * 4u;
+        asm volatile("" : "+v"(off0));
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int i = 8 * tt + e;
+            const uint32_t off = off0 + (uint32_t)((e >> 2) * 8 + (e & 3)) * ts * 4u;
+            vf[i] = *reinterpret_cast<const vrow_t*>(vt + (off < last ? off : last));
+        }
+    };
+    const bf16_t* q_frag = q_s + l32 * QROW + 8 * hh;
+    auto read_q = [&](int st) {
+        return Split8{*reinterpret_cast<const u32x4_native*>(q_frag + 16 * st),
+                      *reinterpret_cast<const u32x4_native*>(q_frag + kUnitRows * QROW + 16 * st)};
+    };
+
     if (t < t_end) { locate(t); load_k(); }
     while (t < t_end) {
-        // A operand of O^T += V^T P^T: row l32 of block b is value column NB * l32 + b, so one
-        // wide load per key serves all blocks; step i contracts over the two keys of accumulator i
-        const int nv = nvalid;
-        const char* vt = reinterpret_cast<const char*>(vbase + (int64_t)pos * a.tok_stride);   // scalar
-        if (nv == 32) {
-            const uint32_t off = ((uint32_t)hh * 4u * ts + (uint32_t)(NB * l32)) * 4u;
+        const int nv = nvalid, vpos = pos;
+        turn_k();
+        // each key's own scale; the accumulators need those of 16 other keys
+        float most = 0.f, k_sc;
 #pragma unroll
-            for (int i = 0; i < 16; ++i)
-                vf[i] = *reinterpret_cast<const vrow_t*>(vt + (uint64_t)(((i >> 2) * 8 + (i & 3)) * ts) * 4u + off);
-        } else {
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                int key = (i >> 2) * 8 + hh * 4 + (i & 3);
-                key = key < nv ? key : nv - 1;
-                vf[i] = *reinterpret_cast<const vrow_t*>(vt + ((uint32_t)key * ts + (uint32_t)(NB * l32)) * 4u);
-            }
+        for (int j = 0; j < 2 * KS; ++j) most = max_abs4(most, kf[j]);
+        most = fmaxf(most, __shfl_xor(most, 32, FC_WAVE));
+        {
+            float inv;
+            k_sc = split_scale(most, inv);
+            k_scale[wave][l32] = inv;
         }
-        __builtin_amdgcn_sched_barrier(0);
-        f32x16_t s;
+        auto split_k = [&](Split8& x, int st, int p) __attribute__((always_inline)) {
+            split_pair(x, p, kf[2 * st + (p >> 1)][2 * (p & 1)], kf[2 * st + (p >> 1)][2 * (p & 1) + 1], k_sc);
+        };
+        f32x16_t s, s1;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) s[i] = 0.f;
+        for (int i = 0; i < 16; ++i) s[i] = s1[i] = 0.f;
+        Split8 cur, nxt, qc = read_q(0), qn;
 #pragma unroll
-        for (int j = 0; j < D / 8; ++j) {
-            const f32x4_t qf = *reinterpret_cast<const f32x4_t*>(&buf[l32 * ROW + 8 * j + 4 * hh]);
+        for (int p = 0; p < 4; ++p) split_k(cur, 0, p);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[j][i], qf[i], s, 0, 0, 0);
+        for (int st = 0; st < KS; ++st) {
+            if (st + 1 < KS) qn = read_q(st + 1);
+            split_mfma(cur.l, qc.h, s1);
+            if (st + 1 < KS) { split_k(nxt, st + 1, 0); split_k(nxt, st + 1, 1); }
+            __builtin_amdgcn_sched_barrier(0);
+            split_mfma(cur.h, qc.h, s);
+            if (st + 1 < KS) { split_k(nxt, st + 1, 2); split_k(nxt, st + 1, 3); }
+            __builtin_amdgcn_sched_barrier(0);
+            split_mfma(cur.h, qc.l, s1);
+            if (st == KS / 2 - 1) load_v(0, vpos, nv);     // K's first half is used up: its registers are free
+            __builtin_amdgcn_sched_barrier(0);
+            cur = nxt;
+            qc = qn;
         }
-        __builtin_amdgcn_sched_barrier(0);
+        load_v(1, vpos, nv);
         t += kSplitWaves;
         if (t < t_end) { locate(t); load_k(); }        // the next tile's keys, behind the softmax and P V
+        __builtin_amdgcn_sched_barrier(0);
+        s += s1;
+#pragma unroll
+        for (int i = 0; i < 16; i += 4) {
+            const f32x4_t ks = *reinterpret_cast<const f32x4_t*>(&k_scale[wave][2 * i + 4 * hh]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s[i + e] *= ks[e] * qs;
+        }
         if (nv < 32) {
 #pragma unroll
             for (int i = 0; i < 16; ++i)
@@ -149,20 +222,59 @@ __global__ __launch_bounds__(kSplitThreads) void attend_f32_kernel(FcAttendArgs 
         float mx = s[0];
 #pragma unroll
         for (int i = 1; i < 16; ++i) mx = fmaxf(mx, s[i]);
-        mx = fmaxf(mx, __shfl_xor(mx, 32, FC_WAVE));
-        const float mn = fmaxf(m, mx);
-        const float alpha = __builtin_amdgcn_exp2f(m - mn);
-        m = mn;
-        float ps = 0.f;
+        if (__any(mx > m + kTop)) {
+            const float mn = fmaxf(m, fmaxf(mx, __shfl_xor(mx, 32, FC_WAVE)) - kStart);
+            const float alpha = __builtin_amdgcn_exp2f(m - mn);
+            m = mn;
+            l *= alpha;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) { s[i] = __builtin_amdgcn_exp2f(s[i] - mn); ps += s[i]; }
-        l = fmaf(l, alpha, ps);
+            for (int b = 0; b < NB; ++b) o[b] *= alpha;
+        }
+        float p0 = 0.f, p1 = 0.f;
+        Split8 ps[2];
 #pragma unroll
-        for (int b = 0; b < NB; ++b) o[b] *= alpha;
+        for (int i = 0; i < 16; i += 2) {
+            const float x0 = __builtin_amdgcn_exp2f(s[i] - m), x1 = __builtin_amdgcn_exp2f(s[i + 1] - m);
+            p0 += x0;
+            p1 += x1;
+            split_pair(ps[i >> 3], (i & 7) >> 1, x0, x1, 1.0f);
+        }
+        l += p0 + p1;
+        // V's scale leaves a factor of four before it has to follow a larger entry
+        float vm = 0.f;
 #pragma unroll
         for (int i = 0; i < 16; ++i)
 #pragma unroll
-            for (int b = 0; b < NB; ++b) o[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(vf[i][b], s[i], o[b], 0, 0, 0);
+            for (int b = 0; b < NB; ++b) vm = fmaxf(vm, fabsf(vf[i][b]));
+        if (__any(vm > v_most)) {
+            float inv;
+            const float sc = split_scale(4.0f * wave_max_all(vm), inv);
+            const float down = sc * v_inv;                // old scale to new; O is zero while there is no old one
+            v_sc = sc; v_inv = inv; v_most = 32768.0f * inv;
+#pragma unroll
+            for (int b = 0; b < NB; ++b) o[b] *= down;
+        }
+        auto split_v = [&](Split8& x, int g, int p) __attribute__((always_inline)) {
+            split_pair(x, p, vf[8 * (g / NB) + 2 * p][g % NB], vf[8 * (g / NB) + 2 * p + 1][g % NB], v_sc);
+        };
+        // two blocks of O at a time
+        Split8 va, vb, na, nb;
+#pragma unroll
+        for (int p = 0; p < 4; ++p) { split_v(va, 0, p); split_v(vb, 1, p); }
+#pragma unroll
+        for (int g = 0; g < 2 * NB; g += 2) {
+            f32x16_t &oa = o[g % NB], &ob = o[g % NB + 1];
+            const Split8& pc = ps[g / NB];
+            const bool more = g + 2 < 2 * NB;
+            split_mfma(va.l, pc.h, oa); if (more) split_v(na, g + 2, 0); if (more) split_v(na, g + 2, 1); __builtin_amdgcn_sched_barrier(0);
+            split_mfma(vb.l, pc.h, ob); if (more) split_v(na, g + 2, 2); if (more) split_v(na, g + 2, 3); __builtin_amdgcn_sched_barrier(0);
+            split_mfma(va.h, pc.l, oa); if (more) split_v(nb, g + 3, 0); __builtin_amdgcn_sched_barrier(0);
+            split_mfma(vb.h, pc.l, ob); if (more) split_v(nb, g + 3, 1); __builtin_amdgcn_sched_barrier(0);
+            split_mfma(va.h, pc.h, oa); if (more) split_v(nb, g + 3, 2); __builtin_amdgcn_sched_barrier(0);
+            split_mfma(vb.h, pc.h, ob); if (more) split_v(nb, g + 3, 3); __builtin_amdgcn_sched_barrier(0);
+            va = na;
+            vb = nb;
+        }
     }
 
     l += __shfl_xor(l, 32, FC_WAVE);
@@ -172,7 +284,7 @@ __global__ __launch_bounds__(kSplitThreads) void attend_f32_kernel(FcAttendArgs 
     for (int i = 0; i < 16; ++i) {
         vrow_t v;
 #pragma unroll
-        for (int b = 0; b < NB; ++b) v[b] = o[b][i];
+        for (int b = 0; b < NB; ++b) v[b] = o[b][i] * v_inv;
         *reinterpret_cast<vrow_t*>(&buf[(wave * kUnitRows + l32) * ROW + NB * ((i >> 2) * 8 + hh * 4 + (i & 3))]) = v;
     }
     __syncthreads();

@@ -118,3 +118,26 @@ def test_every_form_when_later_keys_dwarf_earlier_ones(driver, H_q, H_k, d, A, L
     assert np.sqrt((err ** 2).sum()) / np.sqrt((ref ** 2).sum()) <= 1e-2
     assert err.max() <= 2e-2 * max(1.0, np.abs(ref).max())
     assert np.abs(res["lse"].cpu().numpy()[:, :A * L_c] - ref_lse).max() <= 2e-2 * np.abs(ref_lse).max()
+
+
+@pytest.mark.parametrize("H_q,H_k,d,A,L_c,L_clean", [
+    (2, 1, 64, 2, 40, 300), (2, 2, 128, 1, 33, 1000), (4, 4, 128, 2, 300, 2100), (6, 3, 64, 2, 400, 1500)])
+def test_f32_operands_of_any_magnitude(H_q, H_k, d, A, L_c, L_clean):
+    """fp32 operands are split into two f16 parts after scaling by powers of two: per query row, per key, and for V by
+    the largest entry so far, which here grows along the keys (its scale is raised again and again), with rows of
+    zeros, a first tile of zeros and subnormal entries.  Each entry is held to 2^-23 and a few thousand terms are
+    added up: the parity bars, per row."""
+    wl = synth.Workload("magnitude", "f32", H_q, H_k, d, A, L_c, L_clean, 1)
+    a = synth.attend_inputs(wl, seed=7)
+    rng = np.random.default_rng(5)
+    rows = lambda n, lo, hi: (10.0 ** rng.uniform(lo, hi, n)).astype(np.float32)
+    a["q"] *= rows(a["q"].shape[0], -4, 0.3)[:, None, None]
+    a["k_cache"] *= rows(wl.capacity, -6, 0.1)[None, :, None]
+    a["k_cache"][:, 5::7] = 0
+    a["v_cache"] *= np.logspace(-12, 9, wl.capacity, dtype=np.float32)[None, :, None]
+    a["v_cache"][:, :40] = 0
+    a["v_cache"][:, 50:60] = 1e-41
+    a["v_new"] *= rows(A * L_c, -3, 10)[:, None, None]
+    a["q"][3] = 0
+    got, ref, res, ref_lse, *_ = run_attend(wl, a, list(range(A)))
+    check_attend(wl, got, ref, res, ref_lse, A)
