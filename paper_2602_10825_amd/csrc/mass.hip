@@ -16,7 +16,7 @@
 // registers: the key's sum over rows is in-lane).  bf16 with more rows, and fp32, are bound by
 // arithmetic and have kernels of their own.  Every sum has a fixed order: the result is
 // deterministic.  No atomics.
-#include "fc_common.hpp"
+#include "f32_split.hpp"
 
 namespace {
 
@@ -38,35 +38,106 @@ __device__ __forceinline__ bool resolve_rows(const FcMassArgs& a, int64_t& row0)
     return true;
 }
 
-// ---- fp32: on the fp32 matrix cores --------------------------------------------------
-// v_mfma_f32_32x32x2_f32, operands read straight into registers in their own layout: lane (half, n)
-// holds elements 8 j + 4 half .. + 4 of row n, and the product of step (j, i) contracts over the
-// two elements 8 j + i and 8 j + 4 + i.  Both passes form S^T = K Q^T, one observation row per lane.
-// A wavefront keeps 32 rows (pass 1) or 32 keys (pass 2) and passes over the others.  Bound by the
-// matrix cores (64 cycles a product) in large calls and by latency in small ones, where one thread per
-// key with a wavefront reduction per row was a serial chain of all the rows.  Whole call, us before /
-// now: four query heads on one x 64, 50 rows on 512 keys 132 / 18; 12 x 128, 50 rows on 4000 keys 135 /
-// 54; 2 x 128, 600 rows on 9000 keys 1723 / 122; 4 x 128, 2040 rows on 700 keys 4826 / 88; one x 64, 64
-// rows on 40000 keys 266 / 31.
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
-typedef float f32x16_t __attribute__((ext_vector_type(16)));
+// ---- fp32: on the f16 matrix cores ----------------------------------------------------
+// Both operands in two f16 parts (f32_split.hpp), scaled per row and per key, read straight into
+// registers in the products' own layout: lane (half, n) holds elements 16 st + 8 half .. + 8 of row n.
+// Both passes form S^T = K Q^T, one observation row per lane.  A wavefront keeps 32 rows (pass 1) or 32 keys
+// (pass 2), split once, and passes over the others, whose next step is split between the products of this
+// one.  Bound by the vector ALU and the lines that a load touches in large calls and by latency in small ones.
+// Whole call, us, one thread per key with a wavefront reduction per row / fp32 matrix cores / now: four query
+// heads on one x 64, 50 rows on 512 keys 132 / 20 / 15; 12 x 128, 50 rows on 4000 keys 135 / 54 / 45, on 51000 - / 358 /
+// 257; 12 x 64, 969 rows on 10647 keys - / 398 / 249; 8 heads on 2 x 128, 1671 rows on 1892 keys - / 293 / 200.  Error
+// against float64 over 12 seeds of 7 shapes 0.90 of that of the fp32 matrix cores, nowhere larger.
 constexpr int kF32Waves = 8;
 
 template <int D>
 __device__ __forceinline__ void load_rows_f32(const float* row, int half, f32x4_t (&f)[D / 8]) {
 #pragma unroll
-    for (int j = 0; j < D / 8; ++j) f[j] = *reinterpret_cast<const f32x4_t*>(row + 8 * j + 4 * half);
+    for (int st = 0; st < D / 16; ++st) {
+        f[2 * st] = *reinterpret_cast<const f32x4_t*>(row + 16 * st + 8 * half);
+        f[2 * st + 1] = *reinterpret_cast<const f32x4_t*>(row + 16 * st + 8 * half + 4);
+    }
+}
+// the scale of the row that this lane and the one 32 away hold
+template <int D>
+__device__ __forceinline__ float row_scale_f32(const f32x4_t (&f)[D / 8], float& inverse) {
+    float most = 0.f;
+#pragma unroll
+    for (int j = 0; j < D / 8; ++j) most = max_abs4(most, f[j]);
+    return split_scale(fmaxf(most, __shfl_xor(most, 32, FC_WAVE)), inverse);
 }
 template <int D>
-__device__ __forceinline__ f32x16_t scores_f32(const f32x4_t (&k)[D / 8], const f32x4_t (&q)[D / 8]) {
-    f32x16_t s;
+__device__ __forceinline__ void split_step_f32(Split8& x, const f32x4_t (&f)[D / 8], int st, int p, float scale) {
+    split_pair(x, p, f[2 * st + (p >> 1)][2 * (p & 1)], f[2 * st + (p >> 1)][2 * (p & 1) + 1], scale);
+}
+// S^T of the resident operand `stay` and the rows in `f`; STAY_K: keys stay (and Q passes).
+template <int D, bool STAY_K>
+__device__ __forceinline__ f32x16_t scores_f32(const Split8 (&stay)[D / 16], const f32x4_t (&f)[D / 8], float scale) {
+    f32x16_t c[2];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) s[i] = 0.f;
+    for (int i = 0; i < 16; ++i) c[0][i] = c[1][i] = 0.f;
+    Split8 cur, nxt;
 #pragma unroll
-    for (int j = 0; j < D / 8; ++j)
+    for (int p = 0; p < 4; ++p) split_step_f32<D>(cur, f, 0, p, scale);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) s = __builtin_amdgcn_mfma_f32_32x32x2f32(k[j][i], q[j][i], s, 0, 0, 0);
-    return s;
+    for (int st = 0; st < D / 16; ++st) {
+        const Split8 &k = STAY_K ? stay[st] : cur, &q = STAY_K ? cur : stay[st];
+        const bool more = st + 1 < D / 16;
+        f32x16_t &c0 = c[st & 1], &c1 = c[1 - (st & 1)];      // no product waits for the one before it
+        split_mfma(k.l, q.h, c0);
+        if (more) { split_step_f32<D>(nxt, f, st + 1, 0, scale); split_step_f32<D>(nxt, f, st + 1, 1, scale); }
+        __builtin_amdgcn_sched_barrier(0);
+        split_mfma(k.h, q.h, c1);
+        if (more) { split_step_f32<D>(nxt, f, st + 1, 2, scale); split_step_f32<D>(nxt, f, st + 1, 3, scale); }
+        __builtin_amdgcn_sched_barrier(0);
+        split_mfma(k.h, q.l, c0);
+        cur = nxt;
+    }
+    return c[0] + c[1];
+}
+template <int D>
+__device__ __forceinline__ void split_rows_f32(Split8 (&x)[D / 16], const f32x4_t (&f)[D / 8], float scale) {
+#pragma unroll
+    for (int st = 0; st < D / 16; ++st)
+#pragma unroll
+        for (int p = 0; p < 4; ++p) split_step_f32<D>(x[st], f, st, p, scale);
+}
+// The 16 keys of a lane's accumulators (8 j + 4 half + e of 32), from `of_key`, one float per key.
+__device__ __forceinline__ void keys_of_lane(const float* of_key, int half, float (&x)[16]) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const f32x4_t v = *reinterpret_cast<const f32x4_t*>(of_key + 8 * j + 4 * half);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[4 * j + e] = v[e];
+    }
+}
+
+// log2-sum-exp from the largest exponent and the sum above it.  log2(sum) = e + log2(f), 1/2 <= f < 1, so that
+// the logarithm's own error (one of its last place) stays below the one rounding of the total: mx + e in two
+// terms.  (mx + log2(sum) as it stands made every entry of the importance wrong by up to 3e-7, now 1e-7.)
+__device__ __forceinline__ float log2_sum(float mx, float sum) {
+    const float e = (float)__builtin_amdgcn_frexp_expf(sum), f = __builtin_amdgcn_frexp_mantf(sum);
+    const float hi = mx + e, b = hi - mx;
+    const float lo = (mx - (hi - b)) + (e - b);
+    return hi + (lo + __builtin_amdgcn_logf(f));
+}
+// A row with at most kFewPartials of them is merged by whoever needs it; the launch between the passes is left out
+// (four heads on one x 64, 50 rows on 512 keys: 3.0 of 22 us).  With more, each block of pass 2 would read and merge
+// them all, and on a full cache that took longer than the launch; and with many tiles of rows each wavefront of
+// pass 2 merges again for every tile (12 x 64, 969 rows on 10647 keys 248 -> 281 us).
+constexpr int kFewPartials = 4, kFewTiles = 8;
+__device__ __forceinline__ float lse_of_few(const float* __restrict__ m, const float* __restrict__ l, int np) {
+    float mi[kFewPartials], li[kFewPartials], mx = kNegBig, sum = 0.f;
+#pragma unroll
+    for (int i = 0; i < kFewPartials; ++i) {
+        mi[i] = i < np ? m[i] : kNegBig;
+        li[i] = i < np ? l[i] : 0.f;
+    }
+#pragma unroll
+    for (int i = 0; i < kFewPartials; ++i) mx = fmaxf(mx, mi[i]);
+#pragma unroll
+    for (int i = 0; i < kFewPartials; ++i) sum = fmaf(li[i], __builtin_amdgcn_exp2f(mi[i] - mx), sum);
+    return log2_sum(mx, sum);
 }
 
 // A tile of rows is 32 of the W * G that use one key head: with a tile of its own for every query head,
@@ -94,29 +165,45 @@ __global__ __launch_bounds__(kF32Waves * 64, 2) void mass_stats_f32_kernel(FcMas
     const int T = (a.mass_len + 31) / 32;
     const int t_end = (int)((int64_t)T * (s + 1) / S);
     const F32Row row = f32_row(a, hk, rt * 32 + n);               // padding rows: computed, not used
-    f32x4_t q[D / 8], k[D / 8];
+    __shared__ __attribute__((aligned(16))) float k_scale[kF32Waves][32];
+    Split8 q[D / 16];
+    f32x4_t k[D / 8];
+    float qc;                                                     // what brings a score back: the row's part, and c2
     auto load_k = [&](int t) {
         const int j = t * 32 + n < a.mass_len ? t * 32 + n : a.mass_len - 1;
         load_rows_f32<D>(kh + (int64_t)j * a.tok_stride, half, k);
     };
     int t = (int)((int64_t)T * s / S) + wave;
-    if (t < t_end) load_k(t);
-    load_rows_f32<D>((const float*)a.q_base + ((row0 + row.w) * a.H_q + row.h) * D, half, q);
+    {
+        f32x4_t f[D / 8];
+        load_rows_f32<D>((const float*)a.q_base + ((row0 + row.w) * a.H_q + row.h) * D, half, f);
+        if (t < t_end) load_k(t);
+        const float sc = row_scale_f32<D>(f, qc);
+        split_rows_f32<D>(q, f, sc);
+        qc *= c2;
+    }
     float m = kNegBig, l = 0.f;
     for (; t < t_end; t += kF32Waves) {
-        const f32x16_t st = scores_f32<D>(k, q);
+        float inv;
+        const float sc = row_scale_f32<D>(k, inv);
+        k_scale[wave][n] = inv;          // the wavefront's own: LDS serves its accesses in order, no barrier is needed
+        const f32x16_t st = scores_f32<D, false>(q, k, sc);
+        float kc[16];
+        keys_of_lane(k_scale[wave], half, kc);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) kc[r] *= qc;
         if (t + kF32Waves < t_end) load_k(t + kF32Waves);
         const int key0 = t * 32 + half * 4;
         const bool full = t * 32 + 32 <= a.mass_len;
         float tm = kNegBig;
 #pragma unroll
         for (int r = 0; r < 16; ++r)
-            if (full || key0 + (r >> 2) * 8 + (r & 3) < a.mass_len) tm = fmaxf(tm, st[r] * c2);
+            if (full || key0 + (r >> 2) * 8 + (r & 3) < a.mass_len) tm = fmaxf(tm, st[r] * kc[r]);
         const float mn = fmaxf(m, tm);
         float acc = 0.f;
 #pragma unroll
         for (int r = 0; r < 16; ++r)
-            if (full || key0 + (r >> 2) * 8 + (r & 3) < a.mass_len) acc += __builtin_amdgcn_exp2f(fmaf(st[r], c2, -mn));
+            if (full || key0 + (r >> 2) * 8 + (r & 3) < a.mass_len) acc += __builtin_amdgcn_exp2f(fmaf(st[r], kc[r], -mn));
         // no real key yet (m and mn both at the floor): keep l = 0
         l = (mn > kNegBig) ? fmaf(l, __builtin_amdgcn_exp2f(m - mn), acc) : 0.f;
         m = mn;
@@ -156,7 +243,8 @@ __device__ __forceinline__ float lanes_sum_scatter(float (&v)[16], int n) {
 // (every parts-th each) and are added up in order.
 template <int D>
 __global__ __launch_bounds__(kF32Waves * 64, 2) void mass_cols_f32_kernel(FcMassArgs a, int nrg, int parts,
-                                                                         const float* __restrict__ lse2) {
+                                                                         const float* __restrict__ lse2, const float* __restrict__ pm,
+                                                                         const float* __restrict__ pl, int np) {
     const int hk = blockIdx.y, kb = kF32Waves / parts;             // key blocks of 32 per block
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int n = lane & 31, half = lane >> 5;
@@ -174,24 +262,38 @@ __global__ __launch_bounds__(kF32Waves * 64, 2) void mass_cols_f32_kernel(FcMass
     float sums[16];
 #pragma unroll
     for (int r = 0; r < 16; ++r) sums[r] = 0.f;
-    f32x4_t k[D / 8], q[D / 8];
-    float ls = 0.f;
+    __shared__ __attribute__((aligned(16))) float k_scale[kF32Waves][32];
+    Split8 k[D / 16];
+    f32x4_t q[D / 8];
+    float ls = 0.f, kc[16];                                        // kc: what brings a score back, the keys' part and c2
     auto load_q = [&](int t) {
         const F32Row row = f32_row(a, hk, t * 32 + n);
         load_rows_f32<D>((const float*)a.q_base + ((row0 + row.w) * a.H_q + row.h) * D, half, q);
-        ls = row.ok ? lse2[(int64_t)row.h * nrg * kRowGroup + row.w] : kPosBig;   // padding rows: their terms vanish
+        const int64_t at = (int64_t)row.h * nrg * kRowGroup + row.w;
+        const float v = lse2 ? lse2[at] : lse_of_few(pm + at * np, pl + at * np, np);
+        ls = row.ok ? v : kPosBig;                                 // padding rows: their terms vanish
     };
     if (part < nt) load_q(part);
     {
         const int j = key0 + n < a.mass_len ? key0 + n : a.mass_len - 1;
-        load_rows_f32<D>((const float*)a.k_cache + (int64_t)hk * a.head_stride + (int64_t)j * a.tok_stride, half, k);
+        f32x4_t f[D / 8];
+        load_rows_f32<D>((const float*)a.k_cache + (int64_t)hk * a.head_stride + (int64_t)j * a.tok_stride, half, f);
+        float inv;
+        const float sc = row_scale_f32<D>(f, inv);
+        k_scale[wave][n] = inv;
+        split_rows_f32<D>(k, f, sc);
+        keys_of_lane(k_scale[wave], half, kc);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) kc[r] *= c2;
     }
     for (int t = part; t < nt; t += parts) {
-        const f32x16_t st = scores_f32<D>(k, q);
+        float inv;
+        const float sc = row_scale_f32<D>(q, inv);
+        const f32x16_t st = scores_f32<D, true>(k, q, sc);
         const float neg = -ls;
         if (t + parts < nt) load_q(t + parts);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) sums[r] += __builtin_amdgcn_exp2f(fmaf(st[r], c2, neg));
+        for (int r = 0; r < 16; ++r) sums[r] += __builtin_amdgcn_exp2f(fmaf(st[r], kc[r] * inv, neg));
     }
     const float v = lanes_sum_scatter(sums, n);
     if (n < 16) merge[wave][(n >> 2) * 8 + half * 4 + (n & 3)] = v;
@@ -319,13 +421,7 @@ __global__ __launch_bounds__(kNT) void mass_lse_kernel(const float* __restrict__
         mx = mn;
     }
     if (part == 0) {
-        // log2(sum) = e + log2(f), 1/2 <= f < 1, so that the logarithm's own error (one of its last
-        // place) stays below the one rounding of the total: mx + e in two terms.  (mx + log2(sum) as
-        // it stands made every entry of the importance wrong by up to 3e-7, now 1e-7.)
-        const float e = (float)__builtin_amdgcn_frexp_expf(sum), f = __builtin_amdgcn_frexp_mantf(sum);
-        const float hi = mx + e, b = hi - mx;
-        const float lo = (mx - (hi - b)) + (e - b);
-        lse2[((int64_t)h * nrg + rg) * kRowGroup + row] = row < nw ? hi + (lo + __builtin_amdgcn_logf(f)) : kPosBig;
+        lse2[((int64_t)h * nrg + rg) * kRowGroup + row] = row < nw ? log2_sum(mx, sum) : kPosBig;
     }
 }
 
@@ -522,7 +618,8 @@ __global__ __launch_bounds__(kNT, 2) void mass_stats_bf16_kernel(FcMassArgs a, i
 
 template <int D>
 __global__ __launch_bounds__(kNT, 2) void mass_cols_bf16_kernel(FcMassArgs a, int tpb,
-                                                             const float* __restrict__ lse2) {
+                                                             const float* __restrict__ lse2, const float* __restrict__ pm,
+                                                             const float* __restrict__ pl, int np) {
     const int hk = gridDim.y - 1 - blockIdx.y;   // the first pass read the last heads last: they may still be cached
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int span = tpb * kTile;
@@ -547,7 +644,10 @@ __global__ __launch_bounds__(kNT, 2) void mass_cols_bf16_kernel(FcMassArgs a, in
         u32x4_native kr[D / 16];
         fetch_ktile<D>(a, kh, jb, kr);         // on its way while the rows are staged
         stage_q_bf16<D>(a, row0, h, sm.q);
-        if (tid < kRowGroup) sm.lse[tid] = lse2[h * kRowGroup + tid];
+        if (tid < kRowGroup) {
+            const int64_t at = (int64_t)h * kRowGroup + tid;
+            sm.lse[tid] = lse2 ? lse2[at] : tid < a.W ? lse_of_few(pm + at * np, pl + at * np, np) : kPosBig;
+        }
         __syncthreads();
         float lr[2][16];
 #pragma unroll
@@ -969,22 +1069,27 @@ int launch_bf16(const FcMassArgs& a, hipStream_t s) {
     float* lse2 = pl + (size_t)a.H_q * kRowGroup * np;
     mass_stats_bf16_kernel<D><<<dim3(np, a.H_q), kNT, 0, s>>>(a, np, tpb, pm, pl);
     FC_LAUNCH_CHECK();
-    mass_lse_kernel<<<dim3(1, a.H_q), kNT, 0, s>>>(pm, pl, 1, np, a.W, lse2);
-    FC_LAUNCH_CHECK();
-    mass_cols_bf16_kernel<D><<<dim3(np, a.H_k), kNT, 0, s>>>(a, tpb, lse2);
+    if (np > kFewPartials) {
+        mass_lse_kernel<<<dim3(1, a.H_q), kNT, 0, s>>>(pm, pl, 1, np, a.W, lse2);
+        FC_LAUNCH_CHECK();
+    } else {
+        lse2 = nullptr;
+    }
+    mass_cols_bf16_kernel<D><<<dim3(np, a.H_k), kNT, 0, s>>>(a, tpb, lse2, pm, pl, np);
     FC_LAUNCH_CHECK();
     return FC_OK;
 }
 
-// With few rows the matrix cores work on padding, and one thread per key is faster (a x b keys: a heads of
-// b; head dimension 64 / 128; one thread per key against matrix cores): one row, 24 x 16384 45 against 65 / 73
-// against 134; four, 24 x 16384 48 : 66 / 79 : 134, 12 x 1024 16 : 16 / 20 : 24, 1 x 16384 20 : 16 / 26 : 26;
-// eight, 24 x 4096 25 : 25 / 38 : 45, 12 x 4096 21 : 16 / 30 : 26.  Few long heads leave most threads' chains of
-// loads uncovered.
+// With few rows the matrix cores work on padding, and one thread per key is faster (heads x keys: head dimension
+// 64 / 128; one thread per key against matrix cores, us): one row, 24 x 16384 46 against 60 / 75 against 102, 12 x 4096
+// 12 : 15 / 18 : 21, 1 x 16384 16 : 16 / 21 : 21, 1 x 60000 33 : 21 / 45 : 28; four, 24 x 16384 49 : 60 / 80 : 103, 24 x 4096
+// 21 : 25 / 31 : 37, 12 x 4096 16 : 15 / 23 : 22, 12 x 1024 14 : 15 / 20 : 20, 8 x 8192 18 : 16 / 25 : 22; eight, 24 x 4096 25 :
+// 25 / 39 : 38, 12 x 4096 (before) 21 : 16 / 30 : 26.  Few long heads leave most threads' chains of loads uncovered.
 inline bool f32_one_thread_per_key(int64_t rows, int H_k, int mass_len) {
-    if (rows <= 2) return true;
-    if (rows <= 4) return H_k >= 8 || mass_len < 8192;
-    return rows <= kFewRows && H_k >= 8 && (int64_t)H_k * mass_len >= 24 * 4096;
+    const bool full = (int64_t)H_k * mass_len >= 24 * 4096;
+    if (rows <= 2) return H_k >= 4 || mass_len < 16384;
+    if (rows <= 4) return (H_k >= 12 && full) || mass_len < 2048;
+    return rows <= kFewRows && H_k >= 8 && full;
 }
 template <int D>
 int launch_f32_few(const FcMassArgs& a, hipStream_t s) {
@@ -1020,12 +1125,16 @@ int launch_f32(const FcMassArgs& a, hipStream_t s) {
     float* lse2 = pl + (size_t)a.H_q * nrg * kRowGroup * S;
     mass_stats_f32_kernel<D><<<dim3(S * rt, a.H_k), kF32Waves * 64, 0, s>>>(a, nrg, S, pm, pl);
     FC_LAUNCH_CHECK();
-    mass_lse_kernel<<<dim3(nrg, a.H_q), kNT, 0, s>>>(pm, pl, nrg, S, a.W, lse2);
-    FC_LAUNCH_CHECK();
+    if (S > kFewPartials || rt > kFewTiles) {
+        mass_lse_kernel<<<dim3(nrg, a.H_q), kNT, 0, s>>>(pm, pl, nrg, S, a.W, lse2);
+        FC_LAUNCH_CHECK();
+    } else {
+        lse2 = nullptr;
+    }
     auto blocks = [&](int parts) { const int keys = kF32Waves / parts * 32; return (a.mass_len + keys - 1) / keys; };
     int parts = 1;
     while (parts < kF32Waves && 2 * parts <= rt && (int64_t)a.H_k * blocks(parts) < 512) parts *= 2;
-    mass_cols_f32_kernel<D><<<dim3(blocks(parts), a.H_k), kF32Waves * 64, 0, s>>>(a, nrg, parts, lse2);
+    mass_cols_f32_kernel<D><<<dim3(blocks(parts), a.H_k), kF32Waves * 64, 0, s>>>(a, nrg, parts, lse2, pm, pl, S);
     FC_LAUNCH_CHECK();
     return FC_OK;
 }

@@ -51,3 +51,21 @@ def test_mass_f32_of_more_rows_than_a_grid_dimension_has_blocks():
     # a lane adds W / 32 / 8 terms one after the other: at most that many roundings of 2^-24, far fewer as
     # they go both ways; a tenth of that bound
     assert float((got[0] - ref).abs().max() / ref.min()) <= 0.1 * (W / 256) * 2.0 ** -24
+
+
+@pytest.mark.parametrize("d,H_q,H_k,W,L", [(64, 4, 1, 64, 1024), (64, 4, 1, 65, 1290), (128, 2, 2, 40, 256), (128, 1, 1, 257, 900)])
+def test_mass_f32_rows_and_keys_of_any_magnitude(d, H_q, H_k, W, L):
+    """Queries and keys are split into two f16 parts after scaling by powers of two, per row and per key: rows of zeros,
+    of subnormal numbers and of magnitudes over 30 decimal orders whose scores stay O(1); up to eight tiles of rows and
+    four partials per row are merged without the launch between the passes, more with it.  The usual bars."""
+    rng = np.random.default_rng(W)
+    q = rng.standard_normal((W, H_q, d)).astype(np.float32)
+    k = rng.standard_normal((H_k, L, d)).astype(np.float32)
+    k *= (10.0 ** rng.uniform(-8, 0.2, L)).astype(np.float32)[None, :, None]
+    q *= (10.0 ** rng.uniform(-20, 0.2, W)).astype(np.float32)[:, None, None]
+    k[:, 3::5] = 0
+    k[:, 4::50] *= np.float32(1e-35)
+    q[::7] = 0
+    q[1::9] *= np.float32(1e-20)
+    got = B.flowcache_attention_mass(dev(q, "f32"), dev(k, "f32"), L).cpu().numpy().astype(np.float64)
+    assert_mass_close(got, O.attention_mass(q, k, L), "f32", f"W={W} L={L}")
