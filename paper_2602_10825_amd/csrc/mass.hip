@@ -693,7 +693,12 @@ __global__ __launch_bounds__(kNT, 2) void mass_cols_bf16_kernel(FcMassArgs a, in
 // queries double-buffered in LDS with a barrier per tile and group, a running maximum in pass 1, the
 // products and the vector work of a tile one after the other, before / this, whole call, us: 24 x 128,
 // 1872 rows on 74880 keys 2833 / 1681 (passes 880 and 935); 2 heads on 1, 700 rows on 60000 keys 180
-// / 87; 4 x 128, 2040 rows on 700 keys 459 / 72; 24 x 64, 130 rows on 84240 keys 235 / 212.)
+// / 87; 4 x 128, 2040 rows on 700 keys 459 / 72; 24 x 64, 130 rows on 84240 keys 235 / 210.)  The loads of the
+// passing tiles take a scalar base and a 32-bit offset per lane (a 64-bit product per row, lane and tile was a tenth
+// of the vector work), padding rows are not cleared (their normaliser makes the terms vanish), and a sum is not added
+// right behind its own exponential: 1715 -> 1630 on one card; 4 x 128, 2040 rows on 700 keys 72 -> 62; 8 heads on 2
+// x 128, 97 rows on 5000 keys 33.2 -> 29.4; 24 x 64, 130 rows on 84240 keys 210 and 212.  (Exponent, exponential and
+// sum of an element beside three products in turn, no vector instruction behind one that it needs: the same.)
 constexpr int kStream = 64;             // rows of a tile that passes
 constexpr int kRing = 3;                // tiles in LDS: read, complete, being written
 constexpr float kTooBig = 1.0995116e12f;   // 2^40
@@ -740,13 +745,20 @@ __device__ __forceinline__ void mass_step(f32x16_t (&nxt)[2], const f32x16_t (&p
             if (b == 1)
                 frag[kb % kAhead] = *reinterpret_cast<const bf16x8_t*>(
                     kb + kAhead < KS ? cur + (kb + kAhead) * 16 : after + (kb + kAhead - KS) * 16);
+            // the exponentials first: a sum right behind its own waits for it
+            float w[E];
+#pragma unroll
+            for (int i = 0; i < E; ++i) {
+                const int e = (2 * kb + b) * E + i;
+                w[i] = __builtin_amdgcn_exp2f(fmaf(prev[e >> 4][e & 15], c2, neg[e >> 4]));
+                asm volatile("" : "+v"(w[i]));      // computed here, next to the matrix products
+            }
 #pragma unroll
             for (int i = 0; i < E; ++i) {
                 const int e = (2 * kb + b) * E + i, q = e >> 4, r = e & 15;
-                float w = __builtin_amdgcn_exp2f(fmaf(prev[q][r], c2, neg[q]));
                 float& sum = sums[q][COLS ? r : r & 1];
-                sum += w;
-                asm volatile("" : "+v"(sum));       // computed here, next to the matrix products
+                sum += w[i];
+                asm volatile("" : "+v"(sum));
             }
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -811,13 +823,17 @@ __global__ __launch_bounds__(NW * 64, 2) void mass_stats_wide_kernel(FcMassArgs 
         }
     }
     u32x4_native kr[LD];
+    const uint32_t row_b = (uint32_t)a.tok_stride * 2u, col_b = (uint32_t)(tid % PR) * 16u;   // (NT is a multiple of PR)
+    const uint32_t off0 = (uint32_t)(tid / PR) * row_b + col_b, step = (uint32_t)(NT / PR) * row_b;
     auto fetch = [&](int t) {                     // rows past the end re-read the last one and are masked
         const int j0 = (t_lo + (t < nt ? t : nt - 1)) * kStream;
+        const char* base = reinterpret_cast<const char*>(kh + (int64_t)j0 * a.tok_stride);
+        const int left = a.mass_len - j0 - 1;
+        const uint32_t last = (uint32_t)(left < kStream - 1 ? left : kStream - 1) * row_b + col_b;
 #pragma unroll
         for (int i = 0; i < LD; ++i) {
-            const int p = tid + NT * i;
-            const int j = j0 + p / PR < a.mass_len ? j0 + p / PR : a.mass_len - 1;
-            kr[i] = *reinterpret_cast<const u32x4_native*>(kh + (int64_t)j * a.tok_stride + (p % PR) * 8);
+            const uint32_t off = off0 + (uint32_t)i * step;
+            kr[i] = *reinterpret_cast<const u32x4_native*>(base + (off < last ? off : last));
         }
     };
     auto store = [&](int buf) {
@@ -909,27 +925,20 @@ __global__ __launch_bounds__(NW * 64, 2) void mass_cols_wide_kernel(FcMassArgs a
     const int key0 = jb + wave * 64;
     const bool active = key0 < a.mass_len;
 
-    bf16x8_t stay[2][KS];
-#pragma unroll
-    for (int b = 0; b < 2; ++b) {
-        const int j = key0 + b * 32 + n < a.mass_len ? key0 + b * 32 + n : a.mass_len - 1;
-#pragma unroll
-        for (int kb = 0; kb < KS; ++kb)
-            stay[b][kb] = *reinterpret_cast<const bf16x8_t*>(kh + (int64_t)j * a.tok_stride + kb * 16 + half * 8);
-    }
     const int nt = G * nrg;                       // tiles of 64 rows: query head g = t / nrg, group t % nrg
     int ft = 0, fg = 0, frg = 0;                  // the tile that is fetched next
     u32x4_native qr[LD];
     float lr = 0.f;
-    auto fetch = [&]() {                          // padding rows: a valid row is read, zeros are stored
-        const int h = hk * G + fg;
+    const uint32_t row_b = (uint32_t)a.H_q * D * 2u, col_b = (uint32_t)(tid % PR) * 16u;   // (NT is a multiple of PR)
+    const uint32_t off0 = (uint32_t)(tid / PR) * row_b + col_b, step = (uint32_t)(NT / PR) * row_b;
+    auto fetch = [&]() {                          // padding rows: the last one again; their normaliser makes the terms vanish
+        const int h = hk * G + fg, left = a.W - frg * kRowGroup - 1;
+        const char* base = reinterpret_cast<const char*>((const bf16_t*)a.q_base + ((row0 + frg * kRowGroup) * a.H_q + h) * D);
+        const uint32_t last = (uint32_t)(left < kRowGroup - 1 ? left : kRowGroup - 1) * row_b + col_b;
 #pragma unroll
         for (int i = 0; i < LD; ++i) {
-            const int p = tid + NT * i, w = frg * kRowGroup + p / PR;
-            u32x4_native v = *reinterpret_cast<const u32x4_native*>(
-                (const bf16_t*)a.q_base + ((row0 + (w < a.W ? w : 0)) * a.H_q + h) * D + (p % PR) * 8);
-            if (w >= a.W) v = u32x4_native{0u, 0u, 0u, 0u};
-            qr[i] = v;
+            const uint32_t off = off0 + (uint32_t)i * step;
+            qr[i] = *reinterpret_cast<const u32x4_native*>(base + (off < last ? off : last));
         }
         if (tid < kRowGroup) lr = lse2[((int64_t)h * nrg + frg) * kRowGroup + tid];
         if (++ft < nt && ++frg == nrg) { frg = 0; ++fg; }      // past the last tile: that one again
@@ -942,7 +951,15 @@ __global__ __launch_bounds__(NW * 64, 2) void mass_cols_wide_kernel(FcMassArgs a
         }
         if (tid < kRowGroup) sm.lse[buf][tid] = lr;
     };
-    fetch();
+    fetch();                                      // before the keys: it is needed first
+    bf16x8_t stay[2][KS];
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+        const int j = key0 + b * 32 + n < a.mass_len ? key0 + b * 32 + n : a.mass_len - 1;
+#pragma unroll
+        for (int kb = 0; kb < KS; ++kb)
+            stay[b][kb] = *reinterpret_cast<const bf16x8_t*>(kh + (int64_t)j * a.tok_stride + kb * 16 + half * 8);
+    }
     store(0);
     fetch();
     __syncthreads();
