@@ -60,16 +60,6 @@ typedef float f32x4_t __attribute__((ext_vector_type(4)));
 constexpr int BQ = kWideRows;   // query rows per workgroup
 constexpr int BK = 64;       // keys per tile
 
-typedef short s16x4_t __attribute__((ext_vector_type(4)));
-
-// Transposing LDS load: within each group of 16 lanes, lane s passes the address of 4
-// consecutive bf16; lane i receives element (i % 4) of the data addressed by lanes
-// i/4, i/4 + 4, i/4 + 8, i/4 + 12.
-__device__ __forceinline__ s16x4_t lds_read_tr(const bf16_t* p) {
-    return __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-        (s16x4_t __attribute__((address_space(3)))*)(p));
-}
-
 constexpr int NT = 64 * (BQ / 32);   // 8 wavefronts of 32 query rows, two per SIMD
 
 // f(0), ..., f(N - 1) with the argument a compile-time constant: every choice made on it is made when
@@ -107,7 +97,7 @@ __device__ __forceinline__ void attend_wide(const FcAttendArgs& a, const FcAtten
     constexpr int NPV = 4 * DVB, NQK = 2 * KS, N = NPV + NQK;   // matrix products of a step: P V, Q K^T
     constexpr int PF = 4;             // fragments are read this many products ahead
 
-    const WideItem wi = wide_item(a, p, valid, blockIdx.x);
+    const WideItem wi = wide_item<BQ, true>(a, p, valid, blockIdx.x);
     if (!wi.ok) return;
     const int r = wi.r, h = wi.h, tile = wi.tile;
     const int c = a.rec_idx[r];
@@ -642,7 +632,7 @@ int launch_bf16(const FcAttendArgs& a, hipStream_t s) {
         attend_bf16_kernel<D, true, true><<<p.grid, NT, 0, s>>>(a, p, (float*)a.ws);
     FC_LAUNCH_CHECK();
     if (p.merge_grid > 0) {
-        attend_merge_kernel<bf16_t, D><<<p.merge_grid, 256, 0, s>>>(a, p, (const float*)a.ws);
+        attend_merge_kernel<bf16_t, D, BQ, true><<<p.merge_grid, 256, 0, s>>>(a, p, (const float*)a.ws);
         FC_LAUNCH_CHECK();
     }
     return FC_OK;

@@ -291,15 +291,316 @@ __global__ __launch_bounds__(kSplitThreads) void attend_f32_kernel(FcAttendArgs 
     finish_unit<float, D, ROW>(a, p, it, buf, m_s, l_s, parts);
 }
 
+// ---- many query rows ----------------------------------------------------------------------------
+// 128 query rows per block, 32 per wavefront, two blocks per compute unit.  The four wavefronts share every
+// 32-key tile: it is read once, split into its f16 parts once (an eighth of the vector work of the body
+// above) and double-buffered in LDS.  Step t: tile t's products and softmax, with the splitting of tile t + 1
+// between the products of Q K^T, the loads of tile t + 2 behind them, and one barrier at the end.  V's scale
+// is the block's; it is fixed a step before the tile is split, when the wavefronts have exchanged the
+// largest entries that it does not fit yet.  The plan takes this body where it is cheaper over the recompute
+// counts (attend_split.hpp).  us on the fp32 matrix cores / in 32-row blocks / here: 12 x 128, 2 chunks of 1021 rows on
+// 4083 clean keys 650 / 357 / 277; 24 x 128, 460 rows on 3350 keys 237 / 130 / 114, 4 chunks of 460 617 / - / 311; 4 x 128, 4 of
+// 1500 on 2000 815 / - / 292; 24 x 64, 2 of 500 on 4000 292 / - / 148.  Matrix cores 30 % busy: a wavefront issues for 2300
+// of the 5400 cycles that a tile takes it and waits for LDS, memory and the barrier in the rest; half an XCD's blocks
+// more would help, registers (256) and LDS (76 KB a block) allow two per compute unit.
+template <int CTRL>
+__device__ __forceinline__ float max_dpp(float v) {
+    return fmaxf(v, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true)));
+}
+// the maximum over each group of N consecutive lanes (8 or 16)
+template <int N>
+__device__ __forceinline__ float max_lanes(float v) {
+    v = max_dpp<0xB1>(v);                   // quad_perm: neighbours
+    v = max_dpp<0x4E>(v);                   // quad_perm: pairs
+    v = max_dpp<0x141>(v);                  // row_half_mirror: the other four of eight
+    return N == 16 ? max_dpp<0x140>(v) : v; // row_mirror: the other eight of sixteen
+}
+
+constexpr int kSharedThreads = 2 * kSharedRows;
+
+template <int D>
+__global__ __launch_bounds__(kSharedThreads, 2) void attend_f32_shared_kernel(FcAttendArgs a, FcAttendPlan p, float* parts) {
+    constexpr int KS = D / 16;           // contraction steps of Q K^T
+    constexpr int NB = D / 32;           // 32-wide blocks of the value dimension
+    constexpr int KROW = D + 8, VROW = D + 32;       // padded rows, as in the bf16 kernel
+    constexpr int LPR = D / 8;           // threads per row of a tile, eight entries each
+    constexpr int RPP = kSharedThreads / LPR, NP = 32 / RPP;   // rows per pass, passes per tile
+    constexpr float kTop = 15.0f, kStart = 12.0f;    // as above
+    __shared__ __attribute__((aligned(16))) bf16_t K_s[2][2][32 * KROW], V_s[2][2][32 * VROW];   // [buffer][part]
+    __shared__ __attribute__((aligned(16))) float k_scale[2][32], v_over[2][4];
+    __shared__ Segments sg;
+
+    const uint32_t valid = valid_blocks(a);
+    if (valid == 0) return;
+    const WideItem wi = wide_item<kSharedRows, false>(a, p, valid, blockIdx.x);
+    if (!wi.ok) return;
+    const int hk = wi.h / (a.H_q / a.H_k);
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int l32 = lane & 31, hh = lane >> 5, l16 = lane & 15;
+    const float c2 = a.scale * 1.4426950408889634f;
+    if (tid == 0) list_segments(a, a.rec_idx[wi.r], sg);
+
+    // B operand of S^T = K Q^T: lane holds Q[q = l32][16 st + 8 hh .. + 8), scaled per row
+    const int row_in_chunk = wi.tile * kSharedRows + wave * 32 + l32;
+    Split8 qf[KS];
+    float qs;
+    {
+        const int rc = row_in_chunk > a.L_c - 1 ? a.L_c - 1 : row_in_chunk;
+        const float* qp = (const float*)a.q + (((int64_t)wi.r * a.L_c + rc) * a.H_q + wi.h) * D + 8 * hh;
+        f32x4_t x[2 * KS];
+        float most = 0.f;
+#pragma unroll
+        for (int j = 0; j < 2 * KS; ++j) {
+            x[j] = *reinterpret_cast<const f32x4_t*>(qp + 16 * (j >> 1) + 4 * (j & 1)) * c2;
+            most = max_abs4(most, x[j]);
+        }
+        most = fmaxf(most, __shfl_xor(most, 32, FC_WAVE));
+        const float sc = split_scale(most, qs);
+#pragma unroll
+        for (int st = 0; st < KS; ++st)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                split_pair(qf[st], e, x[2 * st + (e >> 1)][2 * (e & 1)], x[2 * st + (e >> 1)][2 * (e & 1) + 1], sc);
+    }
+    __syncthreads();
+
+    const float* kbase = (const float*)a.k_cache + (int64_t)hk * a.head_stride;
+    const float* vbase = (const float*)a.v_cache + (int64_t)hk * a.head_stride;
+    const uint32_t ts = (uint32_t)a.tok_stride;
+    const int nt_all = __builtin_amdgcn_readfirstlane(sg.tile0[sg.n]);
+    const int t_lo = (int)((int64_t)nt_all * wi.s / wi.S), nt = (int)((int64_t)nt_all * (wi.s + 1) / wi.S) - t_lo;
+
+    f32x16_t o[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) o[b][i] = 0.f;
+    float m = kNegBig, l = 0.f;
+    float v_most = 0.f, v_sc = 1.f, v_inv = 1.f;      // V's scale of the next tile to be split
+
+    // tile t of the range -> registers, eight entries of a row per thread; rows past the end: the last one again
+    f32x4_t kr[2 * NP], vr[2 * NP];
+    int seg = 0, nv_load = 32;                        // valid keys of the tile loaded last
+    const int ld_row = tid / LPR, ld_col = 8 * (tid % LPR);
+    const uint32_t ld_off = ((uint32_t)ld_row * ts + (uint32_t)ld_col) * 4u;
+    auto load = [&](int t) {
+        const int tt = t_lo + (t < nt ? t : nt - 1);
+        while (tt >= __builtin_amdgcn_readfirstlane(sg.tile0[seg + 1])) ++seg;
+        const int off = (tt - __builtin_amdgcn_readfirstlane(sg.tile0[seg])) * 32;
+        const int left = __builtin_amdgcn_readfirstlane(sg.len[seg]) - off;
+        const int64_t pos = (int64_t)(__builtin_amdgcn_readfirstlane(sg.start[seg]) + off) * a.tok_stride;
+        nv_load = left < 32 ? left : 32;
+        const char* kt = reinterpret_cast<const char*>(kbase + pos);
+        const char* vt = reinterpret_cast<const char*>(vbase + pos);
+        const uint32_t last = ((uint32_t)(nv_load - 1) * ts + (uint32_t)ld_col) * 4u;
+#pragma unroll
+        for (int j = 0; j < NP; ++j) {
+            uint32_t at = ld_off + (uint32_t)(j * RPP) * ts * 4u;
+            at = at < last ? at : last;
+            kr[2 * j] = *reinterpret_cast<const f32x4_t*>(kt + at);
+            kr[2 * j + 1] = *reinterpret_cast<const f32x4_t*>(kt + at + 16);
+            vr[2 * j] = *reinterpret_cast<const f32x4_t*>(vt + at);
+            vr[2 * j + 1] = *reinterpret_cast<const f32x4_t*>(vt + at + 16);
+        }
+    };
+    // what of the loaded V tile the scale does not fit: its largest entry per wavefront, or 0
+    auto report_v = [&](int buf) {
+        float vm = 0.f;
+#pragma unroll
+        for (int j = 0; j < 2 * NP; ++j) vm = max_abs4(vm, vr[j]);
+        float over = 0.f;
+        if (__any(vm > v_most)) over = wave_max_all(vm);
+        if (lane == 0) v_over[buf][wave] = over;
+    };
+    // the scale for the tile reported in `buf`; returns what O is to be multiplied with before that tile is added
+    auto follow_v = [&](int buf) {
+        const f32x4_t x = *reinterpret_cast<const f32x4_t*>(v_over[buf]);
+        const float over = fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3]));
+        if (!(over > v_most)) return 1.0f;
+        float inv;
+        const float sc = split_scale(4.0f * over, inv);   // room for entries four times as large
+        const float down = sc * v_inv;
+        v_sc = sc; v_inv = inv; v_most = 32768.0f * inv;
+        return down;
+    };
+    const int st_k = ld_row * KROW + ld_col, st_v = ld_row * VROW + ld_col;
+    // The loaded tile into buffer `buf`, in pieces: piece i < 4 NP is a pair of K (i even) or V entries, the last of a
+    // row's part stores it.
+    Split8 ksp, vsp;
+    float k_sc = 1.f;
+    auto stage = [&](int buf, int j, int e) __attribute__((always_inline)) {
+        if (e == 0) {
+            const float most = max_lanes<LPR>(max_abs4(max_abs4(0.f, kr[2 * j]), kr[2 * j + 1]));
+            float inv;
+            k_sc = split_scale(most, inv);
+            if (tid % LPR == 0) k_scale[buf][j * RPP + ld_row] = inv;
+        }
+        split_pair(ksp, e, kr[2 * j + (e >> 1)][2 * (e & 1)], kr[2 * j + (e >> 1)][2 * (e & 1) + 1], k_sc);
+        split_pair(vsp, e, vr[2 * j + (e >> 1)][2 * (e & 1)], vr[2 * j + (e >> 1)][2 * (e & 1) + 1], v_sc);
+        if (e == 3) {
+            *reinterpret_cast<u32x4_native*>(&K_s[buf][0][st_k + j * RPP * KROW]) = ksp.h;
+            *reinterpret_cast<u32x4_native*>(&K_s[buf][1][st_k + j * RPP * KROW]) = ksp.l;
+            *reinterpret_cast<u32x4_native*>(&V_s[buf][0][st_v + j * RPP * VROW]) = vsp.h;
+            *reinterpret_cast<u32x4_native*>(&V_s[buf][1][st_v + j * RPP * VROW]) = vsp.l;
+        }
+    };
+    const int k_frag = l32 * KROW + 8 * hh;
+    const int v_frag = (hh * 4 + (l16 >> 2)) * VROW + ((lane >> 4) & 1) * 16 + (l16 & 3) * 4;
+    auto read_k = [&](int buf, int st) __attribute__((always_inline)) {
+        return Split8{*reinterpret_cast<const u32x4_native*>(&K_s[buf][0][k_frag + 16 * st]),
+                      *reinterpret_cast<const u32x4_native*>(&K_s[buf][1][k_frag + 16 * st])};
+    };
+    auto read_v1 = [&](const bf16_t* vp) __attribute__((always_inline)) {
+        const s16x4_t lo = lds_read_tr(vp), hi = lds_read_tr(vp + 8 * VROW);
+        return __builtin_bit_cast(u32x4_native, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    };
+    auto read_v = [&](int buf, int g) __attribute__((always_inline)) {    // g: 16-key step g / NB, value block g % NB
+        const int at = v_frag + (g / NB) * 16 * VROW + (g % NB) * 32;
+        return Split8{read_v1(&V_s[buf][0][at]), read_v1(&V_s[buf][1][at])};
+    };
+
+    if (nt > 0) {
+        load(0);
+        int nv = nv_load;
+        report_v(0);
+        __syncthreads();
+        follow_v(0);                                  // (O is zero)
+#pragma unroll
+        for (int j = 0; j < NP; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) stage(0, j, e);
+        load(1);
+        report_v(1);
+        __syncthreads();
+        for (int t = 0; t < nt; ++t) {
+            const int buf = t & 1;
+            const float down = follow_v(buf ^ 1);
+            const int nv_next = nv_load;
+            f32x16_t s, s1;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) s[i] = s1[i] = 0.f;
+            Split8 f0 = read_k(buf, 0), f1 = read_k(buf, 1), f2;
+#pragma unroll
+            for (int st = 0; st < KS; ++st) {
+                if (st + 2 < KS) f2 = read_k(buf, st + 2);
+                f32x16_t &c0 = st & 1 ? s : s1, &c1 = st & 1 ? s1 : s;   // no product waits for the one before it
+                split_mfma(f0.l, qf[st].h, c0);
+                __builtin_amdgcn_sched_barrier(0);
+                split_mfma(f0.h, qf[st].h, c1);
+                // tile t + 1: NP * 4 pieces over the steps
+                if (st < 4 * NP) stage(buf ^ 1, st / 4, st % 4);
+                __builtin_amdgcn_sched_barrier(0);
+                split_mfma(f0.h, qf[st].l, c0);
+                __builtin_amdgcn_sched_barrier(0);
+                f0 = f1;
+                f1 = f2;
+            }
+            load(t + 2);
+            __builtin_amdgcn_sched_barrier(0);
+            s += s1;
+#pragma unroll
+            for (int i = 0; i < 16; i += 4) {
+                const f32x4_t ks = *reinterpret_cast<const f32x4_t*>(&k_scale[buf][2 * i + 4 * hh]);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) s[i + e] *= ks[e] * qs;
+            }
+            if (nv < 32) {
+#pragma unroll
+                for (int i = 0; i < 16; ++i)
+                    if ((i >> 2) * 8 + hh * 4 + (i & 3) >= nv) s[i] = kNegBig;
+            }
+            nv = nv_next;
+            float mx = s[0];
+#pragma unroll
+            for (int i = 1; i < 16; ++i) mx = fmaxf(mx, s[i]);
+            if (__any(mx > m + kTop)) {
+                const float mn = fmaxf(m, fmaxf(mx, __shfl_xor(mx, 32, FC_WAVE)) - kStart);
+                const float alpha = __builtin_amdgcn_exp2f(m - mn);
+                m = mn;
+                l *= alpha;
+#pragma unroll
+                for (int b = 0; b < NB; ++b) o[b] *= alpha;
+            }
+            Split8 va = read_v(buf, 0), vb = read_v(buf, 1), na, nb;
+            float p0 = 0.f, p1 = 0.f;
+            Split8 ps[2];
+#pragma unroll
+            for (int i = 0; i < 16; i += 2) {
+                const float x0 = __builtin_amdgcn_exp2f(s[i] - m), x1 = __builtin_amdgcn_exp2f(s[i + 1] - m);
+                p0 += x0;
+                p1 += x1;
+                split_pair(ps[i >> 3], (i & 7) >> 1, x0, x1, 1.0f);
+            }
+            l += p0 + p1;
+            // two blocks of O at a time
+#pragma unroll
+            for (int g = 0; g < 2 * NB; g += 2) {
+                f32x16_t &oa = o[g % NB], &ob = o[g % NB + 1];
+                const Split8& pc = ps[g / NB];
+                if (g + 2 < 2 * NB) { na = read_v(buf, g + 2); nb = read_v(buf, g + 3); }
+                split_mfma(va.l, pc.h, oa);
+                split_mfma(vb.l, pc.h, ob);
+                split_mfma(va.h, pc.l, oa);
+                split_mfma(vb.h, pc.l, ob);
+                split_mfma(va.h, pc.h, oa);
+                split_mfma(vb.h, pc.h, ob);
+                va = na;
+                vb = nb;
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (down != 1.0f) {
+#pragma unroll
+                for (int b = 0; b < NB; ++b) o[b] *= down;
+            }
+            report_v(buf);
+            __syncthreads();
+        }
+    }
+
+    const float ltot = l + __shfl_xor(l, 32, FC_WAVE);
+    if (wi.S > 1) {
+        const int64_t part = (wi.unit * (kSharedRows / kUnitRows) + wave) * wi.S + wi.s;   // 32 rows each
+        float* po = parts + (part * kUnitRows + l32) * D;
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+                store_out(po + b * 32 + g * 8 + hh * 4, o[b][4 * g] * v_inv, o[b][4 * g + 1] * v_inv, o[b][4 * g + 2] * v_inv,
+                          o[b][4 * g + 3] * v_inv);
+        if (hh == 0) {
+            float* ml = parts + (int64_t)p.parts * kUnitRows * D + part * 2 * kUnitRows;
+            ml[l32] = m;
+            ml[kUnitRows + l32] = ltot;
+        }
+        return;
+    }
+    if (row_in_chunk >= a.L_c) return;
+    const float inv = 1.0f / ltot;
+    const int64_t row = (int64_t)wi.r * a.L_c + row_in_chunk;
+    float* op = (float*)a.out + (row * a.H_q + wi.h) * D;
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+            store_out(op + b * 32 + g * 8 + hh * 4, o[b][4 * g] * v_inv * inv, o[b][4 * g + 1] * v_inv * inv,
+                      o[b][4 * g + 2] * v_inv * inv, o[b][4 * g + 3] * v_inv * inv);
+    if (a.lse && hh == 0)
+        a.lse[(int64_t)wi.h * a.A * a.L_c + row] = (m + __builtin_amdgcn_logf(ltot)) * 0.6931471805599453f;
+}
+
 template <int D>
 int launch_f32(const FcAttendArgs& a, hipStream_t s) {
     FcAttendPlan p = fc_attend_plan_f32(a.A, a.L_c, a.L_clean, a.H_q, true);
     if (!fc_room_for_partials(a.ws, a.ws_bytes, p.parts, D))
         p = fc_attend_plan_f32(a.A, a.L_c, a.L_clean, a.H_q, false);
-    attend_f32_kernel<D><<<p.grid, kSplitThreads, 0, s>>>(a, p, (float*)a.ws);
+    if (p.narrow[0])                                   // one form for every recompute count
+        attend_f32_kernel<D><<<p.grid, kSplitThreads, 0, s>>>(a, p, (float*)a.ws);
+    else
+        attend_f32_shared_kernel<D><<<p.grid, kSharedThreads, 0, s>>>(a, p, (float*)a.ws);
     FC_LAUNCH_CHECK();
     if (p.merge_grid > 0) {
-        attend_merge_kernel<float, D><<<p.merge_grid, 256, 0, s>>>(a, p, (const float*)a.ws);
+        attend_merge_kernel<float, D, kSharedRows, false><<<p.merge_grid, 256, 0, s>>>(a, p, (const float*)a.ws);
         FC_LAUNCH_CHECK();
     }
     return FC_OK;
