@@ -368,6 +368,10 @@ __device__ __forceinline__ uint64_t score_key(double score) {
     return (b >> 63) ? ~b : (b | 0x8000000000000000ull);
 }
 
+__device__ __forceinline__ double key_score(uint64_t key) {   // the score of a key
+    return __longlong_as_double((long long)((key >> 63) ? key & 0x7fffffffffffffffull : ~key));
+}
+
 // Eq. (11) and (12) of one token: e = exp(r), the pooled importance, z = sum of e over the head
 __device__ __forceinline__ uint64_t token_key(double e, double pooled, double z, double lambda) {
     const double red = e / z;
@@ -856,7 +860,7 @@ __global__ __launch_bounds__(kThreads) void write_kept_kernel(const uint64_t* __
 
 // ---- a head of at most kSmallL keys: scores, select and kept positions by one block.  Such a call is
 // bound by its launches, each a chain of dependent round trips (4 heads of 1312 keys: the three
-// kernels above 25 us of the call's 44, this one 14).  Same operations per token, same order of the
+// kernels above 25 us of the call's 44, this one 11).  Same operations per token, same order of the
 // sum of e, so the same keys.
 template <typename MT>
 __global__ __launch_bounds__(kSelThreads) void select_small_kernel(
@@ -938,10 +942,42 @@ __global__ __launch_bounds__(kSelThreads) void select_small_kernel(
         kmin = red[0][w] < kmin ? red[0][w] : kmin;
         kmax = red[1][w] > kmax ? red[1][w] : kmax;
     }
-    // digits of the distance from the smallest key, until few candidates are left
+    // The first cut in bins of equal width in the score: with scores of both signs the keys' leading digits are their
+    // exponents, and most of a head shares two or three of those.  The bin number never falls as the score
+    // rises, so the bin that holds the wanted key is a range of keys.  Scoring and selection of 4 heads of 1312 keys
+    // 24.5 -> 21.7 us, 12 of 4096 29.3 -> 23.8, 24 of 3000 33.2 -> 28.3: one histogram instead of two or three.
     uint32_t need = (uint32_t)budget, count = (uint32_t)L;
     uint64_t prefix = 0ull;
     int rem = kmax > kmin ? 64 - __clzll((long long)(kmax - kmin)) : 0;
+    const double smin = key_score(kmin), width = key_score(kmax) - smin;
+    if (count > (uint32_t)kRank && width > 0.0 && width < 1.0e300) {
+        const double per = (double)kBins / width;
+        uint32_t bin[PER];
+        for (int i = tid; i < kBins; i += kSelThreads) hist[i] = 0u;
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const bool in = i * kSelThreads + tid < L;
+            const double at = (key_score(kv[i]) - smin) * per;
+            bin[i] = in ? (uint32_t)(at < (double)(kBins - 1) ? at : (double)(kBins - 1)) : ~0u;
+            if (in) atomicAdd(&hist[bin[i]], 1u);
+        }
+        __syncthreads();
+        pick_bin_parallel(hist, kBins, need, wtot[0], 0ull, 0, &sh_prefix, &sh_need, &sh_count);
+        __syncthreads();
+        if (sh_count <= (uint32_t)kRank) {
+            const uint32_t want = (uint32_t)sh_prefix, left = sh_need;
+#pragma unroll
+            for (int i = 0; i < PER; ++i) list_append(few, &sh_n, bin[i] == want, kv[i] - kmin);
+            __syncthreads();
+            rank_select(few, sh_n, left, &sh_prefix, &sh_need);
+            __syncthreads();
+            prefix = sh_prefix;
+            need = sh_need;
+            rem = 0;
+        }
+    }
+    // digits of the distance from the smallest key, until few candidates are left
     while (rem > 0) {
         const uint64_t himask = (rem >= 64) ? 0ull : (~0ull << rem);
         if (count <= (uint32_t)kRank) {

@@ -107,3 +107,30 @@ def test_compaction_draws_every_tile_once(H, d, L, budget):
         B.flowcache_kv_compact(k, v, L, budget, kept, check_status=True)
         for x, x0 in ((k, k0), (v, v0)):
             assert torch.equal(x[:, :budget], x0.gather(1, rows)) and torch.equal(x[:, budget:], x0[:, budget:])
+
+
+@pytest.mark.parametrize("kind,L,budget", [
+    ("256", 1500, 100), ("257", 1500, 100), ("256", 4096, 256), ("257", 4096, 258), ("256", 300, 257), ("outlier", 2000, 700),
+    ("outlier", 2000, 1), ("signed", 1312, 984), ("signed", 4096, 2000), ("signed", 257, 128), ("tiny", 1000, 400),
+])
+def test_first_cut_of_short_heads(kind, L, budget):
+    """Heads of at most 4096 keys are cut into 2048 bins of equal width in the score first; what the wanted bin
+    holds is compared with each other up to 256 keys, and otherwise the digits of the keys decide: a bin of exactly
+    256 and 257 nearly equal scores, one outlier that leaves all others in one bin, scores of both signs, and
+    subnormal scores."""
+    rng = np.random.default_rng(L + budget)
+    m = rng.random((2, L)).astype(np.float32)
+    if kind in ("256", "257"):                # bins of 0.49: the n scores at 1.5 have one to themselves
+        n = min(int(kind), L - 2)
+        m[:, :n] = np.float32(1.5) + rng.permutation(n).astype(np.float32) * np.float32(2.0 ** -22)
+        m[:, n] = 1000.0
+        m = np.take_along_axis(m, rng.permuted(np.tile(np.arange(L), (2, 1)), axis=1), 1)
+    elif kind == "outlier":
+        m[:, 77] = 1e30
+    elif kind == "signed":
+        m = rng.standard_normal((2, L)).astype(np.float32)
+    else:
+        m *= np.float32(1e-41)
+    k = synth.to_storage(rng.standard_normal((2, L, 64)).astype(np.float32), "bf16")
+    kept = B.flowcache_kv_select(dev(k, "bf16"), L, budget, torch.from_numpy(m).to(DEV), 1, 1.0)
+    assert np.array_equal(kept.cpu().numpy(), np.stack([O.select_top_b(x.astype(np.float64), budget) for x in m]))
