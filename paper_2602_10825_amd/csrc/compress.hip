@@ -42,6 +42,8 @@ constexpr int kDigitBits = 11;
 constexpr int kBins = 1 << kDigitBits;
 constexpr int kCand = 4096;   // candidates resolved in LDS
 constexpr int kRank = 256;    // candidates resolved by comparing each with each
+constexpr int kScoreThreads = 512, kScoreItems = 4;                 // of score_keys
+constexpr int kScoreBlk = kScoreThreads * kScoreItems;
 constexpr int kHalo = 192;    // importance beside a block's tokens that score_keys can keep in LDS
 constexpr int kSmallL = kSelThreads * 4;   // heads up to this length are selected by one block
 constexpr int kUnroll = 8;    // independent loads in flight per thread in the selection scans
@@ -390,19 +392,24 @@ __device__ __forceinline__ int first_digit_shift(const uint64_t* edge, int n) {
 // Where the first digit's bins lie decides how many keys the select has to look at again: every block
 // takes the same 128 keys of the head and lays the bins between those some ranks above and below the
 // wanted one (select_bins.hpp).  A wanted key outside (5 deviations) costs time only.
+// Every block compares the sampled keys with each other, 16384 comparisons, which more threads share and larger blocks
+// make rarer (scoring and selection, us; threads x tokens each 256 x 8 / 512 x 4 / 1024 x 4 / 1024 x 8: 24 heads of 74880 keys
+// 220.7 / 217.4 / 216.6 / 213.8, 12 of 51000 91.5 / 89.5 / 88.6 / 91.7, 8 of 20000 46.8 / 44.2 / 45.1 / 48.6, 4 of 5000 36.0 /
+// 33.3 / 34.8 / 36.2).
 template <typename MT>   // importance as given (float) or pooled over a key group (double)
-__global__ __launch_bounds__(kThreads) void score_keys_kernel(
+__global__ __launch_bounds__(kScoreThreads) void score_keys_kernel(
     const double* __restrict__ e_all, const MT* __restrict__ mass_all,
     const double* __restrict__ pz_all, int nblkz, int L, int budget, int pool_k,
     double lambda, uint64_t* __restrict__ keys_all, uint64_t* __restrict__ edge_all,
     uint32_t* __restrict__ hist_all, uint32_t* __restrict__ sync, int ntile, uint32_t* __restrict__ selsync,
-    uint64_t* __restrict__ agg_all) {
+    uint64_t* __restrict__ agg_all, int n_agg) {
+    constexpr int TPS = kScoreThreads / kSample;   // threads per sampled token
     const int h = blockIdx.y, tid = threadIdx.x;
     const double* e = e_all + (int64_t)h * L;
     const MT* mass = mass_all + (int64_t)h * L;
     uint64_t* keys = keys_all + (int64_t)h * L;
     __shared__ double shd[kThreads + 1];
-    __shared__ MT ms[kTokBlk + 2 * kHalo];
+    __shared__ MT ms[kScoreBlk + 2 * kHalo];
     __shared__ uint64_t sample[kSample];
     __shared__ uint64_t edge[kEdges];
     __shared__ uint32_t hist[kFirstBins];
@@ -410,18 +417,18 @@ __global__ __launch_bounds__(kThreads) void score_keys_kernel(
     const FcBracket br = fc_bracket(budget, L);
     const int n_int = br.bottom - br.top;
     // The sample: one token of each 128th of the head (L >= kSample), not always the same one of it.
-    // Threads 2q and 2q + 1 take token q, every other distance of its importance window each; everything
+    // TPS neighbouring threads take token q, every TPS-th distance of its importance window each; everything
     // is requested before the sums that z needs.
-    const int sq = tid >> 1, slen = L / kSample;
+    const int sq = tid / TPS, slen = L / kSample;
     const int sj = (int)((int64_t)sq * L / kSample) + (int)(((uint32_t)sq * 2654435761u >> 12) % (uint32_t)slen);
     const double se = e[sj];
     MT simp = mass[sj];
-    auto window = [&](auto n, int d0) {           // every other distance from d0 on, n of them in flight together
+    auto window = [&](auto n, int d0) {           // every TPS-th distance from d0 on, n of them in flight together
         constexpr int N = decltype(n)::value;
         MT lo[N], hi[N];
 #pragma unroll
         for (int i = 0; i < N; ++i) {
-            const int d = d0 + 2 * i < half ? d0 + 2 * i : half;
+            const int d = d0 + TPS * i < half ? d0 + TPS * i : half;
             lo[i] = mass[sj - d >= 0 ? sj - d : 0];
             hi[i] = mass[sj + d < L ? sj + d : L - 1];
         }
@@ -431,62 +438,65 @@ __global__ __launch_bounds__(kThreads) void score_keys_kernel(
             simp = simp > nb ? simp : nb;
         }
     };
-    int d0 = 1 + (tid & 1);
-    for (; d0 + 23 < half; d0 += 32) window(std::integral_constant<int, 16>(), d0);
-    for (; d0 <= half; d0 += 4) window(std::integral_constant<int, 2>(), d0);
-    {
-        const MT nb = __shfl_xor(simp, 1, FC_WAVE);
+    int d0 = 1 + tid % TPS;
+    for (; d0 + 12 * TPS <= half; d0 += 16 * TPS) window(std::integral_constant<int, 16>(), d0);
+    for (; d0 <= half; d0 += 2 * TPS) window(std::integral_constant<int, 2>(), d0);
+#pragma unroll
+    for (int o = 1; o < TPS; o <<= 1) {
+        const MT nb = __shfl_xor(simp, o, FC_WAVE);
         simp = simp > nb ? simp : nb;
     }
     if (blockIdx.x == 0) {   // state later kernels of this call start from: tile flags, tickets
         uint32_t* flags = sync_flags(sync, gridDim.y, ntile, h);
-        for (int i = tid; i < ntile; i += kThreads) flags[i] = 0u;
+        for (int i = tid; i < ntile; i += kScoreThreads) flags[i] = 0u;
         if (tid == 0) sync[64 * (h + 1)] = 0u;
         if (h == 0 && tid == 0) sync[0] = 0u;
         if (tid < 3) selsync[h * 64 + tid] = 0u;
-        for (int i = tid; i < (int)gridDim.x; i += kThreads) agg_all[(int64_t)h * gridDim.x + i] = 0ull;
+        for (int i = tid; i < n_agg; i += kScoreThreads) agg_all[(int64_t)h * n_agg + i] = 0ull;
     }
-    for (int i = tid; i < kFirstBins; i += kThreads) hist[i] = 0u;
+    for (int i = tid; i < kFirstBins; i += kScoreThreads) hist[i] = 0u;
     if (tid < kEdges) edge[tid] = ~0ull;
-    const int j0 = blockIdx.x * kTokBlk;
-    double ev[kItems];
-    MT imp[kItems];
+    const int j0 = blockIdx.x * kScoreBlk;
+    double ev[kScoreItems];
+    MT imp[kScoreItems];
 #pragma unroll
-    for (int i = 0; i < kItems; ++i) {
-        const int j = j0 + i * kThreads + tid;
+    for (int i = 0; i < kScoreItems; ++i) {
+        const int j = j0 + i * kScoreThreads + tid;
         ev[i] = (j < L) ? e[j] : 0.0;
         imp[i] = (j < L) ? mass[j] : (MT)0;
     }
     const bool staged = half <= kHalo;            // the window comes from LDS
     if (staged) {
         auto beside = [&](int i) {                // i < 2 half: the tokens to the left, then those to the right
-            const int j = i < half ? j0 - 1 - i : j0 + kTokBlk + i - half;
+            const int j = i < half ? j0 - 1 - i : j0 + kScoreBlk + i - half;
             return mass[j < 0 ? 0 : (j < L ? j : L - 1)];
         };
-        auto slot = [&](int i) { return i < half ? kHalo - 1 - i : kHalo + kTokBlk + i - half; };
+        auto slot = [&](int i) { return i < half ? kHalo - 1 - i : kHalo + kScoreBlk + i - half; };
         const MT first = tid < 2 * half ? beside(tid) : (MT)0;
 #pragma unroll
-        for (int i = 0; i < kItems; ++i) ms[kHalo + i * kThreads + tid] = imp[i];
+        for (int i = 0; i < kScoreItems; ++i) ms[kHalo + i * kScoreThreads + tid] = imp[i];
         if (tid < 2 * half) ms[slot(tid)] = first;
-        for (int i = tid + kThreads; i < 2 * half; i += kThreads) ms[slot(i)] = beside(i);
+        for (int i = tid + kScoreThreads; i < 2 * half; i += kScoreThreads) ms[slot(i)] = beside(i);
     }
     // Z = sum_j e_j: the block partials of the pass that wrote e, in a fixed order
     double z = 0.0;
-    for (int i = tid; i < nblkz; i += kThreads) z += pz_all[(int64_t)h * nblkz + i];
+    if (tid < kThreads)
+        for (int i = tid; i < nblkz; i += kThreads) z += pz_all[(int64_t)h * nblkz + i];
     z = block_sum_fixed(z, shd);   // its barriers publish ms too
     const uint64_t sk = token_key(se, (double)simp, z, lambda);
-    if (!(tid & 1)) sample[sq] = sk;
+    if (tid % TPS == 0) sample[sq] = sk;
     __syncthreads();
-    {   // rank of each sampled key from the top (ties by index); the two threads count half each
+    {   // rank of each sampled key from the top (ties by index); its threads count a part each
         uint32_t above = 0;
-        const int c0 = (tid & 1) * (kSample / 2);
+        const int c0 = tid % TPS * (kSample / TPS);
 #pragma unroll 8
-        for (int i = c0; i < c0 + kSample / 2; ++i) {
+        for (int i = c0; i < c0 + kSample / TPS; ++i) {
             const uint64_t o = sample[i];
             above += (o > sk || (o == sk && i < sq)) ? 1u : 0u;
         }
-        above += __shfl_xor(above, 1, FC_WAVE);
-        if (!(tid & 1) && (int)above >= br.top && (int)above <= br.bottom) edge[br.bottom - (int)above] = sk;
+#pragma unroll
+        for (int o = 1; o < TPS; o <<= 1) above += __shfl_xor(above, o, FC_WAVE);
+        if (tid % TPS == 0 && (int)above >= br.top && (int)above <= br.bottom) edge[br.bottom - (int)above] = sk;
     }
     __syncthreads();
     if (blockIdx.x == 0 && tid < kEdges) edge_all[(int64_t)h * kEdges + tid] = edge[tid];
@@ -495,8 +505,8 @@ __global__ __launch_bounds__(kThreads) void score_keys_kernel(
     auto pool = [&](auto at) {   // Eq. (10): window max, -inf outside [0, L)
         for (int d = 1; d <= half; ++d) {
 #pragma unroll
-            for (int i = 0; i < kItems; ++i) {
-                const int j = j0 + i * kThreads + tid;
+            for (int i = 0; i < kScoreItems; ++i) {
+                const int j = j0 + i * kScoreThreads + tid;
                 if (j < L) {
                     const MT lo = (j - d >= 0) ? at(j - d) : imp[i];
                     const MT hi = (j + d < L) ? at(j + d) : imp[i];
@@ -508,10 +518,10 @@ __global__ __launch_bounds__(kThreads) void score_keys_kernel(
     };
     if (staged) pool([&](int j) { return ms[j - j0 + kHalo]; });
     else pool([&](int j) { return mass[j]; });
-    uint64_t kv[kItems];
+    uint64_t kv[kScoreItems];
 #pragma unroll
-    for (int i = 0; i < kItems; ++i) {
-        const int j = j0 + i * kThreads + tid;
+    for (int i = 0; i < kScoreItems; ++i) {
+        const int j = j0 + i * kScoreThreads + tid;
         kv[i] = 0ull;
         if (j < L) {
             kv[i] = token_key(ev[i], (double)imp[i], z, lambda);
@@ -521,8 +531,8 @@ __global__ __launch_bounds__(kThreads) void score_keys_kernel(
     // the two outer bins hold most of the keys: counted by the wavefront; the others are spread
     uint32_t below = 0, above = 0;
 #pragma unroll
-    for (int i = 0; i < kItems; ++i) {
-        const bool in = j0 + i * kThreads + tid < L;
+    for (int i = 0; i < kScoreItems; ++i) {
+        const bool in = j0 + i * kScoreThreads + tid < L;
         const uint32_t dgt = fc_first_digit(kv[i], edge, n_int, even_sh);
         below += __popcll(__ballot(in && dgt == 0u));
         above += __popcll(__ballot(in && dgt == (uint32_t)(kFirstBins - 1)));
@@ -533,7 +543,7 @@ __global__ __launch_bounds__(kThreads) void score_keys_kernel(
         atomicAdd(&hist[kFirstBins - 1], above);
     }
     __syncthreads();
-    for (int i = tid; i < kFirstBins; i += kThreads)
+    for (int i = tid; i < kFirstBins; i += kScoreThreads)
         if (hist[i]) atomicAdd(&hist_all[(int64_t)h * kFirstBins + i], hist[i]);
 }
 
@@ -1311,9 +1321,9 @@ int launch_typed(const FcCompressArgs& a, const MT* mass, hipStream_t s, bool co
                                                               a.kept, sync, w.ntile, TR);
         FC_LAUNCH_CHECK();
     } else {
-        score_keys_kernel<MT><<<dim3(w.nb2, a.H_k), kThreads, 0, s>>>(e, mass, pz, w.nblk, a.L_k, a.budget, a.pool_k,
+        score_keys_kernel<MT><<<dim3((a.L_k + kScoreBlk - 1) / kScoreBlk, a.H_k), kScoreThreads, 0, s>>>(e, mass, pz, w.nblk, a.L_k, a.budget, a.pool_k,
                                                                   a.lambda, keys, edge, hist, sync, w.ntile,
-                                                                  selsync, agg);
+                                                                  selsync, agg, w.nb2);
         FC_LAUNCH_CHECK();
         // blocks per head that scan for the candidates: one batch of loads each, up to 131072 keys
         constexpr int kBatch = kSelThreads * kUnroll;
