@@ -1,8 +1,9 @@
 // Measured-achievable peaks on this GPU, to set beside the datasheet figures:
 //   - bf16 matrix-core rate of a register-resident v_mfma_f32_32x32x16_bf16 loop, with
-//     constant and with random operands (clocks are power-limited, so the data matter),
+//     constant and with random operands (the clock depends on the operand bits that toggle),
 //   - HBM rate of a plain device copy and of a plain read.
 //   - matrix-core rate against wavefronts per SIMD and independent accumulator chains,
+//     and beside the LDS reads and the vector work of the attention kernel,
 //   - LDS read rate per compute unit for the attention kernel's two fragment patterns.
 // Stand-alone program (built next to the library); prints one line per measurement.
 #include <hip/hip_runtime.h>
@@ -24,6 +25,10 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
         }                                                                         \
     } while (0)
 
+// Every loop below has 32 products or more: with four, 44 bytes of code, the rate is 1.28 or 1.78 PFLOP/s (constant
+// operands 1.63 or 2.48) by where the loop lies modulo 32, as both wavefronts of a SIMD wait for the jump at once.
+constexpr int kBody = 32;
+
 template <bool RANDOM>
 __global__ __launch_bounds__(256) void mfma_loop(const bf16x8* in, float* out, long long* ticks, int iters) {
     const long long c0 = clock64(), w0 = wall_clock64();   // shader-clock and fixed-rate counters
@@ -41,7 +46,10 @@ __global__ __launch_bounds__(256) void mfma_loop(const bf16x8* in, float* out, l
         for (int i = 0; i < 16; ++i) c[j][i] = 0.f;
     for (int it = 0; it < iters; ++it) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) c[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[j], b[j], c[j], 0, 0, 0);
+        for (int j = 0; j < kBody; ++j) {
+            c[j % 4] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[j % 4], b[j % 4], c[j % 4], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        }
     }
     out[blockIdx.x * 256 + threadIdx.x] = c[0][0] + c[1][1] + c[2][2] + c[3][3];
     if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -60,7 +68,7 @@ __global__ __launch_bounds__(256) void mfma_chains(float* out, int iters) {
         for (int i = 0; i < 16; ++i) c[j][i] = 0.f;
     for (int it = 0; it < iters; ++it) {
 #pragma unroll
-        for (int j = 0; j < NCH; ++j) c[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c[j], 0, 0, 0);
+        for (int j = 0; j < kBody; ++j) c[j % NCH] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c[j % NCH], 0, 0, 0);
     }
     float s = 0.f;
     for (int j = 0; j < NCH; ++j) s += c[j][0];
@@ -108,9 +116,75 @@ __global__ __launch_bounds__(512) void lds_reads(int* out, int iters, long long*
     if (blockIdx.x == 0 && threadIdx.x == 0) ticks[0] = t1 - t0;
 }
 
+// 32 products with random operands, one fragment read from LDS for each LDSN of them (0: none), and the attention
+// kernel's vector work beside each (VALU: one exponential and its fma, half a conversion and half a dot product);
+// 8 wavefronts per block.
+template <int LDSN, bool VALU>
+__global__ __launch_bounds__(512) void mfma_beside(const bf16x8* in, float* out, int iters) {
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    __shared__ __attribute__((aligned(16))) bf16x8 buf[64 * 17];     // 64 rows of 272 bytes
+    for (int i = threadIdx.x; i < 64 * 17; i += 512) buf[i] = in[i];
+    __syncthreads();
+    const int lane = threadIdx.x & 63, l32 = lane & 31, hh = lane >> 5;
+    const bf16x8* frag = &buf[l32 * 17 + hh];
+    bf16x8 a[4], b[4];
+    for (int j = 0; j < 4; ++j) { a[j] = in[1100 + lane * 4 + j]; b[j] = in[(threadIdx.x & 255) + 256 * j]; }
+    f32x16 c[4];
+    for (int j = 0; j < 4; ++j)
+        for (int i = 0; i < 16; ++i) c[j][i] = 0.f;
+    float x[8], ps = 0.f;
+    for (int i = 0; i < 8; ++i) x[i] = 0.1f * i - (float)lane * 0.01f;
+    const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
+#pragma unroll 1
+    for (int it = 0; it < iters; ++it) {
+#pragma unroll
+        for (int i = 0; i < kBody; ++i) {
+            constexpr int N = LDSN ? LDSN : 1;
+            c[i % 4] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i / N % 4], b[LDSN == 2 ? i % 2 * 2 + i / 8 % 2 : i / 8], c[i % 4], 0, 0, 0);
+            if (LDSN && i % N == N - 1) {
+                const int f = i / N;
+                bf16x8 v = frag[(f / 8 % 2) * 32 * 17 + (f % 8) * 2];
+                asm volatile("" : "+v"(v));
+                a[f % 4] = v;
+            }
+            if (VALU) {
+                float w = __builtin_amdgcn_exp2f(fmaf(x[i % 8], 1.01f, -1.0f));
+                asm volatile("" : "+v"(w));
+                x[i % 8] = w;
+                if (i & 1) {
+                    bf16x2 p = {(__bf16)x[i % 8], (__bf16)x[(i - 1) % 8]};
+                    asm volatile("" : "+v"(p));
+                    ps = __builtin_amdgcn_fdot2_f32_bf16(p, ones, ps, false);
+                    asm volatile("" : "+v"(ps));
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    float s = ps;
+    for (int j = 0; j < 4; ++j)
+        for (int i = 0; i < 16; ++i) s += c[j][i];
+    out[blockIdx.x * 512 + threadIdx.x] = s;
+}
+template <int LDSN, bool VALU>
+static int run_beside(const bf16x8* din, float* dout, hipEvent_t e0, hipEvent_t e1) {
+    const int iters = 20000;
+    float ms = 0.f;
+    for (int rep = 0; rep < 3; ++rep) {
+        CK(hipEventRecord(e0));
+        mfma_beside<LDSN, VALU><<<256, 512>>>(din, dout, iters);
+        CK(hipEventRecord(e1));
+        CK(hipEventSynchronize(e1));
+        CK(hipEventElapsedTime(&ms, e0, e1));
+    }
+    printf("mfma, random operands, LDS fragments per 4 products: %d, softmax work: %s: %.1f TFLOP/s\n", LDSN ? 4 / LDSN : 0,
+           VALU ? "yes" : "no", 256.0 * 8 * iters * kBody * 32768.0 / ms / 1e9);
+    return 0;
+}
+
 template <int NCH>
 static int run_chains(int blocks, float* dout, hipEvent_t e0, hipEvent_t e1) {
-    const int iters = 40000;
+    const int iters = 5000;
     float ms = 0.f;
     for (int rep = 0; rep < 3; ++rep) {
         CK(hipEventRecord(e0));
@@ -119,7 +193,7 @@ static int run_chains(int blocks, float* dout, hipEvent_t e0, hipEvent_t e1) {
         CK(hipEventSynchronize(e1));
         CK(hipEventElapsedTime(&ms, e0, e1));
     }
-    const double flops = (double)blocks * 4 * iters * NCH * 32768.0;
+    const double flops = (double)blocks * 4 * iters * kBody * 32768.0;
     printf("mfma, constant operands, %d chain(s) per wavefront, %.0f wavefront(s) per SIMD: %.1f TFLOP/s\n", NCH,
            blocks * 4 / 1024.0, flops / ms / 1e9);
     return 0;
@@ -202,7 +276,10 @@ __global__ __launch_bounds__(256) void mfma16_loop(const bf16x8* in, float* out,
         for (int i = 0; i < 4; ++i) c[j][i] = 0.f;
     for (int it = 0; it < iters; ++it) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) c[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[j], b[j], c[j], 0, 0, 0);
+        for (int j = 0; j < 2 * kBody; ++j) {
+            c[j % 4] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[j % 4], b[j % 4], c[j % 4], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        }
     }
     out[blockIdx.x * 256 + threadIdx.x] = c[0][0] + c[1][1] + c[2][2] + c[3][3];
 }
@@ -282,11 +359,11 @@ int main() {
     CK(hipDeviceGetAttribute(&wall_khz, hipDeviceAttributeWallClockRate, 0));
     // launch lengths from under 1 ms to tens of ms: the power limit acts over milliseconds, so
     // short launches run at higher clocks than a sustained kernel does
-    const int lengths[4] = {5000, 25000, 100000, 400000};
+    const int lengths[4] = {625, 3125, 12500, 50000};
     for (int mode = 0; mode < 2; ++mode) {
         for (int li = 0; li < 4; ++li) {
             const int iters = lengths[li];
-            const double flops = 512.0 * 4 * (double)iters * 4 * 32768.0;
+            const double flops = 512.0 * 4 * (double)iters * kBody * 32768.0;
             for (int rep = 0; rep < 3; ++rep) {
                 CK(hipEventRecord(e0));
                 if (mode == 0) mfma_loop<false><<<512, 256>>>(din, dout, dticks, iters);
@@ -308,9 +385,12 @@ int main() {
         run_chains<2>(256, dout, e0, e1) || run_chains<4>(256, dout, e0, e1) ||
         run_chains<4>(512, dout, e0, e1))
         return 1;
+    if (run_beside<0, false>(din, dout, e0, e1) || run_beside<1, false>(din, dout, e0, e1) || run_beside<2, false>(din, dout, e0, e1) ||
+        run_beside<0, true>(din, dout, e0, e1) || run_beside<1, true>(din, dout, e0, e1) || run_beside<2, true>(din, dout, e0, e1))
+        return 1;
     for (int mode = 0; mode < 2; ++mode) {
-        const int iters = 200000;
-        const double flops = 512.0 * 4 * (double)iters * 4 * 16384.0;
+        const int iters = 12500;
+        const double flops = 512.0 * 4 * (double)iters * 2 * kBody * 16384.0;
         for (int rep = 0; rep < 3; ++rep) {
             CK(hipEventRecord(e0));
             if (mode == 0) mfma16_loop<false><<<512, 256>>>(din, dout, iters);
