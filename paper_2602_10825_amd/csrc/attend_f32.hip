@@ -212,7 +212,7 @@ __global__ __launch_bounds__(kSplitThreads) void attend_f32_kernel(FcAttendArgs 
         for (int i = 0; i < 16; i += 4) {
             const f32x4_t ks = *reinterpret_cast<const f32x4_t*>(&k_scale[wave][2 * i + 4 * hh]);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) s[i + e] *= ks[e] * qs;
+            for (int e = 0; e < 4; ++e) s[i + e] = s[i + e] * ks[e] * qs;
         }
         if (nv < 32) {
 #pragma unroll
@@ -247,8 +247,15 @@ __global__ __launch_bounds__(kSplitThreads) void attend_f32_kernel(FcAttendArgs 
 #pragma unroll
             for (int b = 0; b < NB; ++b) vm = fmaxf(vm, fabsf(vf[i][b]));
         if (__any(vm > v_most)) {
+            vm = v_most;                                  // an infinity spoils its own column only
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+#pragma unroll
+                for (int b = 0; b < NB; ++b) vm = max_finite(vm, vf[i][b]);
+        }
+        if (__any(vm > v_most)) {
             float inv;
-            const float sc = split_scale(4.0f * wave_max_all(vm), inv);
+            const float sc = split_scale(wave_max_all(vm), inv, 2);
             const float down = sc * v_inv;                // old scale to new; O is zero while there is no old one
             v_sc = sc; v_inv = inv; v_most = 32768.0f * inv;
 #pragma unroll
@@ -410,7 +417,14 @@ __global__ __launch_bounds__(kSharedThreads, 2) void attend_f32_shared_kernel(Fc
 #pragma unroll
         for (int j = 0; j < 2 * NP; ++j) vm = max_abs4(vm, vr[j]);
         float over = 0.f;
-        if (__any(vm > v_most)) over = wave_max_all(vm);
+        if (__any(vm > v_most)) {                         // an infinity spoils its own column only
+            vm = 0.f;
+#pragma unroll
+            for (int j = 0; j < 2 * NP; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) vm = max_finite(vm, vr[j][e]);
+            over = wave_max_all(vm);
+        }
         if (lane == 0) v_over[buf][wave] = over;
     };
     // the scale for the tile reported in `buf`; returns what O is to be multiplied with before that tile is added
@@ -419,7 +433,7 @@ __global__ __launch_bounds__(kSharedThreads, 2) void attend_f32_shared_kernel(Fc
         const float over = fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3]));
         if (!(over > v_most)) return 1.0f;
         float inv;
-        const float sc = split_scale(4.0f * over, inv);   // room for entries four times as large
+        const float sc = split_scale(over, inv, 2);       // room for entries four times as large
         const float down = sc * v_inv;
         v_sc = sc; v_inv = inv; v_most = 32768.0f * inv;
         return down;
@@ -503,7 +517,7 @@ __global__ __launch_bounds__(kSharedThreads, 2) void attend_f32_shared_kernel(Fc
             for (int i = 0; i < 16; i += 4) {
                 const f32x4_t ks = *reinterpret_cast<const f32x4_t*>(&k_scale[buf][2 * i + 4 * hh]);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) s[i + e] *= ks[e] * qs;
+                for (int e = 0; e < 4; ++e) s[i + e] = s[i + e] * ks[e] * qs;
             }
             if (nv < 32) {
 #pragma unroll
@@ -592,6 +606,8 @@ __global__ __launch_bounds__(kSharedThreads, 2) void attend_f32_shared_kernel(Fc
 template <int D>
 int launch_f32(const FcAttendArgs& a, hipStream_t s) {
     FcAttendPlan p = fc_attend_plan_f32(a.A, a.L_c, a.L_clean, a.H_q, true);
+    if (!fc_room_for_partials(a.ws, a.ws_bytes, p.parts, D))    // (those of 32-row blocks are a third or less)
+        p = fc_attend_plan_f32(a.A, a.L_c, a.L_clean, a.H_q, true, false);
     if (!fc_room_for_partials(a.ws, a.ws_bytes, p.parts, D))
         p = fc_attend_plan_f32(a.A, a.L_c, a.L_clean, a.H_q, false);
     if (p.narrow[0])                                   // one form for every recompute count

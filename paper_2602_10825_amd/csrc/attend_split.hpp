@@ -81,7 +81,7 @@ inline double fc_shared_cost(int64_t units, int key_tiles, int narrow_splits, in
 // Launches with fewer units than this, whatever the recompute count, stay with 32-row blocks (and their workspace small).
 inline bool fc_shared_allowed(int A, int L_c, int H_q) { return (int64_t)A * H_q * ((L_c + kSharedRows - 1) / kSharedRows) >= 96; }
 
-inline FcAttendPlan fc_attend_plan_f32(int A, int L_c, int L_clean, int H_q, bool may_split) {
+inline FcAttendPlan fc_attend_plan_f32(int A, int L_c, int L_clean, int H_q, bool may_split, bool may_share = true) {
     constexpr int kBlockCost = 8;
     FcAttendPlan p{};
     p.tiles = (L_c + kUnitRows - 1) / kUnitRows;
@@ -90,7 +90,7 @@ inline FcAttendPlan fc_attend_plan_f32(int A, int L_c, int L_clean, int H_q, boo
     // The form is the same for every recompute count (two kernels): shared tiles where they are cheaper on average.
     int Sn[FC_MAX_ACTIVE], Sh[FC_MAX_ACTIVE];
     double ratios = 0.0;
-    bool shared = may_split && fc_shared_allowed(A, L_c, H_q);
+    bool shared = may_split && may_share && fc_shared_allowed(A, L_c, H_q);
     for (int R = 1; R <= A; ++R) {
         Sn[R - 1] = Sh[R - 1] = 1;
         const double narrow = fc_narrow_cost((int64_t)R * H_q * p.tiles, key_tiles, kBlockCost, may_split, &Sn[R - 1]);

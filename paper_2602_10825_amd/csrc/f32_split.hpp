@@ -31,15 +31,20 @@ __device__ __forceinline__ void split_pair(Split8& s, int p, float x0, float x1,
     s.l[p] = __builtin_bit_cast(uint32_t, lv);
 }
 
-// The power of two that brings numbers of magnitude `most` to [2^14, 2^15), and its inverse.
-__device__ __forceinline__ float split_scale(float most, float& inverse) {
-    int e = __builtin_amdgcn_frexp_expf(most);   // most = f 2^e, 1/2 <= f < 1; 0 for 0
+// The power of two that brings numbers of magnitude `most` to [2^14, 2^15) / 2^room, and its inverse.
+__device__ __forceinline__ float split_scale(float most, float& inverse, int room = 0) {
+    int e = __builtin_amdgcn_frexp_expf(most) + room;   // most = f 2^e, 1/2 <= f < 1; 0 for 0
     e = e < -100 ? -100 : e;
     inverse = __builtin_amdgcn_ldexpf(1.0f, e - 15);
     return __builtin_amdgcn_ldexpf(1.0f, 15 - e);
 }
 __device__ __forceinline__ float max_abs4(float m, const f32x4_t& x) {
     return fmaxf(fmaxf(fmaxf(m, fabsf(x[0])), fabsf(x[1])), fmaxf(fabsf(x[2]), fabsf(x[3])));
+}
+
+// |x| if that is finite and above m, else m
+__device__ __forceinline__ float max_finite(float m, float x) {
+    return fabsf(x) > m && fabsf(x) < __builtin_inff() ? fabsf(x) : m;
 }
 
 __device__ __forceinline__ void split_mfma(const u32x4_native& a, const u32x4_native& b, f32x16_t& c) {
