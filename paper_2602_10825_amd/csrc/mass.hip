@@ -684,8 +684,9 @@ __global__ __launch_bounds__(kNT, 2) void mass_cols_bf16_kernel(FcMassArgs a, in
 // of 64 rows that all wavefronts of the block read:
 //   stats  64 observation rows stay, a range of keys passes: per lane one row's running sum
 //   cols   64 keys stay, the rows of all the head's groups pass: per lane 32 keys' running sums
-// Bound: the vector ALU, 24 cycles per 64 scores and pass (fma, exp2, add: 1.0 ms for 24 heads,
-// 1872 rows, 74880 keys) against 16 of matrix products.  So each score costs nothing but those
+// Bound: vector ALU and matrix cores alike, 16 cycles each per 64 scores and pass (fma 4, exp2 8, add 4), at the
+// 1.82 GHz that the chip runs under both: 0.93 ms for 24 heads, 1872 rows, 74880 keys.  (Counters: matrix cores busy in 0.52
+// of the cycles, the vector ALU in 0.6, both at once in 0.34.)  So each score costs nothing but those
 // three instructions -- no running maximum: the reference point m of a lane is raised only when a
 // sum of 16 terms exceeds 2^40 -- and the products of a 32-row step are issued between the
 // exponentials of the step before, one set of accumulators filled while the other is read.  Each
@@ -722,7 +723,9 @@ __device__ __forceinline__ void lds_barrier() {
 
 // One step: nxt = products of the 32 rows whose fragments start at `cur`, sums += exponentials of
 // `prev`.  `frag` holds the first kAhead fragments of the step on entry and of the next one (at `after`)
-// on exit.  COLS: the resident operand is K and sums[b][r] one key each; else it is Q and sums[b][0..1]
+// on exit.  At raised priority, so that the other wavefront of the SIMD fills the step's gaps and stores and loads
+// its tiles in them: 24 x 128, 1872 rows on 74880 keys 1596 -> 1588 us, 24 x 64 1137 -> 1091, 130 rows on 84240 keys 211 ->
+// 201.  COLS: the resident operand is K and sums[b][r] one key each; else it is Q and sums[b][0..1]
 // are two halves of the sum of row b.  neg[b]: what the exponents are lowered by.
 constexpr int kAhead = 4;
 template <int D, bool COLS, int NS>
@@ -730,6 +733,7 @@ __device__ __forceinline__ void mass_step(f32x16_t (&nxt)[2], const f32x16_t (&p
                                           bf16x8_t (&frag)[kAhead], const bf16_t* cur, const bf16_t* after, float c2,
                                           const float (&neg)[2], float (&sums)[2][NS]) {
     constexpr int KS = D / 16, E = 32 / (2 * KS);   // exponentials beside each product
+    __builtin_amdgcn_s_setprio(1);
     f32x16_t zero;
 #pragma unroll
     for (int i = 0; i < 16; ++i) zero[i] = 0.f;
@@ -763,6 +767,7 @@ __device__ __forceinline__ void mass_step(f32x16_t (&nxt)[2], const f32x16_t (&p
             __builtin_amdgcn_sched_barrier(0);
         }
     }
+    __builtin_amdgcn_s_setprio(0);
 }
 
 // The sums of step `prev` (32 keys from `key0` on, of which those below `end` count) once more, from a
