@@ -39,12 +39,15 @@ __global__ __launch_bounds__(256) void scatter_kv_kernel(
 //   and the accumulators of S^T already are the B operand of  O^T += V^T P^T.
 //   Q is split once, a scale per row; K a scale per key, read as rows and turned to the operand's layout
 //   in LDS (read straight into that layout, 32 bytes of 32 rows a load: 357 -> 379 us below); V one scale
-//   that follows the largest entry the wavefront has seen; the weights none, their range is the choice
+//   that follows the largest finite entry the wavefront has seen; the weights none, their range is the choice
 //   of the reference.
 // 12 heads x 128, 2 chunks of 1021 rows on 4083 clean keys: 650 us on the fp32 matrix cores (69 % busy, no
 // vector instruction beside them), now 357; 24 x 128, 460 rows on 4890 keys 237 / 130; 12 x 64, 2 x 174 rows on
 // 18580 keys 246 / 163; 4 query heads on 1 x 64, 2 x 128 rows on 512: 19 / 14.  Relative error against float64
 // 3.4e-7 .. 6.3e-7 before, 2.9e-7 .. 4.2e-7 now; at twice the logits 8e-7 .. 16e-7 and 5e-7 .. 7e-7.
+// The two chains of products run at raised priority (the other wavefront of the SIMD fills their gaps): 8 heads on 2 x 128,
+// 2 x 200 rows on 3000 keys 43.0 -> 41.4, 12 x 64, 300 rows on 3000 27.8 -> 27.0.  (The body with shared tiles below: 24 x 64
+// 133.6 -> 131.0, but 24 x 128, 460 rows on 3350 keys 107.7 -> 109.4: not taken.)
 template <int N> struct VecF;
 template <> struct VecF<4> { typedef float type __attribute__((ext_vector_type(4))); };
 template <> struct VecF<2> { typedef float type __attribute__((ext_vector_type(2))); };
@@ -186,6 +189,7 @@ __global__ __launch_bounds__(kSplitThreads) void attend_f32_kernel(FcAttendArgs 
 #pragma unroll
         for (int i = 0; i < 16; ++i) s[i] = s1[i] = 0.f;
         Split8 cur, nxt, qc = read_q(0), qn;
+        __builtin_amdgcn_s_setprio(1);
 #pragma unroll
         for (int p = 0; p < 4; ++p) split_k(cur, 0, p);
 #pragma unroll
@@ -203,6 +207,7 @@ __global__ __launch_bounds__(kSplitThreads) void attend_f32_kernel(FcAttendArgs 
             cur = nxt;
             qc = qn;
         }
+        __builtin_amdgcn_s_setprio(0);
         load_v(1, vpos, nv);
         t += kSplitWaves;
         if (t < t_end) { locate(t); load_k(); }        // the next tile's keys, behind the softmax and P V
@@ -266,6 +271,7 @@ __global__ __launch_bounds__(kSplitThreads) void attend_f32_kernel(FcAttendArgs 
         };
         // two blocks of O at a time
         Split8 va, vb, na, nb;
+        __builtin_amdgcn_s_setprio(1);
 #pragma unroll
         for (int p = 0; p < 4; ++p) { split_v(va, 0, p); split_v(vb, 1, p); }
 #pragma unroll
@@ -282,6 +288,7 @@ __global__ __launch_bounds__(kSplitThreads) void attend_f32_kernel(FcAttendArgs 
             va = na;
             vb = nb;
         }
+        __builtin_amdgcn_s_setprio(0);
     }
 
     l += __shfl_xor(l, 32, FC_WAVE);
