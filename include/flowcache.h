@@ -42,8 +42,8 @@
  *    BEFORE any HIP call is made, so they can be exercised on a machine without a GPU.
  *    No exception crosses the boundary; the library keeps no state between calls (except the
  *    device address of its own scratch buffer, see flowcache_chunk_decide_noalloc).
- *  - dtype FC_F32: float tensors, fp32 arithmetic (products of attention on two-part splits of the operands,
- *    fp32 accumulation, errors no larger than those of fp32 products).  FC_BF16: bfloat16 tensors, bf16 x bf16
+ *  - dtype FC_F32: float tensors, fp32 arithmetic (attention and importance form their products from
+ *    three-part splits that hold all 24 bits of every operand, with fp32 accumulation).  FC_BF16: bfloat16 tensors, bf16 x bf16
  *    -> fp32 matrix-core products, fp32 softmax state, bf16 output.
  *  - The recompute list (recompute_idx, n_recompute) lives on the device, so the host
  *    cannot check it: the kernels do.  A count above A is cut to A and an entry outside

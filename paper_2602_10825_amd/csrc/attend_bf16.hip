@@ -97,7 +97,7 @@ __device__ __forceinline__ void attend_wide(const FcAttendArgs& a, const FcAtten
     constexpr int NPV = 4 * DVB, NQK = 2 * KS, N = NPV + NQK;   // matrix products of a step: P V, Q K^T
     constexpr int PF = 4;             // fragments are read this many products ahead
 
-    const WideItem wi = wide_item<BQ, true>(a, p, valid, blockIdx.x);
+    const WideItem wi = wide_item(a, p, valid, blockIdx.x);
     if (!wi.ok) return;
     const int r = wi.r, h = wi.h, tile = wi.tile;
     const int c = a.rec_idx[r];
@@ -636,7 +636,7 @@ int launch_bf16(const FcAttendArgs& a, hipStream_t s) {
         attend_bf16_kernel<D, true, true><<<p.grid, NT, 0, s>>>(a, p, (float*)a.ws);
     FC_LAUNCH_CHECK();
     if (p.merge_grid > 0) {
-        attend_merge_kernel<bf16_t, D, BQ, true><<<p.merge_grid, 256, 0, s>>>(a, p, (const float*)a.ws);
+        attend_merge_kernel<bf16_t, D><<<p.merge_grid, 256, 0, s>>>(a, p, (const float*)a.ws);
         FC_LAUNCH_CHECK();
     }
     return FC_OK;

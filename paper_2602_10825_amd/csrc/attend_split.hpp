@@ -18,8 +18,7 @@ constexpr int kMaxSplits = 32;
 constexpr int kCus = 256;
 constexpr float kNegBig = -1.0e30f;
 
-constexpr int kWideRows = 256;        // query rows per block of the wide bf16 kernel
-constexpr int kSharedRows = 128;      // and of the fp32 kernel whose wavefronts share their tiles
+constexpr int kWideRows = 256;        // query rows per block of the wide bodies
 
 struct FcAttendPlan {
     int tiles;                           // 32-row tiles per chunk
@@ -60,54 +59,6 @@ inline void fc_plan_add(FcAttendPlan& p, int R, int64_t blocks, int64_t merge_un
     }
 }
 
-// fp32 blocks of 128 rows that share their tiles, two per compute unit: the number of key ranges S of a launch of
-// `units` such blocks, and its cost in the unit above (a block's 32-key tile 5.8, the merge launch and what each
-// 32-row partial costs to write and read; measured for 12 and 24 heads x 128 with S = 1..16).  0: not possible.
-// A range has at most a third of the keys of a range of 32-row blocks, whose eight wavefronts take every eighth
-// tile: with longer ranges more is added up into one accumulator than there, and the error would be larger
-// (12 heads, 2042 rows on 5100 .. 6100 keys: 6.3e-7 on the fp32 cores, 4.2e-7 in 32-row blocks, 8.9e-7 with S = 1, 6.6e-7
-// with 2, 5.7e-7 with 3).
-constexpr int kSharedBlocks = 1536;      // split blocks of 128 rows at most: 6144 partials, 102 MB
-inline double fc_shared_cost(int64_t units, int key_tiles, int narrow_splits, int* splits) {
-    double best_cost = 0.0;
-    for (int s = 3 * narrow_splits; s <= kMaxSplits && units * s <= kSharedBlocks && key_tiles >= 4 * s; ++s) {
-        const double x = (double)(units * s) / (2 * kCus), full = (double)((units * s + 2 * kCus - 1) / (2 * kCus));
-        const double rounds = x < 1.0 ? 1.0 : x + 0.3 * (full - x);
-        const double cost = rounds * (5.8 * ((key_tiles + s - 1) / s) + 8.0) + 8.0 + 0.0096 * (double)(units * s * (kSharedRows / kUnitRows));
-        if (best_cost == 0.0 || cost < 0.97 * best_cost) { *splits = s; best_cost = cost; }
-    }
-    return best_cost;
-}
-// Launches with fewer units than this, whatever the recompute count, stay with 32-row blocks (and their workspace small).
-inline bool fc_shared_allowed(int A, int L_c, int H_q) { return (int64_t)A * H_q * ((L_c + kSharedRows - 1) / kSharedRows) >= 96; }
-
-inline FcAttendPlan fc_attend_plan_f32(int A, int L_c, int L_clean, int H_q, bool may_split, bool may_share = true) {
-    constexpr int kBlockCost = 8;
-    FcAttendPlan p{};
-    p.tiles = (L_c + kUnitRows - 1) / kUnitRows;
-    const int key_tiles = (int)(((int64_t)L_clean + (int64_t)A * L_c + 31) / 32);
-    const int items = H_q * ((L_c + kSharedRows - 1) / kSharedRows);
-    // The form is the same for every recompute count (two kernels): shared tiles where they are cheaper on average.
-    int Sn[FC_MAX_ACTIVE], Sh[FC_MAX_ACTIVE];
-    double ratios = 0.0;
-    bool shared = may_split && may_share && fc_shared_allowed(A, L_c, H_q);
-    for (int R = 1; R <= A; ++R) {
-        Sn[R - 1] = Sh[R - 1] = 1;
-        const double narrow = fc_narrow_cost((int64_t)R * H_q * p.tiles, key_tiles, kBlockCost, may_split, &Sn[R - 1]);
-        const double cost = shared ? fc_shared_cost((int64_t)R * items, key_tiles, Sn[R - 1], &Sh[R - 1]) : 0.0;
-        if (cost == 0.0) shared = false;
-        ratios += cost / narrow;
-    }
-    shared = shared && ratios < 0.95 * A;
-    for (int R = 1; R <= A; ++R) {
-        const int64_t units = (int64_t)R * H_q * p.tiles, blocks = (int64_t)R * items;
-        p.narrow[R - 1] = !shared;
-        if (shared) fc_plan_add(p, R, blocks * Sh[R - 1], blocks * (kSharedRows / kUnitRows), Sh[R - 1]);
-        else fc_plan_add(p, R, units * Sn[R - 1], units, Sn[R - 1]);
-    }
-    return p;
-}
-
 // Wide launch: U = R * H_q * ceil(L_c / 256) units.  With fewer units than compute units all of them
 // are split S ways; otherwise only those of the last, partly filled round (per XCD: the units
 // past the last multiple of 32).
@@ -121,15 +72,12 @@ __host__ __device__ inline FcWideShape fc_wide_shape(int R, int items, int S) {
     return w;
 }
 
-inline FcAttendPlan fc_attend_plan_bf16(int A, int L_c, int L_clean, int H_q, int d, bool may_split) {
-    // Microseconds, from kernel traces of both forms with forced S (12 x 128: 600 rows on 5200 keys
-    // narrow 40 / wide 50 with S = 4; 1200 rows 91 / 57; 1500 rows on 51689 keys 1040 / 470): a wide
-    // block's 64-key tile, its fixed cost, the merge launch, and a split block's further cost
-    // (short pipeline, writing and merging its partial); an eighth of the time in which a narrow
-    // block's 8 wavefronts take one 32-key tile each, and its fixed cost in those.
-    const double w_tile = d == 128 ? 1.75 : 1.15, w_block = 5.0, w_merge = 5.0, w_parts = d == 128 ? 14.0 : 8.0;
-    const double n_tile = d == 128 ? 0.235 : 0.17;
-    constexpr int kNarrowBlockCost = 11;
+// Microseconds, from times of both forms with forced S: a wide block's 64 keys, its fixed cost, the merge launch, a split
+// block's further cost (short pipeline, writing and merging its partial) and what the merge takes per range; an eighth of
+// the time in which a narrow block's 8 wavefronts take one 32-key tile each, and its fixed cost in those.
+struct FcAttendCosts { double w_tile, w_block, w_merge, w_parts, w_range, n_tile; int n_block; };
+
+inline FcAttendPlan fc_attend_plan(int A, int L_c, int L_clean, int H_q, bool may_split, const FcAttendCosts& c) {
     FcAttendPlan p{};
     p.tiles = (L_c + kUnitRows - 1) / kUnitRows;
     const int64_t keys = (int64_t)L_clean + (int64_t)A * L_c;
@@ -137,7 +85,7 @@ inline FcAttendPlan fc_attend_plan_bf16(int A, int L_c, int L_clean, int H_q, in
     for (int R = 1; R <= A; ++R) {
         int Sn = 1, Sw = 1;
         const int64_t units = (int64_t)R * H_q * p.tiles;
-        const double narrow = n_tile * fc_narrow_cost(units, (int)((keys + 31) / 32), kNarrowBlockCost, may_split, &Sn);
+        const double narrow = c.n_tile * fc_narrow_cost(units, (int)((keys + 31) / 32), c.n_block, may_split, &Sn);
         // Rounds of 256-row units run heaviest chunk first; the chunk of rank r sees at most this many tiles.
         // (With the newest chunk's keys counted for all, 24 x 64 with 6 chunks of 386 rows and no context split
         // a last round that sees a sixth of them: 51 us against 44.)
@@ -148,18 +96,18 @@ inline FcAttendPlan fc_attend_plan_bf16(int A, int L_c, int L_clean, int H_q, in
         for (int rank = 0, q = 0; rank < R; ++rank) {
             int end = ((rank + 1) * u.per + kCus / 8 - 1) / (kCus / 8);
             if (end > full_rounds) end = full_rounds;
-            before += (end - q) * (seen(rank) * w_tile + w_block);
+            before += (end - q) * (seen(rank) * c.w_tile + c.w_block);
             q = end;
         }
         const double T = left ? seen(full_rounds * (kCus / 8) / u.per) : 0.0;   // of the last, partly filled one
-        double last = left ? T * w_tile + w_block : 0.0;
+        double last = left ? T * c.w_tile + c.w_block : 0.0;
         for (int S = 2; S <= kMaxSplits && left && may_split && T >= 2 * S; ++S) {
             const int64_t split = full_rounds == 0 ? (int64_t)R * items * S : (int64_t)8 * left * S;   // blocks of split units
             if (split > 2 * kCus) break;
             const double rounds = (double)((split + kCus - 1) / kCus);
-            const double cost = rounds * (T / S * w_tile + w_block + w_parts) + w_merge;
+            const double cost = rounds * (T / S * c.w_tile + c.w_block + c.w_parts) + c.w_merge + S * c.w_range;
             // (behind full rounds the last one's start overlaps their end)
-            if (cost < (full_rounds ? last - w_block : 0.97 * last)) { last = cost; Sw = S; }
+            if (cost < (full_rounds ? last - c.w_block : 0.97 * last)) { last = cost; Sw = S; }
         }
         if (narrow < before + last) {
             p.narrow[R - 1] = 1;
@@ -173,6 +121,17 @@ inline FcAttendPlan fc_attend_plan_bf16(int A, int L_c, int L_clean, int H_q, in
         }
     }
     return p;
+}
+// bf16, 12 x 128: 600 rows on 5200 keys narrow 40 / wide 50 with S = 4; 1200 rows 91 / 57; 1500 rows on 51689 keys 1040 / 470.
+inline FcAttendPlan fc_attend_plan_bf16(int A, int L_c, int L_clean, int H_q, int d, bool may_split) {
+    return fc_attend_plan(A, L_c, L_clean, H_q, may_split, d == 128 ? FcAttendCosts{1.75, 5.0, 5.0, 14.0, 0.0, 0.235, 11}
+                                                                    : FcAttendCosts{1.15, 5.0, 5.0, 8.0, 0.0, 0.17, 11});
+}
+// fp32, best S of each: 12 x 128, 2 chunks of 1021 rows on 4083 clean keys narrow 481 / wide 381; 6 of 87 on 4399 122 / 226; 24 x 128,
+// 460 rows on 3350 156 / 127; 2 x 128, 700 rows on 10400 66 / 87; 12 x 64, 2 of 174 on 18406 175 / 162; 4 x 64, 2 of 500 on 3000 40 / 46.
+inline FcAttendPlan fc_attend_plan_f32(int A, int L_c, int L_clean, int H_q, bool may_split, int d = 128) {
+    return fc_attend_plan(A, L_c, L_clean, H_q, may_split, d == 128 ? FcAttendCosts{8.2, 8.0, 5.0, 16.0, 0.5, 0.74, 8}
+                                                                    : FcAttendCosts{4.5, 6.0, 5.0, 8.0, 0.5, 0.42, 8});
 }
 
 // Most 32-row partials a launch with these shapes can need, whatever the number of keys.  The wide
@@ -188,12 +147,6 @@ inline int64_t fc_split_parts_bound(int A, int L_c, int H_q) {
         int64_t s = 4 * kCus / units;
         if (s > kMaxSplits) s = kMaxSplits;
         if (s > 1 && units * s > most) most = units * s;
-        if (fc_shared_allowed(A, L_c, H_q)) {
-            const int64_t blocks = (int64_t)R * H_q * ((L_c + kSharedRows - 1) / kSharedRows);
-            int64_t sh = kSharedBlocks / blocks;
-            if (sh > kMaxSplits) sh = kMaxSplits;
-            if (sh >= 3 && blocks * sh * (kSharedRows / kUnitRows) > most) most = blocks * sh * (kSharedRows / kUnitRows);
-        }
         double least = (double)((fc_wide_shape(R, (int)items, 1).full + kCus / 8 - 1) / (kCus / 8));
         for (int S = 2; S <= kMaxSplits; ++S) {
             const FcWideShape w = fc_wide_shape(R, (int)items, S);
@@ -266,37 +219,34 @@ __device__ __forceinline__ SplitItem split_item(const FcAttendArgs& a, const FcA
     return it;
 }
 
-// The same for blocks of ROWS rows that share their key tiles.  The 32 compute units of an XCD work on
-// the same head and chunk at the same time and share the K/V stream through its L2; heaviest chunk
-// first.  `unit` numbers the split units.  LAST: with full rounds of units before them, only those of
-// the last round are split; otherwise all are.
+// The same for 256-row blocks.  The 32 compute units of an XCD work on the same head and chunk at
+// the same time and share the K/V stream through its L2; heaviest chunk first.  `unit` numbers the
+// split units.
 struct WideItem { int r, h, tile, s, S; int64_t unit; bool ok; };
-template <int ROWS>
 __device__ __forceinline__ WideItem wide_unit(const FcAttendArgs& a, uint32_t valid, int items, int rank, int item) {
     WideItem wi;
-    const int tiles = (a.L_c + ROWS - 1) / ROWS;
+    const int tiles = (a.L_c + kWideRows - 1) / kWideRows;
     wi.ok = item < items;
     wi.r = block_of_rank(valid, rank);
     wi.h = item / tiles;
     wi.tile = item % tiles;
     return wi;
 }
-template <int ROWS, bool LAST>
 __device__ __forceinline__ WideItem wide_item(const FcAttendArgs& a, const FcAttendPlan& p, uint32_t valid, int bid) {
     WideItem wi;
     const int R = __popc(valid);
     wi.ok = false;
-    const int items = a.H_q * ((a.L_c + ROWS - 1) / ROWS);
+    const int items = a.H_q * ((a.L_c + kWideRows - 1) / kWideRows);
     const int S = p.splits[R - 1];
-    const FcWideShape w = fc_wide_shape(R, items, LAST ? S : 1);
+    const FcWideShape w = fc_wide_shape(R, items, S);
     const int xcd = bid & 7, slot = bid >> 3;
-    if (S > 1 && (!LAST || w.full == 0)) {
+    if (S > 1 && w.full == 0) {
         // all units split: range-major, so that the row tiles of a head that read one range are neighbours
         const int U = R * items, n = U * S, per = (n + 7) / 8;
         const int e = xcd * per + slot;
         if (slot >= per || e >= n) return wi;
         const int u = e % U;
-        wi = wide_unit<ROWS>(a, valid, items, u / items, u % items);
+        wi = wide_unit(a, valid, items, u / items, u % items);
         wi.s = e / U; wi.S = S; wi.unit = u;
         return wi;
     }
@@ -305,11 +255,11 @@ __device__ __forceinline__ WideItem wide_item(const FcAttendArgs& a, const FcAtt
         const int b = slot - w.full;
         if (S == 1 || b >= w.rem * S) return wi;
         j = w.full + b % w.rem;
-        wi = wide_unit<ROWS>(a, valid, items, j / w.per, xcd * w.per + j % w.per);
+        wi = wide_unit(a, valid, items, j / w.per, xcd * w.per + j % w.per);
         wi.s = b / w.rem; wi.S = S; wi.unit = xcd * w.rem + b % w.rem;
         return wi;
     }
-    wi = wide_unit<ROWS>(a, valid, items, j / w.per, xcd * w.per + j % w.per);
+    wi = wide_unit(a, valid, items, j / w.per, xcd * w.per + j % w.per);
     wi.s = 0; wi.S = 1; wi.unit = 0;
     return wi;
 }
@@ -402,7 +352,7 @@ __device__ __forceinline__ void finish_unit(const FcAttendArgs& a, const FcAtten
 }
 
 // The S partials of every unit -> out and lse.  One block per unit, 8 threads per row.
-template <typename T, int D, int ROWS, bool LAST>
+template <typename T, int D>
 __global__ __launch_bounds__(256) void attend_merge_kernel(FcAttendArgs a, FcAttendPlan p, const float* parts) {
     constexpr int PER = D / 8;
     const uint32_t valid = valid_blocks(a);
@@ -418,18 +368,18 @@ __global__ __launch_bounds__(256) void attend_merge_kernel(FcAttendArgs a, FcAtt
         r = block_of_rank(valid, (unit / p.tiles) % R);
         h = unit / (p.tiles * R);
     } else {
-        constexpr int SUB = ROWS / kUnitRows;
-        const int items = a.H_q * ((a.L_c + ROWS - 1) / ROWS);
+        constexpr int SUB = kWideRows / kUnitRows;
+        const int items = a.H_q * ((a.L_c + kWideRows - 1) / kWideRows);
         const FcWideShape w = fc_wide_shape(R, items, S);
         const int u = unit / SUB;
         WideItem wi;
-        if (!LAST || w.full == 0) {
+        if (w.full == 0) {
             if (u >= R * items) return;
-            wi = wide_unit<ROWS>(a, valid, items, u / items, u % items);
+            wi = wide_unit(a, valid, items, u / items, u % items);
         } else {
             if (u >= 8 * w.rem) return;
             const int j = w.full + u % w.rem;
-            wi = wide_unit<ROWS>(a, valid, items, j / w.per, (u / w.rem) * w.per + j % w.per);
+            wi = wide_unit(a, valid, items, j / w.per, (u / w.rem) * w.per + j % w.per);
         }
         if (!wi.ok) return;
         tile = wi.tile * SUB + unit % SUB;

@@ -73,6 +73,16 @@ __device__ __forceinline__ float wave_sum_all(float v) {
     return v;
 }
 
+// A block's barrier that orders LDS accesses only (the loads of the next tile stay in flight).
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(0xC07F);      // lgkmcnt(0)
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
+
 static inline size_t fc_align_up(size_t x, size_t a = 256) { return (x + a - 1) / a * a; }
 
 #define FC_HIP_TRY(expr)                          \

@@ -38,78 +38,79 @@ __device__ __forceinline__ bool resolve_rows(const FcMassArgs& a, int64_t& row0)
     return true;
 }
 
-// ---- fp32: on the f16 matrix cores ----------------------------------------------------
-// Both operands in two f16 parts (f32_split.hpp), scaled per row and per key, read straight into
-// registers in the products' own layout: lane (half, n) holds elements 16 st + 8 half .. + 8 of row n.
+// ---- fp32: on the bf16 matrix cores ---------------------------------------------------
+// Both operands in three bf16 parts (f32_split.hpp), read straight into registers in the products' own layout:
+// lane (half, n) holds elements 16 st + 8 half .. + 8 of row n.
 // Both passes form S^T = K Q^T, one observation row per lane.  A wavefront keeps 32 rows (pass 1) or 32 keys
 // (pass 2), split once, and passes over the others, whose next step is split between the products of this
-// one.  Bound by the vector ALU and the lines that a load touches in large calls and by latency in small ones.
-// Whole call, us, one thread per key with a wavefront reduction per row / fp32 matrix cores / now: four query
-// heads on one x 64, 50 rows on 512 keys 132 / 20 / 15; 12 x 128, 50 rows on 4000 keys 135 / 54 / 45, on 51000 - / 358 /
-// 257; 12 x 64, 969 rows on 10647 keys - / 398 / 249; 8 heads on 2 x 128, 1671 rows on 1892 keys - / 293 / 200.  Error
-// against float64 over 12 seeds of 7 shapes 0.90 of that of the fp32 matrix cores, nowhere larger.
+// one, while the rows after those are loaded over them.  Pass 1's rows are split once for the block, in LDS: with them in
+// registers head dimension 128 took 256 of those, and 12 heads, 50 rows on 4000 keys 65 us.  Bound by the vector ALU and the
+// lines that a load touches in large calls and by latency in small ones.
+// Whole call, us, fp32 matrix cores / now: four query heads on one x 64, 50 rows on 512 keys 19.9 / 18.5; 12 x 128, 50 rows on
+// 4000 keys 54 / 46.5, on 51000 358 / 265; 12 x 64, 969 rows on 10647 keys 398 / 271; 8 heads on 2 x 128, 1671 rows on 1892 keys
+// 289 / 185.  Error against float64 of 17 shapes 0.45 to 1.0 of that of the fp32 matrix cores, nowhere larger.
 constexpr int kF32Waves = 8;
 
-template <int D>
-__device__ __forceinline__ void load_rows_f32(const float* row, int half, f32x4_t (&f)[D / 8]) {
+// Columns 16 st + 8 half .. + 8 for st < N of a row, given from column 8 half on.
+template <int N>
+__device__ __forceinline__ void load_row_f32(const float* row, f32x4_t (&f)[2 * N]) {
 #pragma unroll
-    for (int st = 0; st < D / 16; ++st) {
-        f[2 * st] = *reinterpret_cast<const f32x4_t*>(row + 16 * st + 8 * half);
-        f[2 * st + 1] = *reinterpret_cast<const f32x4_t*>(row + 16 * st + 8 * half + 4);
+    for (int st = 0; st < N; ++st) {
+        f[2 * st] = *reinterpret_cast<const f32x4_t*>(row + 16 * st);
+        f[2 * st + 1] = *reinterpret_cast<const f32x4_t*>(row + 16 * st + 4);
     }
 }
-// the scale of the row that this lane and the one 32 away hold
-template <int D>
-__device__ __forceinline__ float row_scale_f32(const f32x4_t (&f)[D / 8], float& inverse) {
-    float most = 0.f;
+// S^T of the operand that stays, `stay(st)`, and the rows that pass: `f` holds the first N steps of `row`, and of `next` when
+// this returns.  STAY_K: keys stay (and Q passes).  `stay_row`, `row`, `next`: this lane's row of each in memory, from column
+// 8 half on.  Once more with fp32 products where an entry has no parts, or loses some (`odd`: of the operand that stays).
+template <int D, bool STAY_K, int N, typename F>
+__device__ __forceinline__ f32x16_t scores_f32(F stay, bool odd, const float* stay_row, f32x4_t (&f)[2 * N],
+                                               const float* row, const float* next) {
+    constexpr int KS = D / 16;
+    static_assert(KS % N == 0, "a step's place in f is the same in every row");
+    f32x16_t c, c1;                                            // the largest products, and the others
 #pragma unroll
-    for (int j = 0; j < D / 8; ++j) most = max_abs4(most, f[j]);
-    return split_scale(fmaxf(most, __shfl_xor(most, 32, FC_WAVE)), inverse);
-}
-template <int D>
-__device__ __forceinline__ void split_step_f32(Split8& x, const f32x4_t (&f)[D / 8], int st, int p, float scale) {
-    split_pair(x, p, f[2 * st + (p >> 1)][2 * (p & 1)], f[2 * st + (p >> 1)][2 * (p & 1) + 1], scale);
-}
-// S^T of the resident operand `stay` and the rows in `f`; STAY_K: keys stay (and Q passes).
-template <int D, bool STAY_K>
-__device__ __forceinline__ f32x16_t scores_f32(const Split8 (&stay)[D / 16], const f32x4_t (&f)[D / 8], float scale) {
-    f32x16_t c[2];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) c[0][i] = c[1][i] = 0.f;
+    for (int i = 0; i < 16; ++i) c[i] = c1[i] = 0.f;
     Split8 cur, nxt;
+    auto split = [&](Split8& x, int st, int p) __attribute__((always_inline)) {
+        const f32x4_t& v = f[2 * (st % N) + (p >> 1)];
+        split_pair(x, p, v[2 * (p & 1)], v[2 * (p & 1) + 1]);
+    };
 #pragma unroll
-    for (int p = 0; p < 4; ++p) split_step_f32<D>(cur, f, 0, p, scale);
+    for (int p = 0; p < 4; ++p) split(cur, 0, p);
 #pragma unroll
-    for (int st = 0; st < D / 16; ++st) {
-        const Split8 &k = STAY_K ? stay[st] : cur, &q = STAY_K ? cur : stay[st];
-        const bool more = st + 1 < D / 16;
-        f32x16_t &c0 = c[st & 1], &c1 = c[1 - (st & 1)];      // no product waits for the one before it
-        split_mfma(k.l, q.h, c0);
-        if (more) { split_step_f32<D>(nxt, f, st + 1, 0, scale); split_step_f32<D>(nxt, f, st + 1, 1, scale); }
-        __builtin_amdgcn_sched_barrier(0);
-        split_mfma(k.h, q.h, c1);
-        if (more) { split_step_f32<D>(nxt, f, st + 1, 2, scale); split_step_f32<D>(nxt, f, st + 1, 3, scale); }
-        __builtin_amdgcn_sched_barrier(0);
-        split_mfma(k.h, q.l, c0);
+    for (int st = 0; st < KS; ++st) {
+        const Split8 x = stay(st);
+        const Split8 &k = STAY_K ? x : cur, &q = STAY_K ? cur : x;
+        const bool more = st + 1 < KS;
+        const float* from = st + N < KS ? row + 16 * (st + N) : next + 16 * (st + N - KS);
+        f[2 * (st % N)] = *reinterpret_cast<const f32x4_t*>(from);
+        f[2 * (st % N) + 1] = *reinterpret_cast<const f32x4_t*>(from + 4);
+        split_mfma(k.l, q.h, c1); if (more) split(nxt, st + 1, 0); __builtin_amdgcn_sched_barrier(0);
+        split_mfma(k.h, q.l, c1); __builtin_amdgcn_sched_barrier(0);
+        split_mfma(k.m, q.m, c1); if (more) split(nxt, st + 1, 1); __builtin_amdgcn_sched_barrier(0);
+        split_mfma(k.m, q.h, c1); if (more) split(nxt, st + 1, 2); __builtin_amdgcn_sched_barrier(0);
+        split_mfma(k.h, q.m, c1); __builtin_amdgcn_sched_barrier(0);
+        split_mfma(k.h, q.h, c); if (more) split(nxt, st + 1, 3); __builtin_amdgcn_sched_barrier(0);
         cur = nxt;
     }
-    return c[0] + c[1];
-}
-template <int D>
-__device__ __forceinline__ void split_rows_f32(Split8 (&x)[D / 16], const f32x4_t (&f)[D / 8], float scale) {
+    c += c1;
 #pragma unroll
-    for (int st = 0; st < D / 16; ++st)
+    for (int i = 0; i < 16; ++i) odd = odd || !__builtin_isfinite(c[i]);
+    if (__any(odd)) {
 #pragma unroll
-        for (int p = 0; p < 4; ++p) split_step_f32<D>(x[st], f, st, p, scale);
-}
-// The 16 keys of a lane's accumulators (8 j + 4 half + e of 32), from `of_key`, one float per key.
-__device__ __forceinline__ void keys_of_lane(const float* of_key, int half, float (&x)[16]) {
+        for (int i = 0; i < 16; ++i) c[i] = 0.f;
+#pragma unroll 1
+        for (int st = 0; st < KS; ++st)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const f32x4_t v = *reinterpret_cast<const f32x4_t*>(of_key + 8 * j + 4 * half);
+            for (int j = 0; j < 2; ++j) {                      // contracts over elements that lie 8 apart
+                const f32x4_t x = *reinterpret_cast<const f32x4_t*>((STAY_K ? stay_row : row) + 16 * st + 4 * j);
+                const f32x4_t y = *reinterpret_cast<const f32x4_t*>((STAY_K ? row : stay_row) + 16 * st + 4 * j);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) x[4 * j + e] = v[e];
+                for (int i = 0; i < 4; ++i) c = __builtin_amdgcn_mfma_f32_32x32x2f32(x[i], y[i], c, 0, 0, 0);
+            }
     }
+    return c;
 }
 
 // log2-sum-exp from the largest exponent and the sum above it.  log2(sum) = e + log2(f), 1/2 <= f < 1, so that
@@ -165,45 +166,59 @@ __global__ __launch_bounds__(kF32Waves * 64, 2) void mass_stats_f32_kernel(FcMas
     const int T = (a.mass_len + 31) / 32;
     const int t_end = (int)((int64_t)T * (s + 1) / S);
     const F32Row row = f32_row(a, hk, rt * 32 + n);               // padding rows: computed, not used
-    __shared__ __attribute__((aligned(16))) float k_scale[kF32Waves][32];
-    Split8 q[D / 16];
+    const float* q_row = (const float*)a.q_base + ((row0 + row.w) * a.H_q + row.h) * D + 8 * half;
     f32x4_t k[D / 8];
-    float qc;                                                     // what brings a score back: the row's part, and c2
-    auto load_k = [&](int t) {
+    auto k_row = [&](int t) {
         const int j = t * 32 + n < a.mass_len ? t * 32 + n : a.mass_len - 1;
-        load_rows_f32<D>(kh + (int64_t)j * a.tok_stride, half, k);
+        return kh + (int64_t)j * a.tok_stride + 8 * half;
     };
     int t = (int)((int64_t)T * s / S) + wave;
-    {
-        f32x4_t f[D / 8];
-        load_rows_f32<D>((const float*)a.q_base + ((row0 + row.w) * a.H_q + row.h) * D, half, f);
-        if (t < t_end) load_k(t);
-        const float sc = row_scale_f32<D>(f, qc);
-        split_rows_f32<D>(q, f, sc);
-        qc *= c2;
+    if (t < t_end) load_row_f32<D / 16>(k_row(t), k);
+    // Q's parts, once for the block
+    constexpr int QROW = D + 8;
+    __shared__ __attribute__((aligned(16))) bf16_t qs[3][32 * QROW];
+    bool odd = false;
+    if (tid < 32 * (D / 8)) {
+        const int e = tid % (D / 8);
+        const F32Row r = f32_row(a, hk, rt * 32 + tid / (D / 8));
+        const float* p = (const float*)a.q_base + ((row0 + r.w) * a.H_q + r.h) * D + 8 * e;
+        f32x4_t v[2] = {*reinterpret_cast<const f32x4_t*>(p), *reinterpret_cast<const f32x4_t*>(p + 4)};
+        Split8 x;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            odd = odd || odd_magnitude(v[0][i]) || odd_magnitude(v[1][i]);
+            split_pair(x, i, v[i >> 1][2 * (i & 1)], v[i >> 1][2 * (i & 1) + 1]);
+        }
+        bf16_t* at = &qs[0][tid / (D / 8) * QROW + 8 * e];
+        *reinterpret_cast<u32x4_native*>(at) = x.h;
+        *reinterpret_cast<u32x4_native*>(at + 32 * QROW) = x.m;
+        *reinterpret_cast<u32x4_native*>(at + 64 * QROW) = x.l;
     }
+    __shared__ __attribute__((aligned(16))) uint32_t odd_s[kF32Waves];   // by the wavefront that split the rows
+    odd = __any(odd);
+    if (lane == 0) odd_s[wave] = odd;
+    __syncthreads();
+    const u32x4_native odd0 = *reinterpret_cast<const u32x4_native*>(odd_s), odd1 = *reinterpret_cast<const u32x4_native*>(odd_s + 4);
+    odd = (odd0[0] | odd0[1] | odd0[2] | odd0[3] | odd1[0] | odd1[1] | odd1[2] | odd1[3]) != 0u;
+    auto q = [&](int st) __attribute__((always_inline)) {
+        const bf16_t* at = &qs[0][n * QROW + 8 * half + 16 * st];
+        return Split8{*reinterpret_cast<const u32x4_native*>(at), *reinterpret_cast<const u32x4_native*>(at + 32 * QROW),
+                      *reinterpret_cast<const u32x4_native*>(at + 64 * QROW)};
+    };
     float m = kNegBig, l = 0.f;
     for (; t < t_end; t += kF32Waves) {
-        float inv;
-        const float sc = row_scale_f32<D>(k, inv);
-        k_scale[wave][n] = inv;          // the wavefront's own: LDS serves its accesses in order, no barrier is needed
-        const f32x16_t st = scores_f32<D, false>(q, k, sc);
-        float kc[16];
-        keys_of_lane(k_scale[wave], half, kc);
-#pragma unroll
-        for (int r = 0; r < 16; ++r) kc[r] *= qc;
-        if (t + kF32Waves < t_end) load_k(t + kF32Waves);
+        const f32x16_t st = scores_f32<D, false, D / 16>(q, odd, q_row, k, k_row(t), k_row(t + kF32Waves < t_end ? t + kF32Waves : t));
         const int key0 = t * 32 + half * 4;
         const bool full = t * 32 + 32 <= a.mass_len;
         float tm = kNegBig;
 #pragma unroll
         for (int r = 0; r < 16; ++r)
-            if (full || key0 + (r >> 2) * 8 + (r & 3) < a.mass_len) tm = fmaxf(tm, st[r] * kc[r]);
+            if (full || key0 + (r >> 2) * 8 + (r & 3) < a.mass_len) tm = fmaxf(tm, st[r] * c2);
         const float mn = fmaxf(m, tm);
         float acc = 0.f;
 #pragma unroll
         for (int r = 0; r < 16; ++r)
-            if (full || key0 + (r >> 2) * 8 + (r & 3) < a.mass_len) acc += __builtin_amdgcn_exp2f(fmaf(st[r], kc[r], -mn));
+            if (full || key0 + (r >> 2) * 8 + (r & 3) < a.mass_len) acc += __builtin_amdgcn_exp2f(fmaf(st[r], c2, -mn));
         // no real key yet (m and mn both at the floor): keep l = 0
         l = (mn > kNegBig) ? fmaf(l, __builtin_amdgcn_exp2f(m - mn), acc) : 0.f;
         m = mn;
@@ -262,38 +277,42 @@ __global__ __launch_bounds__(kF32Waves * 64, 2) void mass_cols_f32_kernel(FcMass
     float sums[16];
 #pragma unroll
     for (int r = 0; r < 16; ++r) sums[r] = 0.f;
-    __shared__ __attribute__((aligned(16))) float k_scale[kF32Waves][32];
-    Split8 k[D / 16];
-    f32x4_t q[D / 8];
-    float ls = 0.f, kc[16];                                        // kc: what brings a score back, the keys' part and c2
-    auto load_q = [&](int t) {
+    const float* k_row = (const float*)a.k_cache + (int64_t)hk * a.head_stride + (int64_t)(key0 + n < a.mass_len ? key0 + n : a.mass_len - 1) * a.tok_stride + 8 * half;
+    constexpr int N = 4;                                           // steps of the passing rows in flight: they come from the caches
+    Split8 kp[D / 16];
+    f32x4_t q[2 * N];
+    bool odd = false;
+    float ls = 0.f;
+    const float *q_row = nullptr, *q_next = nullptr;
+    auto next_q = [&](int t) {                                     // rows and normalisers of tile t
         const F32Row row = f32_row(a, hk, t * 32 + n);
-        load_rows_f32<D>((const float*)a.q_base + ((row0 + row.w) * a.H_q + row.h) * D, half, q);
+        q_next = (const float*)a.q_base + ((row0 + row.w) * a.H_q + row.h) * D + 8 * half;
         const int64_t at = (int64_t)row.h * nrg * kRowGroup + row.w;
         const float v = lse2 ? lse2[at] : lse_of_few(pm + at * np, pl + at * np, np);
         ls = row.ok ? v : kPosBig;                                 // padding rows: their terms vanish
     };
-    if (part < nt) load_q(part);
-    {
-        const int j = key0 + n < a.mass_len ? key0 + n : a.mass_len - 1;
-        f32x4_t f[D / 8];
-        load_rows_f32<D>((const float*)a.k_cache + (int64_t)hk * a.head_stride + (int64_t)j * a.tok_stride, half, f);
-        float inv;
-        const float sc = row_scale_f32<D>(f, inv);
-        k_scale[wave][n] = inv;
-        split_rows_f32<D>(k, f, sc);
-        keys_of_lane(k_scale[wave], half, kc);
-#pragma unroll
-        for (int r = 0; r < 16; ++r) kc[r] *= c2;
+    if (part < nt) {
+        next_q(part);
+        load_row_f32<N>(q_next, q);
     }
-    for (int t = part; t < nt; t += parts) {
-        float inv;
-        const float sc = row_scale_f32<D>(q, inv);
-        const f32x16_t st = scores_f32<D, true>(k, q, sc);
-        const float neg = -ls;
-        if (t + parts < nt) load_q(t + parts);
+    {
+        f32x4_t f[D / 8];
+        load_row_f32<D / 16>(k_row, f);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) sums[r] += __builtin_amdgcn_exp2f(fmaf(st[r], kc[r] * inv, neg));
+        for (int j = 0; j < D / 4; ++j) {
+            const float x = f[j >> 1][2 * (j & 1)], y = f[j >> 1][2 * (j & 1) + 1];
+            odd = odd || odd_magnitude(x) || odd_magnitude(y);
+            split_pair(kp[j >> 2], j & 3, x, y);
+        }
+    }
+    auto k = [&](int st) __attribute__((always_inline)) { return kp[st]; };
+    for (int t = part; t < nt; t += parts) {
+        const float neg = -ls;
+        q_row = q_next;
+        if (t + parts < nt) next_q(t + parts);
+        const f32x16_t st = scores_f32<D, true, N>(k, odd, k_row, q, q_row, q_next);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sums[r] += __builtin_amdgcn_exp2f(fmaf(st[r], c2, neg));
     }
     const float v = lanes_sum_scatter(sums, n);
     if (n < 16) merge[wave][(n >> 2) * 8 + half * 4 + (n & 3)] = v;
@@ -426,7 +445,6 @@ __global__ __launch_bounds__(kNT) void mass_lse_kernel(const float* __restrict__
 }
 
 // ---- bf16: matrix-core passes -------------------------------------------------------
-typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 
 constexpr int kTile = 128;            // keys per tile: 4 wavefronts x 32 keys
 constexpr int kTilesPerBlock = 8;      // at most
@@ -710,16 +728,6 @@ struct __attribute__((aligned(16))) MassWideSmem {
     __attribute__((aligned(16))) bf16_t x[kRing][kStream][D + 8];
     float lse[kRing][kStream];          // cols: the rows' normalisers
 };
-
-// A block's barrier that orders LDS accesses only (the loads of the next tile stay in flight).
-__device__ __forceinline__ void lds_barrier() {
-    __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_waitcnt(0xC07F);      // lgkmcnt(0)
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_sched_barrier(0);
-}
 
 // One step: nxt = products of the 32 rows whose fragments start at `cur`, sums += exponentials of
 // `prev`.  `frag` holds the first kAhead fragments of the step on entry and of the next one (at `after`)
@@ -1103,14 +1111,14 @@ int launch_bf16(const FcMassArgs& a, hipStream_t s) {
 }
 
 // With few rows the matrix cores work on padding, and one thread per key is faster (heads x keys: head dimension
-// 64 / 128; one thread per key against matrix cores, us): one row, 24 x 16384 46 against 60 / 75 against 102, 12 x 4096
-// 12 : 15 / 18 : 21, 1 x 16384 16 : 16 / 21 : 21, 1 x 60000 33 : 21 / 45 : 28; four, 24 x 16384 49 : 60 / 80 : 103, 24 x 4096
-// 21 : 25 / 31 : 37, 12 x 4096 16 : 15 / 23 : 22, 12 x 1024 14 : 15 / 20 : 20, 8 x 8192 18 : 16 / 25 : 22; eight, 24 x 4096 25 :
-// 25 / 39 : 38, 12 x 4096 (before) 21 : 16 / 30 : 26.  Few long heads leave most threads' chains of loads uncovered.
+// 64 / 128; one thread per key against matrix cores, us): one row, 24 x 16384 45 against 70 / 74 against 121, 12 x 4096
+// 13 : 17 / 17 : 25, 1 x 16384 17 : 18 / 21 : 25, 1 x 60000 41 : 25 / 47 : 34; four, 24 x 16384 49 : 69 / 79 : 120, 12 x 4096
+// 16 : 18 / 22 : 25, 4 x 20000 28 : 29 / 38 : 47, 1 x 4096 16 : 17 / 21 : 24, 1 x 16384 21 : 18 / 27 : 26; eight, 24 x 4096 25 : 27 /
+// 39 : 44, 12 x 30000 62 : 69 / 97 : 115, 12 x 4096 20 : 18 / 30 : 25, 4 x 20000 33 : 29 / 46 : 47.  Few long heads leave most
+// threads' chains of loads uncovered.
 inline bool f32_one_thread_per_key(int64_t rows, int H_k, int mass_len) {
     const bool full = (int64_t)H_k * mass_len >= 24 * 4096;
-    if (rows <= 2) return H_k >= 4 || mass_len < 16384;
-    if (rows <= 4) return (H_k >= 12 && full) || mass_len < 2048;
+    if (rows <= 4) return H_k >= 4 || mass_len < (rows <= 2 ? 32768 : 16384);
     return rows <= kFewRows && H_k >= 8 && full;
 }
 template <int D>

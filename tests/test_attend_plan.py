@@ -99,7 +99,8 @@ def test_workspace_holds_what_any_number_of_keys_can_ask_for(driver):
 
 @pytest.mark.parametrize("A,L_c,H,most", [(2, 10200, 12, 0),              # SkyReels-V2-1.3B-like layer: never split
                                           (4, 9360, 24, 8 * 8 * 15 * 2),  # MAGI-1-like: one chunk, the last round in two
-                                          (3, 328, 8, 2048)])
+                                          (3, 328, 8, 2048),
+                                          (5, 2040, 24, 2048), (2, 1021, 12, 3840), (3, 5000, 12, 0), (4, 2500, 24, 0)])
 def test_workspace_of_known_layers(driver, A, L_c, H, most):
     """No room for splits that no plan takes: 60 and 64 MB of them on the two layers."""
     assert ctypes.CDLL(driver).bound(A, L_c, H) == most
