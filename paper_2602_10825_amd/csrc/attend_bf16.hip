@@ -295,8 +295,9 @@ __device__ __forceinline__ void attend_wide(const FcAttendArgs& a, const FcAtten
             ps0 = ps1 = 0.f;
             constexpr int NEXP = NPV + KS - 1;         // products over which the exponentials are spread
             constexpr int BAR = NPV + KS / 2;
-            // the chain before the other wavefront's masks and address steps (24 x 64, 2 chunks of 2040 rows on 18360
-            // keys 453 -> 447 us, 458 -> 454 on another card; 12 x 128, 10200 rows on 61200 3188 -> 3183, 3260 -> 3244)
+            // the chain before the other wavefront's masks and address steps (in turn on one card, medians: 24 x 64, 2 chunks
+            // of 2040 rows on 18360 keys 452 -> 448 us; 12 x 128, 10200 rows on 61200 3195 -> 3182; 24 x 128, 4 x 9360 rows on
+            // 74880 clean keys 37.59 -> 37.36 ms)
             __builtin_amdgcn_s_setprio(1);
             static_for<N>([&](auto F) __attribute__((always_inline)) {
                 constexpr int f = F;

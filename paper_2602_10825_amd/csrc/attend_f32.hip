@@ -115,7 +115,8 @@ __device__ __forceinline__ bool to_do_in_fp32(bool odd, const f32x16_t (&o)[NB],
 // Q's parts are in LDS; K is read as rows and turned to the operand's layout there.  us on the fp32 matrix cores / here: 12 x 128,
 // 6 chunks of 87 rows on 4399 clean keys 208 / 136; 2 x 128, 700 rows on 10400 keys 106 / 69; 8 x 64, 86 rows on 16100 54 / 42; 4
 // query heads on 1 x 64, 2 x 128 rows on 512 clean keys 22 / 16.5.  (Each tile's sum by itself, as in the body below: 60
-// registers too many at head dimension 128, 136 -> 200.)
+// registers too many at head dimension 128, 136 -> 200.)  The two chains of products run at raised priority (in turn on one
+// card: 123 -> 121 and 15.8 -> 15.0 for the first and the last of these).
 template <int N> struct VecF;
 template <> struct VecF<4> { typedef float type __attribute__((ext_vector_type(4))); };
 template <> struct VecF<2> { typedef float type __attribute__((ext_vector_type(2))); };

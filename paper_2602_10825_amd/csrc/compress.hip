@@ -393,9 +393,9 @@ __device__ __forceinline__ int first_digit_shift(const uint64_t* edge, int n) {
 // takes the same 128 keys of the head and lays the bins between those some ranks above and below the
 // wanted one (select_bins.hpp).  A wanted key outside (5 deviations) costs time only.
 // Every block compares the sampled keys with each other, 16384 comparisons, which more threads share and larger blocks
-// make rarer (scoring and selection, us; threads x tokens each 256 x 8 / 512 x 4 / 1024 x 4 / 1024 x 8: 24 heads of 74880 keys
-// 220.7 / 217.4 / 216.6 / 213.8, 12 of 51000 91.5 / 89.5 / 88.6 / 91.7, 8 of 20000 46.8 / 44.2 / 45.1 / 48.6, 4 of 5000 36.0 /
-// 33.3 / 34.8 / 36.2).
+// make rarer (scoring and selection, us; threads x tokens each 256 x 8 / 512 x 4 in turn on one card: 12 heads of 51000 keys
+// 90.7 / 88.9, 8 of 20000 52.9 / 50.3, 4 of 5000 35.1 / 32.7, 24 of 74880 214.5 / 214.8; on another 1024 x 4 and 1024 x 8 are
+// slower than 512 x 4 for the short ones, 33.3 / 34.8 / 36.2 for 4 of 5000).
 template <typename MT>   // importance as given (float) or pooled over a key group (double)
 __global__ __launch_bounds__(kScoreThreads) void score_keys_kernel(
     const double* __restrict__ e_all, const MT* __restrict__ mass_all,

@@ -703,8 +703,8 @@ __global__ __launch_bounds__(kNT, 2) void mass_cols_bf16_kernel(FcMassArgs a, in
 //   stats  64 observation rows stay, a range of keys passes: per lane one row's running sum
 //   cols   64 keys stay, the rows of all the head's groups pass: per lane 32 keys' running sums
 // Bound: vector ALU and matrix cores alike, 16 cycles each per 64 scores and pass (fma 4, exp2 8, add 4), at the
-// 1.82 GHz that the chip runs under both: 0.93 ms for 24 heads, 1872 rows, 74880 keys.  (Counters: matrix cores busy in 0.52
-// of the cycles, the vector ALU in 0.6, both at once in 0.34.)  So each score costs nothing but those
+// 1.8 to 1.95 GHz that the chip runs under both: 0.9 ms for 24 heads, 1872 rows, 74880 keys.  (Counters: matrix cores busy in
+// 0.53 of the cycles, the vector ALU in 0.65, both at once in 0.35, neither in 0.17.)  So each score costs nothing but those
 // three instructions -- no running maximum: the reference point m of a lane is raised only when a
 // sum of 16 terms exceeds 2^40 -- and the products of a 32-row step are issued between the
 // exponentials of the step before, one set of accumulators filled while the other is read.  Each
@@ -732,8 +732,8 @@ struct __attribute__((aligned(16))) MassWideSmem {
 // One step: nxt = products of the 32 rows whose fragments start at `cur`, sums += exponentials of
 // `prev`.  `frag` holds the first kAhead fragments of the step on entry and of the next one (at `after`)
 // on exit.  At raised priority, so that the other wavefront of the SIMD fills the step's gaps and stores and loads
-// its tiles in them: 24 x 128, 1872 rows on 74880 keys 1596 -> 1588 us, 24 x 64 1137 -> 1091, 130 rows on 84240 keys 211 ->
-// 201.  COLS: the resident operand is K and sums[b][r] one key each; else it is Q and sums[b][0..1]
+// its tiles in them (in turn on one card, medians): 24 x 64, 1872 rows on 74880 keys 1149 -> 1100 us, 130 rows on 84240 keys
+// 212 -> 202; 24 x 128, 1872 rows 1616 -> 1605, which is within the spread.  COLS: the resident operand is K and sums[b][r] one key each; else it is Q and sums[b][0..1]
 // are two halves of the sum of row b.  neg[b]: what the exponents are lowered by.
 constexpr int kAhead = 4;
 template <int D, bool COLS, int NS>
