@@ -46,8 +46,8 @@ __device__ __forceinline__ bool resolve_rows(const FcMassArgs& a, int64_t& row0)
 // one, while the rows after those are loaded over them.  Pass 1's rows are split once for the block, in LDS: with them in
 // registers head dimension 128 took 256 of those, and 12 heads, 50 rows on 4000 keys 65 us.  Bound by the vector ALU and the
 // lines that a load touches in large calls and by latency in small ones.
-// Whole call, us, fp32 matrix cores / now: four query heads on one x 64, 50 rows on 512 keys 19.9 / 18.5; 12 x 128, 50 rows on
-// 4000 keys 54 / 46.5, on 51000 358 / 265; 12 x 64, 969 rows on 10647 keys 398 / 271; 8 heads on 2 x 128, 1671 rows on 1892 keys
+// Whole call, us, fp32 matrix cores / now: four query heads on one x 64, 50 rows on 512 keys 19.5 / 15.3; 12 x 128, 50 rows on
+// 4000 keys 54 / 44, on 51000 358 / 263; 12 x 64, 969 rows on 10647 keys 398 / 271; 8 heads on 2 x 128, 1671 rows on 1892 keys
 // 289 / 185.  Error against float64 of 17 shapes 0.45 to 1.0 of that of the fp32 matrix cores, nowhere larger.
 constexpr int kF32Waves = 8;
 
@@ -255,12 +255,15 @@ __device__ __forceinline__ float lanes_sum_scatter(float (&v)[16], int n) {
 }
 
 // Pass 2: a wavefront keeps 32 keys; `parts` wavefronts of a block share the 32-row tiles of the key head
-// (every parts-th each) and are added up in order.
-template <int D>
-__global__ __launch_bounds__(kF32Waves * 64, 2) void mass_cols_f32_kernel(FcMassArgs a, int nrg, int parts,
+// (every parts-th each) and are added up in order.  NW wavefronts per block: with few tiles of rows four, of which the
+// registers of head dimension 64 let three blocks run at once where one of eight would (50 rows, 4 heads on one x 64, 512
+// keys 17.7 -> 15.3 us for the call; 12 x 128, 4000 keys 47 -> 43.7; 2 x 64, 32 rows on 39849 keys 32.3 -> 29.5); with many the eight
+// wavefronts share their rows in the L1 (12 x 64, 969 rows on 10647 keys 271, in blocks of four 292).
+template <int D, int NW>
+__global__ __launch_bounds__(NW * 64, D == 64 && NW < kF32Waves ? 3 : 2) void mass_cols_f32_kernel(FcMassArgs a, int nrg, int parts,
                                                                          const float* __restrict__ lse2, const float* __restrict__ pm,
                                                                          const float* __restrict__ pl, int np) {
-    const int hk = blockIdx.y, kb = kF32Waves / parts;             // key blocks of 32 per block
+    const int hk = blockIdx.y, kb = NW / parts;             // key blocks of 32 per block
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int n = lane & 31, half = lane >> 5;
     const int jb = blockIdx.x * kb * 32;
@@ -269,7 +272,7 @@ __global__ __launch_bounds__(kF32Waves * 64, 2) void mass_cols_f32_kernel(FcMass
         if (tid < kb * 32 && jb + tid < a.mass_len) a.mass[(int64_t)hk * a.mass_len + jb + tid] = __uint_as_float(0x7fc00000u);
         return;
     }
-    __shared__ float merge[kF32Waves][32];
+    __shared__ float merge[NW][32];
     const int G = a.H_q / a.H_k;
     const int part = wave / kb, key0 = jb + (wave % kb) * 32;
     const float c2 = a.scale * kLog2e;
@@ -1111,15 +1114,16 @@ int launch_bf16(const FcMassArgs& a, hipStream_t s) {
 }
 
 // With few rows the matrix cores work on padding, and one thread per key is faster (heads x keys: head dimension
-// 64 / 128; one thread per key against matrix cores, us): one row, 24 x 16384 45 against 70 / 74 against 121, 12 x 4096
-// 13 : 17 / 17 : 25, 1 x 16384 17 : 18 / 21 : 25, 1 x 60000 41 : 25 / 47 : 34; four, 24 x 16384 49 : 69 / 79 : 120, 12 x 4096
-// 16 : 18 / 22 : 25, 4 x 20000 28 : 29 / 38 : 47, 1 x 4096 16 : 17 / 21 : 24, 1 x 16384 21 : 18 / 27 : 26; eight, 24 x 4096 25 : 27 /
-// 39 : 44, 12 x 30000 62 : 69 / 97 : 115, 12 x 4096 20 : 18 / 30 : 25, 4 x 20000 33 : 29 / 46 : 47.  Few long heads leave most
-// threads' chains of loads uncovered.
-inline bool f32_one_thread_per_key(int64_t rows, int H_k, int mass_len) {
-    const bool full = (int64_t)H_k * mass_len >= 24 * 4096;
-    if (rows <= 4) return H_k >= 4 || mass_len < (rows <= 2 ? 32768 : 16384);
-    return rows <= kFewRows && H_k >= 8 && full;
+// 64 / 128; one thread per key against matrix cores, us): one row, 24 x 16384 45 against 63 / 74 against 113, 12 x 4096
+// 13.5 : 18 / 17 : 26, 4 x 20000 24 : 25 / 33 : 43, 8 x 60000 75 : 65 / 119 : 120, 2 x 38000 33 : 27 / 41 : 45, 1 x 20000 18 : 17 / 21.5 :
+// 24, 1 x 38000 25 : 21 / 34 : 29; four, 24 x 4096 20 : 24 / 31 : 42, 12 x 4096 16 : 18 / 22 : 26, 8 x 20000 34 : 33 / 50 : 55, 4 x
+// 20000 28 : 25 / 38 : 42, 2 x 20000 22 : 20 / 30 : 27, 1 x 4096 16 : 15.5 / 21 : 21; eight, 24 x 4096 25 : 24 / 39.5 : 42, 12 x
+// 12000 33 : 35 / 53.5 : 60, 12 x 4096 20.5 : 18 / 30 : 26, 8 x 20000 39 : 33 / 58 : 55.  Few long heads leave most threads'
+// chains of loads uncovered.
+inline bool f32_one_thread_per_key(int64_t rows, int H_k, int mass_len, int d) {
+    if (rows <= 2) return H_k >= 12 || mass_len < (d == 128 && H_k > 1 ? 49152 : 24576);
+    if (rows <= 4) return H_k >= 12 || (d == 128 && H_k >= 4 && mass_len < 49152);
+    return rows <= kFewRows && H_k >= 12 && (int64_t)H_k * mass_len >= 24 * 4096;
 }
 template <int D>
 int launch_f32_few(const FcMassArgs& a, hipStream_t s) {
@@ -1143,7 +1147,7 @@ int launch_f32_few(const FcMassArgs& a, hipStream_t s) {
 template <int D>
 int launch_f32(const FcMassArgs& a, hipStream_t s) {
     const int64_t rows = (int64_t)a.W * (a.H_q / a.H_k);
-    if (f32_one_thread_per_key(rows, a.H_k, a.mass_len)) return launch_f32_few<D>(a, s);
+    if (f32_one_thread_per_key(rows, a.H_k, a.mass_len, D)) return launch_f32_few<D>(a, s);
     const int nrg = (a.W + kRowGroup - 1) / kRowGroup, rt = (int)((rows + 31) / 32);
     const int most = nrg == 1 ? a.mass_len / 256 : a.mass_len / 512;
     const int64_t units = (int64_t)a.H_k * rt;
@@ -1161,10 +1165,13 @@ int launch_f32(const FcMassArgs& a, hipStream_t s) {
     } else {
         lse2 = nullptr;
     }
-    auto blocks = [&](int parts) { const int keys = kF32Waves / parts * 32; return (a.mass_len + keys - 1) / keys; };
+    auto blocks = [&](int parts, int waves) { const int keys = waves / parts * 32; return (a.mass_len + keys - 1) / keys; };
     int parts = 1;
-    while (parts < kF32Waves && 2 * parts <= rt && (int64_t)a.H_k * blocks(parts) < 512) parts *= 2;
-    mass_cols_f32_kernel<D><<<dim3(blocks(parts), a.H_k), kF32Waves * 64, 0, s>>>(a, nrg, parts, lse2, pm, pl, S);
+    while (parts < kF32Waves && 2 * parts <= rt && (int64_t)a.H_k * blocks(parts, kF32Waves) < 512) parts *= 2;
+    if (parts <= kF32Waves / 2 && rt <= kFewTiles)
+        mass_cols_f32_kernel<D, kF32Waves / 2><<<dim3(blocks(parts, kF32Waves / 2), a.H_k), kF32Waves * 32, 0, s>>>(a, nrg, parts, lse2, pm, pl, S);
+    else
+        mass_cols_f32_kernel<D, kF32Waves><<<dim3(blocks(parts, kF32Waves), a.H_k), kF32Waves * 64, 0, s>>>(a, nrg, parts, lse2, pm, pl, S);
     FC_LAUNCH_CHECK();
     return FC_OK;
 }
