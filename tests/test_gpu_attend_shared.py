@@ -107,3 +107,27 @@ def test_workspaces_too_small_for_the_partials():
         outs.append(r["out"].cpu().numpy())
     for o in outs[1:]:
         assert np.linalg.norm(o - outs[0]) <= 1e-5 * np.linalg.norm(outs[0])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("H_q,H_k,d,A", [(96, 8, 64, 1), (48, 4, 128, 2)])
+def test_long_ranges_add_up_as_many_tiles(form, H_q, H_k, d, A):
+    """More units than compute units on a long cache: a wavefront adds up 1272 tiles or more.  O is rounded once per tile, by
+    2^-24 at most, and a random walk of that ends below 2^-24 sqrt(1300 / 3) = 1.25e-6 of the sum (earlier sums are
+    smaller); scores and exponentials are off by some 2^-23 each, 3e-7 of a sum of many."""
+    L_c, L_clean = 700, 40000
+    assert form(A, L_c, L_clean, H_q, d, A) == LAST_SPLIT
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(d)
+    n = L_clean + A * L_c
+    q, k, v = (torch.randn(s, generator=gen, device=DEV) for s in ((A * L_c, H_q, d), (H_k, n, d), (H_k, n, d)))
+    idx, count = torch.arange(A, dtype=torch.int32, device=DEV), torch.tensor([A], dtype=torch.int32, device=DEV)
+    out = B.flowcache_attend(q, None, None, k, v, L_c, L_clean, [L_clean + i * L_c for i in range(A)], idx, count)["out"]
+    for h in (0, H_q // 2 - 1, H_q - 1):
+        hk = h // (H_q // H_k)
+        for c in range(A):
+            seen = L_clean + (c + 1) * L_c
+            s = q[c * L_c:(c + 1) * L_c, h].double() @ k[hk, :seen].double().T * d ** -0.5
+            ref = torch.softmax(s, -1) @ v[hk, :seen].double()
+            err = (out[c * L_c:(c + 1) * L_c, h].double() - ref).norm() / ref.norm()
+            assert float(err) <= 1.5e-6, (h, c, float(err))
