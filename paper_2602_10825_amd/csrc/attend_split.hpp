@@ -25,6 +25,7 @@ struct FcAttendPlan {
     int grid;                            // blocks of the attention launch
     int merge_grid;                      // blocks of the merge launch (0: never needed)
     int parts;                           // 32-row partials the workspace has to hold
+    int by_chunk;                        // order of the blocks where all 256-row units are split
     uint8_t narrow[FC_MAX_ACTIVE];       // for R = 1 .. A: 32-row blocks (else 256-row blocks)
     uint8_t splits[FC_MAX_ACTIVE];       // and the number of key ranges S
 };
@@ -75,10 +76,11 @@ __host__ __device__ inline FcWideShape fc_wide_shape(int R, int items, int S) {
 // Microseconds, from times of both forms with forced S: a wide block's 64 keys, its fixed cost, the merge launch, a split
 // block's further cost (short pipeline, writing and merging its partial) and what the merge takes per range; an eighth of
 // the time in which a narrow block's 8 wavefronts take one 32-key tile each, and its fixed cost in those.
-struct FcAttendCosts { double w_tile, w_block, w_merge, w_parts, w_range, n_tile; int n_block; };
+struct FcAttendCosts { double w_tile, w_block, w_merge, w_parts, w_range, n_tile; int n_block; bool by_chunk; };
 
 inline FcAttendPlan fc_attend_plan(int A, int L_c, int L_clean, int H_q, bool may_split, const FcAttendCosts& c) {
     FcAttendPlan p{};
+    p.by_chunk = c.by_chunk;
     p.tiles = (L_c + kUnitRows - 1) / kUnitRows;
     const int64_t keys = (int64_t)L_clean + (int64_t)A * L_c;
     const int items = H_q * ((L_c + kWideRows - 1) / kWideRows);
@@ -116,7 +118,8 @@ inline FcAttendPlan fc_attend_plan(int A, int L_c, int L_clean, int H_q, bool ma
             const FcWideShape w = fc_wide_shape(R, items, Sw);
             const bool flat = Sw > 1 && w.full == 0;
             const int64_t split_units = Sw == 1 ? 0 : flat ? (int64_t)R * items : (int64_t)8 * w.rem;
-            fc_plan_add(p, R, flat ? split_units * Sw : (int64_t)8 * w.full + split_units * Sw,
+            const int64_t share = ((c.by_chunk ? 1 : R) * (int64_t)items * Sw + 7) / 8;      // of an XCD
+            fc_plan_add(p, R, flat ? (int64_t)8 * (c.by_chunk ? R : 1) * share : (int64_t)8 * w.full + split_units * Sw,
                         split_units * (kWideRows / kUnitRows), Sw);
         }
     }
@@ -124,14 +127,14 @@ inline FcAttendPlan fc_attend_plan(int A, int L_c, int L_clean, int H_q, bool ma
 }
 // bf16, 12 x 128: 600 rows on 5200 keys narrow 40 / wide 50 with S = 4; 1200 rows 91 / 57; 1500 rows on 51689 keys 1040 / 470.
 inline FcAttendPlan fc_attend_plan_bf16(int A, int L_c, int L_clean, int H_q, int d, bool may_split) {
-    return fc_attend_plan(A, L_c, L_clean, H_q, may_split, d == 128 ? FcAttendCosts{1.75, 5.0, 5.0, 14.0, 0.0, 0.235, 11}
-                                                                    : FcAttendCosts{1.15, 5.0, 5.0, 8.0, 0.0, 0.17, 11});
+    return fc_attend_plan(A, L_c, L_clean, H_q, may_split, d == 128 ? FcAttendCosts{1.75, 5.0, 5.0, 14.0, 0.0, 0.235, 11, false}
+                                                                    : FcAttendCosts{1.15, 5.0, 5.0, 8.0, 0.0, 0.17, 11, false});
 }
 // fp32, best S of each: 12 x 128, 2 chunks of 1021 rows on 4083 clean keys narrow 481 / wide 381; 6 of 87 on 4399 122 / 226; 24 x 128,
 // 460 rows on 3350 156 / 127; 2 x 128, 700 rows on 10400 66 / 87; 12 x 64, 2 of 174 on 18406 175 / 162; 4 x 64, 2 of 500 on 3000 40 / 46.
 inline FcAttendPlan fc_attend_plan_f32(int A, int L_c, int L_clean, int H_q, bool may_split, int d = 128) {
-    return fc_attend_plan(A, L_c, L_clean, H_q, may_split, d == 128 ? FcAttendCosts{8.2, 8.0, 5.0, 16.0, 0.5, 0.74, 8}
-                                                                    : FcAttendCosts{4.5, 6.0, 5.0, 8.0, 0.5, 0.42, 8});
+    return fc_attend_plan(A, L_c, L_clean, H_q, may_split, d == 128 ? FcAttendCosts{8.2, 8.0, 5.0, 16.0, 0.5, 0.74, 8, true}
+                                                                    : FcAttendCosts{4.5, 6.0, 5.0, 8.0, 0.5, 0.42, 8, true});
 }
 
 // Most 32-row partials a launch with these shapes can need, whatever the number of keys.  The wide
@@ -241,11 +244,14 @@ __device__ __forceinline__ WideItem wide_item(const FcAttendArgs& a, const FcAtt
     const FcWideShape w = fc_wide_shape(R, items, S);
     const int xcd = bid & 7, slot = bid >> 3;
     if (S > 1 && w.full == 0) {
-        // all units split: range-major, so that the row tiles of a head that read one range are neighbours
-        const int U = R * items, n = U * S, per = (n + 7) / 8;
-        const int e = xcd * per + slot;
-        if (slot >= per || e >= n) return wi;
-        const int u = e % U;
+        // all units split: range-major, so that the row tiles of a head that read one range are neighbours; by_chunk:
+        // every XCD has its share of each chunk's blocks, heaviest first (fp32, 12 x 128, 2 chunks of 1021 rows on 4083 clean
+        // keys 432 -> 404 us, 12 x 64 240 -> 228, 4 chunks of 385 rows 178 -> 167, 8 x 128, 3 of 500 160 -> 162.5; bf16 gains or
+        // loses, 2 x 128, 6 of 2000 rows 189 -> 170, 12 x 128, 2 of 1000 on 53000 keys 625 -> 643, and keeps the other order)
+        const int chunks = p.by_chunk ? 1 : R, U = chunks * items, n = U * S, per = (n + 7) / 8;
+        const int rank = p.by_chunk ? slot / per : 0, e = xcd * per + slot - rank * per;
+        if (slot >= (p.by_chunk ? R : 1) * per || e >= n) return wi;
+        const int u = rank * items + e % U;
         wi = wide_unit(a, valid, items, u / items, u % items);
         wi.s = e / U; wi.S = S; wi.unit = u;
         return wi;

@@ -1,6 +1,6 @@
 """fp32 attention in blocks of 256 rows whose wavefronts share every key tile, in every form of the launch: a ragged last
 block of rows, one row past a block, one key more or less than a tile in every segment, slots in reverse order, grouped
-heads, a launch that runs 32-row blocks for other recompute counts, values that grow along the keys; against the float64
+heads, split blocks that do not divide evenly among the XCDs, a launch that runs 32-row blocks for other recompute counts, values that grow along the keys; against the float64
 oracle at the parity bars."""
 import ctypes
 import subprocess
@@ -30,6 +30,7 @@ FORMS = [
     ((24, 12, 128, 2, 511, 95, [0, 1]), ALL_SPLIT), ((96, 96, 64, 1, 257, 129, [0]), WHOLE),
     ((24, 4, 64, 4, 330, 333, [0, 1, 2, 3]), WHOLE), ((48, 12, 64, 2, 600, 40, [0, 1]), LAST_SPLIT),
     ((64, 8, 64, 2, 520, 100, [0, 1]), LAST_SPLIT),
+    ((3, 1, 128, 3, 900, 5000, [0, 1, 2]), ALL_SPLIT), ((1, 1, 128, 3, 1500, 2500, [0, 1, 2]), ALL_SPLIT),
     ((48, 48, 64, 2, 128, 1600, [0, 1]), NARROW), ((24, 24, 64, 3, 384, 1, [0, 1, 2]), NARROW),
 ]
 SHAPES = [shape for shape, _ in FORMS]
