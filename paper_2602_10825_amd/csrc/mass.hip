@@ -63,9 +63,11 @@ __device__ __forceinline__ void load_row_f32(const float* row, f32x4_t (&f)[2 * 
 // S^T of the operand that stays, `stay(st)`, and the rows that pass: `f` holds the first N steps of `row`, and of `next` when
 // this returns.  STAY_K: keys stay (and Q passes).  `stay_row`, `row`, `next`: this lane's row of each in memory, from column
 // 8 half on.  Once more with fp32 products where an entry has no parts, or loses some (`odd`: of the operand that stays).
+// Times c2, rounded: unrounded in one instruction with the maximum's subtraction, the largest score would not cancel, and from
+// 2^31 on its exponential is infinite.
 template <int D, bool STAY_K, int N, typename F>
 __device__ __forceinline__ f32x16_t scores_f32(F stay, bool odd, const float* stay_row, f32x4_t (&f)[2 * N],
-                                               const float* row, const float* next) {
+                                               const float* row, const float* next, float c2) {
     constexpr int KS = D / 16;
     static_assert(KS % N == 0, "a step's place in f is the same in every row");
     f32x16_t c, c1;                                            // the largest products, and the others
@@ -110,7 +112,10 @@ __device__ __forceinline__ f32x16_t scores_f32(F stay, bool odd, const float* st
                 for (int i = 0; i < 4; ++i) c = __builtin_amdgcn_mfma_f32_32x32x2f32(x[i], y[i], c, 0, 0, 0);
             }
     }
-    return c;
+    {
+#pragma clang fp contract(off)
+        return c * c2;
+    }
 }
 
 // log2-sum-exp from the largest exponent and the sum above it.  log2(sum) = e + log2(f), 1/2 <= f < 1, so that
@@ -207,18 +212,18 @@ __global__ __launch_bounds__(kF32Waves * 64, 2) void mass_stats_f32_kernel(FcMas
     };
     float m = kNegBig, l = 0.f;
     for (; t < t_end; t += kF32Waves) {
-        const f32x16_t st = scores_f32<D, false, D / 16>(q, odd, q_row, k, k_row(t), k_row(t + kF32Waves < t_end ? t + kF32Waves : t));
+        const f32x16_t st = scores_f32<D, false, D / 16>(q, odd, q_row, k, k_row(t), k_row(t + kF32Waves < t_end ? t + kF32Waves : t), c2);
         const int key0 = t * 32 + half * 4;
         const bool full = t * 32 + 32 <= a.mass_len;
         float tm = kNegBig;
 #pragma unroll
         for (int r = 0; r < 16; ++r)
-            if (full || key0 + (r >> 2) * 8 + (r & 3) < a.mass_len) tm = fmaxf(tm, st[r] * c2);
+            if (full || key0 + (r >> 2) * 8 + (r & 3) < a.mass_len) tm = fmaxf(tm, st[r]);
         const float mn = fmaxf(m, tm);
         float acc = 0.f;
 #pragma unroll
         for (int r = 0; r < 16; ++r)
-            if (full || key0 + (r >> 2) * 8 + (r & 3) < a.mass_len) acc += __builtin_amdgcn_exp2f(fmaf(st[r], c2, -mn));
+            if (full || key0 + (r >> 2) * 8 + (r & 3) < a.mass_len) acc += __builtin_amdgcn_exp2f(st[r] - mn);
         // no real key yet (m and mn both at the floor): keep l = 0
         l = (mn > kNegBig) ? fmaf(l, __builtin_amdgcn_exp2f(m - mn), acc) : 0.f;
         m = mn;
@@ -292,7 +297,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW < kF32Waves ? 3 : 2) void ma
         q_next = (const float*)a.q_base + ((row0 + row.w) * a.H_q + row.h) * D + 8 * half;
         const int64_t at = (int64_t)row.h * nrg * kRowGroup + row.w;
         const float v = lse2 ? lse2[at] : lse_of_few(pm + at * np, pl + at * np, np);
-        ls = row.ok ? v : kPosBig;                                 // padding rows: their terms vanish
+        ls = row.ok ? v : __builtin_inff();                        // padding rows: their terms vanish
     };
     if (part < nt) {
         next_q(part);
@@ -313,9 +318,9 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW < kF32Waves ? 3 : 2) void ma
         const float neg = -ls;
         q_row = q_next;
         if (t + parts < nt) next_q(t + parts);
-        const f32x16_t st = scores_f32<D, true, N>(k, odd, k_row, q, q_row, q_next);
+        const f32x16_t st = scores_f32<D, true, N>(k, odd, k_row, q, q_row, q_next, c2);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) sums[r] += __builtin_amdgcn_exp2f(fmaf(st[r], c2, neg));
+        for (int r = 0; r < 16; ++r) sums[r] += __builtin_amdgcn_exp2f(st[r] + neg);
     }
     const float v = lanes_sum_scatter(sums, n);
     if (n < 16) merge[wave][(n >> 2) * 8 + half * 4 + (n & 3)] = v;

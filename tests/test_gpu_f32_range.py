@@ -133,8 +133,8 @@ def test_infinite_entries(shape):
 
 
 # ------------------------------------------------------------------ importance
-# (d, H_q, H_k, W, L): merged with and without the launch between the passes; two and four tiles of rows
-MASS_SHAPES = [(64, 4, 1, 50, 512), (128, 2, 2, 40, 3000), (128, 8, 2, 130, 900)]
+# (d, H_q, H_k, W, L): merged with and without the launch between the passes; two and four tiles of rows, and few rows
+MASS_SHAPES = [(64, 4, 1, 50, 512), (128, 2, 2, 40, 3000), (128, 8, 2, 130, 900), (64, 2, 2, 3, 3000)]
 
 
 def check_mass(d, H_q, H_k, W, L, q, k, k_ref=None):
@@ -144,7 +144,7 @@ def check_mass(d, H_q, H_k, W, L, q, k, k_ref=None):
 
 
 @pytest.mark.parametrize("d,H_q,H_k,W,L", MASS_SHAPES)
-@pytest.mark.parametrize("kind", ["channels", "apart", "keys large", "keys small", "infinite"])
+@pytest.mark.parametrize("kind", ["channels", "apart", "keys large", "keys small", "infinite", "far apart", "very far apart"])
 def test_importance_over_the_range(d, H_q, H_k, W, L, kind):
     rng = np.random.default_rng(W)
     q = rng.standard_normal((W, H_q, d)).astype(np.float32)
@@ -162,6 +162,10 @@ def test_importance_over_the_range(d, H_q, H_k, W, L, kind):
         q, k = q * np.float32(2.0 ** -120), k * np.float32(2.0 ** 120)
     elif kind == "keys small":
         q, k = q * np.float32(2.0 ** 100), k * np.float32(2.0 ** -100)
+    elif kind == "far apart":                    # scores to 1e13, by far the most of a row in one key
+        q, k = np.float32(2.0 ** 20) * q, np.float32(2.0 ** 20) * k
+    elif kind == "very far apart":               # and to 1e32
+        q, k = np.float32(2.0 ** 52) * q, np.float32(2.0 ** 52) * k
     else:
         q[:, :, 0] = np.abs(q[:, :, 0]) + 0.1
         k_ref = k.copy()
