@@ -97,7 +97,7 @@ __device__ __forceinline__ void attend_wide(const FcAttendArgs& a, const FcAtten
     constexpr int NPV = 4 * DVB, NQK = 2 * KS, N = NPV + NQK;   // matrix products of a step: P V, Q K^T
     constexpr int PF = 4;             // fragments are read this many products ahead
 
-    const WideItem wi = wide_item(a, p, valid, blockIdx.x);
+    const WideItem wi = wide_item<false>(a, p, valid, blockIdx.x);
     if (!wi.ok) return;
     const int r = wi.r, h = wi.h, tile = wi.tile;
     const int c = a.rec_idx[r];

@@ -379,7 +379,7 @@ __device__ __forceinline__ void attend_wide(const FcAttendArgs& a, const FcAtten
     static_assert(NT / LPR == BK && EPT % 4 == 0, "one pass per tile");
     Segments& sg = sm.sg;
 
-    const WideItem wi = wide_item(a, p, valid, blockIdx.x);
+    const WideItem wi = wide_item<true>(a, p, valid, blockIdx.x);
     if (!wi.ok) return;
     const int hk = wi.h / (a.H_q / a.H_k);
     const int tid = threadIdx.x;

@@ -25,7 +25,6 @@ struct FcAttendPlan {
     int grid;                            // blocks of the attention launch
     int merge_grid;                      // blocks of the merge launch (0: never needed)
     int parts;                           // 32-row partials the workspace has to hold
-    int by_chunk;                        // order of the blocks where all 256-row units are split
     uint8_t narrow[FC_MAX_ACTIVE];       // for R = 1 .. A: 32-row blocks (else 256-row blocks)
     uint8_t splits[FC_MAX_ACTIVE];       // and the number of key ranges S
 };
@@ -80,7 +79,6 @@ struct FcAttendCosts { double w_tile, w_block, w_merge, w_parts, w_range, n_tile
 
 inline FcAttendPlan fc_attend_plan(int A, int L_c, int L_clean, int H_q, bool may_split, const FcAttendCosts& c) {
     FcAttendPlan p{};
-    p.by_chunk = c.by_chunk;
     p.tiles = (L_c + kUnitRows - 1) / kUnitRows;
     const int64_t keys = (int64_t)L_clean + (int64_t)A * L_c;
     const int items = H_q * ((L_c + kWideRows - 1) / kWideRows);
@@ -235,6 +233,10 @@ __device__ __forceinline__ WideItem wide_unit(const FcAttendArgs& a, uint32_t va
     wi.tile = item % tiles;
     return wi;
 }
+// BY_CHUNK: where all units are split, every XCD has its share of each chunk's blocks, heaviest first (fp32, 12 x 128, 2 chunks of
+// 1021 rows on 4083 clean keys 432 -> 404 us, 12 x 64 240 -> 228, 4 chunks of 385 rows 178 -> 167, 8 x 128, 3 of 500 160 -> 162.5;
+// bf16 gains or loses, 2 x 128, 6 of 2000 rows 189 -> 170, 12 x 128, 2 of 1000 on 53000 keys 625 -> 643, and keeps the other order).
+template <bool BY_CHUNK>
 __device__ __forceinline__ WideItem wide_item(const FcAttendArgs& a, const FcAttendPlan& p, uint32_t valid, int bid) {
     WideItem wi;
     const int R = __popc(valid);
@@ -244,14 +246,18 @@ __device__ __forceinline__ WideItem wide_item(const FcAttendArgs& a, const FcAtt
     const FcWideShape w = fc_wide_shape(R, items, S);
     const int xcd = bid & 7, slot = bid >> 3;
     if (S > 1 && w.full == 0) {
-        // all units split: range-major, so that the row tiles of a head that read one range are neighbours; by_chunk:
-        // every XCD has its share of each chunk's blocks, heaviest first (fp32, 12 x 128, 2 chunks of 1021 rows on 4083 clean
-        // keys 432 -> 404 us, 12 x 64 240 -> 228, 4 chunks of 385 rows 178 -> 167, 8 x 128, 3 of 500 160 -> 162.5; bf16 gains or
-        // loses, 2 x 128, 6 of 2000 rows 189 -> 170, 12 x 128, 2 of 1000 on 53000 keys 625 -> 643, and keeps the other order)
-        const int chunks = p.by_chunk ? 1 : R, U = chunks * items, n = U * S, per = (n + 7) / 8;
-        const int rank = p.by_chunk ? slot / per : 0, e = xcd * per + slot - rank * per;
-        if (slot >= (p.by_chunk ? R : 1) * per || e >= n) return wi;
-        const int u = rank * items + e % U;
+        if (BY_CHUNK) {
+            const int n = items * S, per = (n + 7) / 8, rank = slot / per, e = xcd * per + slot % per;
+            if (rank >= R || e >= n) return wi;
+            wi = wide_unit(a, valid, items, rank, e % items);
+            wi.s = e / items; wi.S = S; wi.unit = (int64_t)rank * items + e % items;
+            return wi;
+        }
+        // all units split: range-major, so that the row tiles of a head that read one range are neighbours
+        const int U = R * items, n = U * S, per = (n + 7) / 8;
+        const int e = xcd * per + slot;
+        if (slot >= per || e >= n) return wi;
+        const int u = e % U;
         wi = wide_unit(a, valid, items, u / items, u % items);
         wi.s = e / U; wi.S = S; wi.unit = u;
         return wi;
