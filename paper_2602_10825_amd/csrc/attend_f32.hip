@@ -345,17 +345,17 @@ __device__ __forceinline__ void attend_narrow(const FcAttendArgs& a, const FcAtt
 }
 
 // ---- many query rows ----------------------------------------------------------------------------
-// 256 query rows per block, 32 per wavefront, whose Q stays in registers.  The eight wavefronts share every 32-key tile: it
-// is read once, split into its parts once (an eighth of the vector work of the body above) and double-buffered in LDS.
-// Step t: tile t's products and softmax, with the splitting of tile t + 1 between the products of Q K^T, the loads of tile
-// t + 2 behind them, and one barrier at the end.  A tile's contribution to O is summed up by itself and then added, which
+// 256 query rows per block, 32 per wavefront, whose Q stays in registers (some of its last parts in LDS).  The eight
+// wavefronts share every 32-key tile: it is read once, split into its parts once (an eighth of the vector work of the body
+// above) and double-buffered in LDS.  Step t: tile t's products and softmax, with the splitting of tile t + 1 between the
+// products of Q K^T, the loads of tile t + 2 among those of P V, and one barrier at the end.  A tile's contribution to O is summed up by itself and then added, which
 // costs nothing, as that is one instruction with the rescaling of O, and rounds O once per 32 keys instead of 12 times.  The
 // smaller products of Q K^T come first for the same reason.  us on the fp32 matrix cores / here: 12 x 128, 2 chunks of 1021
 // rows on 4083 clean keys 690 / 398; 24 x 128, 460 rows on 3350 keys 239 / 132; 24 x 64, 1024 rows on 61024 3110 / 1890; 12 x 64, 2 of
 // 1021 on 4083 349 / 212.  Q K^T runs at raised priority, so that the wavefronts of a SIMD part (in turn: 408 -> 398, 217 -> 212;
 // over P V instead 401, 221).  Relative error against float64, 22 shapes: 3.4e-7 .. 16e-7 and, with the body above, 2.0e-7 ..
 // 5.4e-7, nowhere larger.  Matrix cores 62 % busy while a block runs (1.86 GHz): no product covers the weights of a tile's first
-// half.  (A half-tile shift between the two wavefronts of a SIMD, with a third V buffer: 435 -> 464.)  All of Q's parts in
+// half.  (A half-tile shift between the two wavefronts of a SIMD, with a third V buffer: 442 -> 464.)  All of Q's parts in
 // registers are 24 too many: five were read back from memory in each tile, 435 -> 411.
 template <int D>
 struct WideSmem {

@@ -1,5 +1,6 @@
 // fp32 products on the bf16 matrix cores.  A float is the sum x = h + m + l of three bf16 numbers, each what
-// the ones before it leave, rounded to nearest: all 24 bits for |x| above 2^-110, whatever the other entries of its row or column are.  Of the nine products of two such sums six are formed,
+// the ones before it leave, rounded to nearest: all 24 bits for |x| above 2^-110, whatever the other entries of its row or
+// column are.  Of the nine products of two such sums six are formed,
 //   x y ~= l h' + h l' + m m' + m h' + h m' + h h',
 // with float accumulation; those left out are below 2^-24 |x y|, the rounding of one fp32 product.  Six
 // v_mfma_f32_32x32x16_bf16 take 192 cycles where eight v_mfma_f32_32x32x2_f32 take 512, and an accumulator is rounded 6
